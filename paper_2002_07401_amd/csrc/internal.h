@@ -34,9 +34,15 @@ constexpr int kLamTileK = 16;     // Lambda tile mask granularity: rows (GEMM K 
 constexpr int kLamTileN = 64;     // ... and columns (GEMM N tile)
 constexpr int kOzMaxSlices = 8;   // int8 digits per FP64 row in the error-free products
 constexpr int kOzSlices = 7;      // digits used by the refined evaluation (error 7e-14 of max|x| max|y| K)
-// Screened proposals (QMC_REFINED): the basis functions skipped at r' change the
-// determinant ratio by at most this much in total (absolute)
-constexpr double kScreenTol = 1e-13;
+// Screened proposals (FP64 rows): the basis functions skipped at r' change the
+// determinant ratio by at most this much in total (absolute).  QMC_REFINED
+// takes 1e-13; QMC_FP64 takes 1e-19, a thousandth of the rounding unit of a
+// ratio of order one, so that what is left out is below what FP64 sums of the
+// kept terms round away.  The line lies there because it is nearly free: the
+// kept share of the functions grows only from 28 to 33 % (160 electrons,
+// L = 600), 11 to 14 % (1024 electrons, L = 4096) and 68 to 73 % (20 electrons
+// in an 8-bohr cube, L = 44) between the two.
+constexpr double kScreenTolRefined = 1e-13, kScreenTolF64 = 1e-19;
 
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
@@ -79,9 +85,13 @@ struct SysDev {
   __host__ __device__ bool f32() const {
     return precision == QMC_W_FP32 || precision == QMC_MIXED || precision == QMC_MIXED_BF16;
   }
-  // QMC_REFINED: FP64 storage, refined int8 products, screened proposals
-  // (determinant systems)
-  __host__ __device__ bool screened() const { return precision == QMC_REFINED && !pairing; }
+  // FP64 rows (QMC_FP64, QMC_REFINED; determinant systems): proposals stream
+  // only the columns of P that can change the ratio, from the transposed rows
+  __host__ __device__ bool screened() const { return store() == 0 && !pairing; }
+  __host__ __device__ double screen_tol() const { return precision == QMC_REFINED ? kScreenTolRefined : kScreenTolF64; }
+  // QMC_REFINED (determinant systems): P from refined int8 products, whose
+  // epilogue also writes the transposed rows
+  __host__ __device__ bool oz_rows() const { return precision == QMC_REFINED && !pairing; }
   // QMC_REFINED Pfaffian: the B rows from int8 digit products, FP64 otherwise
   __host__ __device__ bool pf_refined() const { return precision == QMC_REFINED && pairing; }
   __host__ __device__ bool bf16() const { return precision == QMC_MIXED_BF16; }
@@ -90,8 +100,10 @@ struct SysDev {
   __host__ __device__ int store() const { return f32() ? (bf16() ? 2 : 1) : 0; }
   __host__ __device__ int prop_rows() const { return store() == 0 ? kPropRowsF64 : kPropRowsNarrow; }
   // entries per basis function of the transposed rows of the screened
-  // proposals: the N electrons, then the nk unpaired orbitals' values
-  __host__ __device__ int pt_ld() const { return N + nk; }
+  // proposals: ptn for the up rows, then ptn for the down rows and the unpaired
+  // orbitals' values (n_up used of each, zeros after)
+  int ptn;
+  __host__ __device__ int pt_ld() const { return 2 * ptn; }
   double* R;        // [A][3]
   double* Z;        // [A]
   double* j1_b;     // [A]
@@ -238,11 +250,15 @@ struct WalkDev {
   // Lp digits each), and one exponent per row [Wk * n_up + Wk * n_dn]
   int8_t* oz_phi;
   int* oz_ephi;
-  // screened proposals (QMC_REFINED): P transposed per walker, PT[w][mu][i] =
-  // P[w][i][mu] for the N electrons and PT[w][mu][N + l] = U[mu][l] for the
-  // nk unpaired orbitals ([Wk][Lp][N + nk]: one basis function's column over
-  // the rows an up move streams, the down electrons and the unpaired
-  // orbitals, and over the up rows a down move streams is contiguous); per
+  // screened proposals: P transposed per walker, PT[w][mu][i] = P[w][i][mu] for
+  // the up electrons, PT[w][mu][ptn + j] = P[w][n_up + j][mu] for the down
+  // electrons and PT[w][mu][ptn + n_dn + l] = U[mu][l] for the nk unpaired
+  // orbitals ([Wk][Lp][2 ptn]: one basis function's column over the rows an up
+  // move streams, the down electrons and the unpaired orbitals, and over the
+  // up rows a down move streams is contiguous).  QMC_REFINED keeps it beside
+  // P; in QMC_FP64 it shares the memory of Yt (cofactor rows, which hold from
+  // an evaluation to the first proposal after it) and each half is written
+  // before the first proposal that streams it.  Per
   // walker and spin the largest |value| of each column over those rows
   // [Wk][2][Lp] (0: up rows, 1: down rows and unpaired orbitals); the pending
   // proposal's kept basis functions (index and value at r') and their count
@@ -567,6 +583,19 @@ hipError_t launch_P_build_oz(const SysDev& s, const WalkDev& w, int halves, cons
                              int dirty = 0);
 // screened proposals: column maxima of the P halves, and the streaming kernel
 hipError_t launch_screen_colmax(const SysDev& s, const WalkDev& w, int halves, hipStream_t st);
+// (QMC_FP64) the transposed rows of half h (0: up, 1: down and unpaired) from P,
+// with their column maxima
+hipError_t launch_pt_build(const SysDev& s, const WalkDev& w, int h, hipStream_t st);
+// rows of a half padded so that the blocked screened stream takes them: the
+// smallest even m >= n with m / gcd(m, 128) <= 8 (n <= 256), else n made even
+inline int pt_pad(int n) {
+  if (n > 256) return round_up(n, 2);
+  for (int m = round_up(n, 2);; m += 2) {
+    int g = 128;
+    while (m % g) g >>= 1;
+    if (m / g <= 8) return m;
+  }
+}
 // dynamic LDS of the blocked screened stream for a proposal of e (0: the plain one runs)
 size_t screened_stream_lds(const SysDev& s, const WalkDev& w, int e);
 // the unpaired orbitals' entries of every walker's transposed rows

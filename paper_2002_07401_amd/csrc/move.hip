@@ -142,15 +142,13 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
   } else if (chunks <= 8) {
 #define QMC_ROWS(T, NC) \
     case NC: hipExtLaunchKernelGGL((propose_rows_kernel<T, NC>), grid, dim3(256), 0, st, ev_start, ev_stop, 0, s, w, e, S); break;
+    if (store == 0) return hipErrorInvalidValue;   // FP64 proposals without a drift are screened
     if (store == 2) {
       switch (chunks) { QMC_ROWS(bf16s, 1) QMC_ROWS(bf16s, 2) QMC_ROWS(bf16s, 3) QMC_ROWS(bf16s, 4)
                         QMC_ROWS(bf16s, 5) QMC_ROWS(bf16s, 6) QMC_ROWS(bf16s, 7) QMC_ROWS(bf16s, 8) }
-    } else if (store == 1) {
+    } else {
       switch (chunks) { QMC_ROWS(float, 1) QMC_ROWS(float, 2) QMC_ROWS(float, 3) QMC_ROWS(float, 4)
                         QMC_ROWS(float, 5) QMC_ROWS(float, 6) QMC_ROWS(float, 7) QMC_ROWS(float, 8) }
-    } else {
-      switch (chunks) { QMC_ROWS(double, 1) QMC_ROWS(double, 2) QMC_ROWS(double, 3) QMC_ROWS(double, 4)
-                        QMC_ROWS(double, 5) QMC_ROWS(double, 6) QMC_ROWS(double, 7) QMC_ROWS(double, 8) }
     }
 #undef QMC_ROWS
   } else {
@@ -165,20 +163,19 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
 }
 
 // ---------------------------------------------------------------------------
-// Screened proposals (QMC_REFINED).  The new W row (column) of walker wk is
+// Screened proposals (FP64 rows).  The new W row (column) of walker wk is
 //   w'_j = sum over the kept mu of psi_mu(r') PT[wk][mu][i0 + j],  j < n_up,
 // one contiguous column of the rows the move streams per kept basis function
 // (for an up move the down electrons' rows and the unpaired orbitals; the
-// skipped ones change the ratio by at most kScreenTol, see screen_list_body).
-// One workgroup per walker: wave v takes kept functions v, v + 4, ..., four at
-// a time, lane l the rows l, l + 64, ...; the waves' partial rows are added in
-// a fixed order through LDS, then the ratio sum_j w'_j c_j.  The ratio goes to
-// the first of the walker's S partial slots (the others are zeroed), which the
-// accept and finalize kernels sum as usual.
+// skipped ones change the ratio by at most s.screen_tol(), see
+// screen_list_body).  Blocked stream: one workgroup per walker, the ratio in
+// the first of its S partial slots (the others zeroed).  Plain stream: one
+// workgroup per 128 rows, one slot each.  The accept and finalize kernels sum
+// the slots as usual.
 // ---------------------------------------------------------------------------
-template <int NB>
-__global__ void __launch_bounds__(256) propose_screened_kernel(SysDev s, WalkDev w, int e, int S) {
-  screened_rows_walker<NB>(s, w, blockIdx.x, e, S);
+constexpr int kScreenRowsNB = 2;   // plain stream: 64 rows per lane slot, two slots
+__global__ void __launch_bounds__(256) propose_screened_kernel(SysDev s, WalkDev w, int e, int S, int chunks) {
+  screened_rows_walker<kScreenRowsNB>(s, w, blockIdx.x / chunks, e, S, blockIdx.x % chunks);
 }
 
 template <int IPB>
@@ -243,13 +240,70 @@ __global__ void __launch_bounds__(256) screen_colmax_kernel(SysDev s, WalkDev w,
   }
 }
 
-// PT[w][mu][N + l] = U[mu][l] for every walker (constant: written once)
+// The transposed rows of half h of every walker from P (QMC_FP64), with their
+// column maxima.  One workgroup per 32 columns of a walker, 128 rows at a time
+// through LDS: 256-byte row segments in, whole columns (8 ptn bytes,
+// contiguous) out; rows past n_up are written zero.  Bound by HBM: P half in,
+// PT half out (2 x 393 MB at 1024 walkers x 80 rows x L = 600).
+__device__ __forceinline__ double max_nan(double m, double v) { return (v > m || v != v) ? v : m; }
+
+__global__ void __launch_bounds__(256) pt_build_kernel(SysDev s, WalkDev w, int h) {
+  constexpr int TC = 32, TR = 128, LD = TC + 1;
+  __shared__ double tile[TR * LD];
+  __shared__ double mx[16][TC];
+  const int tid = threadIdx.x, wk = blockIdx.y, c0 = blockIdx.x * TC;
+  const int Lp = s.Lp, np = s.ptn, n = s.nu, nrow = h == 0 ? s.nu : s.nd;
+  const double* P = (const double*)w.P + ((long)wk * s.N + (h == 0 ? 0 : s.nu)) * Lp + c0;
+  double* out = w.PT + ((long)wk * Lp + c0) * s.pt_ld() + (h == 0 ? 0 : np);
+  const int cp = 2 * (tid & 15), rg = tid >> 4;
+  double2 m = double2{0.0, 0.0};
+  for (int j0 = 0; j0 < np; j0 += TR) {
+    double2 v[TR / 16];
+#pragma unroll
+    for (int k = 0; k < TR / 16; ++k) {
+      const int j = j0 + rg + 16 * k;
+      const double* src = j < nrow ? P + (long)j * Lp : (j < n ? s.Uph + (long)(j - nrow) * Lp + c0 : nullptr);
+      v[k] = src ? *reinterpret_cast<const double2*>(src + cp) : double2{0.0, 0.0};
+    }
+    if (j0) __syncthreads();   // the previous rows are written out
+#pragma unroll
+    for (int k = 0; k < TR / 16; ++k) {
+      m.x = max_nan(m.x, fabs(v[k].x));
+      m.y = max_nan(m.y, fabs(v[k].y));
+      tile[(rg + 16 * k) * LD + cp] = v[k].x;
+      tile[(rg + 16 * k) * LD + cp + 1] = v[k].y;
+    }
+    __syncthreads();
+    const int half = min(TR, np - j0) / 2;   // row pairs of this pass (np even)
+    for (int q = tid; q < TC * half; q += 256) {
+      const int mu = q / half, j = 2 * (q - mu * half);
+      const double2 o = double2{tile[j * LD + mu], tile[(j + 1) * LD + mu]};
+      *reinterpret_cast<double2*>(out + (long)mu * s.pt_ld() + j0 + j) = o;
+    }
+  }
+  mx[rg][cp] = m.x;
+  mx[rg][cp + 1] = m.y;
+  __syncthreads();
+  if (tid < TC) {
+    double t = 0.0;
+    for (int k = 0; k < 16; ++k) t = max_nan(t, mx[k][tid]);
+    w.cmax[((long)wk * 2 + h) * Lp + c0 + tid] = t;
+  }
+}
+
+hipError_t launch_pt_build(const SysDev& s, const WalkDev& w, int h, hipStream_t st) {
+  if (!w.PT || !w.cmax || s.Lp % 32 || s.ptn % 2 || s.ptn < s.nu) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pt_build_kernel, dim3(s.Lp / 32, w.Wk), dim3(256), 0, st, s, w, h);
+  return hipGetLastError();
+}
+
+// PT[w][mu][ptn + n_dn + l] = U[mu][l] for every walker (QMC_REFINED: written once)
 __global__ void __launch_bounds__(256) pt_unpaired_kernel(SysDev s, WalkDev w) {
   const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const long per = (long)s.Lp * s.nk;
   if (t >= per * w.Wk) return;
   const long wk = t / per, q = t % per, mu = q / s.nk, l = q % s.nk;
-  w.PT[(wk * s.Lp + mu) * s.pt_ld() + s.N + l] = s.Uph[l * s.Lp + mu];
+  w.PT[(wk * s.Lp + mu) * s.pt_ld() + s.ptn + s.nd + l] = s.Uph[l * s.Lp + mu];
 }
 
 hipError_t launch_pt_unpaired(const SysDev& s, const WalkDev& w, hipStream_t st) {
@@ -297,7 +351,6 @@ size_t screened_stream_lds(const SysDev& s, const WalkDev& w, int e) {
 hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, double* ratio, bool finalize,
                                    hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!w.PT || !w.muk) return hipErrorInvalidValue;
-  const int n = e < s.nu ? s.nd + s.nk : s.nu;   // rows streamed (= n_up)
   const int S = propose_splits(s);
   const dim3 grid(w.Wk), blk(256);
   int IPB, FB;
@@ -306,12 +359,11 @@ hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, dou
 #define QMC_SBLK(I) case I: hipExtLaunchKernelGGL(propose_screened_blk_kernel<I>, grid, blk, lds, st, ev_start, ev_stop, 0, s, w, e, S, FB); break;
     switch (IPB) { QMC_SBLK(1) QMC_SBLK(2) QMC_SBLK(3) QMC_SBLK(4) QMC_SBLK(5) QMC_SBLK(6) QMC_SBLK(7) QMC_SBLK(8) }
 #undef QMC_SBLK
-  } else if (n <= 64) hipExtLaunchKernelGGL(propose_screened_kernel<1>, grid, blk, 0, st, ev_start, ev_stop, 0, s, w, e, S);
-  else if (n <= 128) hipExtLaunchKernelGGL(propose_screened_kernel<2>, grid, blk, 0, st, ev_start, ev_stop, 0, s, w, e, S);
-  else if (n <= 256) hipExtLaunchKernelGGL(propose_screened_kernel<4>, grid, blk, 0, st, ev_start, ev_stop, 0, s, w, e, S);
-  else if (n <= 512) hipExtLaunchKernelGGL(propose_screened_kernel<8>, grid, blk, 0, st, ev_start, ev_stop, 0, s, w, e, S);
-  else if (n <= 1024) hipExtLaunchKernelGGL(propose_screened_kernel<16>, grid, blk, 0, st, ev_start, ev_stop, 0, s, w, e, S);
-  else return hipErrorNotSupported;
+  } else if (s.nu <= kBigMaxN) {
+    const int chunks = (s.nu + 64 * kScreenRowsNB - 1) / (64 * kScreenRowsNB);
+    hipExtLaunchKernelGGL(propose_screened_kernel, dim3((unsigned)(w.Wk * chunks)), blk, 0, st, ev_start, ev_stop, 0, s, w,
+                          e, S, chunks);
+  } else return hipErrorNotSupported;
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || !finalize) return err;
   hipLaunchKernelGGL(propose_finalize_kernel, dim3((w.Wk + 255) / 256), dim3(256), 0, st, w, S, ratio,

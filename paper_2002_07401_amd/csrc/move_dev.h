@@ -202,14 +202,14 @@ __device__ void jastrow_change(const SysDev& s, const WalkDev& w, int wk, int e,
   }
 }
 
-// Screened proposals (QMC_REFINED): the basis functions at r' whose column of
+// Screened proposals: the basis functions at r' whose column of
 // the streamed P rows can change the ratio.  Over the rows j of the other spin,
 //   |sum_j c_j P_j[mu] psi_mu(r')| <= |psi_mu(r')| cmax_mu sum_j |c_j|,
 // cmax_mu = max_j |P_j[mu]|, c the current inverse column (row) of the moved
-// electron.  Functions with |psi_mu| cmax_mu |c|_1 <= kScreenTol / L are
-// skipped, so all skipped ones together change the ratio by at most
-// kScreenTol (and each new W entry by at most kScreenTol / |c|_1).  The kept
-// ones are listed in increasing mu with their values.  Called by every thread
+// electron.  Functions with |psi_mu| cmax_mu |c|_1 <= tol / L (s.screen_tol())
+// are skipped, so all skipped ones together change the ratio by at most tol
+// (and each new W entry by at most tol / |c|_1).  Values that are not numbers
+// are kept.  The kept ones are listed in increasing mu with their values.  Called by every thread
 // of the workgroup after psi_new and cvec of electron e are written.
 __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int e) {
   __shared__ double red[8];
@@ -222,7 +222,7 @@ __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int 
   double c1 = 0.0;
   for (int j = tid; j < s.nu; j += blockDim.x) c1 += fabs(cv[j]);
   c1 = block_sum_mv(c1, red);
-  const double thr = (c1 > 0.0) ? kScreenTol / ((double)s.L * c1) : 0.0;
+  const double thr = (c1 > 0.0) ? s.screen_tol() / ((double)s.L * c1) : 0.0;
   const double* cm = w.cmax + ((long)wk * 2 + (up ? 1 : 0)) * s.Lp;   // the rows the proposal streams
   const double* psi = w.psi_new + (long)wk * s.Lp;
   int* mk = w.muk + (long)wk * s.Lp;
@@ -235,7 +235,7 @@ __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int 
     bool keep = false;
     if (mu < s.L) {
       v = psi[mu];
-      keep = fabs(v) * cm[mu] > thr;
+      keep = !(fabs(v) * cm[mu] <= thr);
     }
     const unsigned long long b = __ballot(keep);
     if (lane == 0) wcount[wave] = __popcll(b);
@@ -283,15 +283,15 @@ __device__ void prep_body(const SysDev& s, const WalkDev& w, int wk, int e, cons
     if (DRIFT) { w.gJ_new[3 * wk] = gxn; w.gJ_new[3 * wk + 1] = gyn; w.gJ_new[3 * wk + 2] = gzn; }
   }
   inverse_line_body(s, w, wk, e);
-  if (s.screened()) screen_list_body(s, w, wk, e);
+  // (with a drift the proposal streams whole rows; QMC_REFINED still reports
+  // the kept count)
+  if (s.screened() && (!DRIFT || s.oz_rows())) screen_list_body(s, w, wk, e);
 }
 
 template <typename T> struct Vec16;
-template <> struct Vec16<double> { typedef double2 type; static constexpr int n = 2; };
 template <> struct Vec16<float> { typedef float4 type; static constexpr int n = 4; };
 template <> struct Vec16<bf16s> { typedef uint4 type; static constexpr int n = 8; };
 
-__device__ __forceinline__ double vget(const double2& v, int i) { return i == 0 ? v.x : v.y; }
 __device__ __forceinline__ double vget(const float4& v, int i) {
   return (double)(i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)));
 }
@@ -343,9 +343,8 @@ __device__ __forceinline__ void block_partial(double part, double gx, double gy,
 // 16-byte loads per lane (NC = ceil(Lp / (64 * 16 / sizeof(T))); chunks past Lp
 // contribute exact zeros).  The entries of the current inverse's column (up) or
 // row (down) that weight the rows are loaded once at the start, lane k holding
-// the one of the wave's k-th row.  FP64 rows are loaded non-temporally: on
-// MI355X that streams them at 80 % of the HBM peak instead of 71 %, while it
-// slows the FP32 rows (34 -> 50 us per launch), which keep ordinary loads.
+// the one of the wave's k-th row.  Ordinary loads: non-temporal ones slow the
+// FP32 rows on MI355X (34 -> 50 us per launch).  (FP64 rows: the screened stream.)
 template <typename T, int NC>
 __device__ void rows_body(const SysDev& s, const WalkDev& w, int wk, int sb, int S, int e, int R) {
   typedef typename Vec16<T>::type V;
@@ -388,13 +387,8 @@ __device__ void rows_body(const SysDev& s, const WalkDev& w, int wk, int sb, int
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int i0 = c * STEP + lane * VN;
-      if constexpr (sizeof(T) == 8) {
-        va[c] = (i0 < s.Lp) ? load16_nt<V>(pa + i0) : V{};
-        vb[c] = (two && i0 < s.Lp) ? load16_nt<V>(pb + i0) : V{};
-      } else {
-        va[c] = (i0 < s.Lp) ? *reinterpret_cast<const V*>(pa + i0) : V{};
-        vb[c] = (two && i0 < s.Lp) ? *reinterpret_cast<const V*>(pb + i0) : V{};
-      }
+      va[c] = (i0 < s.Lp) ? *reinterpret_cast<const V*>(pa + i0) : V{};
+      vb[c] = (two && i0 < s.Lp) ? *reinterpret_cast<const V*>(pb + i0) : V{};
     }
     double xa = 0.0, xb = 0.0;
 #pragma unroll

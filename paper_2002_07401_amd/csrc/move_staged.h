@@ -20,11 +20,11 @@ __device__ __forceinline__ int phase_tid() {
   return (int)threadIdx.x + z;
 }
 
-// Blocked form of the same sum, for an even row count n: the kept functions
-// are taken FB at a time (FB n a multiple of 128, IPB = FB n / 128 <= 8), and
-// a wave reads a block's FB columns (FB n doubles) with IPB 16-byte loads of
-// all 64 lanes: lane l of load i holds the two rows j, j + 1 of function f
-// with 2 (64 i + l) = f n + j, fixed over the blocks.  The kept list and the
+// Blocked form of the same sum, over the padded row count n (s.ptn): the kept
+// functions are taken FB at a time (FB n a multiple of 128, IPB = FB n / 128 <=
+// 8), and a wave reads a block's FB columns (FB n doubles) with IPB 16-byte
+// loads of all 64 lanes: lane l of load i holds the two rows j, j + 1 of
+// function f with 2 (64 i + l) = f n + j, fixed over the blocks.  The kept list and the
 // inverse line come first (one round), then every wave issues about eight
 // loads at once (8 / IPB blocks), some 32 KiB in flight per walker.  The
 // per-lane sums go to LDS and row j adds its FB x 4 partial sums in a fixed
@@ -75,8 +75,8 @@ __device__ void screened_stream_walker(const SysDev& s, const WalkDev& w, int wk
   __shared__ double red[8];
   const int tid = phase_tid(), lane = tid & 63, wave = tid >> 6;
   const bool up = e < s.nu;
-  const int i0 = up ? s.nu : 0;
-  const int n = up ? s.nd + s.nk : s.nu;   // = n_up either way (unpaired orbitals after the down rows)
+  const int n = s.nu, np = s.ptn;   // rows of either half (unpaired orbitals after the down rows), padded
+  const int i0 = up ? np : 0;
   const int Lp = s.Lp, ld = s.pt_ld();
   const double* base = w.PT + (long)wk * Lp * ld + i0;
   int* lmu = (int*)lds;
@@ -113,8 +113,8 @@ __device__ void screened_stream_walker(const SysDev& s, const WalkDev& w, int wk
 #pragma unroll
   for (int i = 0; i < IPB; ++i) {
     const int el = 2 * (64 * i + lane);
-    fi[i] = el / n;
-    ji[i] = el - fi[i] * n;
+    fi[i] = el / np;
+    ji[i] = el - fi[i] * np;
   }
   dbl2 acc[IPB];
 #pragma unroll
@@ -151,7 +151,7 @@ __device__ void screened_stream_walker(const SysDev& s, const WalkDev& w, int wk
   if (tid < n) {
     double t = 0.0;
     for (int v = 0; v < 4; ++v)
-      for (int f = 0; f < FB; ++f) t += pd[v * 128 * IPB + f * n + tid];
+      for (int f = 0; f < FB; ++f) t += pd[v * 128 * IPB + f * np + tid];
     wn[tid] = t;
     if (HAND) hand->wn[tid] = t;
     rp = t * cj;
@@ -166,18 +166,20 @@ __device__ void screened_stream_walker(const SysDev& s, const WalkDev& w, int wk
 // The plain screened stream of one walker (any row count), one workgroup of
 // 256 threads: wave v takes kept functions v, v + 4, ..., four at a time, lane
 // l the rows l, l + 64, ...; the waves' partial rows are added in a fixed order
-// through LDS, then the ratio sum_j w'_j c_j, which goes to the first of the
-// walker's S partial slots (the others are zeroed).
+// through LDS, then the ratio sum_j w'_j c_j.  The workgroup takes the rows
+// [64 NB c, 64 NB (c + 1)) and writes partial ratio c of the walker's S (chunk 0
+// also zeroes the slots past the last chunk): a walker's rows over several
+// workgroups, so that a few walkers of a large system still fill the chip.
 template <int NB>
-__device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, int e, int S) {
+__device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, int e, int S, int c) {
   __shared__ double part[4][64 * NB];
   __shared__ double red[8];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool up = e < s.nu;
-  const int i0 = up ? s.nu : 0;
-  const int n = up ? s.nd + s.nk : s.nu;   // = n_up either way
+  const int j0 = 64 * NB * c;
+  const int n = min(s.nu - j0, 64 * NB);   // this chunk's rows
   const int ld = s.pt_ld();
-  const double* base = w.PT + (long)wk * s.Lp * ld + i0;
+  const double* base = w.PT + (long)wk * s.Lp * ld + (up ? s.ptn : 0) + j0;
   const int cnt = w.nkeep[wk];
   const int* mk = w.muk + (long)wk * s.Lp;
   const double* pk = w.psk + (long)wk * s.Lp;
@@ -215,8 +217,8 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 #pragma unroll
   for (int b = 0; b < NB; ++b) part[wave][lane + 64 * b] = acc[b];
   __syncthreads();
-  const double* cv = w.cvec + (long)wk * s.nu;
-  double* wn = w.w_new + (long)wk * s.nu;
+  const double* cv = w.cvec + (long)wk * s.nu + j0;
+  double* wn = w.w_new + (long)wk * s.nu + j0;
   double rp = 0.0;
   for (int j = tid; j < n; j += blockDim.x) {
     const double x = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
@@ -224,24 +226,27 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
     rp += x * cv[j];
   }
   const double R = block_sum_mv(rp, red);
-  for (int q = tid; q < S; q += blockDim.x) w.rdet_part[(long)wk * S + q] = q == 0 ? R : 0.0;
+  const int chunks = (s.nu + 64 * NB - 1) / (64 * NB);
+  if (tid == 0) w.rdet_part[(long)wk * S + c] = R;
+  if (c == 0)
+    for (int q = chunks + tid; q < S; q += blockDim.x) w.rdet_part[(long)wk * S + q] = 0.0;
 }
 
-// The blocked screened stream for proposals of e: n even, FB = 128 /
+// The blocked screened stream for proposals of e: n = s.ptn, FB = 128 /
 // gcd(n, 128) functions per block, IPB = FB n / 128 loads per lane and block,
 // at most 8; n <= 256 (one row per thread in the final sums), Lp <=
 // kFuseMaxLp (the kept list in LDS).  False: the plain screened kernel.
 __host__ __device__ inline bool screened_blk_config(const SysDev& s, const WalkDev& w, int e, int& IPB, int& FB,
                                                    size_t& lds) {
-  const int n = e < s.nu ? s.nd + s.nk : s.nu;
+  const int n = s.ptn;
   int g = 128;
   while (n % g) g >>= 1;
   FB = 128 / g;
   IPB = FB * n / 128;
   lds = pad1k(sizeof(int) * (size_t)s.Lp) + pad1k(sizeof(double) * (size_t)s.Lp) +
         sizeof(dbl2) * 4 * 64 * (size_t)IPB;
-  return n % 2 == 0 && n <= 256 && IPB >= 1 && IPB <= 8 && s.Lp <= kFuseMaxLp && (uintptr_t)w.PT % 16 == 0 &&
-         s.pt_ld() % 2 == 0 && (e < s.nu ? s.nu : 0) % 2 == 0;
+  (void)e;
+  return n <= 256 && IPB >= 1 && IPB <= 8 && s.Lp <= kFuseMaxLp && (uintptr_t)w.PT % 16 == 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -466,27 +471,14 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
       cvl[tid] = c;
     }
   }
-  if (!s.screened()) {
-    if (HAND) {
-      // psi(r') of e2 for the next proposal's stream, at the bottom of the LDS
-      // (the staged rows there are no longer read)
-      __syncthreads();
-      double* psl = (double*)lds;
-#pragma unroll
-      for (int k = 0; k < QL; ++k) {
-        const int mu = tid + 256 * k;
-        if (mu < Lp) psl[mu] = mu < L ? q.sv[k] : 0.0;
-      }
-    }
-    return;
-  }
+  if (!s.screened()) return;
 
   // screened proposals of e2 (screen_list_body)
   __syncthreads();
   double c1 = 0.0;
   for (int j = tid; j < n; j += blockDim.x) c1 += fabs(cvl[j]);
   c1 = block_sum_mv(c1, red);
-  const double thr = (c1 > 0.0) ? kScreenTol / ((double)L * c1) : 0.0;
+  const double thr = (c1 > 0.0) ? s.screen_tol() / ((double)L * c1) : 0.0;
   int* mk = w.muk + (long)wk * Lp;
   double* pk = w.psk + (long)wk * Lp;
   // the kept functions in increasing mu: every slot's ballot first, one
@@ -495,7 +487,7 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
 #pragma unroll
   for (int k = 0; k < QL; ++k) {
     const int mu = 256 * k + tid;
-    const bool keep = mu < L && fabs(q.sv[k]) * q.xc[k] > thr;
+    const bool keep = mu < L && !(fabs(q.sv[k]) * q.xc[k] <= thr);
     bal[k] = __ballot(keep);
     if (lane == 0) wcnt[k][wave] = __popcll(bal[k]);
   }

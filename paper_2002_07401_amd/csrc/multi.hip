@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(256) multi_accept_kernel(MultiArgs a, const in
   }
 }
 
-// QMC_REFINED members: one item per walker, the screened stream the lone
+// FP64 rows: one item per walker, the screened stream the lone
 // proposal would run (blocked with its LDS where screened_blk_config allows,
 // else the plain one), writing the S partial slots the accept sums.
 __global__ void __launch_bounds__(256) multi_screened_rows_kernel(MultiArgs a, const int4* __restrict__ items,
@@ -153,10 +153,8 @@ __global__ void __launch_bounds__(256) multi_screened_rows_kernel(MultiArgs a, c
         case 7: screened_stream_walker<7>(s, wd, q.y, e, S, FB, dyn); break;
         default: screened_stream_walker<8>(s, wd, q.y, e, S, FB, dyn); break;
       }
-    } else if (s.nu <= 64) {
-      screened_rows_walker<1>(s, wd, q.y, e, S);
     } else {
-      screened_rows_walker<2>(s, wd, q.y, e, S);   // members have n_up <= 128
+      screened_rows_walker<2>(s, wd, q.y, e, S, 0);   // members have n_up <= 128: one chunk
     }
   }
 }
@@ -187,12 +185,9 @@ hipError_t launch_multi_rows(const MultiArgs& a, int store, int nc, const int4* 
   if (store == 2) {
     switch (nc) { QMC_MR(bf16s, 1) QMC_MR(bf16s, 2) QMC_MR(bf16s, 3) QMC_MR(bf16s, 4)
                   QMC_MR(bf16s, 5) QMC_MR(bf16s, 6) QMC_MR(bf16s, 7) QMC_MR(bf16s, 8) }
-  } else if (store == 1) {
+  } else if (store == 1) {   // (FP64 rows are screened)
     switch (nc) { QMC_MR(float, 1) QMC_MR(float, 2) QMC_MR(float, 3) QMC_MR(float, 4)
                   QMC_MR(float, 5) QMC_MR(float, 6) QMC_MR(float, 7) QMC_MR(float, 8) }
-  } else {
-    switch (nc) { QMC_MR(double, 1) QMC_MR(double, 2) QMC_MR(double, 3) QMC_MR(double, 4)
-                  QMC_MR(double, 5) QMC_MR(double, 6) QMC_MR(double, 7) QMC_MR(double, 8) }
   }
 #undef QMC_MR
   return hipErrorInvalidValue;

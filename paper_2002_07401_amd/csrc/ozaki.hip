@@ -515,7 +515,7 @@ hipError_t launch_moved_rows(const SysDev& s, const WalkDev& w, int h, bool move
 // phi64: digits of those rows first (oz_phi: up tiles, then down tiles; with
 // have_expo the rows' exponents in oz_ephi are already set), then the
 // products; P64 gets the FP64 result, lo (if given) its FP32 / BF16 copy and PT
-// (if given) its transpose per walker, PT[w][mu][i].
+// (if given) its transpose per walker, PT[w][mu][i] (the down rows from ptn on).
 hipError_t launch_P_build_oz(const SysDev& s, const WalkDev& w, int halves, const double* phi64, double* P64,
                              void* lo, bool lo_bf16, hipStream_t st, bool have_expo, double* PT, int dirty) {
   const long rowst = (long)s.N * s.Lp;
@@ -555,7 +555,7 @@ hipError_t launch_P_build_oz(const SysDev& s, const WalkDev& w, int halves, cons
       g.c2_bf16 = lo_bf16 ? 1 : 0;
     }
     if (PT) {   // PT[w][mu][i] for every electron i of walker w (this half: i = i0 + m % n)
-      g.CT = PT + (h == 0 ? 0 : s.nu);
+      g.CT = PT + (h == 0 ? 0 : s.ptn);
       g.ct_gs = (long)s.Lp * s.pt_ld();
       g.ct_ld = s.pt_ld();
     }

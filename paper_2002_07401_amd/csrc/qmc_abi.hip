@@ -148,6 +148,7 @@ struct qmc_walkers {
   double drift_tol = 1e-6;        // status 3 when the checked residual exceeds this
   bool evaluated = false;
   bool P_up_valid = false, P_dn_valid = false;
+  bool PT_ok[2] = {false, false};   // the transposed rows and column maxima of each P half hold
   // (QMC_REFINED) parameter generation at which each P half's rows were last
   // built with their positions recorded (-1: never): a later build of that
   // half may take only the rows whose electron has moved
@@ -256,6 +257,7 @@ extern "C" qmc_status qmc_system_create(const qmc_system_desc* desc, qmc_system*
   if (hipGetDevice(&s->device) != hipSuccess) s->device = 0;
   d.n_nuc = q.n_nuc; d.L = L; d.Lp = round_up(L, 32);
   d.nu = q.n_up; d.nd = q.n_dn; d.N = q.n_up + q.n_dn; d.nk = pf ? 0 : q.n_up - q.n_dn;
+  d.ptn = pt_pad(q.n_up);
   d.pairing = pf ? 1 : 0; d.pk = pf ? q.pf_k : 0; d.npf = pf ? d.N + q.pf_k : 0;
   d.j1_form = q.j1_form; d.j2_form = q.j2_form;
   for (int k = 0; k < 8; ++k) d.j2[k] = (q.j2 && k < q.n_j2) ? q.j2[k] : 0.0;
@@ -471,7 +473,7 @@ extern "C" qmc_status qmc_system_create(const qmc_system_desc* desc, qmc_system*
     if (!e) e = launch_lam_mask(d, nullptr);
     if (!e) e = hipStreamSynchronize(nullptr);
   }
-  if (!e && (d.refined() || d.screened()) && !pf) {
+  if (!e && (d.refined() || d.oz_rows()) && !pf) {
     // int8 digits of Lambda for the error-free P products of the evaluation
     d.oz_s = kOzSlices;
     const size_t plane = (size_t)oz_plane_bytes(Lp, Lp);
@@ -539,7 +541,9 @@ static void walker_layout(const SysDev& s, int n_walkers, bool adjoint, Carver& 
   const size_t nsq = s.pairing ? (size_t)s.npf * s.npf : (size_t)s.nu * s.nu;   // G~ or W
   c.take(&d.W, sizeof(double) * Wk * nsq);
   c.take(&d.A, sizeof(double) * Wk * nsq);
-  c.take(&d.Yt, sizeof(double) * Wk * N * Lp);
+  // (QMC_FP64: the transposed rows of the proposals share it)
+  const bool pt_in_yt = s.screened() && !s.oz_rows();
+  c.take(&d.Yt, sizeof(double) * Wk * (pt_in_yt ? std::max(N, (size_t)s.pt_ld()) : N) * Lp);
   c.take(&d.D, sizeof(double) * Wk * N * 4);
   c.take(&d.logdet, sizeof(double) * Wk);
   c.take(&d.detsign, sizeof(double) * Wk);
@@ -565,17 +569,18 @@ static void walker_layout(const SysDev& s, int n_walkers, bool adjoint, Carver& 
     c.take(&d.phi64, sizeof(double) * Wk * N * s.Lp);
     c.take(&d.P64, sizeof(double) * Wk * N * s.Lp);
   }
-  if ((s.refined() || s.screened() || s.pf_refined()) && s.oz_s > 0) {
+  if ((s.refined() || s.oz_rows() || s.pf_refined()) && s.oz_s > 0) {
     c.take(&d.oz_phi, (size_t)oz_phi_bytes(s, (long)Wk));
     c.take(&d.oz_ephi, sizeof(int) * Wk * N);
   }
   if (s.screened()) {
-    c.take(&d.PT, sizeof(double) * Wk * s.pt_ld() * s.Lp);
+    if (pt_in_yt) d.PT = d.Yt;
+    else c.take(&d.PT, sizeof(double) * Wk * s.pt_ld() * s.Lp);
     c.take(&d.cmax, sizeof(double) * Wk * 2 * s.Lp);
     c.take(&d.muk, sizeof(int) * Wk * s.Lp);
     c.take(&d.psk, sizeof(double) * Wk * s.Lp);
     c.take(&d.nkeep, sizeof(int) * Wk);
-    c.take(&d.oz_ephi_c, sizeof(int) * Wk * N);
+    if (s.oz_rows()) c.take(&d.oz_ephi_c, sizeof(int) * Wk * N);
   }
   if (!s.refined() && !s.pairing) {   // P builds of the moved rows only (FP64, FP32, QMC_REFINED)
     c.take(&d.rpos_P, sizeof(double) * Wk * N * 3);
@@ -733,7 +738,7 @@ extern "C" qmc_status qmc_walkers_create(qmc_system* sys, int32_t n_walkers, int
   walker_layout(sys->d, n_walkers, adjoint, cv, *wk);
   wk->aw_ready = adjoint;
   hipError_t e = hipMemset(base, 0, need);
-  if (e == hipSuccess && sys->d.screened() && sys->d.nk > 0) {   // the unpaired orbitals' transposed rows
+  if (e == hipSuccess && sys->d.oz_rows() && sys->d.nk > 0) {   // the unpaired orbitals' transposed rows
     e = launch_pt_unpaired(sys->d, wk->d, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   }
@@ -788,7 +793,7 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
   }
   // the FP32 / BF16 copies of Phi and P are written by the producing kernels
   // the int8 digits of the refined products take their row scales from here
-  const bool oz = (refine || s.screened()) && s.oz_s > 0;
+  const bool oz = (refine || s.oz_rows()) && s.oz_s > 0;
   int* ephi = (oz && s.Lq == 0) ? d.oz_ephi : nullptr;
   TIMED(wk, QMC_T_BASIS, stream, launch_basis_values(se, de, stream, refine ? d.phi : nullptr, s.bf16(), ephi),
         "basis");
@@ -807,18 +812,18 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
       // (QMC_REFINED) a half built before at these parameters: only the rows
       // whose electron has moved since
       int dirty = 0;
-      if (s.screened() && d.rpos_P)
+      if (s.oz_rows() && d.rpos_P)
         for (int h = 0; h < 2; ++h)
           if (wk->P_gen[h] == sys->generation) dirty |= 1 << h;
       TIMED(wk, QMC_T_P_BUILD, stream,
             launch_P_build_oz(s, d, halves, de.phi == d.phi64 ? d.phi64 : (const double*)d.phi,
                               refine ? d.P64 : (double*)d.P, refine ? d.P : nullptr, s.bf16(), stream,
-                              ephi != nullptr, s.screened() ? d.PT : nullptr, dirty & halves),
+                              ephi != nullptr, s.oz_rows() ? d.PT : nullptr, dirty & halves),
             "P build");
-      if (s.screened())
+      if (s.oz_rows())
         for (int h = 0; h < 2; ++h)
           if ((halves >> h) & 1) wk->P_gen[h] = sys->generation;
-      if (s.screened())
+      if (s.oz_rows())
         TIMED(wk, QMC_T_OTHER, stream, launch_screen_colmax(s, d, halves, stream), "column maxima");
     }
   } else if (halves) {
@@ -852,6 +857,7 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
   wk->lr_ready = false;
   wk->generation = sys->generation;
   wk->P_up_valid = wk->P_dn_valid = true;
+  wk->PT_ok[0] = wk->PT_ok[1] = s.oz_rows();
   wk->attempts = 0;
   wk->since = 0;
   wk->buf_spin = -1;
@@ -863,7 +869,9 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
 static hipError_t rebuild_P(qmc_walkers* wk, int halves, hipStream_t stream) {
   const SysDev& s = wk->sys->d;
   const WalkDev& d = wk->d;
-  if (!s.screened()) {
+  if (!s.oz_rows()) {
+    for (int h = 0; h < 2; ++h)
+      if ((halves >> h) & 1) wk->PT_ok[h] = false;
     int dirty = 0;
     if (d.rpos_P)
       for (int h = 0; h < 2; ++h)
@@ -889,7 +897,9 @@ static hipError_t rebuild_P(qmc_walkers* wk, int halves, hipStream_t stream) {
   return e;
 }
 
-static qmc_status ensure_P(qmc_walkers* wk, int e, hipStream_t stream) {
+// The rows a proposal of e streams: the other spin's half of P and, for the
+// screened proposals (screen = false with a drift: whole rows), its transpose.
+static qmc_status ensure_P(qmc_walkers* wk, int e, hipStream_t stream, bool screen = true) {
   const SysDev& s = wk->sys->d;
   const bool up = e < s.nu;
   if (up && !wk->P_dn_valid) {
@@ -898,6 +908,11 @@ static qmc_status ensure_P(qmc_walkers* wk, int e, hipStream_t stream) {
   } else if (!up && !wk->P_up_valid) {
     TIMED(wk, QMC_T_P_REBUILD, stream, rebuild_P(wk, 1, stream), "P_up rebuild");
     wk->P_up_valid = true;
+  }
+  const int h = up ? 1 : 0;
+  if (screen && s.screened() && !wk->PT_ok[h]) {
+    TIMED(wk, QMC_T_OTHER, stream, launch_pt_build(s, wk->d, h, stream), "transposed rows");
+    wk->PT_ok[h] = true;
   }
   return QMC_OK;
 }
@@ -924,7 +939,7 @@ extern "C" qmc_status qmc_propose_move(qmc_system* sys, qmc_walkers* wk, int32_t
   }
   c = before_propose(wk, electron, stream);
   if (c) return c;
-  c = ensure_P(wk, electron, stream);
+  c = ensure_P(wk, electron, stream, drift_new == nullptr);
   if (c) return c;
   TIMED(wk, QMC_T_PROPOSE_PREP, stream,
         launch_propose_prep(s, wk->d, electron, r_new, nullptr, drift_new != nullptr, stream), "propose prep");
@@ -1220,7 +1235,7 @@ extern "C" qmc_status qmc_walkers_read(qmc_walkers* wk, int32_t item, double* ds
       return QMC_OK;
     case QMC_STATE_RESIDUAL: src = wk->res_v; bytes = sizeof(double) * Wk; break;
     case QMC_STATE_KEPT:
-      if (!s.screened()) return fail(QMC_ERR_ARG, "QMC_STATE_KEPT needs a QMC_REFINED system");
+      if (!s.oz_rows()) return fail(QMC_ERR_ARG, "QMC_STATE_KEPT needs a QMC_REFINED system");
       HIP_TRY(launch_export_kept(d, dst, stream), "export kept counts");
       return QMC_OK;
     default: return fail(QMC_ERR_ARG, "unknown state item");
@@ -1464,7 +1479,7 @@ struct qmc_multi {
   int grid_rows = 2048, grid_items = 1024;
   int nc = 1;
   int store = 0;        // 0 FP64, 1 FP32, 2 BF16 rows
-  size_t scr_lds = 0;   // QMC_REFINED members: dynamic LDS of the screened streams (0: other modes)
+  size_t scr_lds = 0;   // FP64 rows: dynamic LDS of the screened streams (0: other modes)
   hipStream_t own = nullptr;
   hipEvent_t ev_a = nullptr, ev_b = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -1483,7 +1498,7 @@ static hipError_t multi_build_rows(qmc_multi* m) {
   std::vector<int4> items;
   for (int k : m->order) {
     const SysDev& s = m->h_sys[k];
-    // (QMC_REFINED: one screened stream per walker)
+    // (FP64 rows: one screened stream per walker)
     const int S = s.screened() ? 1 : (s.nu + m->rows[k] - 1) / m->rows[k];
     for (int w = 0; w < m->h_wk[k].Wk; ++w)
       for (int sb = 0; sb < S; ++sb) items.push_back(make_int4(k, w, sb, S));
@@ -1601,17 +1616,22 @@ static hipError_t multi_upload(qmc_multi* m) {
 struct MemberState {
   Sched q;
   char up_ok, dn_ok;   // P halves valid
+  char pt_ok[2];       // their transposed rows (screened proposals)
 };
 
 // One member's host-side plan for its next step: electron, P half to rebuild
-// (0 none, 1 up, 2 down), refreshes before the proposal and after the accept.
+// (0 none, 1 up, 2 down), half to transpose likewise, refreshes before the proposal and after the accept.
 // The same rules as the one-system path (sched_before / ensure_P / sched_after).
-static void plan_member(const SysDev& s, MemberState& st, int& pbuild, bool& pre, bool& post) {
+static void plan_member(const SysDev& s, MemberState& st, int& pbuild, int& ptbuild, bool& pre, bool& post) {
   const int e = (int)(st.q.attempts % s.N);
   pre = sched_before(s, st.q, e);
   pbuild = 0;
   if (e < s.nu && !st.dn_ok) { pbuild = 2; st.dn_ok = 1; }
   else if (e >= s.nu && !st.up_ok) { pbuild = 1; st.up_ok = 1; }
+  if (pbuild) st.pt_ok[pbuild - 1] = s.oz_rows();   // (QMC_REFINED: written by the build itself)
+  const int h = e < s.nu ? 1 : 0;
+  ptbuild = s.screened() && !st.pt_ok[h] ? h + 1 : 0;
+  if (ptbuild) st.pt_ok[h] = 1;
   if (e < s.nu) st.up_ok = 0; else st.dn_ok = 0;
   post = sched_after(s, st.q);
 }
@@ -1634,20 +1654,24 @@ static hipError_t multi_enqueue(qmc_multi* m, int n_steps, bool explicit_draws, 
     a.t = t;
     unsigned pre_mask = 0, post_mask = 0;
     for (int k = 0; k < m->n; ++k) {
-      int pb;
+      int pb, ptb;
       bool pre, post;
-      plan_member(m->h_sys[k], st[k], pb, pre, post);
+      plan_member(m->h_sys[k], st[k], pb, ptb, pre, post);
       if (pb) {
         const SysDev& sk = m->h_sys[k];
         const WalkDev& wkd = m->h_wk[k];
         hipError_t r;
-        if (sk.screened()) {   // the refined rows with their transposes and column maxima
+        if (sk.oz_rows()) {   // the refined rows with their transposes and column maxima
           r = launch_P_build_oz(sk, wkd, pb, (const double*)wkd.phi, (double*)wkd.P, nullptr, false, m->own, false,
                                 wkd.PT, 0);
           if (r == hipSuccess) r = launch_screen_colmax(sk, wkd, pb, m->own);
         } else {
           r = launch_P_build(sk, wkd, pb, m->own);
         }
+        if (r != hipSuccess) return r;
+      }
+      if (ptb) {
+        const hipError_t r = launch_pt_build(m->h_sys[k], m->h_wk[k], ptb - 1, m->own);
         if (r != hipSuccess) return r;
       }
       if (pre) pre_mask |= 1u << k;
@@ -1695,7 +1719,8 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
   std::vector<MemberState> st(m->n);
   for (int k = 0; k < m->n; ++k) {
     const qmc_walkers* w = m->wk[k];
-    st[k] = MemberState{Sched{w->attempts, w->since, w->buf_spin}, (char)w->P_up_valid, (char)w->P_dn_valid};
+    st[k] = MemberState{Sched{w->attempts, w->since, w->buf_spin}, (char)w->P_up_valid, (char)w->P_dn_valid,
+                        {(char)w->PT_ok[0], (char)w->PT_ok[1]}};
   }
   if (use_graph) {
     // the captured schedule is determined by each member's electron phase,
@@ -1706,7 +1731,7 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
       const SysDev& s = m->h_sys[k];
       key += ":" + std::to_string(st[k].q.attempts % s.N) + "," + std::to_string(st[k].q.since) + "," +
              std::to_string(st[k].q.buf_spin) + "," + std::to_string((int)st[k].up_ok) +
-             std::to_string((int)st[k].dn_ok) + "," + std::to_string(m->rows[k]);
+             std::to_string((int)st[k].dn_ok) + std::to_string((int)st[k].pt_ok[0]) + std::to_string((int)st[k].pt_ok[1]) + "," + std::to_string(m->rows[k]);
     }
     std::vector<MemberState> st2 = st;
     if (!m->gexec || key != m->gkey) {
@@ -1725,9 +1750,9 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
       // replay: the schedule is the captured one; advance the host state the same way
       for (int t = 0; t < n_steps; ++t)
         for (int k = 0; k < m->n; ++k) {
-          int pb;
+          int pb, ptb;
           bool pre, post;
-          plan_member(m->h_sys[k], st2[k], pb, pre, post);
+          plan_member(m->h_sys[k], st2[k], pb, ptb, pre, post);
         }
     }
     HIP_TRY(hipGraphLaunch(m->gexec, m->own), "graph launch");
@@ -1742,6 +1767,8 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     w->buf_spin = st[k].q.buf_spin;
     w->P_up_valid = st[k].up_ok;
     w->P_dn_valid = st[k].dn_ok;
+    w->PT_ok[0] = st[k].pt_ok[0];
+    w->PT_ok[1] = st[k].pt_ok[1];
   }
   HIP_TRY(hipEventRecord(m->ev_b, m->own), "event");
   HIP_TRY(hipStreamWaitEvent(stream, m->ev_b, 0), "wait");
