@@ -480,8 +480,10 @@ qmc_status qmc_multi_autotune(qmc_multi *m, int32_t *rows, int32_t *grid, hipStr
  * member's move count, walker and member index; see qmc_philox_draws).
  * use_graph != 0 (Philox draws only): the whole n_steps sequence is captured
  * once into a HIP graph and replayed by later calls in the same phase (move
- * counts modulo N_k and refresh_every, cached basis products).  Members must
- * have been evaluated. */
+ * counts modulo N_k and refresh_every, cached basis products); members with
+ * FP64 rows (QMC_FP64, QMC_REFINED) run as few launches each, on streams of
+ * their own, and are launched directly either way.  Members must have been
+ * evaluated. */
 qmc_status qmc_multi_vmc_steps(qmc_multi *m, int32_t n_steps, const double *const *disp,
                                const double *const *unif, uint64_t seed, double sigma, int32_t use_graph,
                                hipStream_t stream);

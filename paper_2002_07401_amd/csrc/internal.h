@@ -44,6 +44,16 @@ constexpr int kOzSlices = 7;      // digits used by the refined evaluation (erro
 // in an 8-bohr cube, L = 44) between the two.
 constexpr double kScreenTolRefined = 1e-13, kScreenTolF64 = 1e-19;
 
+// A launch that records ev_start / ev_stop in its own dispatch when they are
+// given (include <hip/hip_ext.h>), and is an ordinary one otherwise.
+#define QMC_LAUNCH_EV(kernel, grid, blk, lds, st, ev_start, ev_stop, ...)                              \
+  do {                                                                                                 \
+    if ((ev_start) || (ev_stop))                                                                       \
+      hipExtLaunchKernelGGL(kernel, grid, blk, lds, st, ev_start, ev_stop, 0, __VA_ARGS__);            \
+    else                                                                                               \
+      hipLaunchKernelGGL(kernel, grid, blk, lds, st, __VA_ARGS__);                                     \
+  } while (0)
+
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
 // Record msg as this host thread's last error (qmc_last_error) and return st.
@@ -315,7 +325,7 @@ struct AdjWork {
   int chunk_walkers;
   int chunks;
 };
-// Arguments of the persistent multi-system phase kernels.
+// Arguments of the persistent multi-system phase kernels (FP32 / BF16 rows).
 struct MultiArgs {
   const SysDev* sysv;             // [members] device copies
   const WalkDev* wkv;             // [members]
@@ -328,13 +338,14 @@ struct MultiArgs {
   double sigma;                   // displacement width
 };
 hipError_t launch_multi_prep(const MultiArgs& a, const int2* items, int n_items, int grid, hipStream_t st);
-// screened_lds > 0: QMC_REFINED members (the screened streams, with that much
-// dynamic LDS)
 hipError_t launch_multi_rows(const MultiArgs& a, int store, int nc, const int4* items, int n_items, int grid,
-                             hipStream_t st, size_t screened_lds = 0);
+                             hipStream_t st);
 hipError_t launch_multi_accept(const MultiArgs& a, int store, const int2* items, int n_items, int grid,
                                hipStream_t st);
 hipError_t launch_multi_advance(long long* steps, int n, hipStream_t st);
+// The draws of `steps` steps from step *step0 + t0 on: disp [steps][Wk][3], unif [steps][Wk]
+hipError_t launch_philox_steps(unsigned long long seed, int member, int Wk, const long long* step0, int t0, int steps,
+                               double sigma, double* disp, double* unif, hipStream_t st);
 hipError_t launch_philox_draws(unsigned long long seed, int member, int Wk, unsigned long long step, double sigma,
                                double* disp, double* unif, hipStream_t st);
 
@@ -385,7 +396,9 @@ constexpr int kSlaterBit = 16;
 __device__ __forceinline__ int kind_ang(int kind) { return kind & (kSlaterBit - 1); }
 
 __device__ __forceinline__ double radial_e(int kind, double zt, double q) {
-  return (kind & kSlaterBit) ? exp(-zt * sqrt(q)) : exp(-zt * q);
+  double x = q;
+  if (kind & kSlaterBit) x = sqrt(q);
+  return exp(-zt * x);
 }
 
 struct Radial { double e, h1, h2, cl, gl, zp, zq, dcl; };
@@ -547,6 +560,38 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// Maximum of a 64-bit key over the wave, in every lane: within each row of 16
+// lanes by register-to-register DPP moves (quad_perm [1,0,3,2], [2,3,0,1],
+// row_ror:4, row_ror:8: every lane ends with its row's maximum), then over the
+// four rows' lanes 0, 16, 32, 48 through scalar reads.  A maximum does not
+// depend on the order, so this equals the butterfly over the whole wave; it
+// needs no LDS round trip per stage (a Gauss-Jordan step was 7 % faster).
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)v, CTRL, 0xF, 0xF, false);
+  const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(v >> 32), CTRL, 0xF, 0xF, false);
+  return ((unsigned long long)hi << 32) | lo;
+}
+__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
+  unsigned long long u = dpp_u64<0xB1>(v);
+  v = u > v ? u : v;
+  u = dpp_u64<0x4E>(v);
+  v = u > v ? u : v;
+  u = dpp_u64<0x124>(v);
+  v = u > v ? u : v;
+  u = dpp_u64<0x128>(v);
+  v = u > v ? u : v;
+  unsigned long long m = 0ull;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, 16 * r);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 16 * r);
+    const unsigned long long x = ((unsigned long long)hi << 32) | lo;
+    m = x > m ? x : m;
+  }
+  return m;
+}
+
 // ---------------------------------------------------------------------------
 // launchers (all asynchronous on `st`)
 // ---------------------------------------------------------------------------
@@ -596,8 +641,6 @@ inline int pt_pad(int n) {
     if (m / g <= 8) return m;
   }
 }
-// dynamic LDS of the blocked screened stream for a proposal of e (0: the plain one runs)
-size_t screened_stream_lds(const SysDev& s, const WalkDev& w, int e);
 // the unpaired orbitals' entries of every walker's transposed rows
 hipError_t launch_pt_unpaired(const SysDev& s, const WalkDev& w, hipStream_t st);
 hipError_t launch_export_kept(const WalkDev& w, double* dst, hipStream_t st);
@@ -671,6 +714,15 @@ bool sweep_segment_ok(const SysDev& s, const WalkDev& w, int e0);
 hipError_t launch_sweep_segment(const SysDev& s, const WalkDev& w, int e0, int k, const double* disp,
                                 const double* unif, int32_t* accept_count, int since0, hipStream_t st,
                                 hipEvent_t ev_start, hipEvent_t ev_stop);
+// Resident chain: `steps` Metropolis moves e0, e0 + 1, ... (mod N) of a small
+// system with every refresh and P rebuild between them, in one launch.
+// since0, buf_spin0, valid0 (P halves that hold, bit 0 up): the schedule state
+// at the start; Ainv [Wk][n][n]: the inverse there.  At the end A is the
+// inverse and the delayed-update buffer is empty.
+bool chain_ok(const SysDev& s, const WalkDev& w);
+hipError_t launch_chain(const SysDev& s, const WalkDev& w, int e0, int steps, const double* disp, const double* unif,
+                        int32_t* accept_count, int since0, int buf_spin0, int valid0, bool all_rows, const double* Ainv,
+                        hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
 hipError_t launch_refresh_finish(const SysDev& s, const WalkDev& w, int32_t* status, hipStream_t st);
 // max |W X - I| per walker (P = W X given) and status 3 where it exceeds tol
 hipError_t launch_refresh_residual(const double* Pm, int n, int Wk, double tol, double* res, int32_t* status,

@@ -44,38 +44,6 @@ struct GjRowShared {
   int red_i[4];
 };
 
-// Maximum of a 64-bit key over the wave, in every lane: within each row of 16
-// lanes by register-to-register DPP moves (quad_perm [1,0,3,2], [2,3,0,1],
-// row_ror:4, row_ror:8: every lane ends with its row's maximum), then over the
-// four rows' lanes 0, 16, 32, 48 through scalar reads.  A maximum does not
-// depend on the order, so this equals the butterfly over the whole wave; it
-// needs no LDS round trip per stage (a Gauss-Jordan step was 7 % faster).
-template <int CTRL>
-__device__ __forceinline__ unsigned long long dpp_u64(unsigned long long v) {
-  const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)v, CTRL, 0xF, 0xF, false);
-  const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(v >> 32), CTRL, 0xF, 0xF, false);
-  return ((unsigned long long)hi << 32) | lo;
-}
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long v) {
-  unsigned long long u = dpp_u64<0xB1>(v);
-  v = u > v ? u : v;
-  u = dpp_u64<0x4E>(v);
-  v = u > v ? u : v;
-  u = dpp_u64<0x124>(v);
-  v = u > v ? u : v;
-  u = dpp_u64<0x128>(v);
-  v = u > v ? u : v;
-  unsigned long long m = 0ull;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, 16 * r);
-    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 16 * r);
-    const unsigned long long x = ((unsigned long long)hi << 32) | lo;
-    m = x > m ? x : m;
-  }
-  return m;
-}
-
 template <int NMAX>
 __device__ __forceinline__ void gj_row_body(const double* __restrict__ W, double* __restrict__ A, double* __restrict__ logdet,
                             double* __restrict__ detsign, int* __restrict__ singular, int n, GjRowShared& sm) {

@@ -134,14 +134,14 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
   const int vn = store == 0 ? 2 : (store == 1 ? 4 : 8);   // elements per 16-byte load
   const int chunks = (s.Lp + 64 * vn - 1) / (64 * vn);
 #define QMC_GEN(D)                                                                                         \
-  if (store == 2) hipExtLaunchKernelGGL((propose_rows_generic_kernel<bf16s, D>), grid, dim3(256), 0, st, ev_start, ev_stop, 0, s, w, e, S); \
-  else if (store == 1) hipExtLaunchKernelGGL((propose_rows_generic_kernel<float, D>), grid, dim3(256), 0, st, ev_start, ev_stop, 0, s, w, e, S); \
-  else hipExtLaunchKernelGGL((propose_rows_generic_kernel<double, D>), grid, dim3(256), 0, st, ev_start, ev_stop, 0, s, w, e, S);
+  if (store == 2) { QMC_LAUNCH_EV((propose_rows_generic_kernel<bf16s, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); } \
+  else if (store == 1) { QMC_LAUNCH_EV((propose_rows_generic_kernel<float, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); } \
+  else { QMC_LAUNCH_EV((propose_rows_generic_kernel<double, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); }
   if (drift) {
     QMC_GEN(true)
   } else if (chunks <= 8) {
 #define QMC_ROWS(T, NC) \
-    case NC: hipExtLaunchKernelGGL((propose_rows_kernel<T, NC>), grid, dim3(256), 0, st, ev_start, ev_stop, 0, s, w, e, S); break;
+    case NC: QMC_LAUNCH_EV((propose_rows_kernel<T, NC>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); break;
     if (store == 0) return hipErrorInvalidValue;   // FP64 proposals without a drift are screened
     if (store == 2) {
       switch (chunks) { QMC_ROWS(bf16s, 1) QMC_ROWS(bf16s, 2) QMC_ROWS(bf16s, 3) QMC_ROWS(bf16s, 4)
@@ -342,12 +342,6 @@ hipError_t launch_screen_colmax(const SysDev& s, const WalkDev& w, int halves, h
   return hipGetLastError();
 }
 
-size_t screened_stream_lds(const SysDev& s, const WalkDev& w, int e) {
-  int IPB = 0, FB = 0;
-  size_t lds = 0;
-  return screened_blk_config(s, w, e, IPB, FB, lds) ? lds : 0;
-}
-
 hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, double* ratio, bool finalize,
                                    hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!w.PT || !w.muk) return hipErrorInvalidValue;
@@ -356,13 +350,13 @@ hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, dou
   int IPB, FB;
   size_t lds;
   if (screened_blk_config(s, w, e, IPB, FB, lds)) {
-#define QMC_SBLK(I) case I: hipExtLaunchKernelGGL(propose_screened_blk_kernel<I>, grid, blk, lds, st, ev_start, ev_stop, 0, s, w, e, S, FB); break;
+#define QMC_SBLK(I) case I: QMC_LAUNCH_EV(propose_screened_blk_kernel<I>, grid, blk, lds, st, ev_start, ev_stop, s, w, e, S, FB); break;
     switch (IPB) { QMC_SBLK(1) QMC_SBLK(2) QMC_SBLK(3) QMC_SBLK(4) QMC_SBLK(5) QMC_SBLK(6) QMC_SBLK(7) QMC_SBLK(8) }
 #undef QMC_SBLK
   } else if (s.nu <= kBigMaxN) {
     const int chunks = (s.nu + 64 * kScreenRowsNB - 1) / (64 * kScreenRowsNB);
-    hipExtLaunchKernelGGL(propose_screened_kernel, dim3((unsigned)(w.Wk * chunks)), blk, 0, st, ev_start, ev_stop, 0, s, w,
-                          e, S, chunks);
+    QMC_LAUNCH_EV(propose_screened_kernel, dim3((unsigned)(w.Wk * chunks)), blk, 0, st, ev_start, ev_stop, s, w, e, S,
+                  chunks);
   } else return hipErrorNotSupported;
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || !finalize) return err;

@@ -69,8 +69,29 @@ hipError_t launch_philox_draws(unsigned long long seed, int member, int Wk, unsi
   return hipGetLastError();
 }
 
+// The same draws for many steps at once (one thread per step and walker): the
+// members that run as chains of their own (FP64 rows) take them from memory.
+__global__ void __launch_bounds__(256)
+philox_steps_kernel(unsigned long long seed, int member, int Wk, const long long* __restrict__ step0, int t0, int steps,
+                    double sigma, double* __restrict__ disp, double* __restrict__ unif) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= (long)steps * Wk) return;
+  double d[3], u;
+  metropolis_draw(seed, member, (int)(i % Wk), (unsigned long long)(*step0 + t0 + i / Wk), sigma, d, &u);
+  disp[3 * i] = d[0]; disp[3 * i + 1] = d[1]; disp[3 * i + 2] = d[2];
+  unif[i] = u;
+}
+
+hipError_t launch_philox_steps(unsigned long long seed, int member, int Wk, const long long* step0, int t0, int steps,
+                               double sigma, double* disp, double* unif, hipStream_t st) {
+  const long n = (long)steps * Wk;
+  hipLaunchKernelGGL(philox_steps_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, seed, member, Wk, step0, t0,
+                     steps, sigma, disp, unif);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
-// persistent phase kernels
+// persistent phase kernels (FP32 / BF16 rows)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void member_draw(const MultiArgs& a, int k, int w, int Wk, double d[3], double* u) {
   if (a.disp) {
@@ -127,38 +148,6 @@ __global__ void __launch_bounds__(256) multi_accept_kernel(MultiArgs a, const in
   }
 }
 
-// FP64 rows: one item per walker, the screened stream the lone
-// proposal would run (blocked with its LDS where screened_blk_config allows,
-// else the plain one), writing the S partial slots the accept sums.
-__global__ void __launch_bounds__(256) multi_screened_rows_kernel(MultiArgs a, const int4* __restrict__ items,
-                                                                  int n_items) {
-  extern __shared__ __align__(16) char dyn[];
-  for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
-    __syncthreads();
-    const int4 q = items[it];   // member, walker, 0, 1
-    const SysDev& s = a.sysv[q.x];
-    const WalkDev& wd = a.wkv[q.x];
-    const int e = (int)(a.steps[q.x] % s.N);
-    const int S = (s.nu + a.rows[q.x] - 1) / a.rows[q.x];
-    int IPB = 0, FB = 0;
-    size_t lds = 0;
-    if (screened_blk_config(s, wd, e, IPB, FB, lds)) {
-      switch (IPB) {
-        case 1: screened_stream_walker<1>(s, wd, q.y, e, S, FB, dyn); break;
-        case 2: screened_stream_walker<2>(s, wd, q.y, e, S, FB, dyn); break;
-        case 3: screened_stream_walker<3>(s, wd, q.y, e, S, FB, dyn); break;
-        case 4: screened_stream_walker<4>(s, wd, q.y, e, S, FB, dyn); break;
-        case 5: screened_stream_walker<5>(s, wd, q.y, e, S, FB, dyn); break;
-        case 6: screened_stream_walker<6>(s, wd, q.y, e, S, FB, dyn); break;
-        case 7: screened_stream_walker<7>(s, wd, q.y, e, S, FB, dyn); break;
-        default: screened_stream_walker<8>(s, wd, q.y, e, S, FB, dyn); break;
-      }
-    } else {
-      screened_rows_walker<2>(s, wd, q.y, e, S, 0);   // members have n_up <= 128: one chunk
-    }
-  }
-}
-
 __global__ void multi_advance_kernel(long long* steps, int n) {
   const int k = threadIdx.x;
   if (k < n) steps[k] += 1;
@@ -176,16 +165,12 @@ hipError_t launch_multi_prep(const MultiArgs& a, const int2* items, int n_items,
 }
 
 hipError_t launch_multi_rows(const MultiArgs& a, int store, int nc, const int4* items, int n_items, int grid,
-                             hipStream_t st, size_t screened_lds) {
-  if (screened_lds > 0) {
-    hipLaunchKernelGGL(multi_screened_rows_kernel, dim3(grid), dim3(256), screened_lds, st, a, items, n_items);
-    return hipGetLastError();
-  }
+                             hipStream_t st) {
 #define QMC_MR(T, NC) case NC: return rows_launch<T, NC>(a, items, n_items, grid, st);
   if (store == 2) {
     switch (nc) { QMC_MR(bf16s, 1) QMC_MR(bf16s, 2) QMC_MR(bf16s, 3) QMC_MR(bf16s, 4)
                   QMC_MR(bf16s, 5) QMC_MR(bf16s, 6) QMC_MR(bf16s, 7) QMC_MR(bf16s, 8) }
-  } else if (store == 1) {   // (FP64 rows are screened)
+  } else if (store == 1) {
     switch (nc) { QMC_MR(float, 1) QMC_MR(float, 2) QMC_MR(float, 3) QMC_MR(float, 4)
                   QMC_MR(float, 5) QMC_MR(float, 6) QMC_MR(float, 7) QMC_MR(float, 8) }
   }
@@ -196,8 +181,7 @@ hipError_t launch_multi_rows(const MultiArgs& a, int store, int nc, const int4* 
 hipError_t launch_multi_accept(const MultiArgs& a, int store, const int2* items, int n_items, int grid,
                                hipStream_t st) {
   if (store == 2) hipLaunchKernelGGL(multi_accept_kernel<bf16s>, dim3(grid), dim3(256), 0, st, a, items, n_items);
-  else if (store == 1) hipLaunchKernelGGL(multi_accept_kernel<float>, dim3(grid), dim3(256), 0, st, a, items, n_items);
-  else hipLaunchKernelGGL(multi_accept_kernel<double>, dim3(grid), dim3(256), 0, st, a, items, n_items);
+  else hipLaunchKernelGGL(multi_accept_kernel<float>, dim3(grid), dim3(256), 0, st, a, items, n_items);
   return hipGetLastError();
 }
 

@@ -148,6 +148,7 @@ struct qmc_walkers {
   double drift_tol = 1e-6;        // status 3 when the checked residual exceeds this
   bool evaluated = false;
   bool P_up_valid = false, P_dn_valid = false;
+  bool delayed = false;             // the delayed-update buffer may hold moves
   bool PT_ok[2] = {false, false};   // the transposed rows and column maxima of each P half hold
   // (QMC_REFINED) parameter generation at which each P half's rows were last
   // built with their positions recorded (-1: never): a later build of that
@@ -822,7 +823,10 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
             "P build");
       if (s.oz_rows())
         for (int h = 0; h < 2; ++h)
-          if ((halves >> h) & 1) wk->P_gen[h] = sys->generation;
+          if ((halves >> h) & 1) {
+            wk->P_gen[h] = sys->generation;
+            if (!((dirty >> h) & 1)) wk->PT_ok[h] = true;   // (a build of the moved rows leaves the others as they are)
+          }
       if (s.oz_rows())
         TIMED(wk, QMC_T_OTHER, stream, launch_screen_colmax(s, d, halves, stream), "column maxima");
     }
@@ -857,7 +861,8 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
   wk->lr_ready = false;
   wk->generation = sys->generation;
   wk->P_up_valid = wk->P_dn_valid = true;
-  wk->PT_ok[0] = wk->PT_ok[1] = s.oz_rows();
+  if (!s.oz_rows()) wk->PT_ok[0] = wk->PT_ok[1] = false;   // (their memory holds the cofactor rows)
+  wk->delayed = false;
   wk->attempts = 0;
   wk->since = 0;
   wk->buf_spin = -1;
@@ -893,7 +898,10 @@ static hipError_t rebuild_P(qmc_walkers* wk, int halves, hipStream_t stream) {
   if (e == hipSuccess) e = launch_screen_colmax(s, d, halves, stream);
   if (e == hipSuccess)
     for (int h = 0; h < 2; ++h)
-      if ((halves >> h) & 1) wk->P_gen[h] = wk->sys->generation;
+      if ((halves >> h) & 1) {
+        wk->P_gen[h] = wk->sys->generation;
+        if (!((dirty >> h) & 1)) wk->PT_ok[h] = true;
+      }
   return e;
 }
 
@@ -1002,6 +1010,7 @@ static hipError_t residual_before(const SysDev& s, qmc_walkers* wk, hipStream_t 
 }
 
 static hipError_t refresh(const SysDev& s, qmc_walkers* wk, int32_t* status, hipStream_t stream) {
+  wk->delayed = false;
   const bool check = status && wk->drift_tol >= 0.0;
   if (check) {
     hipError_t e = residual_before(s, wk, stream);
@@ -1031,6 +1040,7 @@ static qmc_status after_accept(qmc_walkers* wk, int e, int32_t* status, hipStrea
   const SysDev& s = wk->sys->d;
   if (e < s.nu) wk->P_up_valid = false; else wk->P_dn_valid = false;
   wk->pending_e = -1;
+  wk->delayed = true;
   Sched q{wk->attempts, wk->since, wk->buf_spin};
   const bool post = sched_after(s, q);
   wk->attempts = q.attempts;
@@ -1113,31 +1123,52 @@ static int fused_run(const qmc_walkers* wk, int e_start, int t, int n_steps) {
   return k;
 }
 
-extern "C" qmc_status qmc_vmc_steps(qmc_system* sys, qmc_walkers* wk, int32_t e_start, int32_t n_steps,
-                                    const double* disp, const double* unif, int32_t* accept_count,
-                                    hipStream_t stream) {
-  qmc_status c = check_pair(sys, wk);
-  if (c) return c;
-  const SysDev& s = sys->d;
-  if (!wk->evaluated) return fail(QMC_ERR_STATE, "vmc_steps before eval_batch");
-  if (wk->generation != sys->generation) return fail(QMC_ERR_STATE, "parameters changed since the last eval_batch");
-  if (!disp || !unif) return fail(QMC_ERR_ARG, "null random arrays");
-  if (n_steps < 0 || e_start < 0) return fail(QMC_ERR_ARG, "negative step count or electron");
-  if (s.pairing) {
-    wk->yt_valid = wk->lr_ready = false;
-    for (int t = 0; t < n_steps; ++t) {
-      const int e = (int)((e_start + (long)t) % s.N);
-      TIMED(wk, QMC_T_PROPOSE, stream,
-            launch_pf_propose(s, wk->d, e, nullptr, disp + (long)t * wk->d.Wk * 3, nullptr, nullptr, stream),
-            "Pfaffian proposal");
-      TIMED(wk, QMC_T_ACCEPT, stream,
-            launch_pf_accept(s, wk->d, e, nullptr, unif + (long)t * wk->d.Wk, accept_count, stream),
-            "Pfaffian Metropolis");
-      c = pf_after_accept(wk, nullptr, stream);
-      if (c) return c;
-    }
-    return QMC_OK;
+// The moves of a small system: the resident chain, then the same bookkeeping
+// as the per-move path's.
+static qmc_status chain_steps(qmc_walkers* wk, int32_t e_start, int32_t n_steps, const double* disp, const double* unif,
+                              int32_t* accept_count, hipStream_t stream) {
+  const SysDev& s = wk->sys->d;
+  if (n_steps == 0) return QMC_OK;
+  const double* Ainv = wk->d.A;
+  if (wk->delayed) {   // moves of the per-move path since the last refresh
+    TIMED(wk, QMC_T_OTHER, stream,
+          launch_materialize_inverse(s, wk->d, wk->buf_spin == 1, wk->rd_scratch, wk->res_x, stream), "current inverse");
+    Ainv = wk->res_x;
   }
+  const bool all = wk->P_gen[0] != wk->sys->generation || wk->P_gen[1] != wk->sys->generation;
+  hipEvent_t ea, eb;
+  HIP_TRY(wk->tm.begin_ext(QMC_T_SWEEP, &ea, &eb), "timer begin");
+  HIP_TRY(launch_chain(s, wk->d, (int)(e_start % s.N), n_steps, disp, unif, accept_count, wk->since, wk->buf_spin,
+                       (wk->P_up_valid ? 1 : 0) | (wk->P_dn_valid ? 2 : 0), all, Ainv, stream, ea, eb),
+          "resident chain");
+  wk->yt_valid = wk->lr_ready = false;
+  wk->delayed = false;
+  wk->pending_e = -1;
+  Sched q{wk->attempts, wk->since, wk->buf_spin};
+  for (int t = 0; t < n_steps; ++t) {
+    const int e = (int)((e_start + (long)t) % s.N);
+    sched_before(s, q, e);
+    bool& need = e < s.nu ? wk->P_dn_valid : wk->P_up_valid;
+    if (!need) {
+      need = true;
+      wk->P_gen[e < s.nu ? 1 : 0] = wk->sys->generation;
+      wk->PT_ok[e < s.nu ? 1 : 0] = false;   // (the chain rebuilds P alone)
+    }
+    if (e < s.nu) wk->P_up_valid = false; else wk->P_dn_valid = false;
+    sched_after(s, q);
+  }
+  wk->attempts = q.attempts;
+  wk->since = q.since;
+  wk->buf_spin = q.buf_spin;
+  return QMC_OK;
+}
+
+// n_steps Metropolis moves of a determinant system from electron e_start on.
+static qmc_status run_moves(qmc_walkers* wk, int32_t e_start, int32_t n_steps, const double* disp, const double* unif,
+                            int32_t* accept_count, hipStream_t stream) {
+  const SysDev& s = wk->sys->d;
+  if (chain_ok(s, wk->d)) return chain_steps(wk, e_start, n_steps, disp, unif, accept_count, stream);
+  qmc_status c;
   const long Wk = wk->d.Wk;
   bool prepped = false;   // the set-up of step t ran in step t-1's fused accept
   for (int t = 0; t < n_steps; ++t) {
@@ -1209,6 +1240,34 @@ extern "C" qmc_status qmc_vmc_steps(qmc_system* sys, qmc_walkers* wk, int32_t e_
     }
   }
   return QMC_OK;
+}
+
+extern "C" qmc_status qmc_vmc_steps(qmc_system* sys, qmc_walkers* wk, int32_t e_start, int32_t n_steps,
+                                    const double* disp, const double* unif, int32_t* accept_count,
+                                    hipStream_t stream) {
+  qmc_status c = check_pair(sys, wk);
+  if (c) return c;
+  const SysDev& s = sys->d;
+  if (!wk->evaluated) return fail(QMC_ERR_STATE, "vmc_steps before eval_batch");
+  if (wk->generation != sys->generation) return fail(QMC_ERR_STATE, "parameters changed since the last eval_batch");
+  if (!disp || !unif) return fail(QMC_ERR_ARG, "null random arrays");
+  if (n_steps < 0 || e_start < 0) return fail(QMC_ERR_ARG, "negative step count or electron");
+  if (s.pairing) {
+    wk->yt_valid = wk->lr_ready = false;
+    for (int t = 0; t < n_steps; ++t) {
+      const int e = (int)((e_start + (long)t) % s.N);
+      TIMED(wk, QMC_T_PROPOSE, stream,
+            launch_pf_propose(s, wk->d, e, nullptr, disp + (long)t * wk->d.Wk * 3, nullptr, nullptr, stream),
+            "Pfaffian proposal");
+      TIMED(wk, QMC_T_ACCEPT, stream,
+            launch_pf_accept(s, wk->d, e, nullptr, unif + (long)t * wk->d.Wk, accept_count, stream),
+            "Pfaffian Metropolis");
+      c = pf_after_accept(wk, nullptr, stream);
+      if (c) return c;
+    }
+    return QMC_OK;
+  }
+  return run_moves(wk, e_start, n_steps, disp, unif, accept_count, stream);
 }
 
 extern "C" qmc_status qmc_walkers_read(qmc_walkers* wk, int32_t item, double* dst, hipStream_t stream) {
@@ -1479,7 +1538,16 @@ struct qmc_multi {
   int grid_rows = 2048, grid_items = 1024;
   int nc = 1;
   int store = 0;        // 0 FP64, 1 FP32, 2 BF16 rows
-  size_t scr_lds = 0;   // FP64 rows: dynamic LDS of the screened streams (0: other modes)
+  // FP64 rows: each member runs as a chain of its own on its own stream, forked
+  // from and joined to the group's; Philox draws are filled for `draw_steps`
+  // steps at a time
+  struct Chain {
+    hipStream_t st = nullptr;
+    hipEvent_t done = nullptr;
+    double *disp = nullptr, *unif = nullptr;
+    int draw_steps = 0;
+  };
+  std::vector<Chain> chains;
   hipStream_t own = nullptr;
   hipEvent_t ev_a = nullptr, ev_b = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -1489,6 +1557,10 @@ struct qmc_multi {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (ev_a) (void)hipEventDestroy(ev_a);
     if (ev_b) (void)hipEventDestroy(ev_b);
+    for (auto& c : chains) {
+      if (c.st) { (void)hipStreamSynchronize(c.st); (void)hipStreamDestroy(c.st); }
+      if (c.done) (void)hipEventDestroy(c.done);
+    }
     if (own) { (void)hipStreamSynchronize(own); (void)hipStreamDestroy(own); }
     for (void* p : allocs) (void)hipFree(p);
   }
@@ -1498,8 +1570,7 @@ static hipError_t multi_build_rows(qmc_multi* m) {
   std::vector<int4> items;
   for (int k : m->order) {
     const SysDev& s = m->h_sys[k];
-    // (FP64 rows: one screened stream per walker)
-    const int S = s.screened() ? 1 : (s.nu + m->rows[k] - 1) / m->rows[k];
+    const int S = (s.nu + m->rows[k] - 1) / m->rows[k];
     for (int w = 0; w < m->h_wk[k].Wk; ++w)
       for (int sb = 0; sb < S; ++sb) items.push_back(make_int4(k, w, sb, S));
   }
@@ -1539,15 +1610,6 @@ extern "C" qmc_status qmc_multi_create(int32_t n_members, qmc_system* const* sys
     m->rows.push_back(s.prop_rows());
   }
   m->store = systems[0]->d.store();
-  if (systems[0]->d.screened()) {
-    // the largest LDS any member's blocked screened stream needs (both spins);
-    // at least the 1 KiB granule, so that the screened kernel is chosen
-    m->scr_lds = 1024;
-    for (int k = 0; k < n_members; ++k) {
-      const SysDev& s = m->h_sys[k];
-      for (int e : {0, s.N - 1}) m->scr_lds = std::max(m->scr_lds, screened_stream_lds(s, m->h_wk[k], e));
-    }
-  }
   m->order.resize(n_members);
   std::iota(m->order.begin(), m->order.end(), 0);
   std::stable_sort(m->order.begin(), m->order.end(), [&](int a, int b) {
@@ -1584,6 +1646,19 @@ extern "C" qmc_status qmc_multi_create(int32_t n_members, qmc_system* const* sys
   if (!e) e = hipEventCreateWithFlags(&m->ev_a, hipEventDisableTiming);
   if (!e) e = hipEventCreateWithFlags(&m->ev_b, hipEventDisableTiming);
   m->grid_rows = std::min(m->n_rows_items, 2048);
+  if (m->store == 0) {
+    m->chains.resize(n_members);
+    for (int k = 0; k < n_members; ++k) {
+      auto& c = m->chains[k];
+      const size_t Wk = m->h_wk[k].Wk;
+      // up to 256 steps' draws, 8 MiB (at least 32 steps) a member
+      c.draw_steps = (int)std::max<size_t>(32, std::min<size_t>(256, (size_t)8 * 1024 * 1024 / (32 * Wk)));
+      al((void**)&c.disp, sizeof(double) * 3 * Wk * c.draw_steps);
+      al((void**)&c.unif, sizeof(double) * Wk * c.draw_steps);
+      if (!e) e = hipStreamCreateWithFlags(&c.st, hipStreamNonBlocking);
+      if (!e) e = hipEventCreateWithFlags(&c.done, hipEventDisableTiming);
+    }
+  }
   if (e != hipSuccess) { delete m; return hip_fail(e, "multi_create"); }
   *out = m;
   return QMC_OK;
@@ -1616,22 +1691,17 @@ static hipError_t multi_upload(qmc_multi* m) {
 struct MemberState {
   Sched q;
   char up_ok, dn_ok;   // P halves valid
-  char pt_ok[2];       // their transposed rows (screened proposals)
 };
 
 // One member's host-side plan for its next step: electron, P half to rebuild
-// (0 none, 1 up, 2 down), half to transpose likewise, refreshes before the proposal and after the accept.
+// (0 none, 1 up, 2 down), refreshes before the proposal and after the accept.
 // The same rules as the one-system path (sched_before / ensure_P / sched_after).
-static void plan_member(const SysDev& s, MemberState& st, int& pbuild, int& ptbuild, bool& pre, bool& post) {
+static void plan_member(const SysDev& s, MemberState& st, int& pbuild, bool& pre, bool& post) {
   const int e = (int)(st.q.attempts % s.N);
   pre = sched_before(s, st.q, e);
   pbuild = 0;
   if (e < s.nu && !st.dn_ok) { pbuild = 2; st.dn_ok = 1; }
   else if (e >= s.nu && !st.up_ok) { pbuild = 1; st.up_ok = 1; }
-  if (pbuild) st.pt_ok[pbuild - 1] = s.oz_rows();   // (QMC_REFINED: written by the build itself)
-  const int h = e < s.nu ? 1 : 0;
-  ptbuild = s.screened() && !st.pt_ok[h] ? h + 1 : 0;
-  if (ptbuild) st.pt_ok[h] = 1;
   if (e < s.nu) st.up_ok = 0; else st.dn_ok = 0;
   post = sched_after(s, st.q);
 }
@@ -1654,24 +1724,11 @@ static hipError_t multi_enqueue(qmc_multi* m, int n_steps, bool explicit_draws, 
     a.t = t;
     unsigned pre_mask = 0, post_mask = 0;
     for (int k = 0; k < m->n; ++k) {
-      int pb, ptb;
+      int pb;
       bool pre, post;
-      plan_member(m->h_sys[k], st[k], pb, ptb, pre, post);
+      plan_member(m->h_sys[k], st[k], pb, pre, post);
       if (pb) {
-        const SysDev& sk = m->h_sys[k];
-        const WalkDev& wkd = m->h_wk[k];
-        hipError_t r;
-        if (sk.oz_rows()) {   // the refined rows with their transposes and column maxima
-          r = launch_P_build_oz(sk, wkd, pb, (const double*)wkd.phi, (double*)wkd.P, nullptr, false, m->own, false,
-                                wkd.PT, 0);
-          if (r == hipSuccess) r = launch_screen_colmax(sk, wkd, pb, m->own);
-        } else {
-          r = launch_P_build(sk, wkd, pb, m->own);
-        }
-        if (r != hipSuccess) return r;
-      }
-      if (ptb) {
-        const hipError_t r = launch_pt_build(m->h_sys[k], m->h_wk[k], ptb - 1, m->own);
+        const hipError_t r = launch_P_build(m->h_sys[k], m->h_wk[k], pb, m->own);
         if (r != hipSuccess) return r;
       }
       if (pre) pre_mask |= 1u << k;
@@ -1681,13 +1738,52 @@ static hipError_t multi_enqueue(qmc_multi* m, int n_steps, bool explicit_draws, 
     hipError_t r = multi_refresh(m, pre_mask);
     if (r == hipSuccess) r = launch_multi_prep(a, m->d_items, m->n_items, m->grid_items, m->own);
     if (r == hipSuccess)
-      r = launch_multi_rows(a, m->store, m->nc, m->d_rows_items, m->n_rows_items, m->grid_rows, m->own, m->scr_lds);
+      r = launch_multi_rows(a, m->store, m->nc, m->d_rows_items, m->n_rows_items, m->grid_rows, m->own);
     if (r == hipSuccess) r = launch_multi_accept(a, m->store, m->d_items, m->n_items, m->grid_items, m->own);
     if (r == hipSuccess) r = multi_refresh(m, post_mask);
     if (r == hipSuccess) r = launch_multi_advance(m->d_steps, m->n, m->own);
     if (r != hipSuccess) return r;
   }
   return hipSuccess;
+}
+
+// FP64 rows: every member's n_steps as a chain of its own (the one-system moves,
+// so a member evolves exactly as it would alone) on its own stream, between a
+// fork from the group's stream and a join to it.  A member alone leaves most of
+// the chip idle (256 walkers are one workgroup per compute unit, waiting on
+// their own dependent steps), and the members share no state, so their chains
+// overlap; in step with each other, phase by phase, they would wait for the
+// largest one in every launch.  Larger members are enqueued first.
+static qmc_status chains_enqueue(qmc_multi* m, int n_steps, bool expl, unsigned long long seed, double sigma) {
+  HIP_TRY(hipEventRecord(m->ev_b, m->own), "fork");
+  qmc_status c = QMC_OK;
+  for (int k : m->order) {
+    auto& ch = m->chains[k];
+    qmc_walkers* w = m->wk[k];
+    HIP_TRY(hipStreamWaitEvent(ch.st, m->ev_b, 0), "fork");
+    const int N = w->sys->d.N;
+    const bool timed = w->tm.on;
+    w->tm.on = false;   // (group moves are not timed)
+    if (expl) {
+      c = run_moves(w, (int)(w->attempts % N), n_steps, m->h_disp[k], m->h_unif[k], nullptr, ch.st);
+    } else {
+      for (int t = 0; t < n_steps && !c; t += ch.draw_steps) {
+        const int steps = std::min(ch.draw_steps, n_steps - t);
+        const hipError_t e =
+            launch_philox_steps(seed, k, w->d.Wk, m->d_steps + k, t, steps, sigma, ch.disp, ch.unif, ch.st);
+        c = e != hipSuccess ? hip_fail(e, "draws")
+                            : run_moves(w, (int)(w->attempts % N), steps, ch.disp, ch.unif, nullptr, ch.st);
+      }
+    }
+    w->tm.on = timed;
+    // joined whatever happened, so that the group's stream never leaves a
+    // member's work behind
+    const hipError_t e1 = hipEventRecord(ch.done, ch.st);
+    const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(m->own, ch.done, 0) : e1;
+    if (c) return c;
+    HIP_TRY(e2, "join");
+  }
+  return c;
 }
 
 extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const double* const* disp,
@@ -1716,11 +1812,17 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     HIP_TRY(hipMemcpyAsync(m->d_disp, m->h_disp.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
     HIP_TRY(hipMemcpyAsync(m->d_unif, m->h_unif.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
   }
+  if (m->store == 0) {
+    const qmc_status c = chains_enqueue(m, n_steps, expl, seed, sigma);
+    if (c) return c;
+    HIP_TRY(hipEventRecord(m->ev_b, m->own), "event");
+    HIP_TRY(hipStreamWaitEvent(stream, m->ev_b, 0), "wait");
+    return QMC_OK;
+  }
   std::vector<MemberState> st(m->n);
   for (int k = 0; k < m->n; ++k) {
     const qmc_walkers* w = m->wk[k];
-    st[k] = MemberState{Sched{w->attempts, w->since, w->buf_spin}, (char)w->P_up_valid, (char)w->P_dn_valid,
-                        {(char)w->PT_ok[0], (char)w->PT_ok[1]}};
+    st[k] = MemberState{Sched{w->attempts, w->since, w->buf_spin}, (char)w->P_up_valid, (char)w->P_dn_valid};
   }
   if (use_graph) {
     // the captured schedule is determined by each member's electron phase,
@@ -1731,7 +1833,7 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
       const SysDev& s = m->h_sys[k];
       key += ":" + std::to_string(st[k].q.attempts % s.N) + "," + std::to_string(st[k].q.since) + "," +
              std::to_string(st[k].q.buf_spin) + "," + std::to_string((int)st[k].up_ok) +
-             std::to_string((int)st[k].dn_ok) + std::to_string((int)st[k].pt_ok[0]) + std::to_string((int)st[k].pt_ok[1]) + "," + std::to_string(m->rows[k]);
+             std::to_string((int)st[k].dn_ok) + "," + std::to_string(m->rows[k]);
     }
     std::vector<MemberState> st2 = st;
     if (!m->gexec || key != m->gkey) {
@@ -1750,9 +1852,9 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
       // replay: the schedule is the captured one; advance the host state the same way
       for (int t = 0; t < n_steps; ++t)
         for (int k = 0; k < m->n; ++k) {
-          int pb, ptb;
+          int pb;
           bool pre, post;
-          plan_member(m->h_sys[k], st2[k], pb, ptb, pre, post);
+          plan_member(m->h_sys[k], st2[k], pb, pre, post);
         }
     }
     HIP_TRY(hipGraphLaunch(m->gexec, m->own), "graph launch");
@@ -1767,8 +1869,7 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     w->buf_spin = st[k].q.buf_spin;
     w->P_up_valid = st[k].up_ok;
     w->P_dn_valid = st[k].dn_ok;
-    w->PT_ok[0] = st[k].pt_ok[0];
-    w->PT_ok[1] = st[k].pt_ok[1];
+    w->delayed = true;
   }
   HIP_TRY(hipEventRecord(m->ev_b, m->own), "event");
   HIP_TRY(hipStreamWaitEvent(stream, m->ev_b, 0), "wait");
@@ -1780,6 +1881,11 @@ extern "C" qmc_status qmc_multi_autotune(qmc_multi* m, int32_t* rows_out, int32_
   for (int k = 0; k < m->n; ++k)
     if (!m->wk[k]->evaluated) return fail(QMC_ERR_STATE, "member not evaluated");
   HIP_TRY(hipStreamSynchronize(stream), "sync");
+  if (m->store == 0) {   // (FP64 rows: the members' chains have nothing to choose)
+    if (rows_out) *rows_out = m->rows[0];
+    if (grid_out) *grid_out = m->grid_rows;
+    return QMC_OK;
+  }
   HIP_TRY(multi_upload(m), "upload");
   MultiArgs a{m->d_sys, m->d_wk, m->d_steps, m->d_rows, nullptr, nullptr, 0, 12345ULL, 0.3};
   hipEvent_t e0, e1;
@@ -1798,10 +1904,10 @@ extern "C" qmc_status qmc_multi_autotune(qmc_multi* m, int32_t* rows_out, int32_
     if (err != hipSuccess) break;
     for (int g : cand_grid) {
       const int grid = std::min(g, m->n_rows_items);
-      err = launch_multi_rows(a, m->store, m->nc, m->d_rows_items, m->n_rows_items, grid, m->own, m->scr_lds);
+      err = launch_multi_rows(a, m->store, m->nc, m->d_rows_items, m->n_rows_items, grid, m->own);
       if (err == hipSuccess) err = hipEventRecord(e0, m->own);
       for (int rep = 0; rep < 5 && err == hipSuccess; ++rep)
-        err = launch_multi_rows(a, m->store, m->nc, m->d_rows_items, m->n_rows_items, grid, m->own, m->scr_lds);
+        err = launch_multi_rows(a, m->store, m->nc, m->d_rows_items, m->n_rows_items, grid, m->own);
       if (err == hipSuccess) err = hipEventRecord(e1, m->own);
       if (err == hipSuccess) err = hipEventSynchronize(e1);
       float ms = 0.f;

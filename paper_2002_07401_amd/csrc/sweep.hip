@@ -118,8 +118,8 @@ hipError_t launch_sweep_segment(const SysDev& s, const WalkDev& w, int e0, int k
   const size_t lds = stage_layout(n, kb, mcl, o.vec_min).total;   // >= vec_min >= the stream's region
   const dim3 grid(w.Wk), blk(256);
 #define QMC_SWEEP(Q, I)                                                                                        \
-  hipExtLaunchKernelGGL((sweep_segment_kernel<Q, I>), grid, blk, lds, st, ev_start, ev_stop, 0, s, w, e0, k,  \
-                        disp, unif, accept_count, S, FB, since0, mcl, (int)o.vec_min)
+  QMC_LAUNCH_EV((sweep_segment_kernel<Q, I>), grid, blk, lds, st, ev_start, ev_stop, s, w, e0, k, disp, unif, \
+                accept_count, S, FB, since0, mcl, (int)o.vec_min)
 #define QMC_SWEEP_IPB(Q)                                                        \
   switch (IPB) {                                                                \
     case 1: QMC_SWEEP(Q, 1); break; case 2: QMC_SWEEP(Q, 2); break;             \
