@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqmc_jagp.so")
-SOURCES = ["qmc_abi.hip", "gemm.hip", "linalg.hip", "eval.hip", "move.hip", "sweep.hip", "chain.hip", "adjoint.hip", "multi.hip",
+SOURCES = ["qmc_abi.hip", "gemm.hip", "linalg.hip", "eval.hip", "move.hip", "chain.hip", "adjoint.hip", "multi.hip",
            "lrdmc.hip", "jas3.hip", "estimators.hip", "pfaff.hip", "ozaki.hip"]
 ARCH = os.environ.get("QMC_OFFLOAD_ARCH", "gfx950")
 
@@ -21,9 +21,10 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wno-unused-result",
 ]
-# per-source additions: the move loops of the persistent sweep and the resident
-# chain are compiled without machine loop-invariant code motion (see sweep.hip)
-EXTRA = {"sweep.hip": ["-mllvm", "-disable-machine-licm"], "chain.hip": ["-mllvm", "-disable-machine-licm"]}
+# per-source additions: the resident move loop is compiled without machine
+# loop-invariant code motion, which would hold every phase's constants and
+# addresses in registers across the loop, past the 256 VGPRs of two waves a SIMD
+EXTRA = {"chain.hip": ["-mllvm", "-disable-machine-licm"]}
 NOISE = "is not a recognized feature for this target"
 
 

@@ -1,25 +1,41 @@
-// Resident chain: a whole run of Metropolis moves of a small system in one
-// launch, one workgroup per walker, refreshes, changes of spin and P rebuilds
-// included.
+// Resident moves: one workgroup per walker makes a run of Metropolis moves with
+// the walker's moving state in LDS.
 //
-// What bounds small systems is latency: with a launch per phase a move of 20
-// electrons is some thirty dependent trips to memory (25.7 us a move at 256
-// walkers x 20 e, L = 44 with a Jastrow basis, 2.1 ms of a 2.9 ms run of 100
-// moves; the arithmetic of a move is well under 1 us).  Nothing in a move
-// leaves its walker, so one workgroup keeps the walker's state in LDS and the
-// moves follow each other with two barriers for a rejected move and four for
-// an accepted one:
-//   draws (64 steps at a time), positions, nuclei, the Jastrow basis state;
-//   the streamed half of P transposed, PT[mu][j] (all of it is read: at these
-//   sizes the screening would cost more than the skipped columns);
+// What bounds the moves is latency and, for large walker sets, the stream of P.
+// With a launch per phase a move of 20 electrons was some thirty dependent trips
+// to memory (25.7 us a move at 256 walkers x 20 e, L = 44 with a Jastrow basis;
+// the arithmetic of a move is well under 1 us).  A run in one launch that staged
+// the delayed-update buffers anew for every move took 36 us a move at 1024
+// walkers x 160 e, 27 us at 256 walkers x 256 e (one workgroup per compute unit,
+// waiting on its own dependent steps).  Nothing in a move leaves its walker, so
+// here a workgroup holds in LDS
 //   the inverse itself in the orientation of the moving spin, B = W^{-1} for up
-//   moves, its transpose for down moves, so that both spins read column e and
-//   update by the same Sherman-Morrison step
-//     R = sum_j w_j B[j][e],  B[j][k] -= B[j][e] (sum_i w_i B[i][k] - delta_ek) / R.
-// W's row or column, the basis row and (at a rebuild) the P rows go to the
-// walker's arrays in global memory, which hold the usual state at the end with
-// an empty delayed-update buffer.  The refresh and rebuild schedule is that of
-// the per-move path.
+//   moves, its transpose for down moves: both spins read column e and update by
+//   the same Sherman-Morrison step
+//     R = sum_j w_j B[j][e],  B[j][k] -= B[j][e] (sum_i w_i B[i][k] - delta_ek) / R,
+//   a column read and an n x n update in place of the chains of dependent
+//   products of the delayed form;
+//   positions, nuclei, the Jastrow basis state and the draws of 64 steps.
+// A wave computes psi(r') of its own basis functions, lists those it keeps and
+// streams their columns of the transposed P rows without waiting for the other
+// waves; the waves meet once for a rejected move (the sums of w and of the
+// Jastrow change) and twice more for an accepted one.  Columns are read a row
+// pair a lane, several functions a load where n is small, 12 loads in flight.
+//
+// Two forms, chosen by size (chain_class):
+//   small   (W of at most 64 rows, a half of P in LDS, 80 KiB in all): the
+//           refreshes, changes of spin and P rebuilds run in the kernel too, so
+//           any number of moves is one launch; every function is streamed (from
+//           LDS, where screening would cost more than it saves).
+//   large   (W of at most 128 rows): the transposed rows stay in global memory
+//           and are screened; a launch ends where the schedule refreshes or
+//           changes spin.  Walkers past two (n <= 90) or one per compute unit
+//           wait for the first ones to finish their run, which keeps the rows in
+//           use within the 256 MB last-level cache.  Single proposals and accepts
+//           of these systems are the same code with one move (bitwise).
+// W's row or column and the basis row (and in the small form P's rows) go to the
+// walker's arrays in global memory; at the end they hold the usual state with an
+// empty delayed-update buffer.  The schedule is that of the per-move path.
 #include <hip/hip_ext.h>
 
 #include "internal.h"
@@ -27,13 +43,18 @@
 
 namespace qmc {
 
-constexpr int kChainT = 256;        // threads
-constexpr int kChainMaxN = 64;      // rows of W (one per lane)
-constexpr int kChainDraws = 64;     // steps whose draws are staged together
-constexpr int kChainMaxLds = 80 * 1024;   // two workgroups per compute unit
+constexpr int kChainT = 256;               // threads
+constexpr int kChainMaxN = 128;            // rows of W: two a lane
+constexpr int kChainSmallN = 64;           // rows of a rebuild: four matrix tiles
+constexpr int kChainDraws = 32;            // steps whose draws are staged together
+constexpr int kChainU = 12;                // column loads in flight per wave
+constexpr int kChainG = 8;                 // row groups of an n x n pass
+constexpr int kChainLogs = 32;             // accepted moves whose logarithms are taken together
+constexpr int kChainSmallLds = 80 * 1024;  // two workgroups per compute unit
+constexpr int kChainMaxLds = 160 * 1024;
 
 struct ChainLayout {   // byte offsets in LDS
-  int area, B, psi, r, nuc, draw, red, part, pu, list, prow, chi, hv, G, jm, chin, jb, jk, M3, total;
+  int area, B, lv, lm, r, nuc, draw, red, part, ws, cs, lg, list, prow, chi, hv, G, jm, chin, jb, jk, M3, total;
 };
 
 struct ChainArgs {
@@ -42,31 +63,47 @@ struct ChainArgs {
   int since0, buf_spin0;    // schedule state at the start
   int valid0;               // P halves that hold (bit 0 up, 1 down)
   int all_rows;             // rebuild every row of a half, not only the moved ones
+  int store_A;              // write the inverse back (0: a refresh follows)
   const double* Ainv;       // [Wk][n][n] the inverse at the start
-  const double* disp;       // [steps][Wk][3]
+  const double* disp;       // [steps][Wk][3] (propose: null)
   const double* unif;       // [steps][Wk]
+  const double* r_new;      // propose: [Wk][3]
+  double* ratio_out;        // propose: [Wk]
+  const uint8_t* acc;       // accept: [Wk]
   int32_t* cnt;             // [Wk] or null
-  int area_bytes;
+  int groups, pst;          // row groups of an n x n pass; doubles of one move's partial sums
+  int area_bytes, cw, lsh, nuc_lds;   // P area, list entries a wave, log2 of the lanes a column takes, nuclei in LDS
   ChainLayout ly;
 };
 
-static ChainLayout chain_layout(const SysDev& s, int& area_bytes) {
+// leading dimension of B: even (column pairs), and a column's entries over
+// different banks
+__host__ __device__ inline int chain_ld(int n) { return (n + 1) / 2 * 2 + 2; }
+
+static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a) {
   ChainLayout o{};
-  const int n = s.nu, ld = n | 1, f8 = 8;
-  area_bytes = f8 * std::max(s.ptn * s.Lp, 16 * (s.Lp + 2));
+  const int n = s.nu, ld = chain_ld(n), f8 = 8;
+  a.area_bytes = small ? f8 * std::max(s.ptn * s.Lp, 16 * (s.Lp + 2)) : 0;
+  a.cw = 64 * ((s.L + kChainT - 1) / kChainT);
+  a.lsh = 2;
+  while ((2 << a.lsh) < s.ptn) ++a.lsh;
   int at = 0;
   auto take = [&](int& p, int bytes) { p = at; at += (bytes + 15) / 16 * 16; };
-  take(o.area, area_bytes);
+  take(o.area, a.area_bytes);
   take(o.B, f8 * n * ld);
-  take(o.psi, f8 * s.Lp);
+  take(o.lv, f8 * 4 * a.cw);
+  take(o.lm, 2 * 4 * a.cw);
   take(o.r, f8 * 3 * s.N);
-  take(o.nuc, f8 * 5 * s.n_nuc);
   take(o.draw, f8 * 4 * kChainDraws);
   take(o.red, f8 * 16);   // partial sums of two moves, the two-body parameters
-  take(o.part, f8 * 4 * kChainMaxN);
-  take(o.pu, f8 * 4 * kChainMaxN);
-  take(o.list, 4 * (kChainMaxN + 1));
-  take(o.prow, 4 * kChainMaxN);
+  a.groups = std::min(kChainT / ((n + 1) / 2), kChainG);
+  a.pst = std::max(4 * s.ptn, a.groups * s.ptn);
+  take(o.part, f8 * std::max(2 * a.pst, 2 * kChainSmallN));   // (and two pivot columns of a refresh)
+  take(o.ws, f8 * (n + 1));
+  take(o.cs, f8 * (n + 1));
+  take(o.lg, f8 * 2 * kChainLogs);
+  take(o.prow, 4 * (small ? kChainSmallN : 4));
+  if (small) take(o.list, 4 * (kChainSmallN + 1));
   if (s.LJ > 0) {
     take(o.chi, f8 * s.N * s.LJ);
     take(o.hv, f8 * s.N * s.LJ);
@@ -77,31 +114,70 @@ static ChainLayout chain_layout(const SysDev& s, int& area_bytes) {
     take(o.jk, 4 * s.LJ);
     take(o.M3, f8 * 2 * s.LJ * (2 * s.LJ + 1));
   }
+  // the nuclei last: a system that only just fits reads them from global memory
+  a.nuc_lds = at + f8 * 5 * s.n_nuc <= kChainMaxLds ? 1 : 0;
+  if (a.nuc_lds) take(o.nuc, f8 * 5 * s.n_nuc);
   o.total = at;
   return o;
+}
+static_assert(kChainLogs <= 64, "one lane a logarithm");
+
+// threadIdx.x through an opaque move: what is computed from it stays in the
+// phase that uses it instead of being held in registers over the move loop.
+__device__ __forceinline__ int chain_tid() {
+  int z;
+  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+  return (int)threadIdx.x + z;
+}
+
+// The last step of chain_invert: inverse element (i, p_c) = T[p_i][c] / pivot_i.
+template <int NQ>
+__device__ __forceinline__ void chain_permute(double* B, int n, int ld, int tid, bool tr, const double* ip, const int* prow) {
+  double t[NQ];
+  int at[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int x = tid + kChainT * q, i = x / n, c = x - i * n;
+    at[q] = -1;
+    if (x < n * n) {
+      t[q] = B[prow[i] * ld + c] * ip[i];
+      at[q] = tr ? prow[c] * ld + i : i * ld + prow[c];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+    if (at[q] >= 0) B[at[q]] = t[q];
 }
 
 // B[n][ld] (LDS) <- its inverse, in place: Gauss-Jordan with the pivot of step k
 // the largest |entry| of column k among the rows not yet pivoted (lowest row on
-// ties; the row kernel's choice).  KP: columns per thread row, a power of two
-// >= n.  Afterwards element (p_k, k') holds inverse element (k, p_k'), which the
-// last step puts in place, transposed when tr.  log|det| and sign to every
-// thread of wave 0; singular: returns true and B is not a number.
-template <int KP>
-__device__ bool chain_invert(double* B, int n, int ld, bool tr, int* prow, double& logdet, double& sign) {
-  constexpr int G = kChainT / KP, NQ = (KP + G - 1) / G;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int j = tid & (KP - 1), g = tid / KP;
+// ties), n <= 64.  Thread (g, j) keeps column j of rows g, g + G, ...; the step
+// publishes the next pivot column as it updates it, every wave finds the pivot
+// for itself, and a pivot row is left unscaled until the end (only its column-k
+// entry becomes 1), so a step takes one barrier.  Afterwards element (p_k, k')
+// over pivot k is inverse element (k, p_k'), put in place by the last step
+// (transposed when tr).  log|det| and sign to wave 0; singular: returns true and
+// B is not a number.
+__device__ bool chain_invert(double* B, int n, int ld, bool tr, double* fc, double* ips, int* prow, double& logdet,
+                             double& sign) {
+  const int tid = chain_tid(), lane = tid & 63;
+  const int G = min(kChainT / n, 16), g = tid / n, j = tid - g * n;
   bool used = lane >= n;
-  double own = 1.0;
+  double own = 1.0, own_ip = 1.0;
   int own_p = lane;
+  if (tid < n) fc[tid] = B[tid * ld];
+  __syncthreads();
   for (int k = 0; k < n; ++k) {
-    const double f = lane < n ? B[lane * ld + k] : 0.0;
+    const double* f = fc + 64 * (k & 1);
+    double* fn = fc + 64 * ((k + 1) & 1);
+    const double fl = lane < n ? f[lane] : 0.0;
     const unsigned long long key =
-        used ? 0ull : ((__double_as_longlong(fabs(f)) & ~0xFFull) | (unsigned long long)(255 - lane));
+        used ? 0ull : ((__double_as_longlong(fabs(fl)) & ~0xFFull) | (unsigned long long)(255 - lane));
     const unsigned long long best = wave_max_u64(key);
     const int p = 255 - (int)(best & 0xFFull);
-    const double piv = best ? __shfl(f, p & 63, 64) : 0.0;
+    const double piv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(fl), p & 63),
+                                        __builtin_amdgcn_readlane(__double2loint(fl), p & 63));
     if (!(piv != 0.0)) {   // the same for every wave
       __syncthreads();
       const double nanv = __longlong_as_double(0x7ff8000000000000LL);
@@ -111,55 +187,38 @@ __device__ bool chain_invert(double* B, int n, int ld, bool tr, int* prow, doubl
       sign = 0.0;
       return true;
     }
-    if (lane == p) used = true;
-    if (lane == k) { own = piv; own_p = p; }
     const double ip = 1.0 / piv;
-    double t[NQ], fi[NQ];
-    const double pr = j < n ? B[p * ld + j] : 0.0;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int i = g + G * q;
-      const bool ok = i < n && j < n;
-      fi[q] = ok ? B[i * ld + k] : 0.0;
-      t[q] = ok ? B[i * ld + j] : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int i = g + G * q;
-      if (i < n && j < n) {
-        const double gi = fi[q] * ip;
-        double v;
-        if (i == p) v = j == k ? ip : pr * ip;
-        else v = j == k ? -gi : fma(-gi, pr, t[q]);
-        B[i * ld + j] = v;
+    if (lane == p) used = true;
+    if (lane == k) { own = piv; own_ip = ip; own_p = p; }
+    if (g < G) {
+      const double pr = B[p * ld + j];
+      for (int i = g; i < n; i += G) {
+        double v = pr;
+        if (i == p) {
+          if (j == k) B[i * ld + j] = 1.0;
+        } else {
+          const double gi = f[i] * ip;
+          v = j == k ? -gi : fma(-gi, pr, B[i * ld + j]);
+          B[i * ld + j] = v;
+        }
+        if (j == k + 1) fn[i] = v;
       }
     }
     __syncthreads();
   }
-  if (tid < n) prow[tid] = own_p;   // wave 0's lanes
-  double t[NQ];
+  if (tid < n) { prow[tid] = own_p; ips[tid] = own_ip; }   // wave 0's lanes
   __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int i = g + G * q;
-    t[q] = i < n && j < n ? B[prow[i] * ld + j] : 0.0;   // inverse element (i, prow[j])
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int i = g + G * q;
-    if (i < n && j < n) B[tr ? prow[j] * ld + i : i * ld + prow[j]] = t[q];
-  }
+  if (n <= 16) chain_permute<1>(B, n, ld, tid, tr, ips, prow);
+  else if (n <= 32) chain_permute<4>(B, n, ld, tid, tr, ips, prow);
+  else chain_permute<16>(B, n, ld, tid, tr, ips, prow);
   if (tid < 64) {
-    int odd = 0;
-    if (lane < n) {
-      odd = own < 0.0;
-      for (int k2 = lane + 1; k2 < n; ++k2) odd += prow[k2] < own_p;
+    // the parity of k -> p_k by counting inversions, and the pivots' signs
+    int odd = __popcll(__ballot(lane < n && own < 0.0));
+    for (int k = 0; k + 1 < n; ++k) {
+      const int pk = __builtin_amdgcn_readlane(own_p, k);
+      odd += __popcll(__ballot(lane > k && lane < n && own_p < pk));
     }
-    const double ls = wave_sum(lane < n ? log(fabs(own)) : 0.0);
-    for (int o = 32; o > 0; o >>= 1) odd += __shfl_xor(odd, o, 64);
-    logdet = ls;
+    logdet = wave_sum(lane < n ? log(fabs(own)) : 0.0);
     sign = (odd & 1) ? -1.0 : 1.0;
   }
   __syncthreads();
@@ -175,7 +234,7 @@ typedef double cdx4 __attribute__((ext_vector_type(4)));
 // from L2 once per chunk of rows.
 __device__ void chain_rebuild(const SysDev& s, const WalkDev& w, int wk, int h, bool all, double* area, int area_bytes,
                               const double* r, int* list) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = chain_tid(), lane = tid & 63, wave = tid >> 6;
   const int n = h == 0 ? s.nu : s.nd, i0 = h == 0 ? 0 : s.nu, Lp = s.Lp, ldp = Lp + 2;
   const double* phi = (const double*)w.phi + ((long)wk * s.N + i0) * Lp;
   double* P = (double*)w.P + ((long)wk * s.N + i0) * Lp;
@@ -241,43 +300,61 @@ __device__ void chain_rebuild(const SysDev& s, const WalkDev& w, int wk, int h, 
   }
 }
 
-template <int KP, int QL>
+enum { kRun = 0, kPropose = 1, kAccept = 2 };
+
+template <int MODE, bool SMALL, int QL>
 __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, ChainArgs a) {
+  static_assert(MODE == kRun || !SMALL, "single moves of small systems take the per-move kernels");
   extern __shared__ __align__(16) char lds[];
-  constexpr int G = kChainT / KP, NQ = (KP + G - 1) / G;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wk = blockIdx.x;
-  const int n = s.nu, ld = n | 1, N = s.N, L = s.L, Lp = s.Lp, np = s.ptn, LJ = s.LJ, nn = s.n_nuc;
+  const int n = s.nu, ld = chain_ld(n), N = s.N, L = s.L, Lp = s.Lp, np = s.ptn, LJ = s.LJ, nn = s.n_nuc;
   const long Wk = w.Wk;
+  if (MODE == kAccept && a.acc[wk] == 0) {
+    if (tid == 0) w.acc[wk] = 0;
+    return;
+  }
   auto at = [&](int off) { return (double*)(lds + off); };
-  double *area = at(a.ly.area), *B = at(a.ly.B), *psi = at(a.ly.psi), *r = at(a.ly.r), *nuc = at(a.ly.nuc),
-         *draw = at(a.ly.draw), *red = at(a.ly.red), *part = at(a.ly.part), *pu = at(a.ly.pu);
+  double *area = at(a.ly.area), *B = at(a.ly.B), *r = at(a.ly.r), *nuc = at(a.ly.nuc), *draw = at(a.ly.draw),
+         *red = at(a.ly.red), *part = at(a.ly.part), *ws = at(a.ly.ws), *cs = at(a.ly.cs), *lg = at(a.ly.lg);
+  double* lv = at(a.ly.lv) + wave * a.cw;
+  uint16_t* lm = (uint16_t*)(lds + a.ly.lm) + wave * a.cw;
   int *list = (int*)(lds + a.ly.list), *prow = (int*)(lds + a.ly.prow);
   double *chi = at(a.ly.chi), *hv = at(a.ly.hv), *Gv = at(a.ly.G), *jm = at(a.ly.jm), *chin = at(a.ly.chin),
          *jb = at(a.ly.jb), *M3 = at(a.ly.M3);
   int* jk = (int*)(lds + a.ly.jk);
   double* Wg = w.W + (long)wk * n * n;
   double* phi = (double*)w.phi + (long)wk * N * Lp;
-  const int j = tid & (KP - 1), g = tid / KP;   // column and row group of the n x n and PT passes
-
-  // this thread's basis functions and the two-body parameters
+  // n x n passes: columns j, j + 1 of rows g, g + G, ... for thread (g, j / 2), g < G
+  const int nh = (n + 1) / 2, G = a.groups, g = tid / nh, j = 2 * (tid - g * nh);
+  // this thread's basis functions: 16 consecutive ones a wave in turn (what is
+  // kept at r' lies close together), or every fourth one (all are kept)
+  int mus[QL];
   double4 bf[QL];
   int bk[QL];
+  double cm[QL];   // their column maxima (large form)
+  int spin = a.e0 < n ? 0 : 1;   // (e0 < N)
 #pragma unroll
   for (int q = 0; q < QL; ++q) {
-    const int mu = tid + kChainT * q;
-    bf[q] = s.bfn[mu < L ? mu : 0];
-    bk[q] = s.kind[mu < L ? mu : 0];
+    mus[q] = SMALL ? 4 * (64 * q + lane) + wave : kChainT * q + ((lane >> 4) * 4 + wave) * 16 + (lane & 15);
+    const int mu = mus[q] < L ? mus[q] : 0;
+    if (MODE != kAccept) {
+      bf[q] = s.bfn[mu];
+      bk[q] = s.kind[mu];
+      cm[q] = SMALL ? 0.0 : w.cmax[((long)wk * 2 + 1 - spin) * Lp + mu];
+    }
   }
   double* j2p = red + 8;
   if (tid < 8) j2p[tid] = s.j2d[tid];
   // state to LDS
-  int spin = (a.e0 % N) < n ? 0 : 1;
-  for (int q = tid; q < n * n; q += kChainT) {
-    const int i = q / n, k = q - i * n;
-    B[spin == 0 ? i * ld + k : k * ld + i] = a.Ainv[(long)wk * n * n + q];
-  }
+  if (MODE != kPropose)
+    for (int q = tid; q < n * n; q += kChainT) {
+      const int i = q / n, k = q - i * n;
+      B[spin == 0 ? i * ld + k : k * ld + i] = a.Ainv[(long)wk * n * n + q];
+    }
+  if (MODE != kPropose && (n & 1))   // the column that makes the pairs
+    for (int q = tid; q < n; q += kChainT) B[q * ld + n] = 0.0;
   for (int q = tid; q < 3 * N; q += kChainT) r[q] = w.r[(long)wk * 3 * N + q];
-  for (int q = tid; q < nn; q += kChainT) {
+  for (int q = tid; a.nuc_lds && q < nn; q += kChainT) {
     nuc[5 * q] = s.R[3 * q]; nuc[5 * q + 1] = s.R[3 * q + 1]; nuc[5 * q + 2] = s.R[3 * q + 2];
     nuc[5 * q + 3] = s.Z[q];
     nuc[5 * q + 4] = s.j1_b[q];
@@ -295,45 +372,48 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     jb[4 * q] = f.x; jb[4 * q + 1] = f.y; jb[4 * q + 2] = f.z; jb[4 * q + 3] = f.w;
     jk[q] = s.jkind[q];
   }
-  for (int q = tid; q < 4 * LJ * LJ; q += kChainT) M3[q / (2 * LJ) * (2 * LJ + 1) + q % (2 * LJ)] = s.M3[q];
+  if (MODE != kPropose)
+    for (int q = tid; q < 4 * LJ * LJ; q += kChainT) M3[q / (2 * LJ) * (2 * LJ + 1) + q % (2 * LJ)] = s.M3[q];
   double la = w.logabs[wk], sg = w.sign[wk], Jt = w.J[wk];   // kept by thread 0
-  int acc_n = 0;
+  int acc_n = 0, logs = 0;   // accepted moves; those whose ratio and Jastrow change wait in lg
+  // log|Psi| of the waiting moves: their logarithms side by side in wave 0, the
+  // sums in order (a logarithm a move in one lane would hold up every wave)
+  auto fold_logs = [&]() {
+    if (wave == 0) {
+      double l = 0.0;
+      if (lane < logs) l = log(fabs(lg[lane]));
+      if (lane < logs) lg[lane] = l;
+      __builtin_amdgcn_wave_barrier();
+      if (lane == 0)
+        for (int k = 0; k < logs; ++k) la += lg[k] + lg[kChainLogs + k];
+    }
+    logs = 0;
+  };
   int since = a.since0, buf = a.buf_spin0, valid = a.valid0, half = -1;
   bool due = false;   // the last move filled the buffer: refresh
-  // thread ranges of the set-up: basis functions from thread 0, then the new and
-  // the old Jastrow sums and the Jastrow basis from the next waves on
+  // thread ranges of the Jastrow sums: the new and the old position and the
+  // Jastrow basis start a wave apart, after the basis functions of the last pass
   const int nj = nn + N;
   const int off1 = (L + 63) / 64 * 64, off2 = off1 + (nj + 63) / 64 * 64, off3 = off2 + (nj + 63) / 64 * 64;
   const int t1 = (tid - off1) & (kChainT - 1), t2 = (tid - off2) & (kChainT - 1), t3 = (tid - off3) & (kChainT - 1);
+  const int lpf = 1 << a.lsh, fpl = 64 >> a.lsh;   // lanes a column takes, columns a load
+  const int fg = lane >> a.lsh, rp = 2 * (lane & (lpf - 1));
+  const bool row_ok = rp < np;
 
-  auto refresh = [&](bool tr) {
-    __syncthreads();
-    for (int q = tid; q < n * n; q += kChainT) {
-      const int i = q / n, k = q - i * n;
-      B[i * ld + k] = Wg[q];
-    }
-    __syncthreads();
-    double ldet = 0.0, sdet = 0.0;
-    const bool sing = chain_invert<KP>(B, n, ld, tr, prow, ldet, sdet);
-    if (tid == 0) {
-      la = sing ? -__builtin_inf() : ldet + Jt;
-      sg = sdet;
-      w.logdet[wk] = ldet;
-      w.detsign[wk] = sdet;
-      w.singular[wk] = sing ? 1 : 0;
-    }
-  };
   auto jsum = [&](int t, int e, double px, double py, double pz) {
     double v = 0.0;
     for (int i = t; i < nj; i += kChainT) {
       const bool isn = i < nn;
       const int je = i - nn;
-      const double* c = isn ? nuc + 5 * i : r + 3 * je;
-      const double dx = px - c[0], dy = py - c[1], dz = pz - c[2];
+      double x, y, z, Z = 0.0, b = 0.0;
+      if (!isn) { x = r[3 * je]; y = r[3 * je + 1]; z = r[3 * je + 2]; }
+      else if (a.nuc_lds) { const double* c = nuc + 5 * i; x = c[0]; y = c[1]; z = c[2]; Z = c[3]; b = c[4]; }
+      else { x = s.R[3 * i]; y = s.R[3 * i + 1]; z = s.R[3 * i + 2]; Z = s.Z[i]; b = s.j1_b[i]; }
+      const double dx = px - x, dy = py - y, dz = pz - z;
       const double d = sqrt(dx * dx + dy * dy + dz * dz);
       double f, f1, f2;
       if (isn) {
-        if (s.j1_form) { j1_radial(s.j1_form, c[3], c[4], d, f, f1, f2); v += f; }
+        if (s.j1_form) { j1_radial(s.j1_form, Z, b, d, f, f1, f2); v += f; }
       } else if (s.j2_form && je != e) {
         j2_radial(s.j2_form, j2p, (e < n) == (je < n), d, f, f1, f2);
         v += f;
@@ -342,53 +422,80 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     return v;
   };
 
+  int e = a.e0 - 1;
   for (int t = 0;; ++t) {
-    const bool last = t == a.steps;   // only a refresh that is due
-    const int e = (int)(((long)a.e0 + t) % N);
+    const bool last = MODE == kRun && t == a.steps;   // only a refresh that is due
+    e = e + 1 == N ? 0 : e + 1;
     const int sp = last ? buf : (e < n ? 0 : 1), ie = sp == 0 ? e : e - n;
-    bool fence = false;   // LDS written since the last barrier
-    // the per-move path's schedule
-    if (due || (since > 0 && sp != buf)) {
-      refresh(sp == 1);
-      spin = sp;
-      since = 0;
-      due = false;
-    }
-    if (last) break;
-    if (sp != spin) {   // nothing buffered: turn the inverse over
-      __syncthreads();
-      double x[NQ];
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) x[q] = (g + G * q < n && j < n) ? B[(g + G * q) * ld + j] : 0.0;
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-        if (g + G * q < n && j < n) B[j * ld + g + G * q] = x[q];
-      fence = true;
-    }
-    spin = buf = sp;
-    const int hs = 1 - sp;   // the half of P this spin's moves stream
-    if (!((valid >> hs) & 1)) {
-      chain_rebuild(s, w, wk, hs, a.all_rows != 0, area, a.area_bytes, r, list);
-      valid |= 1 << hs;
-      half = -1;
-    }
-    if (half != hs) {
-      __syncthreads();
-      const int nrow = hs == 0 ? s.nu : s.nd;
-      const double* P = (const double*)w.P + ((long)wk * N + (hs == 0 ? 0 : n)) * Lp;
-      for (int q = tid; q < n * (Lp / 2); q += kChainT) {
-        const int i = q / (Lp / 2), mu = 2 * (q - i * (Lp / 2));
-        const double2 v = *reinterpret_cast<const double2*>((i < nrow ? P + (long)i * Lp : s.Uph + (long)(i - nrow) * Lp) + mu);
-        area[mu * np + i] = v.x;
-        area[(mu + 1) * np + i] = v.y;
+    bool fence = t == 0;   // LDS written since the last barrier
+    if constexpr (SMALL) {
+      // the per-move path's schedule
+      if (due || (since > 0 && sp != buf)) {
+        __syncthreads();
+        for (int q = chain_tid(); q < n * n; q += kChainT) {
+          const int i = q / n, k = q - i * n;
+          B[i * ld + k] = Wg[q];
+        }
+        __syncthreads();
+        double ldet = 0.0, sdet = 0.0;
+        const bool sing = chain_invert(B, n, ld, sp == 1, part, cs, prow, ldet, sdet);
+        fold_logs();
+        if (tid == 0) {
+          la = sing ? -__builtin_inf() : ldet + Jt;
+          sg = sdet;
+          w.logdet[wk] = ldet;
+          w.detsign[wk] = sdet;
+          w.singular[wk] = sing ? 1 : 0;
+        }
+        spin = sp;
+        since = 0;
+        due = false;
       }
-      half = hs;
-      fence = true;
+      if (last) break;
+      if (sp != spin) {   // nothing buffered: turn the inverse over
+        __syncthreads();
+        const int ct = chain_tid();
+        double x[kChainSmallN * kChainSmallN / kChainT];
+#pragma unroll
+        for (int q = 0; q < kChainSmallN * kChainSmallN / kChainT; ++q) {
+          const int y = ct + kChainT * q, i = y / n, c = y - i * n;
+          x[q] = y < n * n ? B[i * ld + c] : 0.0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kChainSmallN * kChainSmallN / kChainT; ++q) {
+          const int y = ct + kChainT * q, i = y / n, c = y - i * n;
+          if (y < n * n) B[c * ld + i] = x[q];
+        }
+        fence = true;
+      }
+      spin = buf = sp;
+      const int hs = 1 - sp;   // the half of P this spin's moves stream
+      if (!((valid >> hs) & 1)) {
+        chain_rebuild(s, w, wk, hs, a.all_rows != 0, area, a.area_bytes, r, list);
+        valid |= 1 << hs;
+        half = -1;
+      }
+      if (half != hs) {
+        __syncthreads();
+        const int nrow = hs == 0 ? s.nu : s.nd;
+        const double* P = (const double*)w.P + ((long)wk * N + (hs == 0 ? 0 : n)) * Lp;
+        for (int q = chain_tid(); q < np * (Lp / 2); q += kChainT) {
+          const int i = q / (Lp / 2), mu = 2 * (q - i * (Lp / 2));
+          double2 v = double2{0.0, 0.0};   // (the row that makes ptn even)
+          if (i < n) v = *reinterpret_cast<const double2*>((i < nrow ? P + (long)i * Lp : s.Uph + (long)(i - nrow) * Lp) + mu);
+          area[mu * np + i] = v.x;
+          area[(mu + 1) * np + i] = v.y;
+        }
+        half = hs;
+        fence = true;
+      }
+    } else if (last) {
+      break;
     }
-    if (t % kChainDraws == 0) {
+    if (MODE == kRun && t % kChainDraws == 0) {
       __syncthreads();
-      for (int q = tid; q < 4 * kChainDraws; q += kChainT) {
+      for (int q = chain_tid(); q < 4 * kChainDraws; q += kChainT) {
         const int k = q >> 2, c = q & 3;
         if (t + k < a.steps)
           draw[q] = c < 3 ? a.disp[((long)(t + k) * Wk + wk) * 3 + c] : a.unif[(long)(t + k) * Wk + wk];
@@ -397,121 +504,219 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     }
     if (fence) __syncthreads();
 
-    // set-up: psi(r'), the Jastrow change
     const double* dv = draw + 4 * (t % kChainDraws);
     const double ox = r[3 * e], oy = r[3 * e + 1], oz = r[3 * e + 2];
-    const double px = ox + dv[0], py = oy + dv[1], pz = oz + dv[2];
+    double px, py, pz;
+    if constexpr (MODE == kRun) { px = ox + dv[0]; py = oy + dv[1]; pz = oz + dv[2]; }
+    else {
+      const double* p = MODE == kPropose ? a.r_new + 3 * (long)wk : w.r_new + 3 * (long)wk;
+      px = p[0]; py = p[1]; pz = p[2];
+    }
+    // the inverse's column (lanes: rows lane and lane + 64)
+    double c0 = 0.0, c1 = 0.0, w0 = 0.0, w1 = 0.0, R, dJ;
     double sv[QL];
-#pragma unroll
-    for (int q = 0; q < QL; ++q) {
-      const int mu = tid + kChainT * q;
-      sv[q] = 0.0;
-      if (mu < L) {
-        sv[q] = basis_value_rec(bf[q], bk[q], px, py, pz);
-        psi[mu] = sv[q];
+    if constexpr (MODE == kPropose) {
+      const double* A = a.Ainv + (long)wk * n * n;
+      if (lane < n) c0 = sp == 0 ? A[(long)lane * n + ie] : A[(long)ie * n + lane];
+      if (lane + 64 < n) c1 = sp == 0 ? A[(long)(lane + 64) * n + ie] : A[(long)ie * n + lane + 64];
+    } else {
+      if (lane < n) c0 = B[lane * ld + ie];
+      if (lane + 64 < n) c1 = B[(lane + 64) * ld + ie];
+    }
+    if constexpr (MODE != kAccept) {
+      // psi(r') of the wave's functions, the kept ones listed
+      double thr = 0.0;
+      if (!SMALL) {
+        const double s1 = wave_sum(fabs(c0) + fabs(c1));
+        thr = (s1 > 0.0) ? s.screen_tol() / ((double)L * s1) : 0.0;
       }
-    }
-    double dj = jsum(t1, e, px, py, pz) - jsum(t2, e, ox, oy, oz);
-    for (int k = t3; k < LJ; k += kChainT) {
-      const double4 f = double4{jb[4 * k], jb[4 * k + 1], jb[4 * k + 2], jb[4 * k + 3]};
-      const double v = basis_value_rec(f, jk[k], px, py, pz);
-      chin[k] = v;
-      dj += (v - chi[e * LJ + k]) * (Gv[sp * LJ + k] - hv[e * LJ + k] + jm[sp * LJ + k]);
-    }
-    dj = wave_sum(dj);
-    if (lane == 0) red[4 * (t & 1) + wave] = dj;
-    __syncthreads();
-
-    // the new row (column) of W, its product with the inverse's column
-    double x = 0.0;
-    if (j < n) {
-      int mu = g;
-      for (; mu + 3 * G < L; mu += 4 * G) {
-        const double p0 = area[mu * np + j], p1 = area[(mu + G) * np + j], p2 = area[(mu + 2 * G) * np + j],
-                     p3 = area[(mu + 3 * G) * np + j];
-        x += p0 * psi[mu];
-        x += p1 * psi[mu + G];
-        x += p2 * psi[mu + 2 * G];
-        x += p3 * psi[mu + 3 * G];
-      }
-      for (; mu < L; mu += G) x += area[mu * np + j] * psi[mu];
-    }
-#pragma unroll
-    for (int o = KP; o < 64; o <<= 1) x += __shfl_xor(x, o, 64);
-    if (lane < KP) part[wave * 64 + lane] = x;
-    __syncthreads();
-    double wj = 0.0, cj = 0.0;
-    if (lane < n) {
-      wj = ((part[lane] + part[64 + lane]) + part[128 + lane]) + part[192 + lane];
-      cj = B[lane * ld + ie];
-    }
-    const double R = wave_sum(wj * cj);
-    const double* rd = red + 4 * (t & 1);
-    const double dJ = ((rd[0] + rd[1]) + rd[2]) + rd[3];
-    const double ratio = R * exp(dJ);
-    const bool acc = dv[3] < ratio * ratio;   // uniform
-    if (acc) {
-      double u = 0.0;
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int i = g + G * q;
-        const double wi = __shfl(wj, i & 63, 64);
-        if (i < n && j < n) u += wi * B[i * ld + j];
-      }
-#pragma unroll
-      for (int o = KP; o < 64; o <<= 1) u += __shfl_xor(u, o, 64);
-      if (lane < KP) pu[wave * 64 + lane] = u;
-      if (wave == 0 && lane < n) Wg[sp == 0 ? (long)ie * n + lane : (long)lane * n + ie] = wj;
+      int cnt = SMALL ? (L - wave + 3) / 4 : 0;
 #pragma unroll
       for (int q = 0; q < QL; ++q) {
-        const int mu = tid + kChainT * q;
-        if (mu < L) phi[(long)e * Lp + mu] = sv[q];
+        sv[q] = 0.0;
+        bool keep = false;
+        if (mus[q] < L) {
+          sv[q] = basis_value_rec(bf[q], bk[q], px, py, pz);
+          keep = !(fabs(sv[q]) * cm[q] <= thr);
+        }
+        if constexpr (SMALL) {   // function k of the wave is 4 k + wave
+          lv[64 * q + lane] = sv[q];
+          continue;
+        }
+        const unsigned long long b = __ballot(keep);
+        if (keep) {
+          const int k = cnt + __popcll(b & ((1ull << lane) - 1ull));
+          lm[k] = (uint16_t)mus[q];
+          lv[k] = sv[q];
+        }
+        cnt += __popcll(b);
       }
-      for (int o = tid; o < 3 * LJ; o += kChainT) {
+      __builtin_amdgcn_wave_barrier();   // (the list is the wave's own: its LDS accesses run in order)
+      // their columns: the wave's share of the new row (column) of W
+      // (32-bit offsets: a walker's transposed rows are at most 2 MB)
+      const char* src = SMALL ? (const char*)area : (const char*)(w.PT + (long)wk * Lp * s.pt_ld() + (sp == 0 ? np : 0));
+      const uint32_t col = 8u * (uint32_t)(SMALL ? np : s.pt_ld());
+      constexpr int U = SMALL ? 4 : (QL > 3 ? kChainU - 2 : kChainU);
+      double ax = 0.0, ay = 0.0;
+      for (int k0 = fg; k0 - fg < cnt; k0 += U * fpl) {
+        double2 x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = k0 + u * fpl;
+          x[u] = double2{0.0, 0.0};
+          const uint32_t mu = SMALL ? 4u * (uint32_t)k + (uint32_t)wave : (uint32_t)lm[k < cnt ? k : 0];
+          if (k < cnt && row_ok) x[u] = *reinterpret_cast<const double2*>(src + (mu * col + 8u * (uint32_t)rp));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int k = k0 + u * fpl;
+          const double v = k < cnt ? lv[k] : 0.0;
+          ax += v * x[u].x;
+          ay += v * x[u].y;
+        }
+      }
+      ax = lane_group_sum(ax, lpf);
+      ay = lane_group_sum(ay, lpf);
+      double* pt = part + (t & 1) * a.pst + wave * np;
+      if (lane < lpf && row_ok) { pt[rp] = ax; pt[rp + 1] = ay; }
+      // the Jastrow change
+      double dj = jsum(t1, e, px, py, pz) - jsum(t2, e, ox, oy, oz);
+      for (int k = t3; k < LJ; k += kChainT) {
+        const double4 f = double4{jb[4 * k], jb[4 * k + 1], jb[4 * k + 2], jb[4 * k + 3]};
+        const double v = basis_value_rec(f, jk[k], px, py, pz);
+        chin[k] = v;
+        dj += (v - chi[e * LJ + k]) * (Gv[sp * LJ + k] - hv[e * LJ + k] + jm[sp * LJ + k]);
+      }
+      dj = wave_sum(dj);
+      if (lane == 0) red[4 * (t & 1) + wave] = dj;
+      if (MODE == kPropose && lane == 0) prow[wave] = cnt;
+      __syncthreads();
+      const double* ps = part + (t & 1) * a.pst;
+      if (lane < n) w0 = ((ps[lane] + ps[np + lane]) + ps[2 * np + lane]) + ps[3 * np + lane];
+      if (lane + 64 < n)
+        w1 = ((ps[lane + 64] + ps[np + lane + 64]) + ps[2 * np + lane + 64]) + ps[3 * np + lane + 64];
+      R = wave_sum(w0 * c0 + w1 * c1);
+      const double* rd = red + 4 * (t & 1);
+      dJ = ((rd[0] + rd[1]) + rd[2]) + rd[3];
+    } else {
+      if (lane < n) w0 = w.w_new[(long)wk * n + lane];
+      if (lane + 64 < n) w1 = w.w_new[(long)wk * n + lane + 64];
+      R = w.rdet[wk];
+      dJ = w.dJ[wk];
+      for (int k = tid; k < LJ; k += kChainT) chin[k] = w.chi_new[(long)wk * LJ + k];
+      __syncthreads();
+    }
+    const double ratio = R * exp(dJ);
+    if constexpr (MODE == kPropose) {
+      // the pending proposal
+      if (wave == 0) {
+        if (lane < n) w.w_new[(long)wk * n + lane] = w0;
+        if (lane + 64 < n) w.w_new[(long)wk * n + lane + 64] = w1;
+      }
+#pragma unroll
+      for (int q = 0; q < QL; ++q)
+        if (mus[q] < L) w.psi_new[(long)wk * Lp + mus[q]] = sv[q];
+      for (int k = tid; k < LJ; k += kChainT) w.chi_new[(long)wk * LJ + k] = chin[k];
+      if (tid == 0) {
+        w.r_new[3 * wk] = px; w.r_new[3 * wk + 1] = py; w.r_new[3 * wk + 2] = pz;
+        w.rdet[wk] = R;
+        w.ratio[wk] = ratio;
+        w.dJ[wk] = dJ;
+        w.nkeep[wk] = prow[0] + prow[1] + prow[2] + prow[3];
+        if (a.ratio_out) a.ratio_out[wk] = ratio;
+      }
+      return;
+    }
+    const bool acc = MODE == kAccept || dv[3] < ratio * ratio;   // uniform
+    if (acc) {
+      // every wave writes the same w and column: its own reads need no barrier
+      if (lane < n) { ws[lane] = w0; cs[lane] = c0; }
+      if (lane + 64 < n) { ws[lane + 64] = w1; cs[lane + 64] = c1; }
+      __builtin_amdgcn_wave_barrier();
+      const double ir = 1.0 / R;
+      double* pu = part + ((t + 1) & 1) * a.pst;   // (the previous move's partial sums are read)
+      if (g < G) {
+        double2 u = double2{0.0, 0.0};
+#pragma unroll 4
+        for (int i = g; i < n; i += G) {
+          const double2 b = *reinterpret_cast<const double2*>(B + i * ld + j);
+          u.x += ws[i] * b.x;
+          u.y += ws[i] * b.y;
+        }
+        pu[2 * (g * nh) + j] = u.x;
+        pu[2 * (g * nh) + j + 1] = u.y;
+      }
+      if (wave == 0) {
+        if (lane < n) Wg[sp == 0 ? (long)ie * n + lane : (long)lane * n + ie] = w0;
+        if (lane + 64 < n) Wg[sp == 0 ? (long)ie * n + lane + 64 : (long)(lane + 64) * n + ie] = w1;
+      }
+#pragma unroll
+      for (int q = 0; q < QL; ++q)
+        if (mus[q] < L) phi[(long)e * Lp + mus[q]] = MODE == kAccept ? w.psi_new[(long)wk * Lp + mus[q]] : sv[q];
+      // [G_u; G_d] += M3[:, s] (chi(r') - chi_e), h_e = M^{ss} chi(r'): four lanes a sum
+      for (int q = tid; q < 12 * LJ; q += kChainT) {
+        const int o = q >> 2, sub = q & 3;
         const bool first = o < 2 * LJ;
         const double* row = M3 + (first ? o : sp * LJ + o - 2 * LJ) * (2 * LJ + 1) + sp * LJ;
         double v = 0.0;
-        if (first) {
-          for (int k = 0; k < LJ; ++k) v += row[k] * (chin[k] - chi[e * LJ + k]);
-          Gv[o] += v;
-        } else {
-          for (int k = 0; k < LJ; ++k) v += row[k] * chin[k];
-          hv[e * LJ + o - 2 * LJ] = v;
+        for (int k = sub; k < LJ; k += 4) v += row[k] * (first ? chin[k] - chi[e * LJ + k] : chin[k]);
+        v += dpp_f64<0xB1>(v);
+        v += dpp_f64<0x4E>(v);
+        if (sub == 0) {
+          if (first) Gv[o] += v;
+          else hv[e * LJ + o - 2 * LJ] = v;
         }
       }
       __syncthreads();
-      if (j < n) {
-        u = ((pu[j] + pu[64 + j]) + pu[128 + j]) + pu[192 + j];
-        if (j == ie) u -= 1.0;
-        u *= 1.0 / R;
-      }
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int i = g + G * q;
-        const double ci = __shfl(cj, i & 63, 64);
-        if (i < n && j < n) B[i * ld + j] = fma(-ci, u, B[i * ld + j]);
+      if (g < G) {
+        double2 u = *reinterpret_cast<const double2*>(pu + j);
+        for (int q = 1; q < G; ++q) {
+          const double2 v = *reinterpret_cast<const double2*>(pu + 2 * q * nh + j);
+          u.x += v.x;
+          u.y += v.y;
+        }
+        if (j == ie) u.x -= 1.0;
+        if (j + 1 == ie) u.y -= 1.0;
+        u.x *= ir;
+        u.y *= ir;
+#pragma unroll 4
+        for (int i = g; i < n; i += G) {
+          double2* p = reinterpret_cast<double2*>(B + i * ld + j);
+          const double2 b = *p;
+          const double ci = cs[i];
+          *p = double2{fma(-ci, u.x, b.x), fma(-ci, u.y, b.y)};
+        }
       }
       for (int k = tid; k < LJ; k += kChainT) chi[e * LJ + k] = chin[k];
       if (tid == 0) {
         r[3 * e] = px; r[3 * e + 1] = py; r[3 * e + 2] = pz;
-        la += log(fabs(R)) + dJ;
         if (R < 0.0) sg = -sg;
         Jt += dJ;
-        acc_n += 1;
+        if (MODE == kAccept) la += log(fabs(R)) + dJ;
+        else { lg[logs] = R; lg[kChainLogs + logs] = dJ; }
       }
+      acc_n += 1;
+      logs += 1;
+      if (MODE == kRun && logs == kChainLogs) fold_logs();
       __syncthreads();
+    }
+    if constexpr (MODE == kAccept) {
+      if (tid == 0) w.acc[wk] = 1;
+      break;
     }
     valid &= ~(1 << sp);
     since += 1;
-    due = since >= a.cap;
+    due = SMALL && since >= a.cap;
   }
 
   // the walker's state back
+  if (MODE == kRun) fold_logs();
   __syncthreads();
-  for (int q = tid; q < n * n; q += kChainT) {
-    const int i = q / n, k = q - i * n;
-    w.A[(long)wk * n * n + q] = B[spin == 0 ? i * ld + k : k * ld + i];
-  }
+  if (SMALL || a.store_A)
+    for (int q = tid; q < n * n; q += kChainT) {
+      const int i = q / n, k = q - i * n;
+      w.A[(long)wk * n * n + q] = B[spin == 0 ? i * ld + k : k * ld + i];
+    }
   for (int q = tid; q < 3 * N; q += kChainT) w.r[(long)wk * 3 * N + q] = r[q];
   for (int q = tid; q < N * LJ; q += kChainT) {
     w.chi[(long)wk * N * LJ + q] = chi[q];
@@ -522,40 +727,67 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     w.logabs[wk] = la;
     w.sign[wk] = sg;
     w.J[wk] = Jt;
-    w.wm[wk] = 0;
-    if (w.nkeep) w.nkeep[wk] = L;   // the functions a proposal read
-    if (a.cnt) a.cnt[wk] += acc_n;
+    if (SMALL) w.wm[wk] = 0;
+    if (SMALL) w.nkeep[wk] = L;   // the functions a proposal read
+    if (MODE == kRun && a.cnt) a.cnt[wk] += acc_n;
   }
 }
 
-// Systems the resident chain takes: FP64 rows, basis functions as orbitals, W
-// of at most 64 rows, and a walker's state within 80 KiB of LDS (two
-// workgroups per compute unit).
-bool chain_ok(const SysDev& s, const WalkDev& w) {
-  if (!s.screened() || s.Lq > 0 || s.nu > kChainMaxN || s.L > 2 * kChainT || !w.rpos_P || s.Lp % 32) return false;
-  if ((long)s.LJ * s.LJ > 4096 || s.N > 4096 || s.n_nuc > 1024) return false;
-  int area;
-  return chain_layout(s, area).total <= kChainMaxLds;
+// The form that takes a system: FP64 rows, basis functions as orbitals, and a
+// walker's state within the LDS (0: neither).
+int chain_class(const SysDev& s, const WalkDev& w) {
+  if (!s.screened() || s.Lq > 0 || s.nu > kChainMaxN || s.L > 1024 || !w.rpos_P || !w.PT || s.Lp % 32) return 0;
+  if (s.LJ > 128 || s.N > 4096 || s.n_nuc > 4096) return 0;
+  ChainArgs a{};
+  if (s.nu <= kChainSmallN && s.L <= 2 * kChainT && chain_layout(s, true, a).total <= kChainSmallLds) return 1;
+  return chain_layout(s, false, a).total <= kChainMaxLds ? 2 : 0;
 }
 
-hipError_t launch_chain(const SysDev& s, const WalkDev& w, int e0, int steps, const double* disp, const double* unif,
-                        int32_t* accept_count, int since0, int buf_spin0, int valid0, bool all_rows, const double* Ainv,
-                        hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (!chain_ok(s, w) || steps < 1) return hipErrorInvalidValue;
-  ChainArgs a{};
-  a.e0 = e0; a.steps = steps; a.cap = wb_cap(s); a.since0 = since0; a.buf_spin0 = buf_spin0; a.valid0 = valid0;
-  a.all_rows = all_rows ? 1 : 0; a.Ainv = Ainv; a.disp = disp; a.unif = unif; a.cnt = accept_count;
-  a.ly = chain_layout(s, a.area_bytes);
+static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, ChainArgs& a, hipStream_t st,
+                               hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const int cls = chain_class(s, w);
+  if (cls == 0 || (mode != kRun && cls != 2) || a.steps < 1) return hipErrorInvalidValue;
+  a.cap = wb_cap(s);
+  a.ly = chain_layout(s, cls == 1, a);
   const dim3 grid(w.Wk), blk(kChainT);
-#define QMC_CHAIN(K, Q) QMC_LAUNCH_EV((chain_kernel<K, Q>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
-#define QMC_CHAIN_Q(K) if (s.L <= kChainT) { QMC_CHAIN(K, 1); } else { QMC_CHAIN(K, 2); }
-  if (s.nu <= 8) { QMC_CHAIN_Q(8) }
-  else if (s.nu <= 16) { QMC_CHAIN_Q(16) }
-  else if (s.nu <= 32) { QMC_CHAIN_Q(32) }
-  else { QMC_CHAIN_Q(64) }
+#define QMC_CHAIN(M, S, Q) QMC_LAUNCH_EV((chain_kernel<M, S, Q>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
+#define QMC_CHAIN_Q(M)                                                         \
+  if (s.L <= kChainT) { QMC_CHAIN(M, false, 1); }                              \
+  else if (s.L <= 2 * kChainT) { QMC_CHAIN(M, false, 2); }                     \
+  else if (s.L <= 3 * kChainT) { QMC_CHAIN(M, false, 3); }                     \
+  else { QMC_CHAIN(M, false, 4); }
+  if (cls == 1) {
+    if (s.L <= kChainT) { QMC_CHAIN(kRun, true, 1); }
+    else { QMC_CHAIN(kRun, true, 2); }
+  } else if (mode == kRun) { QMC_CHAIN_Q(kRun) }
+  else if (mode == kPropose) { QMC_CHAIN_Q(kPropose) }
+  else { QMC_CHAIN_Q(kAccept) }
 #undef QMC_CHAIN_Q
 #undef QMC_CHAIN
   return hipGetLastError();
+}
+
+hipError_t launch_chain(const SysDev& s, const WalkDev& w, int e0, int steps, const double* disp, const double* unif,
+                        int32_t* accept_count, int since0, int buf_spin0, int valid0, bool all_rows, bool store_A,
+                        const double* Ainv, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  ChainArgs a{};
+  a.e0 = e0 % s.N; a.steps = steps; a.since0 = since0; a.buf_spin0 = buf_spin0; a.valid0 = valid0;
+  a.all_rows = all_rows ? 1 : 0; a.store_A = store_A ? 1 : 0;
+  a.Ainv = Ainv; a.disp = disp; a.unif = unif; a.cnt = accept_count;
+  return chain_launch(s, w, kRun, a, st, ev_start, ev_stop);
+}
+
+hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,
+                                hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  ChainArgs a{};
+  a.e0 = e; a.steps = 1; a.Ainv = w.A; a.r_new = r_new; a.ratio_out = ratio;
+  return chain_launch(s, w, kPropose, a, st, ev_start, ev_stop);
+}
+
+hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, hipStream_t st) {
+  ChainArgs a{};
+  a.e0 = e; a.steps = 1; a.store_A = 1; a.Ainv = w.A; a.acc = acc;
+  return chain_launch(s, w, kAccept, a, st, nullptr, nullptr);
 }
 
 }  // namespace qmc

@@ -110,8 +110,8 @@ struct SysDev {
   __host__ __device__ int store() const { return f32() ? (bf16() ? 2 : 1) : 0; }
   __host__ __device__ int prop_rows() const { return store() == 0 ? kPropRowsF64 : kPropRowsNarrow; }
   // entries per basis function of the transposed rows of the screened
-  // proposals: ptn for the up rows, then ptn for the down rows and the unpaired
-  // orbitals' values (n_up used of each, zeros after)
+  // proposals: ptn = n_up rounded up to 2 for the up rows, then as many for the
+  // down rows and the unpaired orbitals' values (n_up used of each, zeros after)
   int ptn;
   __host__ __device__ int pt_ld() const { return 2 * ptn; }
   double* R;        // [A][3]
@@ -430,26 +430,30 @@ __device__ __forceinline__ Radial radial_all(int kind, double zt, double q) {
   return o;
 }
 
+// (selected, not branched to: the lanes of a wave hold functions of every kind;
+// the roundings written out, so that every kernel gets the same value)
 __device__ __forceinline__ double angular_value(int kind, double x, double y, double z) {
-  switch (kind) {
-    case 0: return 1.0;
-    case 1: return x;
-    case 2: return y;
-    case 3: return z;
-    case 4: return x * y;
-    case 5: return y * z;
-    case 6: return z * x;
-    case 7: return x * x - y * y;
-    default: return 2.0 * z * z - x * x - y * y;
-  }
+#pragma clang fp contract(off)
+  const double yy = y * y;
+  double p = 1.0;
+  p = kind == 1 ? x : p;
+  p = kind == 2 ? y : p;
+  p = kind == 3 ? z : p;
+  p = kind == 4 ? x * y : p;
+  p = kind == 5 ? y * z : p;
+  p = kind == 6 ? z * x : p;
+  p = kind == 7 ? fma(x, x, -yy) : p;
+  p = kind >= 8 ? fma(2.0 * z, z, -fma(x, x, yy)) : p;
+  return p;
 }
 
 // Function mu of a basis table (packed centre + zeta, kind) at point
 // (px,py,pz): value only.  One packed record per function (one round trip).
 // The value from the function's record f and kind k (already loaded).
 __device__ __forceinline__ double basis_value_rec(const double4& f, int k, double px, double py, double pz) {
+#pragma clang fp contract(off)
   const double x = px - f.x, y = py - f.y, z = pz - f.z;
-  const double r2 = x * x + y * y + z * z;
+  const double r2 = fma(z, z, fma(y, y, x * x));
   return angular_value(kind_ang(k), x, y, z) * radial_e(k, f.w, r2);
 }
 
@@ -549,9 +553,49 @@ __device__ __forceinline__ void j2_radial(int form, const double* p, bool same, 
 // ---------------------------------------------------------------------------
 // wave-level reductions (64 lanes)
 // ---------------------------------------------------------------------------
+// Sum over the wave, the same bits in every lane: a butterfly over lane distances
+// 1, 2, 4, 8 by register-to-register DPP moves (quad_perm [1,0,3,2], [2,3,0,1],
+// row_half_mirror, row_mirror; after each step the lanes that exchange hold equal
+// partial sums), then over the rows of 16 and the halves by the row swaps.  A
+// butterfly by LDS permutes waits some 130 cycles a stage: 6 stages were 0.8 of
+// the 1.2 thousand cycles between a proposal's sums and its decision.  The adds
+// are never contracted with what produced v, so every kernel sums alike.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, false);
+  const unsigned hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// v of this lane's row (half) plus v of the row 16 (half 32) lanes away
+template <bool HALF>
+__device__ __forceinline__ double row_pair_sum(double v) {
+#pragma clang fp contract(off)
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  const u2 l = HALF ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  const u2 h = HALF ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __longlong_as_double((long long)(((unsigned long long)h.x << 32) | l.x)) +
+         __longlong_as_double((long long)(((unsigned long long)h.y << 32) | l.y));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+#pragma clang fp contract(off)
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0x141>(v);
+  v += dpp_f64<0x140>(v);
+  v = row_pair_sum<false>(v);
+  return row_pair_sum<true>(v);
+}
+// v summed over the lanes with the same index modulo m (a power of two from 4 to
+// 64, uniform): rotations by 8, then 4, within the rows, then the row swaps
+__device__ __forceinline__ double lane_group_sum(double v, int m) {
+#pragma clang fp contract(off)
+  if (m <= 8) v += dpp_f64<0x128>(v);
+  if (m <= 4) v += dpp_f64<0x124>(v);
+  if (m <= 16) v = row_pair_sum<false>(v);
+  if (m <= 32) v = row_pair_sum<true>(v);
   return v;
 }
 __device__ __forceinline__ float wave_sum(float v) {
@@ -631,16 +675,6 @@ hipError_t launch_screen_colmax(const SysDev& s, const WalkDev& w, int halves, h
 // (QMC_FP64) the transposed rows of half h (0: up, 1: down and unpaired) from P,
 // with their column maxima
 hipError_t launch_pt_build(const SysDev& s, const WalkDev& w, int h, hipStream_t st);
-// rows of a half padded so that the blocked screened stream takes them: the
-// smallest even m >= n with m / gcd(m, 128) <= 8 (n <= 256), else n made even
-inline int pt_pad(int n) {
-  if (n > 256) return round_up(n, 2);
-  for (int m = round_up(n, 2);; m += 2) {
-    int g = 128;
-    while (m % g) g >>= 1;
-    if (m / g <= 8) return m;
-  }
-}
 // the unpaired orbitals' entries of every walker's transposed rows
 hipError_t launch_pt_unpaired(const SysDev& s, const WalkDev& w, hipStream_t st);
 hipError_t launch_export_kept(const WalkDev& w, double* dst, hipStream_t st);
@@ -703,26 +737,23 @@ hipError_t launch_metropolis_accept_prep(const SysDev& s, const WalkDev& w, int 
                                          hipStream_t st);
 hipError_t launch_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc,
                          hipStream_t st);
-// Persistent sweep of k >= 2 moves e0, e0 + 1, ... (mod N): the k proposals and
-// the k - 1 accepts between them fused with the next set-up, in one launch
-// (one workgroup per walker); the set-up of e0 must have run, and the last
-// proposal is left for a plain accept.  No refresh, change of spin or P
-// rebuild may fall inside.  since0: the attempts since the last refresh at the
-// first accept.  sweep_segment_ok: whether the kernel is built for the system
-// and the spin of e0 (hipErrorNotSupported from the launch otherwise).
-bool sweep_segment_ok(const SysDev& s, const WalkDev& w, int e0);
-hipError_t launch_sweep_segment(const SysDev& s, const WalkDev& w, int e0, int k, const double* disp,
-                                const double* unif, int32_t* accept_count, int since0, hipStream_t st,
-                                hipEvent_t ev_start, hipEvent_t ev_stop);
-// Resident chain: `steps` Metropolis moves e0, e0 + 1, ... (mod N) of a small
-// system with every refresh and P rebuild between them, in one launch.
-// since0, buf_spin0, valid0 (P halves that hold, bit 0 up): the schedule state
-// at the start; Ainv [Wk][n][n]: the inverse there.  At the end A is the
-// inverse and the delayed-update buffer is empty.
-bool chain_ok(const SysDev& s, const WalkDev& w);
+// Resident moves (chain.hip): `steps` Metropolis moves e0, e0 + 1, ... (mod N) in
+// one launch.  chain_class: 1 small form (every refresh and P rebuild between the
+// moves runs in the kernel), 2 large form (the caller ends a launch where the
+// schedule refreshes or changes spin; the transposed rows of the streamed half
+// and its column maxima hold), 0 neither.  since0, buf_spin0, valid0 (P halves
+// that hold, bit 0 up): the schedule state at the start (small form); Ainv
+// [Wk][n][n]: the inverse there; store_A: write A back (the small form always
+// does, and leaves the delayed-update buffer empty).  The large form's systems
+// keep the inverse itself in A between calls: their single proposals and accepts
+// are launch_chain_propose and launch_chain_accept.
+int chain_class(const SysDev& s, const WalkDev& w);
 hipError_t launch_chain(const SysDev& s, const WalkDev& w, int e0, int steps, const double* disp, const double* unif,
-                        int32_t* accept_count, int since0, int buf_spin0, int valid0, bool all_rows, const double* Ainv,
-                        hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+                        int32_t* accept_count, int since0, int buf_spin0, int valid0, bool all_rows, bool store_A,
+                        const double* Ainv, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,
+                                hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, hipStream_t st);
 hipError_t launch_refresh_finish(const SysDev& s, const WalkDev& w, int32_t* status, hipStream_t st);
 // max |W X - I| per walker (P = W X given) and status 3 where it exceeds tol
 hipError_t launch_refresh_residual(const double* Pm, int n, int Wk, double tol, double* res, int32_t* status,

@@ -168,20 +168,12 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
 // one contiguous column of the rows the move streams per kept basis function
 // (for an up move the down electrons' rows and the unpaired orbitals; the
 // skipped ones change the ratio by at most s.screen_tol(), see
-// screen_list_body).  Blocked stream: one workgroup per walker, the ratio in
-// the first of its S partial slots (the others zeroed).  Plain stream: one
-// workgroup per 128 rows, one slot each.  The accept and finalize kernels sum
-// the slots as usual.
+// screen_list_body).  One workgroup per 128 rows of a walker, one partial slot
+// each; the accept and finalize kernels sum the slots as usual.
 // ---------------------------------------------------------------------------
-constexpr int kScreenRowsNB = 2;   // plain stream: 64 rows per lane slot, two slots
+constexpr int kScreenRowsNB = 2;   // rows a lane: 128 rows a workgroup
 __global__ void __launch_bounds__(256) propose_screened_kernel(SysDev s, WalkDev w, int e, int S, int chunks) {
   screened_rows_walker<kScreenRowsNB>(s, w, blockIdx.x / chunks, e, S, blockIdx.x % chunks);
-}
-
-template <int IPB>
-__global__ void __launch_bounds__(256) propose_screened_blk_kernel(SysDev s, WalkDev w, int e, int S, int FB) {
-  extern __shared__ __align__(16) char lds[];
-  screened_stream_walker<IPB>(s, w, blockIdx.x, e, S, FB, lds);
 }
 
 // Column maxima of the P halves (bit 0: up rows, bit 1: down rows):
@@ -347,13 +339,7 @@ hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, dou
   if (!w.PT || !w.muk) return hipErrorInvalidValue;
   const int S = propose_splits(s);
   const dim3 grid(w.Wk), blk(256);
-  int IPB, FB;
-  size_t lds;
-  if (screened_blk_config(s, w, e, IPB, FB, lds)) {
-#define QMC_SBLK(I) case I: QMC_LAUNCH_EV(propose_screened_blk_kernel<I>, grid, blk, lds, st, ev_start, ev_stop, s, w, e, S, FB); break;
-    switch (IPB) { QMC_SBLK(1) QMC_SBLK(2) QMC_SBLK(3) QMC_SBLK(4) QMC_SBLK(5) QMC_SBLK(6) QMC_SBLK(7) QMC_SBLK(8) }
-#undef QMC_SBLK
-  } else if (s.nu <= kBigMaxN) {
+  if (s.nu <= kBigMaxN) {
     const int chunks = (s.nu + 64 * kScreenRowsNB - 1) / (64 * kScreenRowsNB);
     QMC_LAUNCH_EV(propose_screened_kernel, dim3((unsigned)(w.Wk * chunks)), blk, 0, st, ev_start, ev_stop, s, w, e, S,
                   chunks);
@@ -371,7 +357,7 @@ accept_prep_staged_kernel(SysDev s, WalkDev w, int e, const double* __restrict__
                           int32_t* __restrict__ accept_count, int S, int e2, const double* __restrict__ disp2,
                           int mc) {
   extern __shared__ __align__(16) char lds[];
-  accept_prep_staged_phase<T, QL>(s, w, blockIdx.x, e, unif, accept_count, S, e2, disp2, mc, mc, lds);
+  accept_prep_staged_phase<T, QL>(s, w, blockIdx.x, e, unif, accept_count, S, e2, disp2, mc, lds);
 }
 
 static hipError_t accept_launch(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc,

@@ -1,6 +1,6 @@
-// Device code shared by the move kernels (move.hip) and the persistent sweep
-// (sweep.hip): the screened proposal's streaming phase and the Metropolis
-// accept fused with the next proposal's set-up, staged through LDS.
+// Device code of the move kernels (move.hip): the screened proposal's
+// streaming phase and the Metropolis accept fused with the next proposal's
+// set-up, staged through LDS.
 #pragma once
 #include "move_dev.h"
 
@@ -10,25 +10,6 @@ constexpr int kStageQL = (kFuseMaxLp + 255) / 256;   // per-thread slots over Lp
 __host__ __device__ inline size_t pad1k(size_t b) { return (b + 1023) & ~(size_t)1023; }
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 
-// threadIdx.x through an opaque move: values computed from it stay inside the
-// phase that computes them.  In the persistent sweep's loop the compiler would
-// otherwise hoist each phase's per-lane addresses and loads out of the loop and
-// keep them live across the other phase, past 128 VGPRs.
-__device__ __forceinline__ int phase_tid() {
-  int z;
-  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
-  return (int)threadIdx.x + z;
-}
-
-// Blocked form of the same sum, over the padded row count n (s.ptn): the kept
-// functions are taken FB at a time (FB n a multiple of 128, IPB = FB n / 128 <=
-// 8), and a wave reads a block's FB columns (FB n doubles) with IPB 16-byte
-// loads of all 64 lanes: lane l of load i holds the two rows j, j + 1 of
-// function f with 2 (64 i + l) = f n + j, fixed over the blocks.  The kept list and the
-// inverse line come first (one round), then every wave issues about eight
-// loads at once (8 / IPB blocks), some 32 KiB in flight per walker.  The
-// per-lane sums go to LDS and row j adds its FB x 4 partial sums in a fixed
-// order (waves outer, functions inner).
 constexpr int kStageMaxN = 128;    // n <= 128 (one W entry per thread)
 constexpr int kStageMaxNe = 256;   // electrons
 constexpr int kStageMaxNuc = 256;  // nuclei (one per thread)
@@ -38,129 +19,14 @@ constexpr size_t kStageMaxLds = 63 * 1024;   // dynamic LDS (the static arrays t
 struct StageLayout {
   size_t V, D, S, vec, total;   // byte offsets of the regions and the size
 };
-// vec_min: the vector area starts at vec_min or later (the persistent sweep
-// keeps its hand-off arrays below it)
-__host__ __device__ inline StageLayout stage_layout(int n, int kb, int mc, size_t vec_min = 0) {
+__host__ __device__ inline StageLayout stage_layout(int n, int kb, int mc) {
   StageLayout o;
   o.V = 0;
   o.D = o.V + pad1k(sizeof(double) * (size_t)(mc + 1) * n);
   o.S = o.D + pad1k(sizeof(double) * (size_t)(mc + 1) * n);
   o.vec = o.S + pad1k(sizeof(double) * (size_t)(mc + 1) * kb);
-  if (o.vec < vec_min) o.vec = vec_min;
   o.total = o.vec + sizeof(double) * (3 * (size_t)n + 5 * (size_t)kb);
   return o;
-}
-
-// The persistent sweep hands values from one phase of a move to the next
-// through LDS rather than global memory (a load of a value the workgroup has
-// just stored waits for the store): the new W line and the partial ratios of a
-// proposal (to the accept), the kept count of a screened set-up (to the next
-// proposal; the kept list itself and psi(r') go to the bottom of the dynamic
-// LDS, the inverse line stays in the vector area).
-struct SweepHand {
-  double wn[kStageMaxN];
-  double part[kStageMaxSplits];
-  int cnt;
-};
-
-
-// HAND (persistent sweep): with from_lds the kept list is already at the
-// bottom of lds, its count in hand->cnt and the inverse line in cvl (the set-up
-// ran in the same workgroup); the new W line and the partial ratios also go to
-// hand.
-template <int IPB, bool HAND = false>
-__device__ void screened_stream_walker(const SysDev& s, const WalkDev& w, int wk, int e, int S, int FB, char* lds,
-                                       SweepHand* hand = nullptr, const double* cvl = nullptr,
-                                       bool from_lds = false) {
-  __shared__ double red[8];
-  const int tid = phase_tid(), lane = tid & 63, wave = tid >> 6;
-  const bool up = e < s.nu;
-  const int n = s.nu, np = s.ptn;   // rows of either half (unpaired orbitals after the down rows), padded
-  const int i0 = up ? np : 0;
-  const int Lp = s.Lp, ld = s.pt_ld();
-  const double* base = w.PT + (long)wk * Lp * ld + i0;
-  int* lmu = (int*)lds;
-  double* lv = (double*)(lds + pad1k(sizeof(int) * (size_t)Lp));
-  dbl2* part = (dbl2*)((char*)lv + pad1k(sizeof(double) * (size_t)Lp));
-  int cnt;
-  double cj;
-  if (HAND && from_lds) {
-    cnt = hand->cnt;
-    cj = cvl[tid < n ? tid : 0];
-  } else {
-    // the kept list (the whole Lp-long arrays: no wait on the count), c
-    const int* mk = w.muk + (long)wk * Lp;
-    const double* pk = w.psk + (long)wk * Lp;
-    int xm[kStageQL];
-    double xv[kStageQL];
-#pragma unroll
-    for (int k = 0; k < kStageQL; ++k) {
-      const int q = tid + 256 * k, qc = q < Lp ? q : 0;
-      xm[k] = mk[qc];
-      xv[k] = pk[qc];
-    }
-    cnt = w.nkeep[wk];
-    cj = w.cvec[(long)wk * s.nu + (tid < n ? tid : 0)];
-#pragma unroll
-    for (int k = 0; k < kStageQL; ++k) {
-      const int q = tid + 256 * k;
-      if (q < Lp) { lmu[q] = xm[k]; lv[q] = xv[k]; }
-    }
-  }
-  __syncthreads();
-  // this lane's (function, row) of each of its IPB loads
-  int fi[IPB], ji[IPB];
-#pragma unroll
-  for (int i = 0; i < IPB; ++i) {
-    const int el = 2 * (64 * i + lane);
-    fi[i] = el / np;
-    ji[i] = el - fi[i] * np;
-  }
-  dbl2 acc[IPB];
-#pragma unroll
-  for (int i = 0; i < IPB; ++i) acc[i] = dbl2{0.0, 0.0};
-  const int nblk = (cnt + FB - 1) / FB;
-  constexpr int UB = 8 / IPB > 1 ? 8 / IPB : 1;   // blocks per wave in flight (8 loads)
-  for (int b0 = wave; b0 < nblk; b0 += 4 * UB) {
-    dbl2 x[UB][IPB];
-    double vv[UB][IPB];
-#pragma unroll
-    for (int u = 0; u < UB; ++u)
-#pragma unroll
-      for (int i = 0; i < IPB; ++i) {
-        const int kk = (b0 + 4 * u) * FB + fi[i];
-        const bool ok = kk < cnt;
-        const int mu = lmu[ok ? kk : 0];
-        vv[u][i] = ok ? lv[kk] : 0.0;
-        x[u][i] = __builtin_nontemporal_load((const dbl2*)(base + (long)mu * ld + ji[i]));
-      }
-#pragma unroll
-    for (int u = 0; u < UB; ++u)
-#pragma unroll
-      for (int i = 0; i < IPB; ++i) {
-        acc[i].x += vv[u][i] * x[u][i].x;
-        acc[i].y += vv[u][i] * x[u][i].y;
-      }
-  }
-#pragma unroll
-  for (int i = 0; i < IPB; ++i) part[wave * 64 * IPB + 64 * i + lane] = acc[i];
-  __syncthreads();
-  const double* pd = (const double*)part;
-  double* wn = w.w_new + (long)wk * s.nu;
-  double rp = 0.0;
-  if (tid < n) {
-    double t = 0.0;
-    for (int v = 0; v < 4; ++v)
-      for (int f = 0; f < FB; ++f) t += pd[v * 128 * IPB + f * np + tid];
-    wn[tid] = t;
-    if (HAND) hand->wn[tid] = t;
-    rp = t * cj;
-  }
-  const double R = block_sum_mv(rp, red);
-  for (int q = tid; q < S; q += blockDim.x) {
-    w.rdet_part[(long)wk * S + q] = q == 0 ? R : 0.0;
-    if (HAND) hand->part[q] = q == 0 ? R : 0.0;
-  }
 }
 
 // The plain screened stream of one walker (any row count), one workgroup of
@@ -230,23 +96,6 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
   if (tid == 0) w.rdet_part[(long)wk * S + c] = R;
   if (c == 0)
     for (int q = chunks + tid; q < S; q += blockDim.x) w.rdet_part[(long)wk * S + q] = 0.0;
-}
-
-// The blocked screened stream for proposals of e: n = s.ptn, FB = 128 /
-// gcd(n, 128) functions per block, IPB = FB n / 128 loads per lane and block,
-// at most 8; n <= 256 (one row per thread in the final sums), Lp <=
-// kFuseMaxLp (the kept list in LDS).  False: the plain screened kernel.
-__host__ __device__ inline bool screened_blk_config(const SysDev& s, const WalkDev& w, int e, int& IPB, int& FB,
-                                                   size_t& lds) {
-  const int n = s.ptn;
-  int g = 128;
-  while (n % g) g >>= 1;
-  FB = 128 / g;
-  IPB = FB * n / 128;
-  lds = pad1k(sizeof(int) * (size_t)s.Lp) + pad1k(sizeof(double) * (size_t)s.Lp) +
-        sizeof(dbl2) * 4 * 64 * (size_t)IPB;
-  (void)e;
-  return n <= 256 && IPB >= 1 && IPB <= 8 && s.Lp <= kFuseMaxLp && (uintptr_t)w.PT % 16 == 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -328,21 +177,20 @@ __device__ __forceinline__ double jastrow_staged(const SysDev& s, int e, double 
   return val;
 }
 
-template <typename T, bool STAGED, int QL, bool HAND = false>
+template <typename T, bool STAGED, int QL>
 __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int wk, int e, double u,
                                         int32_t* __restrict__ cnt, int cnt0, int S, int e2, double px, double py,
                                         double pz, double R, double dJ, int m, int mc, char* lds, const StagePre& q,
                                         const double* j2p, double la, double sg, double jv, double rx, double ry,
-                                        double rz, double ox, double oy, double oz, SweepHand* hand = nullptr,
-                                        size_t vec_min = 0) {
+                                        double rz, double ox, double oy, double oz) {
   __shared__ double red[16];
   __shared__ double gam_s;
   __shared__ int wcnt[QL][4];
-  const int tid = phase_tid(), lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
   const int n = s.nu, kb = w.kb, N = s.N, L = s.L, Lp = s.Lp;
   const bool up = e < n;
   const int ie = up ? e : e - n;
-  const StageLayout ly = stage_layout(n, kb, mc, vec_min);
+  const StageLayout ly = stage_layout(n, kb, mc);
   double* Vl = (double*)(lds + ly.V);
   double* Dl = (double*)(lds + ly.D);
   double* Sl = (double*)(lds + ly.S);
@@ -499,37 +347,28 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
     for (int k2 = 0; k2 < wave; ++k2) before += wcnt[k][k2];
     if ((bal[k] >> lane) & 1ull) {
       const int at = before + __popcll(bal[k] & ((1ull << lane) - 1ull));
-      if (HAND) {   // the list where the screened stream keeps it (the staged rows are no longer read)
-        ((int*)lds)[at] = 256 * k + tid;
-        ((double*)(lds + pad1k(sizeof(int) * (size_t)Lp)))[at] = q.sv[k];
-      } else {
-        mk[at] = 256 * k + tid;
-        pk[at] = q.sv[k];
-      }
+      mk[at] = 256 * k + tid;
+      pk[at] = q.sv[k];
     }
     for (int k2 = 0; k2 < nw; ++k2) off += wcnt[k][k2];
   }
-  if (tid == 0) {
-    w.nkeep[wk] = off;
-    if (HAND) hand->cnt = off;
-  }
+  if (tid == 0) w.nkeep[wk] = off;
 }
 
 // One walker's fused accept and set-up (the staged kernel's work for walker
-// wk): rows below mc of V and D are staged; the LDS regions are laid out for
-// mcl >= mc rows (the persistent sweep keeps one layout for all its moves).
-template <typename T, int QL, bool HAND = false>
+// wk): rows below mc of V and D are staged.
+template <typename T, int QL>
 __device__ void accept_prep_staged_phase(const SysDev& s, const WalkDev& w, int wk, int e,
                                          const double* __restrict__ unif, int32_t* __restrict__ accept_count,
-                                         int S, int e2, const double* __restrict__ disp2, int mc, int mcl,
-                                         char* lds, SweepHand* hand = nullptr, size_t vec_min = 0) {
+                                         int S, int e2, const double* __restrict__ disp2, int mc,
+                                         char* lds) {
   __shared__ double scal[kStageMaxSplits + 22];
   __shared__ int ints_s[2];
-  const int tid = phase_tid();
+  const int tid = threadIdx.x;
   const int n = s.nu, kb = w.kb, N = s.N, L = s.L, Lp = s.Lp;
   const bool up = e < n, up2 = e2 < n;
   const int ie = up ? e : e - n, ie2 = up2 ? e2 : e2 - n;
-  const StageLayout ly = stage_layout(n, kb, mcl, vec_min);
+  const StageLayout ly = stage_layout(n, kb, mc);
   // bulk copies first
   lds_copy_async(lds + ly.V, w.wv + (long)wk * kb * n, 8 * mc * n);
   lds_copy_async(lds + ly.D, w.wd + (long)wk * kb * n, 8 * mc * n);
@@ -554,7 +393,7 @@ __device__ void accept_prep_staged_phase(const SysDev& s, const WalkDev& w, int 
     const int j = tid < n ? tid : 0;
     const double* Ww = w.W + (long)wk * n * n;
     const double* A0 = w.A + (long)wk * n * n;
-    q.wn = HAND ? hand->wn[j] : w.w_new[(long)wk * n + j];
+    q.wn = w.w_new[(long)wk * n + j];
     q.Wo = up ? Ww[(long)ie * n + j] : Ww[(long)j * n + ie];
     q.v0 = w.v0[(long)wk * n + j];
     q.a0 = up2 ? A0[(long)j * n + ie2] : A0[(long)ie2 * n + j];
@@ -573,7 +412,7 @@ __device__ void accept_prep_staged_phase(const SysDev& s, const WalkDev& w, int 
   // r' of e and r of e2 and the eight two-body parameters (wave 1), the
   // buffered-move and accept counts.  Loads first, unconditionally (every
   // address valid), stores after.
-  const double pv = HAND ? hand->part[tid < S ? tid : 0] : w.rdet_part[(long)wk * S + (tid < S ? tid : 0)];
+  const double pv = w.rdet_part[(long)wk * S + (tid < S ? tid : 0)];
   const int t2 = tid - 64;
   const double* sp;
   switch (t2) {
@@ -613,13 +452,11 @@ __device__ void accept_prep_staged_phase(const SysDev& s, const WalkDev& w, int 
   __syncthreads();
   int32_t* cnt = accept_count ? accept_count + wk : nullptr;
   if (m <= mc)
-    accept_prep_staged_body<T, true, QL, HAND>(s, w, wk, e, u, cnt, ints_s[1], S, e2, px, py, pz, R, dJ, m, mcl,
-                                               lds, q, sc + 14, la, sg, jv, rx, ry, rz, sc[11], sc[12], sc[13],
-                                               hand, vec_min);
+    accept_prep_staged_body<T, true, QL>(s, w, wk, e, u, cnt, ints_s[1], S, e2, px, py, pz, R, dJ, m, mc,
+                                               lds, q, sc + 14, la, sg, jv, rx, ry, rz, sc[11], sc[12], sc[13]);
   else
-    accept_prep_staged_body<T, false, QL, HAND>(s, w, wk, e, u, cnt, ints_s[1], S, e2, px, py, pz, R, dJ, m, mcl,
-                                                lds, q, sc + 14, la, sg, jv, rx, ry, rz, sc[11], sc[12], sc[13],
-                                                hand, vec_min);
+    accept_prep_staged_body<T, false, QL>(s, w, wk, e, u, cnt, ints_s[1], S, e2, px, py, pz, R, dJ, m, mc,
+                                                lds, q, sc + 14, la, sg, jv, rx, ry, rz, sc[11], sc[12], sc[13]);
 }
 
 }  // namespace qmc

@@ -149,6 +149,7 @@ struct qmc_walkers {
   bool evaluated = false;
   bool P_up_valid = false, P_dn_valid = false;
   bool delayed = false;             // the delayed-update buffer may hold moves
+  int cls = 0;                      // chain_class of the system
   bool PT_ok[2] = {false, false};   // the transposed rows and column maxima of each P half hold
   // (QMC_REFINED) parameter generation at which each P half's rows were last
   // built with their positions recorded (-1: never): a later build of that
@@ -258,7 +259,7 @@ extern "C" qmc_status qmc_system_create(const qmc_system_desc* desc, qmc_system*
   if (hipGetDevice(&s->device) != hipSuccess) s->device = 0;
   d.n_nuc = q.n_nuc; d.L = L; d.Lp = round_up(L, 32);
   d.nu = q.n_up; d.nd = q.n_dn; d.N = q.n_up + q.n_dn; d.nk = pf ? 0 : q.n_up - q.n_dn;
-  d.ptn = pt_pad(q.n_up);
+  d.ptn = round_up(q.n_up, 2);
   d.pairing = pf ? 1 : 0; d.pk = pf ? q.pf_k : 0; d.npf = pf ? d.N + q.pf_k : 0;
   d.j1_form = q.j1_form; d.j2_form = q.j2_form;
   for (int k = 0; k < 8; ++k) d.j2[k] = (q.j2 && k < q.n_j2) ? q.j2[k] : 0.0;
@@ -738,6 +739,7 @@ extern "C" qmc_status qmc_walkers_create(qmc_system* sys, int32_t n_walkers, int
   Carver cv{(char*)base};
   walker_layout(sys->d, n_walkers, adjoint, cv, *wk);
   wk->aw_ready = adjoint;
+  wk->cls = chain_class(sys->d, wk->d);
   hipError_t e = hipMemset(base, 0, need);
   if (e == hipSuccess && sys->d.oz_rows() && sys->d.nk > 0) {   // the unpaired orbitals' transposed rows
     e = launch_pt_unpaired(sys->d, wk->d, nullptr);
@@ -949,6 +951,13 @@ extern "C" qmc_status qmc_propose_move(qmc_system* sys, qmc_walkers* wk, int32_t
   if (c) return c;
   c = ensure_P(wk, electron, stream, drift_new == nullptr);
   if (c) return c;
+  if (wk->cls == 2 && !drift_new) {
+    hipEvent_t ea, eb;
+    HIP_TRY(wk->tm.begin_ext(QMC_T_PROPOSE, &ea, &eb), "timer begin");
+    HIP_TRY(launch_chain_propose(s, wk->d, electron, r_new, ratio, stream, ea, eb), "resident proposal");
+    wk->pending_e = electron;
+    return QMC_OK;
+  }
   TIMED(wk, QMC_T_PROPOSE_PREP, stream,
         launch_propose_prep(s, wk->d, electron, r_new, nullptr, drift_new != nullptr, stream), "propose prep");
 {
@@ -1040,7 +1049,7 @@ static qmc_status after_accept(qmc_walkers* wk, int e, int32_t* status, hipStrea
   const SysDev& s = wk->sys->d;
   if (e < s.nu) wk->P_up_valid = false; else wk->P_dn_valid = false;
   wk->pending_e = -1;
-  wk->delayed = true;
+  wk->delayed = wk->cls != 2;   // (those keep the inverse itself)
   Sched q{wk->attempts, wk->since, wk->buf_spin};
   const bool post = sched_after(s, q);
   wk->attempts = q.attempts;
@@ -1081,7 +1090,10 @@ extern "C" qmc_status qmc_accept_move(qmc_system* sys, qmc_walkers* wk, int32_t 
           "Pfaffian accept");
     return pf_after_accept(wk, status, stream);
   }
-  TIMED(wk, QMC_T_ACCEPT, stream, launch_accept(sys->d, wk->d, electron, accept, stream), "accept");
+  TIMED(wk, QMC_T_ACCEPT, stream,
+        wk->cls == 2 ? launch_chain_accept(sys->d, wk->d, electron, accept, stream)
+                     : launch_accept(sys->d, wk->d, electron, accept, stream),
+        "accept");
   return after_accept(wk, electron, status, stream);
 }
 
@@ -1111,18 +1123,6 @@ static bool fusable(const qmc_walkers* wk, int e, int e2) {
   MoveState m{Sched{wk->attempts, wk->since, wk->buf_spin}, wk->P_up_valid, wk->P_dn_valid};
   return fuse_step(wk, m, e, e2);
 }
-// Moves t, t + 1, ..., t + k - 1 of a vmc_steps call whose accepts, all but
-// the last, are fusable with the next set-up: the k of the run starting at t.
-static int fused_run(const qmc_walkers* wk, int e_start, int t, int n_steps) {
-  const int N = wk->sys->d.N;
-  MoveState m{Sched{wk->attempts, wk->since, wk->buf_spin}, wk->P_up_valid, wk->P_dn_valid};
-  int k = 1;
-  while (t + k < n_steps &&
-         fuse_step(wk, m, (int)((e_start + (long)t + k - 1) % N), (int)((e_start + (long)t + k) % N)))
-    ++k;
-  return k;
-}
-
 // The moves of a small system: the resident chain, then the same bookkeeping
 // as the per-move path's.
 static qmc_status chain_steps(qmc_walkers* wk, int32_t e_start, int32_t n_steps, const double* disp, const double* unif,
@@ -1139,7 +1139,7 @@ static qmc_status chain_steps(qmc_walkers* wk, int32_t e_start, int32_t n_steps,
   hipEvent_t ea, eb;
   HIP_TRY(wk->tm.begin_ext(QMC_T_SWEEP, &ea, &eb), "timer begin");
   HIP_TRY(launch_chain(s, wk->d, (int)(e_start % s.N), n_steps, disp, unif, accept_count, wk->since, wk->buf_spin,
-                       (wk->P_up_valid ? 1 : 0) | (wk->P_dn_valid ? 2 : 0), all, Ainv, stream, ea, eb),
+                       (wk->P_up_valid ? 1 : 0) | (wk->P_dn_valid ? 2 : 0), all, true, Ainv, stream, ea, eb),
           "resident chain");
   wk->yt_valid = wk->lr_ready = false;
   wk->delayed = false;
@@ -1163,11 +1163,50 @@ static qmc_status chain_steps(qmc_walkers* wk, int32_t e_start, int32_t n_steps,
   return QMC_OK;
 }
 
+// The moves of a system of the large resident form: one launch per run of
+// moves between which the schedule neither refreshes nor changes spin.
+static qmc_status chain_runs(qmc_walkers* wk, int32_t e_start, int32_t n_steps, const double* disp, const double* unif,
+                             int32_t* accept_count, hipStream_t stream) {
+  const SysDev& s = wk->sys->d;
+  const long Wk = wk->d.Wk;
+  for (int t = 0; t < n_steps;) {
+    const int e = (int)((e_start + (long)t) % s.N);
+    qmc_status c = before_propose(wk, e, stream);
+    if (c) return c;
+    c = ensure_P(wk, e, stream);
+    if (c) return c;
+    // moves until the buffer would be full or the other spin's turn comes
+    const int spin = e < s.nu ? 0 : 1;
+    int k = 0;
+    bool post = false, turn = false;
+    while (t + k < n_steps && !post && !turn) {
+      ++k;
+      post = wk->since + k >= wb_cap(s);
+      const int e2 = (int)((e_start + (long)t + k) % s.N);
+      turn = (e2 < s.nu ? 0 : 1) != spin;
+    }
+    // a refresh follows at once, now or before the other spin's first proposal
+    const bool refreshed = post || (turn && t + k < n_steps);
+    hipEvent_t ea, eb;
+    HIP_TRY(wk->tm.begin_ext(QMC_T_SWEEP, &ea, &eb), "timer begin");
+    HIP_TRY(launch_chain(s, wk->d, e, k, disp + (long)t * Wk * 3, unif + (long)t * Wk, accept_count, 0, -1, 3, false,
+                         !refreshed, wk->d.A, stream, ea, eb),
+            "resident moves");
+    for (int j = 0; j < k; ++j) {   // (only the last can refresh)
+      c = after_accept(wk, (int)((e_start + (long)t + j) % s.N), nullptr, stream);
+      if (c) return c;
+    }
+    t += k;
+  }
+  return QMC_OK;
+}
+
 // n_steps Metropolis moves of a determinant system from electron e_start on.
 static qmc_status run_moves(qmc_walkers* wk, int32_t e_start, int32_t n_steps, const double* disp, const double* unif,
                             int32_t* accept_count, hipStream_t stream) {
   const SysDev& s = wk->sys->d;
-  if (chain_ok(s, wk->d)) return chain_steps(wk, e_start, n_steps, disp, unif, accept_count, stream);
+  if (wk->cls == 1) return chain_steps(wk, e_start, n_steps, disp, unif, accept_count, stream);
+  if (wk->cls == 2) return chain_runs(wk, e_start, n_steps, disp, unif, accept_count, stream);
   qmc_status c;
   const long Wk = wk->d.Wk;
   bool prepped = false;   // the set-up of step t ran in step t-1's fused accept
@@ -1180,34 +1219,6 @@ static qmc_status run_moves(qmc_walkers* wk, int32_t e_start, int32_t n_steps, c
       if (c) return c;
       TIMED(wk, QMC_T_PROPOSE_PREP, stream,
             launch_propose_prep(s, wk->d, e, nullptr, disp + (long)t * Wk * 3, false, stream), "propose prep");
-      // a run of fusable moves from here: one persistent launch, then the
-      // bookkeeping of its fused steps (which launches nothing) and a plain
-      // accept of its last proposal
-      const int k = sweep_segment_ok(s, wk->d, e) ? fused_run(wk, e_start, t, n_steps) : 1;
-      if (k >= 2) {
-        hipEvent_t ea, eb;
-        HIP_TRY(wk->tm.begin_ext(QMC_T_SWEEP, &ea, &eb), "timer begin");
-        HIP_TRY(launch_sweep_segment(s, wk->d, e, k, disp + (long)t * Wk * 3, unif + (long)t * Wk, accept_count,
-                                     wk->since, stream, ea, eb),
-                "persistent sweep");
-        for (int j = 0; j + 1 < k; ++j) {
-          const int ej = (int)((e_start + (long)t + j) % s.N), ej2 = (int)((e_start + (long)t + j + 1) % s.N);
-          c = after_accept(wk, ej, nullptr, stream);
-          if (c) return c;
-          c = before_propose(wk, ej2, stream);
-          if (c) return c;
-          c = ensure_P(wk, ej2, stream);
-          if (c) return c;
-        }
-        const long tl = t + k - 1;
-        TIMED(wk, QMC_T_ACCEPT, stream,
-              launch_metropolis_accept(s, wk->d, (int)((e_start + tl) % s.N), unif + tl * Wk, accept_count, stream),
-              "metropolis");
-        c = after_accept(wk, (int)((e_start + tl) % s.N), nullptr, stream);
-        if (c) return c;
-        t += k - 1;
-        continue;
-      }
     }
 {
       hipEvent_t ea, eb;
@@ -1538,16 +1549,20 @@ struct qmc_multi {
   int grid_rows = 2048, grid_items = 1024;
   int nc = 1;
   int store = 0;        // 0 FP64, 1 FP32, 2 BF16 rows
-  // FP64 rows: each member runs as a chain of its own on its own stream, forked
-  // from and joined to the group's; Philox draws are filled for `draw_steps`
+  // FP64 rows: each member runs as a chain of its own, on one of a few streams
+  // forked from and joined to the group's; Philox draws are filled for `draw_steps`
   // steps at a time
   struct Chain {
-    hipStream_t st = nullptr;
-    hipEvent_t done = nullptr;
+    int st = 0;                  // its stream of `streams`
     double *disp = nullptr, *unif = nullptr;
     int draw_steps = 0;
   };
   std::vector<Chain> chains;
+  // as many as the device has hardware queues for one process: streams that
+  // share a queue run one after the other in the order they were filled
+  static constexpr int kStreams = 4;
+  hipStream_t streams[kStreams] = {};
+  hipEvent_t done[kStreams] = {};
   hipStream_t own = nullptr;
   hipEvent_t ev_a = nullptr, ev_b = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -1557,9 +1572,9 @@ struct qmc_multi {
     if (gexec) (void)hipGraphExecDestroy(gexec);
     if (ev_a) (void)hipEventDestroy(ev_a);
     if (ev_b) (void)hipEventDestroy(ev_b);
-    for (auto& c : chains) {
-      if (c.st) { (void)hipStreamSynchronize(c.st); (void)hipStreamDestroy(c.st); }
-      if (c.done) (void)hipEventDestroy(c.done);
+    for (int q = 0; q < kStreams; ++q) {
+      if (streams[q]) { (void)hipStreamSynchronize(streams[q]); (void)hipStreamDestroy(streams[q]); }
+      if (done[q]) (void)hipEventDestroy(done[q]);
     }
     if (own) { (void)hipStreamSynchronize(own); (void)hipStreamDestroy(own); }
     for (void* p : allocs) (void)hipFree(p);
@@ -1655,8 +1670,18 @@ extern "C" qmc_status qmc_multi_create(int32_t n_members, qmc_system* const* sys
       c.draw_steps = (int)std::max<size_t>(32, std::min<size_t>(256, (size_t)8 * 1024 * 1024 / (32 * Wk)));
       al((void**)&c.disp, sizeof(double) * 3 * Wk * c.draw_steps);
       al((void**)&c.unif, sizeof(double) * Wk * c.draw_steps);
-      if (!e) e = hipStreamCreateWithFlags(&c.st, hipStreamNonBlocking);
-      if (!e) e = hipEventCreateWithFlags(&c.done, hipEventDisableTiming);
+    }
+    for (int q = 0; q < qmc_multi::kStreams; ++q) {
+      if (!e) e = hipStreamCreateWithFlags(&m->streams[q], hipStreamNonBlocking);
+      if (!e) e = hipEventCreateWithFlags(&m->done[q], hipEventDisableTiming);
+    }
+    // largest first, each to the stream with the least so far (a member's time
+    // grows about as its rows of W and a constant)
+    long load[qmc_multi::kStreams] = {};
+    for (int k : m->order) {
+      const int q = (int)(std::min_element(load, load + qmc_multi::kStreams) - load);
+      m->chains[k].st = q;
+      load[q] += m->h_sys[k].nu + 32;
     }
   }
   if (e != hipSuccess) { delete m; return hip_fail(e, "multi_create"); }
@@ -1748,40 +1773,42 @@ static hipError_t multi_enqueue(qmc_multi* m, int n_steps, bool explicit_draws, 
 }
 
 // FP64 rows: every member's n_steps as a chain of its own (the one-system moves,
-// so a member evolves exactly as it would alone) on its own stream, between a
-// fork from the group's stream and a join to it.  A member alone leaves most of
+// so a member evolves exactly as it would alone) on one of a few streams, between
+// a fork from the group's stream and a join to it.  A member alone leaves most of
 // the chip idle (256 walkers are one workgroup per compute unit, waiting on
 // their own dependent steps), and the members share no state, so their chains
 // overlap; in step with each other, phase by phase, they would wait for the
 // largest one in every launch.  Larger members are enqueued first.
 static qmc_status chains_enqueue(qmc_multi* m, int n_steps, bool expl, unsigned long long seed, double sigma) {
   HIP_TRY(hipEventRecord(m->ev_b, m->own), "fork");
+  for (int q = 0; q < qmc_multi::kStreams; ++q) HIP_TRY(hipStreamWaitEvent(m->streams[q], m->ev_b, 0), "fork");
   qmc_status c = QMC_OK;
   for (int k : m->order) {
     auto& ch = m->chains[k];
     qmc_walkers* w = m->wk[k];
-    HIP_TRY(hipStreamWaitEvent(ch.st, m->ev_b, 0), "fork");
+    const hipStream_t st = m->streams[ch.st];
     const int N = w->sys->d.N;
     const bool timed = w->tm.on;
     w->tm.on = false;   // (group moves are not timed)
     if (expl) {
-      c = run_moves(w, (int)(w->attempts % N), n_steps, m->h_disp[k], m->h_unif[k], nullptr, ch.st);
+      c = run_moves(w, (int)(w->attempts % N), n_steps, m->h_disp[k], m->h_unif[k], nullptr, st);
     } else {
       for (int t = 0; t < n_steps && !c; t += ch.draw_steps) {
         const int steps = std::min(ch.draw_steps, n_steps - t);
         const hipError_t e =
-            launch_philox_steps(seed, k, w->d.Wk, m->d_steps + k, t, steps, sigma, ch.disp, ch.unif, ch.st);
+            launch_philox_steps(seed, k, w->d.Wk, m->d_steps + k, t, steps, sigma, ch.disp, ch.unif, st);
         c = e != hipSuccess ? hip_fail(e, "draws")
-                            : run_moves(w, (int)(w->attempts % N), steps, ch.disp, ch.unif, nullptr, ch.st);
+                            : run_moves(w, (int)(w->attempts % N), steps, ch.disp, ch.unif, nullptr, st);
       }
     }
     w->tm.on = timed;
-    // joined whatever happened, so that the group's stream never leaves a
-    // member's work behind
-    const hipError_t e1 = hipEventRecord(ch.done, ch.st);
-    const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(m->own, ch.done, 0) : e1;
-    if (c) return c;
-    HIP_TRY(e2, "join");
+    if (c) break;
+  }
+  // joined whatever happened, so that the group's stream never leaves a
+  // member's work behind
+  for (int q = 0; q < qmc_multi::kStreams; ++q) {
+    HIP_TRY(hipEventRecord(m->done[q], m->streams[q]), "join");
+    HIP_TRY(hipStreamWaitEvent(m->own, m->done[q], 0), "join");
   }
   return c;
 }

@@ -43,7 +43,8 @@ def _setup(P, s, Wk, seed=31, precision=None):
 @pytest.mark.parametrize("n_up,n_dn,shells,every,jastrow", [
     (1, 1, (0, 0, 1), 32, False), (2, 0, (0, 0, 1), 32, True), (4, 4, (0, 0, 0, 1), 1, False), (8, 7, (0, 0, 0, 1), 32, True),
     (9, 9, (0, 0, 0, 1), 5, False), (16, 16, (0, 0, 0, 1), 64, False), (17, 15, (0, 0, 1), 16, True),
-    (20, 20, (0, 0, 0, 0, 1, 1, 2), 32, False), (33, 31, (0, 1), 32, False)])
+    (20, 20, (0, 0, 0, 0, 1, 1, 2), 32, False), (33, 31, (0, 1), 32, False), (33, 33, (0, 0, 0, 1), 8, True),
+    (5, 4, (0, 0, 0, 0, 0, 0, 0, 1, 1, 1, 1, 1, 1, 2, 2, 2, 2, 2, 2, 2, 2), 5, False)])
 def test_chain_equals_oracle(n_up, n_dn, shells, every, jastrow):
     P = need_gpu()
     s = _system(n_up, n_dn, shells, every, jastrow)
