@@ -434,7 +434,7 @@ __device__ __forceinline__ Radial radial_all(int kind, double zt, double q) {
 // the roundings written out, so that every kernel gets the same value)
 __device__ __forceinline__ double angular_value(int kind, double x, double y, double z) {
 #pragma clang fp contract(off)
-  const double yy = y * y;
+  const double xx = x * x, yy = y * y;
   double p = 1.0;
   p = kind == 1 ? x : p;
   p = kind == 2 ? y : p;
@@ -442,8 +442,8 @@ __device__ __forceinline__ double angular_value(int kind, double x, double y, do
   p = kind == 4 ? x * y : p;
   p = kind == 5 ? y * z : p;
   p = kind == 6 ? z * x : p;
-  p = kind == 7 ? fma(x, x, -yy) : p;
-  p = kind >= 8 ? fma(2.0 * z, z, -fma(x, x, yy)) : p;
+  p = kind == 7 ? xx - yy : p;
+  p = kind >= 8 ? fma(z, 2.0 * z, -xx) - yy : p;
   return p;
 }
 
@@ -453,7 +453,7 @@ __device__ __forceinline__ double angular_value(int kind, double x, double y, do
 __device__ __forceinline__ double basis_value_rec(const double4& f, int k, double px, double py, double pz) {
 #pragma clang fp contract(off)
   const double x = px - f.x, y = py - f.y, z = pz - f.z;
-  const double r2 = fma(z, z, fma(y, y, x * x));
+  const double r2 = fma(z, z, x * x + y * y);
   return angular_value(kind_ang(k), x, y, z) * radial_e(k, f.w, r2);
 }
 
@@ -554,12 +554,12 @@ __device__ __forceinline__ void j2_radial(int form, const double* p, bool same, 
 // wave-level reductions (64 lanes)
 // ---------------------------------------------------------------------------
 // Sum over the wave, the same bits in every lane: a butterfly over lane distances
-// 1, 2, 4, 8 by register-to-register DPP moves (quad_perm [1,0,3,2], [2,3,0,1],
-// row_half_mirror, row_mirror; after each step the lanes that exchange hold equal
-// partial sums), then over the rows of 16 and the halves by the row swaps.  A
-// butterfly by LDS permutes waits some 130 cycles a stage: 6 stages were 0.8 of
-// the 1.2 thousand cycles between a proposal's sums and its decision.  The adds
-// are never contracted with what produced v, so every kernel sums alike.
+// 32, 16, 8, 4, 2, 1 by register moves (the swaps of halves and rows, row_ror:8,
+// row_ror:4 -- after distance 8 a lane and the one 8 away hold the same bits --,
+// quad_perm [2,3,0,1], [1,0,3,2]).  By LDS permutes a stage waits some 130
+// cycles: six stages were 0.8 of the 1.2 thousand cycles between a proposal's
+// sums and its decision.  The adds are never contracted with what produced v, so
+// every kernel sums alike.
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double v) {
   const long long b = __double_as_longlong(v);
@@ -581,12 +581,13 @@ __device__ __forceinline__ double row_pair_sum(double v) {
 }
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma clang fp contract(off)
-  v += dpp_f64<0xB1>(v);
-  v += dpp_f64<0x4E>(v);
-  v += dpp_f64<0x141>(v);
-  v += dpp_f64<0x140>(v);
+  v = row_pair_sum<true>(v);
   v = row_pair_sum<false>(v);
-  return row_pair_sum<true>(v);
+  v += dpp_f64<0x128>(v);
+  v += dpp_f64<0x124>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0xB1>(v);
+  return v;
 }
 // v summed over the lanes with the same index modulo m (a power of two from 4 to
 // 64, uniform): rotations by 8, then 4, within the rows, then the row swaps
