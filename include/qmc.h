@@ -416,7 +416,10 @@ qmc_status qmc_jastrow_basis_logderiv(qmc_system *sys, qmc_walkers *wk, double *
 qmc_status qmc_pfaffian_logderiv(qmc_system *sys, qmc_walkers *wk, double *d_uu, double *d_dd, double *d_ud,
                                  double *d_unpaired_up, double *d_unpaired_dn, hipStream_t stream);
 
-/* Bytes of device workspace qmc_sr_step needs (0 for non-positive sizes). */
+/* Bytes of device workspace qmc_sr_step makes use of (0 for non-positive
+ * sizes).  For at most 8192 parameters it also runs in less, 8 (6 P + M +
+ * 3 ceil(P / 256) + 16 + 2 s P) bytes with s = min(ceil(M / 128), 64) (P
+ * parameters, M samples), reading O twice per iteration instead of once. */
 size_t qmc_sr_workspace_size(int32_t n_samples, int64_t n_params);
 
 /* Stochastic-reconfiguration step (Stochastic reconfiguration section).  From
@@ -434,7 +437,8 @@ size_t qmc_sr_workspace_size(int32_t n_samples, int64_t n_params);
  *   delta    [n_params] device, written
  *   force    [n_params] device, written, may be NULL
  *   residual [1] device, written, may be NULL: |r| / |f| at exit
- *   work     device, work_bytes >= qmc_sr_workspace_size(n_samples, n_params)
+ *   work     device, work_bytes >= qmc_sr_workspace_size(n_samples, n_params), or the
+ *            smaller size named there
  * The weights must be positive with a positive sum; with max_iter = 0 delta is 0. */
 qmc_status qmc_sr_step(int32_t n_samples, int64_t n_params, const double *O, const double *e_loc,
                        const double *weights, double eps, int32_t max_iter, double tol, double *delta,

@@ -124,7 +124,7 @@ hipError_t launch_reweight(const SysDev& s, const WalkDev& w, double theta, doub
 // The column sums over samples (moments, O^T (w o u)) run on a 2-D grid:
 // blocks of 256 columns times `ms` slices of the samples, each slice writing
 // its partial sums, which a second kernel adds in slice order.
-// Workspace (doubles): Obar, d (= diag S), f, r, p, Sp [P each], u [M],
+// Workspace of the two-pass path (doubles): Obar, d (= diag S), f, r, p, Sp [P each], u [M],
 // part1, part2, part3 [nblk each], colpart [2][ms][P], scalars [16]:
 //   sc[0] = sum w, sc[1] = f . f, sc[2 + (it & 1)] = r . z at iteration it,
 //   sc[4] = Obar . p, sc[5] = done, sc[6] = r . r of the last update
@@ -328,21 +328,250 @@ __global__ void __launch_bounds__(256) sr_finish_kernel(SrWork q, double* __rest
   if (resid && k == 0) resid[0] = q.sc[1] > 0.0 ? sqrt(q.sc[6] / q.sc[1]) : 0.0;
 }
 
-size_t sr_workspace_doubles(int M, long P) {
+// ---------------------------------------------------------------------------
+// One pass over O per iteration (P <= kSrFuseMaxP columns).  The two products of
+// an iteration, u = O p and O^T (w o u), read O twice when they are launches of
+// their own (2 x 268 MB at 6.1 TB/s for 4096 x 8192: 89 of the 109 us of an
+// iteration; four small launches the rest).  Here a workgroup of 1024 threads
+// holds all columns (up to 8 a thread): it reads a row, reduces u_i, and adds
+// w_i u_i O_i to its columns' sums from the registers the row is in, while the
+// next rows are in flight; each workgroup has one contiguous range of samples and
+// writes one row of partial sums.  Since every workgroup holds every column it
+// also does the vector work of the previous iteration for itself (x, r, beta, p
+// and the convergence test, the same bits in each; workgroup 0 writes them),
+// under the latency of its first rows, so that an iteration is two launches: this
+// one and the sum of the partial rows.
+// ---------------------------------------------------------------------------
+constexpr int kSrT = 1024;            // threads of the pass
+constexpr long kSrFuseMaxP = 8192;    // columns: 8 doubles a thread
+constexpr int kSrSlices = 255;        // sample ranges (and one workgroup for Obar . p)
+constexpr size_t kSrFuseDoubles = (size_t)2 << 20;   // the fused workspace stays within this
+
+struct SrFused {
+  double *r2[2], *p2[2];   // r and p of even and odd iterations
+  int S, rows, nsp;        // sample ranges in use, samples a range, workgroups of the sum
+  double tol;
+};
+
+static long sr_fused_fixed(long P) { return 8 * P + 3 * ((P + 63) / 64) + 16; }
+
+// Sample ranges of the fused pass (0: the two-pass path): as many as the
+// workspace bound, the chip and the samples allow, and room for the moments'
+// slices.
+static int sr_fused_slices(int M, long P) {
+  if (P > kSrFuseMaxP) return 0;
+  long s = ((long)kSrFuseDoubles - sr_fused_fixed(P)) / P;
+  s = s < kSrSlices ? s : kSrSlices;
+  if (s < 2L * sr_slices(M)) return 0;
+  const long rows = (M + s - 1) / s;
+  return (int)((M + rows - 1) / rows);
+}
+
+static size_t sr_fused_doubles(int M, long P) {
+  const long S = sr_fused_slices(M, P), ms2 = 2L * sr_slices(M);
+  return S ? (size_t)(sr_fused_fixed(P) + (S > ms2 ? S : ms2) * P) : 0;
+}
+
+// sums of two values over the 1024 threads, the same bits in every thread
+__device__ double2 blk_sum1024(double a, double b, double (*red)[2][16]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  a = wave_sum(a);
+  b = wave_sum(b);
+  if (lane == 0) { (*red)[0][wave] = a; (*red)[1][wave] = b; }
+  __syncthreads();
+  a = (*red)[0][lane & 15];
+  b = (*red)[1][lane & 15];
+  // (every row of 16 lanes holds the sixteen waves' sums)
+  a += dpp_f64<0xB1>(a); a += dpp_f64<0x4E>(a); a += dpp_f64<0x141>(a); a += dpp_f64<0x140>(a);
+  b += dpp_f64<0xB1>(b); b += dpp_f64<0x4E>(b); b += dpp_f64<0x141>(b); b += dpp_f64<0x140>(b);
+  return double2{a, b};
+}
+
+// V columns a load (2: P even and O 16-byte aligned), C loads a row.
+template <int V, int C>
+__global__ void __launch_bounds__(kSrT)
+sr_pass_kernel(SrWork q, SrFused f, const double* __restrict__ O, const double* __restrict__ wts, double* __restrict__ x,
+               int it) {
+  typedef double vec __attribute__((ext_vector_type(V)));
+  __shared__ double red[3][2][16];
+  if (q.sc[5] != 0.0) return;   // converged (uniform)
+  const int tid = threadIdx.x;
+  const bool aux = (int)blockIdx.x == f.S;   // Obar . p
+  const int i0 = aux ? 0 : blockIdx.x * f.rows, i1 = aux ? 1 : min(i0 + f.rows, q.M);
+  bool ok[C];
+  long k0[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    k0[c] = (long)V * (tid + kSrT * c);
+    ok[c] = k0[c] < q.P;
+  }
+  auto load = [&](vec* v, int i) {
+    const double* row = aux ? q.Obar : O + (long)i * q.P;
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = ok[c] && i < i1 ? *reinterpret_cast<const vec*>(row + k0[c]) : vec(0.0);
+  };
+  vec va[C], vb[C], p[C], acc[C];
+  load(va, i0);
+  load(vb, i0 + 1);
+  // the vectors of this iteration
+  const int o = it & 1;
+  const bool w0 = blockIdx.x == 0;
+  if (it == 0) {   // r = f, p = f / m (from the moments); the scalars
+    double rz = 0.0, rr = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      p[c] = vec(0.0);
+      if (!ok[c]) continue;
+      p[c] = *reinterpret_cast<const vec*>(f.p2[0] + k0[c]);
+      const vec rk = *reinterpret_cast<const vec*>(f.r2[0] + k0[c]);
+#pragma unroll
+      for (int v = 0; v < V; ++v) { rz += rk[v] * p[c][v]; rr += rk[v] * rk[v]; }
+    }
+    const double2 s = blk_sum1024(rz, rr, &red[2]);
+    if (w0 && tid == 0) { q.sc[1] = s.y; q.sc[2] = s.x; q.sc[6] = s.y; }
+    if (!(s.y > 0.0)) {   // zero force: the step is zero
+      if (w0 && tid == 0) q.sc[5] = 1.0;
+      return;
+    }
+  } else {
+    const double pSp = blk_sum1024(tid < f.nsp ? q.part1[tid] : 0.0, 0.0, &red[2]).x;
+    const double rzo = q.sc[2 + (o ^ 1)];
+    const double alpha = pSp > 0.0 ? rzo / pSp : 0.0;
+    double rz = 0.0, rr = 0.0;
+    vec rn[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      p[c] = vec(0.0);
+      rn[c] = vec(0.0);
+      if (!ok[c]) continue;
+      p[c] = *reinterpret_cast<const vec*>(f.p2[o ^ 1] + k0[c]);
+      const vec sp = *reinterpret_cast<const vec*>(q.Sp + k0[c]);
+      rn[c] = *reinterpret_cast<const vec*>(f.r2[o ^ 1] + k0[c]) - alpha * sp;
+      if (w0) {
+#pragma unroll
+        for (int v = 0; v < V; ++v) x[k0[c] + v] += alpha * p[c][v];
+        *reinterpret_cast<vec*>(f.r2[o] + k0[c]) = rn[c];
+      }
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        rz += rn[c][v] * rn[c][v] / sr_precond(q, k0[c] + v);
+        rr += rn[c][v] * rn[c][v];
+      }
+    }
+    const double2 s = blk_sum1024(rz, rr, &red[0]);
+    if (w0 && tid == 0) { q.sc[2 + o] = s.x; q.sc[6] = s.y; }
+    if (s.y <= f.tol * f.tol * q.sc[1]) {   // converged: the same in every workgroup
+      if (w0 && tid == 0) q.sc[5] = 1.0;
+      return;
+    }
+    const double beta = rzo > 0.0 ? s.x / rzo : 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      if (!ok[c]) continue;
+#pragma unroll
+      for (int v = 0; v < V; ++v) p[c][v] = rn[c][v] / sr_precond(q, k0[c] + v) + beta * p[c][v];
+      if (w0) *reinterpret_cast<vec*>(f.p2[o] + k0[c]) = p[c];
+    }
+    __syncthreads();   // red[0] is read
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) acc[c] = vec(0.0);
+  // two rows at a time, the next two in flight while these reduce
+  for (int i = i0; i < i1; i += 2) {
+    double ta = 0.0, tb = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int v = 0; v < V; ++v) { ta += va[c][v] * p[c][v]; tb += vb[c][v] * p[c][v]; }
+    vec na[C], nb[C];
+    load(na, i + 2);
+    load(nb, i + 3);
+    const double2 u = blk_sum1024(ta, tb, &red[((i - i0) >> 1) & 1]);
+    if (aux) {
+      if (tid == 0) q.sc[4] = u.x;
+      return;
+    }
+    const double wa = (wts ? wts[i] : 1.0) * u.x, wb = i + 1 < i1 ? (wts ? wts[i + 1] : 1.0) * u.y : 0.0;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      acc[c] += wa * va[c] + wb * vb[c];
+      va[c] = na[c];
+      vb[c] = nb[c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (ok[c]) *reinterpret_cast<vec*>(q.colpart + (long)blockIdx.x * q.P + k0[c]) = acc[c];
+}
+
+// S'p from the partial rows, and partial sums of p . S'p: 64 columns a workgroup,
+// wave g the rows g, g + 16, ...
+__global__ void __launch_bounds__(kSrT) sr_pass_sum_kernel(SrWork q, SrFused f, int it) {
+  __shared__ double part[16][64];
+  if (q.sc[5] != 0.0) return;
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const long k = (long)blockIdx.x * 64 + lane;
+  double t = 0.0;
+  if (k < q.P) {
+#pragma unroll 8
+    for (int s = g; s < f.S; s += 16) t += q.colpart[(long)s * q.P + k];
+  }
+  part[g][lane] = t;
+  __syncthreads();
+  if (g) return;
+  double pp = 0.0;
+  if (k < q.P) {
+    for (int s = 1; s < 16; ++s) t += part[s][lane];
+    const double pk = f.p2[it & 1][k];
+    const double sp = t / q.sc[0] - q.Obar[k] * q.sc[4] + q.eps * q.d[k] * pk;
+    q.Sp[k] = sp;
+    pp = pk * sp;
+  }
+  pp = wave_sum(pp);
+  if (lane == 0) q.part1[blockIdx.x] = pp;
+}
+
+// The last iteration's step (none with its = 0) and the outputs: one workgroup.
+__global__ void __launch_bounds__(kSrT) sr_pass_last_kernel(SrWork q, SrFused f, double* __restrict__ x,
+                                                           double* __restrict__ force, double* __restrict__ resid,
+                                                           int its) {
+  __shared__ double red[2][2][16];
+  const int tid = threadIdx.x, o = (its - 1) & 1;
+  const bool open = q.sc[5] == 0.0;   // not converged (read by all before any write)
+  double ff = q.sc[1], rr = q.sc[6], alpha = 0.0;
+  if (open && its > 0) {
+    const double pSp = blk_sum1024(tid < f.nsp ? q.part1[tid] : 0.0, 0.0, &red[0]).x;
+    alpha = pSp > 0.0 ? q.sc[2 + o] / pSp : 0.0;
+  }
+  double s = 0.0;
+  for (long k = tid; k < q.P; k += kSrT) {
+    if (force) force[k] = q.f[k];
+    if (its == 0) s += q.f[k] * q.f[k];
+    else if (open) {
+      x[k] += alpha * f.p2[o][k];
+      const double rk = f.r2[o][k] - alpha * q.Sp[k];
+      s += rk * rk;
+    }
+  }
+  s = blk_sum1024(s, 0.0, &red[1]).x;
+  if (its == 0) ff = rr = s;
+  else if (open) rr = s;
+  if (tid == 0 && resid) resid[0] = ff > 0.0 ? sqrt(rr / ff) : 0.0;
+}
+
+size_t sr_workspace_min(int M, long P) {
   const long nblk = (P + 255) / 256;
   return (size_t)(6 * P + M + 3 * nblk + 16 + 2L * sr_slices(M) * P);
 }
 
-hipError_t launch_sr_step(int M, long P, const double* O, const double* el, const double* wts, double eps,
-                          int max_iter, double tol, double* delta, double* force, double* resid, double* work,
-                          hipStream_t st) {
-  SrWork q;
-  q.P = P; q.M = M; q.nblk = (int)((P + 255) / 256); q.eps = eps;
-  q.ms = sr_slices(M); q.rows = (M + q.ms - 1) / q.ms;
-  double* p = work;
-  q.Obar = p; p += P; q.d = p; p += P; q.f = p; p += P; q.r = p; p += P; q.p = p; p += P; q.Sp = p; p += P;
-  q.u = p; p += M; q.part1 = p; p += q.nblk; q.part2 = p; p += q.nblk; q.part3 = p; p += q.nblk;
-  q.colpart = p; p += 2L * q.ms * P; q.sc = p;
+size_t sr_workspace_doubles(int M, long P) {
+  const size_t a = sr_workspace_min(M, P), b = sr_fused_doubles(M, P);
+  return a > b ? a : b;
+}
+
+// the moments of the samples: Obar, the diagonal of S, the force; r = f, p = f / m
+static hipError_t sr_moments(const SrWork& q, const double* O, const double* el, const double* wts, double* delta,
+                             hipStream_t st) {
   const dim3 gk(q.nblk), g2(q.nblk, q.ms), blk(256);
   hipLaunchKernelGGL(sr_wsum_kernel, dim3(1), blk, 0, st, q, wts);
   hipLaunchKernelGGL(sr_colsum_kernel, g2, blk, 0, st, q, O, el, wts, 0);
@@ -350,6 +579,57 @@ hipError_t launch_sr_step(int M, long P, const double* O, const double* el, cons
   hipLaunchKernelGGL(sr_colsum_kernel, g2, blk, 0, st, q, O, el, wts, 1);
   hipLaunchKernelGGL(sr_moments_kernel, gk, blk, 0, st, q, delta);
   hipLaunchKernelGGL(sr_init_kernel, dim3(1), dim3(64), 0, st, q);
+  return hipGetLastError();
+}
+
+hipError_t launch_sr_step(int M, long P, const double* O, const double* el, const double* wts, double eps,
+                          int max_iter, double tol, double* delta, double* force, double* resid, double* work,
+                          size_t work_doubles, hipStream_t st) {
+  SrWork q;
+  q.P = P; q.M = M; q.nblk = (int)((P + 255) / 256); q.eps = eps;
+  q.ms = sr_slices(M); q.rows = (M + q.ms - 1) / q.ms;
+  const dim3 gk(q.nblk), g2(q.nblk, q.ms), blk(256);
+  const int S = sr_fused_slices(M, P);
+  if (S > 0 && work_doubles >= sr_fused_doubles(M, P)) {
+    SrFused f;
+    f.S = S; f.rows = (M + S - 1) / S; f.nsp = (int)((P + 63) / 64); f.tol = tol;
+    double* p = work;   // (pairs of columns: the vectors of length P first, 16-byte aligned when P is even)
+    q.Obar = p; p += P; q.d = p; p += P; q.f = p; p += P; q.Sp = p; p += P;
+    f.r2[0] = p; p += P; f.r2[1] = p; p += P; f.p2[0] = p; p += P; f.p2[1] = p; p += P;
+    q.r = f.r2[0]; q.p = f.p2[0]; q.u = nullptr;
+    q.colpart = p; p += (S > 2 * q.ms ? (long)S : 2L * q.ms) * P;
+    q.part1 = p; p += f.nsp; q.part2 = p; p += f.nsp; q.part3 = p; p += f.nsp;
+    q.sc = p;
+    hipError_t e = sr_moments(q, O, el, wts, delta, st);
+    if (e != hipSuccess) return e;
+    e = hipSuccess;
+    const bool pair = P % 2 == 0 && ((uintptr_t)O | (uintptr_t)work | (uintptr_t)delta) % 16 == 0;
+    const int per = (int)((P + kSrT - 1) / kSrT);
+    for (int it = 0; it < max_iter; ++it) {
+#define QMC_SR(V, C) hipLaunchKernelGGL((sr_pass_kernel<V, C>), dim3(S + 1), dim3(kSrT), 0, st, q, f, O, wts, delta, it)
+      if (pair) {
+        if (per <= 2) QMC_SR(2, 1);
+        else if (per <= 4) QMC_SR(2, 2);
+        else if (per <= 6) QMC_SR(2, 3);
+        else QMC_SR(2, 4);
+      } else {
+        if (per <= 1) QMC_SR(1, 1);
+        else if (per <= 2) QMC_SR(1, 2);
+        else if (per <= 4) QMC_SR(1, 4);
+        else QMC_SR(1, 8);
+      }
+#undef QMC_SR
+      hipLaunchKernelGGL(sr_pass_sum_kernel, dim3(f.nsp), dim3(kSrT), 0, st, q, f, it);
+    }
+    hipLaunchKernelGGL(sr_pass_last_kernel, dim3(1), dim3(kSrT), 0, st, q, f, delta, force, resid, max_iter);
+    return hipGetLastError();
+  }
+  double* p = work;
+  q.Obar = p; p += P; q.d = p; p += P; q.f = p; p += P; q.r = p; p += P; q.p = p; p += P; q.Sp = p; p += P;
+  q.u = p; p += M; q.part1 = p; p += q.nblk; q.part2 = p; p += q.nblk; q.part3 = p; p += q.nblk;
+  q.colpart = p; p += 2L * q.ms * P; q.sc = p;
+  const hipError_t e = sr_moments(q, O, el, wts, delta, st);
+  if (e != hipSuccess) return e;
   for (int it = 0; it < max_iter; ++it) {
     hipLaunchKernelGGL(sr_op_kernel, dim3(M + 1), blk, 0, st, q, O);
     hipLaunchKernelGGL(sr_colsum_kernel, g2, blk, 0, st, q, O, el, wts, 2);
@@ -386,7 +666,7 @@ extern "C" qmc_status qmc_sr_step_static(int32_t n_samples, int64_t n_params, co
   if (!O || !e_loc || !delta) return set_error(QMC_ERR_ARG, "null argument");
   if (n_samples <= 0 || n_params <= 0 || max_iter < 0) return set_error(QMC_ERR_ARG, "bad sizes");
   if (!(eps >= 0.0) || !(tol >= 0.0)) return set_error(QMC_ERR_ARG, "eps and tol must be >= 0");
-  if (sr_workspace_doubles(n_samples, (long)n_params) > kSrStaticDoubles)
+  if (sr_workspace_min(n_samples, (long)n_params) > kSrStaticDoubles)
     return set_error(QMC_ERR_SHAPE, "SR problem needs more than the 16 MiB static workspace "
                                     "(qmc_sr_workspace_size > 16777216 bytes): use qmc_sr_step");
   int dev = 0;
@@ -405,7 +685,7 @@ extern "C" qmc_status qmc_sr_step_static(int32_t n_samples, int64_t n_params, co
     ptr = g_scratch_ptr[dev];
   }
   e = launch_sr_step(n_samples, (long)n_params, O, e_loc, weights, eps, max_iter, tol, delta, force, residual, ptr,
-                     stream);
+                     kSrStaticDoubles, stream);
   if (e != hipSuccess) return set_error(QMC_ERR_HIP, hipGetErrorString(e));
   return QMC_OK;
 }

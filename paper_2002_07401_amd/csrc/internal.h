@@ -713,10 +713,12 @@ hipError_t launch_swct(const SysDev& s, int Wk, const double* r, const double* d
                        double* out, hipStream_t st);
 hipError_t launch_reweight(const SysDev& s, const WalkDev& w, double theta, double eps, double* R, double* weight,
                            hipStream_t st);
+// doubles that the step uses at best, and those it cannot do without
 size_t sr_workspace_doubles(int M, long P);
+size_t sr_workspace_min(int M, long P);
 hipError_t launch_sr_step(int M, long P, const double* O, const double* el, const double* wts, double eps,
                           int max_iter, double tol, double* delta, double* force, double* resid, double* work,
-                          hipStream_t st);
+                          size_t work_doubles, hipStream_t st);
 hipError_t launch_jastrow_assemble(const SysDev& s, const WalkDev& w, double* logabs, double* sign,
                                    double* drift, double* e_kin, double* e_loc, int32_t* status,
                                    hipStream_t st);

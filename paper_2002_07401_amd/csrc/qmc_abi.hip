@@ -1472,9 +1472,10 @@ extern "C" qmc_status qmc_sr_step(int32_t n_samples, int64_t n_params, const dou
   if (!O || !e_loc || !delta || !work) return fail(QMC_ERR_ARG, "null argument");
   if (n_samples <= 0 || n_params <= 0 || max_iter < 0) return fail(QMC_ERR_ARG, "bad sizes");
   if (!(eps >= 0.0) || !(tol >= 0.0)) return fail(QMC_ERR_ARG, "eps and tol must be >= 0");
-  if (work_bytes < qmc_sr_workspace_size(n_samples, n_params)) return fail(QMC_ERR_ARG, "workspace too small");
+  if (work_bytes < sizeof(double) * sr_workspace_min(n_samples, (long)n_params))
+    return fail(QMC_ERR_ARG, "workspace too small");
   HIP_TRY(launch_sr_step(n_samples, (long)n_params, O, e_loc, weights, eps, max_iter, tol, delta, force, residual,
-                         (double*)work, stream), "SR step");
+                         (double*)work, work_bytes / sizeof(double), stream), "SR step");
   return QMC_OK;
 }
 
