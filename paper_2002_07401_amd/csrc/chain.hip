@@ -33,19 +33,20 @@
 //           wait for the first ones to finish their run, which keeps the rows in
 //           use within the 256 MB last-level cache.  Single proposals and accepts
 //           of these systems are the same code with one move (bitwise).
+// Contracted orbitals take the same two forms: the primitives at r' go to LDS and
+// the waves meet once more, then each wave combines its own orbitals.
 // W's row or column and the basis row (and in the small form P's rows) go to the
 // walker's arrays in global memory; at the end they hold the usual state with an
 // empty delayed-update buffer.  The schedule is that of the per-move path.
 #include <hip/hip_ext.h>
 
 #include "internal.h"
+#include "resident_dev.h"
 #include <algorithm>
 
 namespace qmc {
 
-constexpr int kChainT = 256;               // threads
 constexpr int kChainMaxN = 128;            // rows of W: two a lane
-constexpr int kChainSmallN = 64;           // rows of a rebuild: four matrix tiles
 constexpr int kChainDraws = 32;            // steps whose draws are staged together
 constexpr int kChainU = 12;                // column loads in flight per wave
 constexpr int kChainG = 8;                 // row groups of an n x n pass
@@ -54,7 +55,7 @@ constexpr int kChainSmallLds = 80 * 1024;  // two workgroups per compute unit
 constexpr int kChainMaxLds = 160 * 1024;
 
 struct ChainLayout {   // byte offsets in LDS
-  int area, B, lv, lm, r, nuc, draw, red, part, ws, cs, lg, list, prow, chi, hv, G, jm, chin, jb, jk, M3, total;
+  int qv, cc, ci, cp, area, B, lv, lm, r, nuc, draw, red, part, ws, cs, lg, list, prow, chi, hv, G, jm, chin, jb, jk, M3, total;
 };
 
 struct ChainArgs {
@@ -73,18 +74,15 @@ struct ChainArgs {
   int32_t* cnt;             // [Wk] or null
   int groups, pst;          // row groups of an n x n pass; doubles of one move's partial sums
   int area_bytes, cw, lsh, nuc_lds;   // P area, list entries a wave, log2 of the lanes a column takes, nuclei in LDS
+  int con_lds;              // the contraction coefficients in LDS
   ChainLayout ly;
 };
-
-// leading dimension of B: even (column pairs), and a column's entries over
-// different banks
-__host__ __device__ inline int chain_ld(int n) { return (n + 1) / 2 * 2 + 2; }
 
 static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a) {
   ChainLayout o{};
   const int n = s.nu, ld = chain_ld(n), f8 = 8;
   a.area_bytes = small ? f8 * std::max(s.ptn * s.Lp, 16 * (s.Lp + 2)) : 0;
-  a.cw = 64 * ((s.L + kChainT - 1) / kChainT);
+  a.cw = 64 * (small && s.Lq > 0 ? 2 : (s.L + kChainT - 1) / kChainT);   // (the kernel's QL)
   a.lsh = 2;
   while ((2 << a.lsh) < s.ptn) ++a.lsh;
   int at = 0;
@@ -114,116 +112,21 @@ static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a) {
     take(o.jk, 4 * s.LJ);
     take(o.M3, f8 * 2 * s.LJ * (2 * s.LJ + 1));
   }
-  // the nuclei last: a system that only just fits reads them from global memory
+  if (s.Lq > 0) take(o.qv, f8 * s.Lq);
+  // the nuclei and the contraction last: a system that only just fits reads them
+  // from global memory
   a.nuc_lds = at + f8 * 5 * s.n_nuc <= kChainMaxLds ? 1 : 0;
   if (a.nuc_lds) take(o.nuc, f8 * 5 * s.n_nuc);
+  a.con_lds = s.Lq > 0 && at + 10 * s.nnz_con + 4 * (s.L + 1) + 48 <= (small ? kChainSmallLds : kChainMaxLds) ? 1 : 0;
+  if (a.con_lds) {
+    take(o.cc, f8 * s.nnz_con);
+    take(o.cp, 4 * (s.L + 1));
+    take(o.ci, 2 * s.nnz_con);
+  }
   o.total = at;
   return o;
 }
 static_assert(kChainLogs <= 64, "one lane a logarithm");
-
-// threadIdx.x through an opaque move: what is computed from it stays in the
-// phase that uses it instead of being held in registers over the move loop.
-__device__ __forceinline__ int chain_tid() {
-  int z;
-  asm volatile("v_mov_b32 %0, 0" : "=v"(z));
-  return (int)threadIdx.x + z;
-}
-
-// The last step of chain_invert: inverse element (i, p_c) = T[p_i][c] / pivot_i.
-template <int NQ>
-__device__ __forceinline__ void chain_permute(double* B, int n, int ld, int tid, bool tr, const double* ip, const int* prow) {
-  double t[NQ];
-  int at[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int x = tid + kChainT * q, i = x / n, c = x - i * n;
-    at[q] = -1;
-    if (x < n * n) {
-      t[q] = B[prow[i] * ld + c] * ip[i];
-      at[q] = tr ? prow[c] * ld + i : i * ld + prow[c];
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-    if (at[q] >= 0) B[at[q]] = t[q];
-}
-
-// B[n][ld] (LDS) <- its inverse, in place: Gauss-Jordan with the pivot of step k
-// the largest |entry| of column k among the rows not yet pivoted (lowest row on
-// ties), n <= 64.  Thread (g, j) keeps column j of rows g, g + G, ...; the step
-// publishes the next pivot column as it updates it, every wave finds the pivot
-// for itself, and a pivot row is left unscaled until the end (only its column-k
-// entry becomes 1), so a step takes one barrier.  Afterwards element (p_k, k')
-// over pivot k is inverse element (k, p_k'), put in place by the last step
-// (transposed when tr).  log|det| and sign to wave 0; singular: returns true and
-// B is not a number.
-__device__ bool chain_invert(double* B, int n, int ld, bool tr, double* fc, double* ips, int* prow, double& logdet,
-                             double& sign) {
-  const int tid = chain_tid(), lane = tid & 63;
-  const int G = min(kChainT / n, 16), g = tid / n, j = tid - g * n;
-  bool used = lane >= n;
-  double own = 1.0, own_ip = 1.0;
-  int own_p = lane;
-  if (tid < n) fc[tid] = B[tid * ld];
-  __syncthreads();
-  for (int k = 0; k < n; ++k) {
-    const double* f = fc + 64 * (k & 1);
-    double* fn = fc + 64 * ((k + 1) & 1);
-    const double fl = lane < n ? f[lane] : 0.0;
-    const unsigned long long key =
-        used ? 0ull : ((__double_as_longlong(fabs(fl)) & ~0xFFull) | (unsigned long long)(255 - lane));
-    const unsigned long long best = wave_max_u64(key);
-    const int p = 255 - (int)(best & 0xFFull);
-    const double piv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(fl), p & 63),
-                                        __builtin_amdgcn_readlane(__double2loint(fl), p & 63));
-    if (!(piv != 0.0)) {   // the same for every wave
-      __syncthreads();
-      const double nanv = __longlong_as_double(0x7ff8000000000000LL);
-      for (int q = tid; q < n * ld; q += kChainT) B[q] = nanv;
-      __syncthreads();
-      logdet = -__builtin_inf();
-      sign = 0.0;
-      return true;
-    }
-    const double ip = 1.0 / piv;
-    if (lane == p) used = true;
-    if (lane == k) { own = piv; own_ip = ip; own_p = p; }
-    if (g < G) {
-      const double pr = B[p * ld + j];
-      for (int i = g; i < n; i += G) {
-        double v = pr;
-        if (i == p) {
-          if (j == k) B[i * ld + j] = 1.0;
-        } else {
-          const double gi = f[i] * ip;
-          v = j == k ? -gi : fma(-gi, pr, B[i * ld + j]);
-          B[i * ld + j] = v;
-        }
-        if (j == k + 1) fn[i] = v;
-      }
-    }
-    __syncthreads();
-  }
-  if (tid < n) { prow[tid] = own_p; ips[tid] = own_ip; }   // wave 0's lanes
-  __syncthreads();
-  if (n <= 16) chain_permute<1>(B, n, ld, tid, tr, ips, prow);
-  else if (n <= 32) chain_permute<4>(B, n, ld, tid, tr, ips, prow);
-  else chain_permute<16>(B, n, ld, tid, tr, ips, prow);
-  if (tid < 64) {
-    // the parity of k -> p_k by counting inversions, and the pivots' signs
-    int odd = __popcll(__ballot(lane < n && own < 0.0));
-    for (int k = 0; k + 1 < n; ++k) {
-      const int pk = __builtin_amdgcn_readlane(own_p, k);
-      odd += __popcll(__ballot(lane > k && lane < n && own_p < pk));
-    }
-    logdet = wave_sum(lane < n ? log(fabs(own)) : 0.0);
-    sign = (odd & 1) ? -1.0 : 1.0;
-  }
-  __syncthreads();
-  return false;
-}
 
 typedef double cdx4 __attribute__((ext_vector_type(4)));
 
@@ -302,7 +205,8 @@ __device__ void chain_rebuild(const SysDev& s, const WalkDev& w, int wk, int h, 
 
 enum { kRun = 0, kPropose = 1, kAccept = 2 };
 
-template <int MODE, bool SMALL, int QL>
+// CON: the orbitals are contractions of Lq primitives
+template <int MODE, bool SMALL, int QL, bool CON = false>
 __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, ChainArgs a) {
   static_assert(MODE == kRun || !SMALL, "single moves of small systems take the per-move kernels");
   extern __shared__ __align__(16) char lds[];
@@ -338,10 +242,22 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     mus[q] = SMALL ? 4 * (64 * q + lane) + wave : kChainT * q + ((lane >> 4) * 4 + wave) * 16 + (lane & 15);
     const int mu = mus[q] < L ? mus[q] : 0;
     if (MODE != kAccept) {
-      bf[q] = s.bfn[mu];
-      bk[q] = s.kind[mu];
+      if (!CON) {
+        bf[q] = s.bfn[mu];
+        bk[q] = s.kind[mu];
+      }
       cm[q] = SMALL ? 0.0 : w.cmax[((long)wk * 2 + 1 - spin) * Lp + mu];
     }
+  }
+  double *qv = at(a.ly.qv), *cc = at(a.ly.cc);
+  uint16_t* ci = (uint16_t*)(lds + a.ly.ci);
+  int* cp = (int*)(lds + a.ly.cp);
+  if (CON && a.con_lds) {
+    for (int q = tid; q < s.nnz_con; q += kChainT) {
+      cc[q] = s.con_coef[q];
+      ci[q] = (uint16_t)s.con_idx[q];
+    }
+    for (int q = tid; q <= L; q += kChainT) cp[q] = s.con_ptr[q];
   }
   double* j2p = red + 8;
   if (tid < 8) j2p[tid] = s.j2d[tid];
@@ -531,12 +447,25 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
         thr = (s1 > 0.0) ? s.screen_tol() / ((double)L * s1) : 0.0;
       }
       int cnt = SMALL ? (L - wave + 3) / 4 : 0;
+      if constexpr (CON) {   // (the last move's readers are past its sums)
+        for (int mu = tid; mu < s.Lq; mu += kChainT) qv[mu] = basis_value(s, mu, px, py, pz);
+        __syncthreads();
+      }
 #pragma unroll
       for (int q = 0; q < QL; ++q) {
         sv[q] = 0.0;
         bool keep = false;
         if (mus[q] < L) {
-          sv[q] = basis_value_rec(bf[q], bk[q], px, py, pz);
+          if constexpr (CON) {
+            double v = 0.0;
+            if (a.con_lds)
+              for (int k = cp[mus[q]]; k < cp[mus[q] + 1]; ++k) v += cc[k] * qv[ci[k]];
+            else
+              for (int k = s.con_ptr[mus[q]]; k < s.con_ptr[mus[q] + 1]; ++k) v += s.con_coef[k] * qv[s.con_idx[k]];
+            sv[q] = v;
+          } else {
+            sv[q] = basis_value_rec(bf[q], bk[q], px, py, pz);
+          }
           keep = !(fabs(sv[q]) * cm[q] <= thr);
         }
         if constexpr (SMALL) {   // function k of the wave is 4 k + wave
@@ -733,10 +662,10 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
   }
 }
 
-// The form that takes a system: FP64 rows, basis functions as orbitals, and a
-// walker's state within the LDS (0: neither).
+// The form that takes a system: FP64 rows and a walker's state within the LDS (0:
+// neither).
 int chain_class(const SysDev& s, const WalkDev& w) {
-  if (!s.screened() || s.Lq > 0 || s.nu > kChainMaxN || s.L > 1024 || !w.rpos_P || !w.PT || s.Lp % 32) return 0;
+  if (!s.screened() || s.nu > kChainMaxN || s.L > 1024 || !w.rpos_P || !w.PT || s.Lp % 32) return 0;
   if (s.LJ > 128 || s.N > 4096 || s.n_nuc > 4096) return 0;
   ChainArgs a{};
   if (s.nu <= kChainSmallN && s.L <= 2 * kChainT && chain_layout(s, true, a).total <= kChainSmallLds) return 1;
@@ -756,6 +685,16 @@ static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, Chai
   else if (s.L <= 2 * kChainT) { QMC_CHAIN(M, false, 2); }                     \
   else if (s.L <= 3 * kChainT) { QMC_CHAIN(M, false, 3); }                     \
   else { QMC_CHAIN(M, false, 4); }
+  if (s.Lq > 0 && mode != kAccept) {   // (an accept takes psi(r') from the proposal)
+#define QMC_CHAIN_C(M, S, Q) QMC_LAUNCH_EV((chain_kernel<M, S, Q, true>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
+    if (cls == 1) { QMC_CHAIN_C(kRun, true, 2); }
+    else if (mode == kRun && s.L <= 2 * kChainT) { QMC_CHAIN_C(kRun, false, 2); }
+    else if (mode == kRun) { QMC_CHAIN_C(kRun, false, 4); }
+    else if (s.L <= 2 * kChainT) { QMC_CHAIN_C(kPropose, false, 2); }
+    else { QMC_CHAIN_C(kPropose, false, 4); }
+#undef QMC_CHAIN_C
+    return hipGetLastError();
+  }
   if (cls == 1) {
     if (s.L <= kChainT) { QMC_CHAIN(kRun, true, 1); }
     else { QMC_CHAIN(kRun, true, 2); }

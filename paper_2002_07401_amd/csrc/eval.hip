@@ -204,7 +204,8 @@ constexpr int kAssembleThreads = 512;
 __global__ void __launch_bounds__(kAssembleThreads)
 jastrow_assemble_kernel(SysDev s, WalkDev w, double* __restrict__ logabs_o, double* __restrict__ sign_o,
                         double* __restrict__ drift_o, double* __restrict__ ekin_o,
-                        double* __restrict__ eloc_o, int32_t* __restrict__ status_o) {
+                        double* __restrict__ eloc_o, double* __restrict__ ekin2_o, double* __restrict__ eloc2_o,
+                        int32_t* __restrict__ status_o) {
   __shared__ double red[3 * (kAssembleThreads / 64)];
   __shared__ double part[kAssembleThreads][4];
   const int wk = blockIdx.x, tid = threadIdx.x, T = blockDim.x;
@@ -310,15 +311,17 @@ jastrow_assemble_kernel(SysDev s, WalkDev w, double* __restrict__ logabs_o, doub
     if (sign_o) sign_o[wk] = sg;
     if (ekin_o) ekin_o[wk] = ekin;
     if (eloc_o) eloc_o[wk] = eloc;
+    if (ekin2_o) ekin2_o[wk] = ekin;
+    if (eloc2_o) eloc2_o[wk] = eloc;
     if (status_o) status_o[wk] = st;
   }
 }
 
 hipError_t launch_jastrow_assemble(const SysDev& s, const WalkDev& w, double* logabs, double* sign,
-                                   double* drift, double* e_kin, double* e_loc, int32_t* status,
-                                   hipStream_t st) {
+                                   double* drift, double* e_kin, double* e_loc, double* e_kin2, double* e_loc2,
+                                   int32_t* status, hipStream_t st) {
   hipLaunchKernelGGL(jastrow_assemble_kernel, dim3(w.Wk), dim3(kAssembleThreads), 0, st, s, w, logabs, sign, drift,
-                     e_kin, e_loc, status);
+                     e_kin, e_loc, e_kin2, e_loc2, status);
   return hipGetLastError();
 }
 

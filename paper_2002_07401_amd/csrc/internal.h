@@ -719,9 +719,14 @@ size_t sr_workspace_min(int M, long P);
 hipError_t launch_sr_step(int M, long P, const double* O, const double* el, const double* wts, double eps,
                           int max_iter, double tol, double* delta, double* force, double* resid, double* work,
                           size_t work_doubles, hipStream_t st);
+// e_kin, e_loc: kept with the walkers; e_kin2, e_loc2 (may be null): the caller's
 hipError_t launch_jastrow_assemble(const SysDev& s, const WalkDev& w, double* logabs, double* sign,
-                                   double* drift, double* e_kin, double* e_loc, int32_t* status,
-                                   hipStream_t st);
+                                   double* drift, double* e_kin, double* e_loc, double* e_kin2, double* e_loc2,
+                                   int32_t* status, hipStream_t st);
+// A small system's evaluation from the positions r (copied to the walkers' own)
+// to the row dots, in one launch, bitwise the batched kernels'
+bool small_eval_ok(const SysDev& s, const WalkDev& w);
+hipError_t launch_small_eval(const SysDev& s, const WalkDev& w, const double* r, hipStream_t st);
 int propose_splits(const SysDev& s);
 // Proposal in two launches: per-walker psi(r') and Jastrow change, then the
 // streaming row kernel (and, when finalize, the ratio sum).

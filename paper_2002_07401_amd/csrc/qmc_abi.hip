@@ -150,6 +150,10 @@ struct qmc_walkers {
   bool P_up_valid = false, P_dn_valid = false;
   bool delayed = false;             // the delayed-update buffer may hold moves
   int cls = 0;                      // chain_class of the system
+  bool small_eval = false;          // evaluated in one launch (small_eval_ok)
+  // (QMC_REFINED) P rows of this half were built in FP64 by the resident chain: an
+  // evaluation builds them all from the digit products
+  bool P_alt[2] = {false, false};
   bool PT_ok[2] = {false, false};   // the transposed rows and column maxima of each P half hold
   // (QMC_REFINED) parameter generation at which each P half's rows were last
   // built with their positions recorded (-1: never): a later build of that
@@ -740,6 +744,7 @@ extern "C" qmc_status qmc_walkers_create(qmc_system* sys, int32_t n_walkers, int
   walker_layout(sys->d, n_walkers, adjoint, cv, *wk);
   wk->aw_ready = adjoint;
   wk->cls = chain_class(sys->d, wk->d);
+  wk->small_eval = small_eval_ok(sys->d, wk->d);
   hipError_t e = hipMemset(base, 0, need);
   if (e == hipSuccess && sys->d.oz_rows() && sys->d.nk > 0) {   // the unpaired orbitals' transposed rows
     e = launch_pt_unpaired(sys->d, wk->d, nullptr);
@@ -774,6 +779,10 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
   if (!r && !wk->evaluated) return fail(QMC_ERR_STATE, "no current positions: evaluate at given positions first");
   const SysDev& s = sys->d;
   WalkDev& d = wk->d;
+  if (wk->small_eval) {
+    TIMED(wk, QMC_T_BASIS, stream, launch_small_eval(s, d, r ? r : d.r, stream), "small evaluation");
+    wk->P_gen[0] = wk->P_gen[1] = sys->generation;
+  } else {
   if (r) HIP_TRY(hipMemcpyAsync(d.r, r, sizeof(double) * d.Wk * s.N * 3, hipMemcpyDeviceToDevice, stream), "copy r");
   // At the current positions, the P rows of a spin none of whose electrons
   // has moved since they were built (the rebuild between the two halves of a
@@ -781,8 +790,8 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
   // them (the rebuilds between moves compute exactly what this build would).
   int halves = 3;
   if (!r && wk->generation == sys->generation && !s.refined() && !s.pairing) {
-    if (wk->P_up_valid) halves &= ~1;
-    if (wk->P_dn_valid) halves &= ~2;
+    if (wk->P_up_valid && !wk->P_alt[0]) halves &= ~1;
+    if (wk->P_dn_valid && !wk->P_alt[1]) halves &= ~2;
   }
   // QMC_MIXED evaluates through the FP64 kernels on the FP64 work arrays, then
   // stores the FP32 basis and P rows the moves stream.
@@ -817,7 +826,7 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
       int dirty = 0;
       if (s.oz_rows() && d.rpos_P)
         for (int h = 0; h < 2; ++h)
-          if (wk->P_gen[h] == sys->generation) dirty |= 1 << h;
+          if (wk->P_gen[h] == sys->generation && !wk->P_alt[h]) dirty |= 1 << h;
       TIMED(wk, QMC_T_P_BUILD, stream,
             launch_P_build_oz(s, d, halves, de.phi == d.phi64 ? d.phi64 : (const double*)d.phi,
                               refine ? d.P64 : (double*)d.P, refine ? d.P : nullptr, s.bf16(), stream,
@@ -827,6 +836,7 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
         for (int h = 0; h < 2; ++h)
           if ((halves >> h) & 1) {
             wk->P_gen[h] = sys->generation;
+            wk->P_alt[h] = false;
             if (!((dirty >> h) & 1)) wk->PT_ok[h] = true;   // (a build of the moved rows leaves the others as they are)
           }
       if (s.oz_rows())
@@ -850,14 +860,12 @@ extern "C" qmc_status qmc_eval_batch(qmc_system* sys, qmc_walkers* wk, const dou
   TIMED(wk, QMC_T_Y_BUILD, stream, launch_Y_build(se, de, stream), "Y build");
   }
   TIMED(wk, QMC_T_ROWDOT, stream, launch_rowdots(s, d, stream), "row dots");
+  }
   if (s.LJ) TIMED(wk, QMC_T_ASSEMBLE, stream, launch_jastrow3_eval(s, d, stream), "Jastrow basis terms");
   // E_kin and E_loc stay with the walkers (the LRDMC step reads them)
   TIMED(wk, QMC_T_ASSEMBLE, stream,
-        launch_jastrow_assemble(s, d, logabs, sign, drift, wk->lr.ekin, wk->lr.eloc, status, stream), "assemble");
-  if (e_kin)
-    HIP_TRY(hipMemcpyAsync(e_kin, wk->lr.ekin, sizeof(double) * d.Wk, hipMemcpyDeviceToDevice, stream), "e_kin");
-  if (e_loc)
-    HIP_TRY(hipMemcpyAsync(e_loc, wk->lr.eloc, sizeof(double) * d.Wk, hipMemcpyDeviceToDevice, stream), "e_loc");
+        launch_jastrow_assemble(s, d, logabs, sign, drift, wk->lr.ekin, wk->lr.eloc, e_kin, e_loc, status, stream),
+        "assemble");
   wk->evaluated = true;
   wk->yt_valid = true;
   wk->lr_ready = false;
@@ -894,7 +902,7 @@ static hipError_t rebuild_P(qmc_walkers* wk, int halves, hipStream_t stream) {
   // transposed rows and column maxima of the screened proposals
   int dirty = 0;
   for (int h = 0; h < 2; ++h)
-    if (((halves >> h) & 1) && wk->P_gen[h] == wk->sys->generation) dirty |= 1 << h;
+    if (((halves >> h) & 1) && wk->P_gen[h] == wk->sys->generation && !wk->P_alt[h]) dirty |= 1 << h;
   hipError_t e = launch_P_build_oz(s, d, halves, (const double*)d.phi, (double*)d.P, nullptr, false, stream, false,
                                    d.PT, dirty);
   if (e == hipSuccess) e = launch_screen_colmax(s, d, halves, stream);
@@ -902,6 +910,7 @@ static hipError_t rebuild_P(qmc_walkers* wk, int halves, hipStream_t stream) {
     for (int h = 0; h < 2; ++h)
       if ((halves >> h) & 1) {
         wk->P_gen[h] = wk->sys->generation;
+        wk->P_alt[h] = false;
         if (!((dirty >> h) & 1)) wk->PT_ok[h] = true;
       }
   return e;
@@ -1153,6 +1162,7 @@ static qmc_status chain_steps(qmc_walkers* wk, int32_t e_start, int32_t n_steps,
       need = true;
       wk->P_gen[e < s.nu ? 1 : 0] = wk->sys->generation;
       wk->PT_ok[e < s.nu ? 1 : 0] = false;   // (the chain rebuilds P alone)
+      wk->P_alt[e < s.nu ? 1 : 0] = s.oz_rows();
     }
     if (e < s.nu) wk->P_up_valid = false; else wk->P_dn_valid = false;
     sched_after(s, q);
