@@ -166,6 +166,7 @@ __global__ void __launch_bounds__(256) sr_wsum_kernel(SrWork q, const double* __
   if (threadIdx.x == 0) q.sc[0] = t;
 }
 
+// (The loops below are unrolled for their loads alone: the sums keep their order.)
 // Column sums over one slice of samples: pass 0: sum w O; pass 1: sum w (O - Obar)^2
 // and sum w e (O - Obar); pass 2: sum w u O (u = O p).
 __global__ void __launch_bounds__(256)
@@ -178,15 +179,18 @@ sr_colsum_kernel(SrWork q, const double* __restrict__ O, const double* __restric
   const int i0 = sl * q.rows, i1 = min(i0 + q.rows, q.M);
   double a = 0.0, b = 0.0;
   if (pass == 0) {
+#pragma unroll 16
     for (int i = i0; i < i1; ++i) a += (wts ? wts[i] : 1.0) * O[(long)i * q.P + k];
   } else if (pass == 1) {
     const double m = q.Obar[k];
+#pragma unroll 8
     for (int i = i0; i < i1; ++i) {
       const double wi = wts ? wts[i] : 1.0, c = O[(long)i * q.P + k] - m;
       a += wi * c * c;
       b += wi * el[i] * c;
     }
   } else {
+#pragma unroll 16
     for (int i = i0; i < i1; ++i) a += (wts ? wts[i] : 1.0) * q.u[i] * O[(long)i * q.P + k];
   }
   q.colpart[(long)sl * q.P + k] = a;
@@ -244,12 +248,18 @@ __global__ void __launch_bounds__(256) sr_op_kernel(SrWork q, const double* __re
   const int i = blockIdx.x;
   const double* row = i < q.M ? O + (long)i * q.P : q.Obar;
   double t = 0.0;
-  for (long k = threadIdx.x; k < q.P; k += blockDim.x) t += row[k] * q.p[k];
+#pragma unroll 8
+  for (long k = threadIdx.x; k < q.P; k += 256) t += row[k] * q.p[k];
   t = blk_sum256(t, red);
   if (threadIdx.x == 0) {
     if (i < q.M) q.u[i] = t;
     else q.sc[4] = t;
   }
+}
+
+// element k of S'p from t = (O^T (w o u))_k
+__device__ inline double sr_sp(const SrWork& q, long k, double t, double pk) {
+  return t / q.sc[0] - q.Obar[k] * q.sc[4] + q.eps * q.d[k] * pk;
 }
 
 // S'p from the slice sums of O^T (w o u), and partial sums of p . S'p
@@ -261,7 +271,7 @@ __global__ void __launch_bounds__(256) sr_sp_kernel(SrWork q) {
   if (k < q.P) {
     double t = 0.0;
     for (int sl = 0; sl < q.ms; ++sl) t += q.colpart[(long)sl * q.P + k];
-    const double sp = t / q.sc[0] - q.Obar[k] * q.sc[4] + q.eps * q.d[k] * q.p[k];
+    const double sp = sr_sp(q, k, t, q.p[k]);
     q.Sp[k] = sp;
     pp = q.p[k] * sp;
   }
@@ -321,6 +331,91 @@ __global__ void __launch_bounds__(64) sr_check_kernel(SrWork q, double tol) {
   if (threadIdx.x == 0 && q.sc[5] == 0.0 && q.sc[6] <= tol * tol * q.sc[1]) q.sc[5] = 1.0;
 }
 
+// The vector work of an iteration (sr_sp, sr_update, sr_dir and sr_check above) in
+// one launch of one workgroup, for up to kSrVecMaxP columns: 4 x 256 threads take
+// the 256-column blocks four at a time and every sum is formed in those kernels'
+// order, so the results are bitwise theirs.  Four launches of some 4.5 us each
+// were two thirds of an iteration of a few hundred samples and parameters.  The
+// slice sums are read 16 loads at a time: one by one, 32 slices of 4096 columns
+// cost more than the launches saved.  200 iterations, with the unrolled loads of
+// the products: 200 x 168 5.57 -> 2.94 ms, 1000 x 1400 7.79 -> 5.08, 4096 x 4096
+// 16.7 -> 14.3, 4096 x 6000 19.65 -> 18.84.
+constexpr int kSrVecT = 1024;
+constexpr long kSrVecMaxP = 8192;
+
+// block sums (wave sums in red, blocks of four waves) added in order
+__device__ double sr_ordered_sum(const double* red, int nblk) {
+  const int lane = threadIdx.x & 63;
+  double s = 0.0;
+  if (lane < nblk)
+    for (int k = 0; k < 4; ++k) s += red[4 * lane + k];
+  double t = 0.0;
+  for (int b = 0; b < nblk; ++b)
+    t += __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(s), b),
+                          __builtin_amdgcn_readlane(__double2loint(s), b));
+  return t;
+}
+
+template <int C>
+__global__ void __launch_bounds__(kSrVecT) sr_vec_kernel(SrWork q, double* __restrict__ x, int it, double tol) {
+  __shared__ double red[3][4 * (kSrVecMaxP / 256)];
+  if (q.sc[5] != 0.0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const double rzo = q.sc[2 + (it & 1)], ff = q.sc[1];
+  double p[C], sp[C], m[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {   // block 4 c + wave / 4
+    const long k = tid + (long)kSrVecT * c;
+    double pp = 0.0;
+    p[c] = sp[c] = 0.0;
+    m[c] = 1.0;
+    if (k < q.P) {
+      double t = 0.0;
+#pragma unroll 16
+      for (int sl = 0; sl < q.ms; ++sl) t += q.colpart[(long)sl * q.P + k];
+      p[c] = q.p[k];
+      m[c] = sr_precond(q, k);
+      sp[c] = sr_sp(q, k, t, p[c]);
+      pp = p[c] * sp[c];
+    }
+    pp = wave_sum(pp);
+    if (lane == 0) red[0][16 * c + wave] = pp;
+  }
+  __syncthreads();
+  const double pSp = sr_ordered_sum(red[0], q.nblk);
+  const double alpha = pSp > 0.0 ? rzo / pSp : 0.0;
+  double r[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const long k = tid + (long)kSrVecT * c;
+    double rz = 0.0, rr = 0.0;
+    r[c] = 0.0;
+    if (k < q.P) {
+      x[k] += alpha * p[c];
+      const double rk = q.r[k] - alpha * sp[c];
+      q.r[k] = r[c] = rk;
+      rz = rk * rk / m[c];
+      rr = rk * rk;
+    }
+    rz = wave_sum(rz);
+    rr = wave_sum(rr);
+    if (lane == 0) { red[1][16 * c + wave] = rz; red[2][16 * c + wave] = rr; }
+  }
+  __syncthreads();
+  const double rzn = sr_ordered_sum(red[1], q.nblk), rrn = sr_ordered_sum(red[2], q.nblk);
+  const double beta = rzo > 0.0 ? rzn / rzo : 0.0;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const long k = tid + (long)kSrVecT * c;
+    if (k < q.P) q.p[k] = r[c] / m[c] + beta * p[c];
+  }
+  if (tid == 0) {
+    q.sc[2 + ((it + 1) & 1)] = rzn;
+    q.sc[6] = rrn;
+    if (rrn <= tol * tol * ff) q.sc[5] = 1.0;
+  }
+}
+
 __global__ void __launch_bounds__(256) sr_finish_kernel(SrWork q, double* __restrict__ force,
                                                         double* __restrict__ resid) {
   const long k = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -358,8 +453,16 @@ static long sr_fused_fixed(long P) { return 8 * P + 3 * ((P + 63) / 64) + 16; }
 // Sample ranges of the fused pass (0: the two-pass path): as many as the
 // workspace bound, the chip and the samples allow, and room for the moments'
 // slices.
+// Nearly square problems keep the order of sums of the two-pass path: their
+// iteration does not converge in 200 steps (the smallest kept singular values of
+// O lie near zero) and carries a change of rounding into the step: 1e-9 of it at
+// 200 samples x 168 parameters, 1e-5 at 168 x 168 and 300 x 330, where the step
+// itself is 1e-8, 5e-4 and 2e-4 from the solution; 1e-12 and less from 200 x 150
+// and 207 x 359 on, which converge in 180 and 140.
+static bool sr_near_square(int M, long P) { return 2L * M < 3 * P && 3 * P < 5L * M; }
+
 static int sr_fused_slices(int M, long P) {
-  if (P > kSrFuseMaxP) return 0;
+  if (P > kSrFuseMaxP || sr_near_square(M, P)) return 0;
   long s = ((long)kSrFuseDoubles - sr_fused_fixed(P)) / P;
   s = s < kSrSlices ? s : kSrSlices;
   if (s < 2L * sr_slices(M)) return 0;
@@ -523,7 +626,7 @@ __global__ void __launch_bounds__(kSrT) sr_pass_sum_kernel(SrWork q, SrFused f, 
   if (k < q.P) {
     for (int s = 1; s < 16; ++s) t += part[s][lane];
     const double pk = f.p2[it & 1][k];
-    const double sp = t / q.sc[0] - q.Obar[k] * q.sc[4] + q.eps * q.d[k] * pk;
+    const double sp = sr_sp(q, k, t, pk);
     q.Sp[k] = sp;
     pp = pk * sp;
   }
@@ -633,6 +736,14 @@ hipError_t launch_sr_step(int M, long P, const double* O, const double* el, cons
   for (int it = 0; it < max_iter; ++it) {
     hipLaunchKernelGGL(sr_op_kernel, dim3(M + 1), blk, 0, st, q, O);
     hipLaunchKernelGGL(sr_colsum_kernel, g2, blk, 0, st, q, O, el, wts, 2);
+    if (P <= kSrVecMaxP) {
+      const int per = (int)((P + kSrVecT - 1) / kSrVecT);
+      if (per <= 1) hipLaunchKernelGGL(sr_vec_kernel<1>, dim3(1), dim3(kSrVecT), 0, st, q, delta, it, tol);
+      else if (per <= 2) hipLaunchKernelGGL(sr_vec_kernel<2>, dim3(1), dim3(kSrVecT), 0, st, q, delta, it, tol);
+      else if (per <= 4) hipLaunchKernelGGL(sr_vec_kernel<4>, dim3(1), dim3(kSrVecT), 0, st, q, delta, it, tol);
+      else hipLaunchKernelGGL(sr_vec_kernel<8>, dim3(1), dim3(kSrVecT), 0, st, q, delta, it, tol);
+      continue;
+    }
     hipLaunchKernelGGL(sr_sp_kernel, gk, blk, 0, st, q);
     hipLaunchKernelGGL(sr_update_kernel, gk, blk, 0, st, q, delta, it);
     hipLaunchKernelGGL(sr_dir_kernel, gk, blk, 0, st, q, it);

@@ -86,3 +86,20 @@ def test_iteration_counts_and_alignment():
             assert all(((p - q).abs().max() <= 1e-10 * q.abs().max()).item() for p, q in zip(u, x)), it
         if it == 0:
             assert x[0].abs().max().item() == 0.0 and x[2].item() == 1.0
+
+
+@pytest.mark.parametrize("M,Pn", [(2, 2), (150, 200), (1000, 1025), (2100, 2049), (1500, 2200)])
+def test_nearly_square_keeps_two_passes(M, Pn):
+    # well conditioned (eps = 1); the workspace does not choose the path of these sizes
+    P = need_gpu()
+    lib = P.load()
+    Ok, el = _inputs(M, Pn, 300 + Pn)
+    small = 8 * (6 * Pn + M + 3 * (-(-Pn // 256)) + 16 + 2 * min(max(-(-M // 128), 1), 64) * Pn)
+    a = _step(lib, Ok, el, None, 1.0, 200, 1e-13, small)
+    b = _step(lib, Ok, el, None, 1.0, 200, 1e-13, small + 8 * 300 * Pn)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    D = Ok - Ok.mean(0)
+    r = (D.T @ (D @ a[0])) / M + (D * D).mean(0) * a[0] - a[1]
+    assert (r.norm() / a[1].norm()).item() <= 1e-10
+    assert a[2].item() <= 1e-12
