@@ -15,7 +15,7 @@
 //     R = sum_j w_j B[j][e],  B[j][k] -= B[j][e] (sum_i w_i B[i][k] - delta_ek) / R,
 //   a column read and an n x n update in place of the chains of dependent
 //   products of the delayed form;
-//   positions, nuclei, the Jastrow basis state and the draws of 64 steps.
+//   positions, nuclei, the sums over the Jastrow basis and the draws of 32 steps.
 // A wave computes psi(r') of its own basis functions, lists those it keeps and
 // streams their columns of the transposed P rows without waiting for the other
 // waves; the waves meet once for a rejected move (the sums of w and of the
@@ -33,6 +33,11 @@
 //           wait for the first ones to finish their run, which keeps the rows in
 //           use within the 256 MB last-level cache.  Single proposals and accepts
 //           of these systems are the same code with one move (bitwise).
+// The Jastrow basis rows and their matrix are in LDS too in the small form; in the
+// large form they stay in global memory (a move reads one row of each ahead of
+// its use, an accept a block of the matrix from L2), where they kept systems out:
+// 149 walkers x 76 e, 152 Jastrow functions 84.9 -> 33.0 us a move, 1024 x 128 e,
+// 256 functions 604 -> 134.
 // Contracted orbitals take the same two forms: the primitives at r' go to LDS and
 // the waves meet once more, then each wave combines its own orbitals.
 // W's row or column and the basis row (and in the small form P's rows) go to the
@@ -103,14 +108,16 @@ static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a) {
   take(o.prow, 4 * (small ? kChainSmallN : 4));
   if (small) take(o.list, 4 * (kChainSmallN + 1));
   if (s.LJ > 0) {
-    take(o.chi, f8 * s.N * s.LJ);
-    take(o.hv, f8 * s.N * s.LJ);
+    if (small) {   // (large form: in global memory)
+      take(o.chi, f8 * s.N * s.LJ);
+      take(o.hv, f8 * s.N * s.LJ);
+      take(o.M3, f8 * 2 * s.LJ * (2 * s.LJ + 1));
+    }
     take(o.G, f8 * 2 * s.LJ);
     take(o.jm, f8 * 2 * s.LJ);
     take(o.chin, f8 * s.LJ);
     take(o.jb, f8 * 4 * s.LJ);
     take(o.jk, 4 * s.LJ);
-    take(o.M3, f8 * 2 * s.LJ * (2 * s.LJ + 1));
   }
   if (s.Lq > 0) take(o.qv, f8 * s.Lq);
   // the nuclei and the contraction last: a system that only just fits reads them
@@ -223,8 +230,13 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
   double* lv = at(a.ly.lv) + wave * a.cw;
   uint16_t* lm = (uint16_t*)(lds + a.ly.lm) + wave * a.cw;
   int *list = (int*)(lds + a.ly.list), *prow = (int*)(lds + a.ly.prow);
-  double *chi = at(a.ly.chi), *hv = at(a.ly.hv), *Gv = at(a.ly.G), *jm = at(a.ly.jm), *chin = at(a.ly.chin),
-         *jb = at(a.ly.jb), *M3 = at(a.ly.M3);
+  double *Gv = at(a.ly.G), *jm = at(a.ly.jm), *chin = at(a.ly.chin), *jb = at(a.ly.jb);
+  // chi, h and M: in LDS, or (large form) the walker's rows and the system's matrix
+  double* chi = SMALL ? at(a.ly.chi) : w.chi + (long)wk * N * LJ;
+  double* hv = SMALL ? at(a.ly.hv) : w.hv + (long)wk * N * LJ;
+  const double* M3 = SMALL ? at(a.ly.M3) : s.M3;
+  const int ldM = SMALL ? 2 * LJ + 1 : 2 * LJ;
+  constexpr int JU = SMALL ? 1 : 8;   // loads of M in flight
   int* jk = (int*)(lds + a.ly.jk);
   double* Wg = w.W + (long)wk * n * n;
   double* phi = (double*)w.phi + (long)wk * N * Lp;
@@ -275,10 +287,11 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     nuc[5 * q + 3] = s.Z[q];
     nuc[5 * q + 4] = s.j1_b[q];
   }
-  for (int q = tid; q < N * LJ; q += kChainT) {
-    chi[q] = w.chi[(long)wk * N * LJ + q];
-    hv[q] = w.hv[(long)wk * N * LJ + q];
-  }
+  if constexpr (SMALL)
+    for (int q = tid; q < N * LJ; q += kChainT) {
+      chi[q] = w.chi[(long)wk * N * LJ + q];
+      hv[q] = w.hv[(long)wk * N * LJ + q];
+    }
   for (int q = tid; q < 2 * LJ; q += kChainT) {
     Gv[q] = w.G3[(long)wk * 2 * LJ + q];
     jm[q] = s.jm[q];
@@ -288,8 +301,8 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     jb[4 * q] = f.x; jb[4 * q + 1] = f.y; jb[4 * q + 2] = f.z; jb[4 * q + 3] = f.w;
     jk[q] = s.jkind[q];
   }
-  if (MODE != kPropose)
-    for (int q = tid; q < 4 * LJ * LJ; q += kChainT) M3[q / (2 * LJ) * (2 * LJ + 1) + q % (2 * LJ)] = s.M3[q];
+  if constexpr (SMALL)
+    for (int q = tid; q < 4 * LJ * LJ; q += kChainT) at(a.ly.M3)[q / (2 * LJ) * ldM + q % (2 * LJ)] = s.M3[q];
   double la = w.logabs[wk], sg = w.sign[wk], Jt = w.J[wk];   // kept by thread 0
   int acc_n = 0, logs = 0;   // accepted moves; those whose ratio and Jastrow change wait in lg
   // log|Psi| of the waiting moves: their logarithms side by side in wave 0, the
@@ -428,6 +441,9 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       const double* p = MODE == kPropose ? a.r_new + 3 * (long)wk : w.r_new + 3 * (long)wk;
       px = p[0]; py = p[1]; pz = p[2];
     }
+    // the Jastrow basis state of e, ahead of its use (LJ <= kChainT)
+    double jchi = 0.0, jhv = 0.0;
+    if (MODE != kAccept && t3 < LJ) { jchi = chi[e * LJ + t3]; jhv = hv[e * LJ + t3]; }
     // the inverse's column (lanes: rows lane and lane + 64)
     double c0 = 0.0, c1 = 0.0, w0 = 0.0, w1 = 0.0, R, dJ;
     double sv[QL];
@@ -510,11 +526,11 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       if (lane < lpf && row_ok) { pt[rp] = ax; pt[rp + 1] = ay; }
       // the Jastrow change
       double dj = jsum(t1, e, px, py, pz) - jsum(t2, e, ox, oy, oz);
-      for (int k = t3; k < LJ; k += kChainT) {
-        const double4 f = double4{jb[4 * k], jb[4 * k + 1], jb[4 * k + 2], jb[4 * k + 3]};
-        const double v = basis_value_rec(f, jk[k], px, py, pz);
-        chin[k] = v;
-        dj += (v - chi[e * LJ + k]) * (Gv[sp * LJ + k] - hv[e * LJ + k] + jm[sp * LJ + k]);
+      if (t3 < LJ) {
+        const double4 f = double4{jb[4 * t3], jb[4 * t3 + 1], jb[4 * t3 + 2], jb[4 * t3 + 3]};
+        const double v = basis_value_rec(f, jk[t3], px, py, pz);
+        chin[t3] = v;
+        dj += (v - jchi) * (Gv[sp * LJ + t3] - jhv + jm[sp * LJ + t3]);
       }
       dj = wave_sum(dj);
       if (lane == 0) red[4 * (t & 1) + wave] = dj;
@@ -586,8 +602,9 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       for (int q = tid; q < 12 * LJ; q += kChainT) {
         const int o = q >> 2, sub = q & 3;
         const bool first = o < 2 * LJ;
-        const double* row = M3 + (first ? o : sp * LJ + o - 2 * LJ) * (2 * LJ + 1) + sp * LJ;
+        const double* row = M3 + (first ? o : sp * LJ + o - 2 * LJ) * ldM + sp * LJ;
         double v = 0.0;
+#pragma unroll JU
         for (int k = sub; k < LJ; k += 4) v += row[k] * (first ? chin[k] - chi[e * LJ + k] : chin[k]);
         v += dpp_f64<0xB1>(v);
         v += dpp_f64<0x4E>(v);
@@ -647,10 +664,11 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       w.A[(long)wk * n * n + q] = B[spin == 0 ? i * ld + k : k * ld + i];
     }
   for (int q = tid; q < 3 * N; q += kChainT) w.r[(long)wk * 3 * N + q] = r[q];
-  for (int q = tid; q < N * LJ; q += kChainT) {
-    w.chi[(long)wk * N * LJ + q] = chi[q];
-    w.hv[(long)wk * N * LJ + q] = hv[q];
-  }
+  if constexpr (SMALL)
+    for (int q = tid; q < N * LJ; q += kChainT) {
+      w.chi[(long)wk * N * LJ + q] = chi[q];
+      w.hv[(long)wk * N * LJ + q] = hv[q];
+    }
   for (int q = tid; q < 2 * LJ; q += kChainT) w.G3[(long)wk * 2 * LJ + q] = Gv[q];
   if (tid == 0) {
     w.logabs[wk] = la;
@@ -666,7 +684,7 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
 // neither).
 int chain_class(const SysDev& s, const WalkDev& w) {
   if (!s.screened() || s.nu > kChainMaxN || s.L > 1024 || !w.rpos_P || !w.PT || s.Lp % 32) return 0;
-  if (s.LJ > 128 || s.N > 4096 || s.n_nuc > 4096) return 0;
+  if (s.LJ > kChainT || s.N > 4096 || s.n_nuc > 4096) return 0;
   ChainArgs a{};
   if (s.nu <= kChainSmallN && s.L <= 2 * kChainT && chain_layout(s, true, a).total <= kChainSmallLds) return 1;
   return chain_layout(s, false, a).total <= kChainMaxLds ? 2 : 0;

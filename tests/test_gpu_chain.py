@@ -99,3 +99,34 @@ def test_calls_of_any_length_and_single_moves(precision, jastrow):
     sy = O.from_workload_system(s)
     rf, _, _ = O.run_chain(sy, r, disp.cpu(), unif.cpu())
     assert torch.equal(res[0][0], rf)
+
+
+@pytest.mark.parametrize("n", [30, 64, 65])
+def test_chain_with_a_wide_jastrow_basis(n):
+    # 120, 256 (the most a workgroup takes) and 260 Jastrow basis functions: ratios
+    # and log|Psi| against evaluations, which do not use the moving Jastrow state
+    P = need_gpu()
+    s = _system(n, n, (0, 0, 0, 1), 16, True)
+    N, Wk, steps = 2 * n, 3, 60
+    disp, unif = (torch.tensor(x).cuda() for x in C.chain_arrays(39, steps, Wk))
+    wk, r = _setup(P, s, Wk)
+    fresh = P.Walkers(P.JAGPSystem(s), Wk, adjoint=False)
+    e0 = n - 30   # over the change of spin
+    t = 0
+    for m in (5, -4, 30, -3, 18):
+        if m > 0:
+            wk.vmc_steps((e0 + t) % N, disp[t:t + m].contiguous(), unif[t:t + m].contiguous())
+        for k in range(t, t - min(m, 0)):
+            e, before = (e0 + k) % N, wk.read(P.STATE_R).cuda()
+            after = before.clone()
+            after[:, e] += disp[k]
+            a, b = fresh.eval_batch(before), fresh.eval_batch(after)
+            q = wk.propose(e, after[:, e].contiguous())
+            want = b["sign"] * a["sign"] * torch.exp(b["logabs"] - a["logabs"])
+            assert rel_err(q.cpu(), want.cpu()).max().item() <= 1e-9
+            wk.accept(e, (unif[k] < q * q).to(torch.uint8))
+        t += abs(m)
+        out = fresh.eval_batch(wk.read(P.STATE_R).cuda())
+        assert rel_err(wk.read(P.STATE_LOGABS).cpu(), out["logabs"].cpu()).max().item() <= 1e-10
+        assert torch.equal(wk.read(P.STATE_SIGN).cpu(), out["sign"].cpu())
+    assert t == steps and not torch.equal(wk.read(P.STATE_R).cpu(), r)
