@@ -23,8 +23,12 @@ FLAGS = [
 ]
 # per-source additions: the resident move loop is compiled without machine
 # loop-invariant code motion, which would hold every phase's constants and
-# addresses in registers across the loop, past the 256 VGPRs of two waves a SIMD
-EXTRA = {"chain.hip": ["-mllvm", "-disable-machine-licm"]}
+# addresses in registers across the loop, past the 256 VGPRs of two waves a SIMD;
+# the dense products' accumulators stay in VGPRs: across a K loop with control
+# flow the compiler otherwise moves them to the accumulation registers and back,
+# four moves for every matrix instruction of a step
+EXTRA = {"chain.hip": ["-mllvm", "-disable-machine-licm"],
+         "gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 NOISE = "is not a recognized feature for this target"
 
 

@@ -628,14 +628,14 @@ static hipError_t launch_jastrow3_backward(const SysDev& s, const WalkDev& w, co
     g.B = s.M3 + (long)sp * LJ * 2 * LJ + (long)sp * LJ; g.ldb = 2 * LJ; g.b_bs = 0;
     g.C = aw.jhu + (long)row0 * LJp; g.ldc = LJp; g.c_bs = (long)s.N * LJp;
     g.batch = Wk;
-    if ((e = gemm_f64(g, false, false, false, st)) != hipSuccess) return e;
+    if ((e = gemm_f64(g, false, false, st)) != hipSuccess) return e;
     // C_s = sum_{i of s} u_i chi_i^T  ([LJ][LJ] per walker)
     GemmArgs c = gemm_args(LJ, LJ, nrow);
     c.A = aw.ju + (long)row0 * LJp; c.lda = LJp; c.a_bs = (long)s.N * LJp;   // op = A^T
     c.B = w.chi + (long)row0 * LJ; c.ldb = LJ; c.b_bs = (long)s.N * LJ;
     c.C = aw.jC + (long)sp * LJ * LJ; c.ldc = LJ; c.c_bs = 2L * LJ * LJ;
     c.batch = Wk;
-    if ((e = gemm_f64(c, true, false, false, st)) != hipSuccess) return e;
+    if ((e = gemm_f64(c, true, false, st)) != hipSuccess) return e;
   }
   const long tot = rows * LJp;
   hipLaunchKernelGGL(j3_adj_chibar_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, s, w, aw, ga, tot);
@@ -687,17 +687,17 @@ static hipError_t geminal_backward(const SysDev& s, const WalkDev& w, const AdjW
     g.A = aw.SU + (long)n * Lp; g.lda = Lp; g.a_bs = stk;
     g.B = (const double*)w.P + (long)n * Lp; g.ldb = Lp; g.b_bs = rowst;
     g.C = aw.VQ; g.ldc = n; g.c_bs = (long)n * n; g.batch = Wk;
-    HT(gemm_f64(g, false, true, false, st));
+    HT(gemm_f64(g, false, true, st));
     g.A = w.P; g.a_bs = rowst;
     g.B = aw.SD + (long)n * Lp; g.b_bs = stk;
     g.accumulate = 1;
-    HT(gemm_f64(g, false, true, false, st));
+    HT(gemm_f64(g, false, true, st));
     if (s.nk > 0) {
       GemmArgs u = gemm_args(n, s.nk, Lp);
       u.A = aw.SU + (long)n * Lp; u.lda = Lp; u.a_bs = stk;
       u.B = s.Uph; u.ldb = Lp; u.b_bs = 0;
       u.C = aw.VQ + nd; u.ldc = n; u.c_bs = (long)n * n; u.batch = Wk;
-      HT(gemm_f64(u, false, true, false, st));
+      HT(gemm_f64(u, false, true, st));
     }
   }
   // 3. M = A V A
@@ -706,9 +706,9 @@ static hipError_t geminal_backward(const SysDev& s, const WalkDev& w, const AdjW
     g.A = w.A; g.lda = n; g.a_bs = (long)n * n;
     g.B = aw.VQ; g.ldb = n; g.b_bs = (long)n * n;
     g.C = aw.T1; g.ldc = n; g.c_bs = (long)n * n; g.batch = Wk;
-    HT(gemm_f64(g, false, false, false, st));
+    HT(gemm_f64(g, false, false, st));
     g.A = aw.T1; g.B = w.A; g.C = aw.M;
-    HT(gemm_f64(g, false, false, false, st));
+    HT(gemm_f64(g, false, false, st));
   }
   // 4. G_W, G_V
   {
@@ -723,17 +723,17 @@ static hipError_t geminal_backward(const SysDev& s, const WalkDev& w, const AdjW
     g.A = aw.GG; g.lda = 2 * n; g.a_bs = 2L * n * n;
     g.B = aw.SD; g.ldb = Lp; g.b_bs = stk;
     g.C = aw.XZ; g.ldc = Lp; g.c_bs = stk; g.batch = Wk;
-    HT(gemm_f64(g, false, false, false, st));
+    HT(gemm_f64(g, false, false, st));
     GemmArgs z = gemm_args(n, Lp, n);
     z.A = aw.GG + n; z.lda = 2 * n; z.a_bs = 2L * n * n;
     z.B = aw.SD; z.ldb = Lp; z.b_bs = stk;
     z.C = aw.XZ + (long)n * Lp; z.ldc = Lp; z.c_bs = stk; z.batch = Wk;
-    HT(gemm_f64(z, false, false, false, st));
+    HT(gemm_f64(z, false, false, st));
     GemmArgs x = gemm_args(n, Lp, 2 * n);
     x.A = aw.GGt; x.lda = n; x.a_bs = 2L * n * n;
     x.B = aw.SU; x.ldb = Lp; x.b_bs = stk;
     x.C = aw.XD; x.ldc = Lp; x.c_bs = (long)n * Lp; x.batch = Wk;
-    HT(gemm_f64(x, true, false, false, st));
+    HT(gemm_f64(x, true, false, st));
   }
   // 6. dF/dPhi: rows of the up spin X_U Lambda^T, of the down spin X_D Lambda
   {
@@ -741,19 +741,19 @@ static hipError_t geminal_backward(const SysDev& s, const WalkDev& w, const AdjW
     g.A = aw.XZ; g.lda = Lp; g.a_grp = n; g.a_gs = stk;
     g.B = s.lamT; g.ldb = Lp;
     g.C = aw.PB; g.ldc = Lp; g.c_grp = n; g.c_gs = rowst;
-    HT(gemm_f64(g, false, false, true, st));
+    HT(gemm_f64(g, false, false, st));
     GemmArgs h = gemm_args(Wk * nd, Lp, Lp);
     h.A = aw.XD; h.lda = Lp; h.a_grp = nd; h.a_gs = (long)n * Lp;
     h.B = s.lam; h.ldb = Lp;
     h.C = aw.PB + (long)n * Lp; h.ldc = Lp; h.c_grp = nd; h.c_gs = rowst;
-    HT(gemm_f64(h, false, false, true, st));
+    HT(gemm_f64(h, false, false, st));
     if (s.nk > 0) {   // dF/dPhi_U += G_W[:, n_dn:] U
       GemmArgs u = gemm_args(n, Lp, s.nk);
       u.A = aw.GG + nd; u.lda = 2 * n; u.a_bs = 2L * n * n;
       u.B = s.Uph; u.ldb = Lp; u.b_bs = 0;
       u.C = aw.PB; u.ldc = Lp; u.c_bs = rowst; u.batch = Wk;
       u.accumulate = 1;
-      HT(gemm_f64(u, false, false, false, st));
+      HT(gemm_f64(u, false, false, st));
     }
   }
   // 7. dF/dLambda = [Phi_U; Q_U]^T [X_U; Z_U]
@@ -763,20 +763,20 @@ static hipError_t geminal_backward(const SysDev& s, const WalkDev& w, const AdjW
       g.A = aw.SU; g.lda = Lp; g.a_bs = stk;
       g.B = aw.XZ; g.ldb = Lp; g.b_bs = stk;
       g.C = dlambda; g.ldc = L; g.c_bs = (long)L * L; g.batch = Wk;
-      HT(gemm_f64(g, true, false, true, st));
+      HT(gemm_f64(g, true, false, st));
     } else {
       const int cw = aw.chunk_walkers, nfull = Wk / cw, rest = Wk % cw;
       GemmArgs g = gemm_args(L, L, 2 * n * cw);
       g.A = aw.SU; g.lda = Lp; g.a_bs = stk * cw;
       g.B = aw.XZ; g.ldb = Lp; g.b_bs = stk * cw;
       g.C = aw.lam_part; g.ldc = L; g.c_bs = (long)L * L; g.batch = nfull;
-      if (nfull) HT(gemm_f64(g, true, false, true, st));
+      if (nfull) HT(gemm_f64(g, true, false, st));
       if (rest) {
         GemmArgs h = g;
         h.K = 2 * n * rest;
         h.A = aw.SU + stk * cw * nfull; h.B = aw.XZ + stk * cw * nfull;
         h.C = aw.lam_part + (long)nfull * L * L; h.batch = 1;
-        HT(gemm_f64(h, true, false, true, st));
+        HT(gemm_f64(h, true, false, st));
       }
       HT(sum_rows(aw.lam_part, nfull + (rest ? 1 : 0), (long)L * L, dlambda, st));
     }
@@ -790,20 +790,20 @@ static hipError_t geminal_backward(const SysDev& s, const WalkDev& w, const AdjW
       g.A = aw.SU; g.lda = Lp; g.a_bs = stk;
       g.B = aw.GGt + nd; g.ldb = n; g.b_bs = 2L * n * n;
       g.C = dunp; g.ldc = k; g.c_bs = (long)L * k; g.batch = Wk;
-      HT(gemm_f64(g, true, false, false, st));
+      HT(gemm_f64(g, true, false, st));
     } else {
       const int cw = aw.chunk_walkers, nfull = Wk / cw, rest = Wk % cw;
       GemmArgs g = gemm_args(L, k, 2 * n * cw);
       g.A = aw.SU; g.lda = Lp; g.a_bs = stk * cw;
       g.B = aw.GGt + nd; g.ldb = n; g.b_bs = 2L * n * n * cw;
       g.C = aw.lam_part; g.ldc = k; g.c_bs = (long)L * k; g.batch = nfull;
-      if (nfull) HT(gemm_f64(g, true, false, false, st));
+      if (nfull) HT(gemm_f64(g, true, false, st));
       if (rest) {
         GemmArgs h = g;
         h.K = 2 * n * rest;
         h.A = aw.SU + stk * cw * nfull; h.B = aw.GGt + nd + 2L * n * n * cw * nfull;
         h.C = aw.lam_part + (long)nfull * L * k; h.batch = 1;
-        HT(gemm_f64(h, true, false, false, st));
+        HT(gemm_f64(h, true, false, st));
       }
       HT(sum_rows(aw.lam_part, nfull + (rest ? 1 : 0), (long)L * k, dunp, st));
     }
@@ -925,13 +925,13 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
       g.A = Q; g.lda = Lp; g.a_bs = stk;
       g.B = sp ? w.Bd : (const double*)w.P; g.ldb = Lp; g.b_bs = rowst;
       g.C = aw.pfT + (long)i0 * np; g.ldc = np; g.c_bs = nn; g.batch = Wk;
-      HT(gemm_f64(g, false, true, false, st));
+      HT(gemm_f64(g, false, true, st));
       if (pk > 0) {
         GemmArgs u = gemm_args(ni, pk, Lp);
         u.A = Q; u.lda = Lp; u.a_bs = stk;
         u.B = s.Upf + (long)sp * pk * Lp; u.ldb = Lp; u.b_bs = 0;
         u.C = aw.pfT + (long)i0 * np + N; u.ldc = np; u.c_bs = nn; u.batch = Wk;
-        HT(gemm_f64(u, false, true, false, st));
+        HT(gemm_f64(u, false, true, st));
       }
     }
     // Z = H T H, then X = Z^T - Z (into pfZ1)
@@ -940,9 +940,9 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
       g.A = w.A; g.lda = np; g.a_bs = nn;
       g.B = aw.pfT; g.ldb = np; g.b_bs = nn;
       g.C = aw.pfZ1; g.ldc = np; g.c_bs = nn; g.batch = Wk;
-      HT(gemm_f64(g, false, false, false, st));
+      HT(gemm_f64(g, false, false, st));
       g.A = aw.pfZ1; g.B = w.A; g.C = aw.pfZ;
-      HT(gemm_f64(g, false, false, false, st));
+      HT(gemm_f64(g, false, false, st));
       const long tot = nn * Wk;
       hipLaunchKernelGGL(pf_skew_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, aw.pfZ, (long)np,
                          tot, aw.pfZ1);
@@ -955,13 +955,13 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
       g.A = w.A; g.lda = np; g.a_bs = nn;
       g.B = aw.SU + (long)n * Lp; g.ldb = Lp; g.b_bs = stk;
       g.C = aw.pfBb; g.ldc = 2L * Lp; g.c_bs = 2 * rowst; g.batch = Wk;
-      HT(gemm_f64(g, false, false, false, st));
+      HT(gemm_f64(g, false, false, st));
       if (nd > 0) {
         g.K = nd;
         g.A = w.A + n;
         g.B = aw.SD + (long)n * Lp;
         g.C = aw.pfBb + Lp;
-        HT(gemm_f64(g, false, false, false, st));
+        HT(gemm_f64(g, false, false, st));
       }
       for (int sp = 0; sp < 2; ++sp) {
         const int j0 = sp ? n : 0, nj = sp ? nd : n;
@@ -972,7 +972,7 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
         k.B = sp ? s.Kcat_d : s.Kcat_u; k.ldb = 2L * Lp; k.b_bs = 0;
         k.C = aw.pfY + (long)j0 * Lp; k.ldc = Lp; k.c_bs = rowst; k.batch = Wk;
         k.accumulate = 1;
-        HT(gemm_f64(k, false, true, false, st));
+        HT(gemm_f64(k, false, true, st));
       }
     }
   }
@@ -1009,7 +1009,7 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
     g.A = aw.pfZ1 + (long)s0 * np + t0; g.lda = np; g.a_bs = nn;
     g.B = Pht; g.ldb = Lp; g.b_bs = stk;
     g.C = aw.pfY; g.ldc = Lp; g.c_bs = rowst; g.batch = Wk;
-    HT(gemm_f64(g, false, false, false, st));
+    HT(gemm_f64(g, false, false, st));
     if (gb) {
       const long te = (long)Wk * ns * Lp;
       hipLaunchKernelGGL(pf_sub_bb_kernel, dim3((unsigned)((te + 255) / 256)), dim3(256), 0, st, aw.pfY, aw.pfBb, ns,
@@ -1021,14 +1021,14 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
     o.A = Phs; o.lda = Lp; o.a_bs = stk;
     o.B = aw.pfY; o.ldb = Lp; o.b_bs = rowst;
     o.C = O; o.ldc = L; o.c_bs = per; o.batch = Wk;
-    HT(gemm_f64(o, true, false, false, st));
+    HT(gemm_f64(o, true, false, st));
     if (gb) {
       GemmArgs b = gemm_args(L, L, nt);
       b.A = aw.pfBb + (long)t0 * 2 * Lp + (long)sg * Lp; b.lda = 2L * Lp; b.a_bs = 2 * rowst;
       b.B = Pht; b.ldb = Lp; b.b_bs = stk;
       b.C = O; b.ldc = L; b.c_bs = per; b.batch = Wk;
       b.accumulate = 1;
-      HT(gemm_f64(b, true, false, false, st));
+      HT(gemm_f64(b, true, false, st));
     }
     if (q > 0) {
       const long th = (long)Wk * L * L;
@@ -1052,14 +1052,14 @@ static hipError_t pf_backward(const SysDev& s, const WalkDev& w, const AdjWork& 
     u.A = S; u.lda = Lp; u.a_bs = stk;
     u.B = aw.pfZ1 + (long)s0 * np + N; u.ldb = np; u.b_bs = nn;
     u.C = O; u.ldc = pk; u.c_bs = per; u.batch = Wk;
-    HT(gemm_f64(u, true, false, false, st));
+    HT(gemm_f64(u, true, false, st));
     if (gb) {
       GemmArgs v = gemm_args(L, pk, ns);
       v.A = S + (long)n * Lp; v.lda = Lp; v.a_bs = stk;
       v.B = w.A + (long)N * np + s0; v.ldb = np; v.b_bs = nn;
       v.C = O; v.ldc = pk; v.c_bs = per; v.batch = Wk;
       v.accumulate = 1;
-      HT(gemm_f64(v, true, true, false, st));
+      HT(gemm_f64(v, true, true, st));
     }
   }
   return hipSuccess;

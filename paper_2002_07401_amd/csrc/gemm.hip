@@ -4,13 +4,15 @@
 //   W    = P_up Phi_dn^T        (the geminal matrix, eq:wfAGPs)
 //   Yt_up = W^{-T} P_dn ... see launch_Y_build
 //
-// One templated kernel: C = op(A) op(B), row-major operands, 256 threads as a
+// The FP32 products (and those that read FP32 rows with FP64 arithmetic), one
+// templated kernel: C = op(A) op(B), row-major operands, 256 threads as a
 // 2x2 grid of waves, each wave owning (BM/2) x (BN/2) of the tile as 16x16
 // MFMA blocks.  K is staged through LDS in steps of 16.  Rows of A and C may be
 // "gathered": row m lives at (m / grp) * gs + (m % grp) * ld, which lets the
 // up (or down) rows of every walker form one tall matrix that multiplies the
 // shared Lambda.
 #include "internal.h"
+#include <type_traits>
 
 namespace qmc {
 
@@ -227,25 +229,301 @@ GemmArgs gemm_args(int M, int N, int K) {
 
 static GemmArgs plain(int M, int N, int K) { return gemm_args(M, N, K); }
 
-hipError_t gemm_f64(const GemmArgs& g, bool ta, bool tb, bool big, hipStream_t st) {
-#define QMC_G(BM, BN, TA_, TB_) run_gemm<BM, BN, TA_, TB_, double, double, double, double, 16>(g, st)
-  if (big) {
-    if (ta) return tb ? QMC_G(64, 64, true, true) : QMC_G(64, 64, true, false);
-    return tb ? QMC_G(64, 64, false, true) : QMC_G(64, 64, false, false);
-  }
-  if (ta) return tb ? QMC_G(32, 32, true, true) : QMC_G(32, 32, true, false);
-  return tb ? QMC_G(32, 32, false, true) : QMC_G(32, 32, false, false);
-#undef QMC_G
+// ---------------------------------------------------------------------------
+// FP64 products.  What bounds them is the SIMD's issue: an FP64 matrix instruction
+// holds it for 64 cycles and every other vector instruction adds its own, so the
+// loop is stripped to the matrix instructions, the operand reads and one address
+// per load:
+//   K advances in steps of 16 through two LDS buffers, one barrier a step, the next
+//   step's operands in flight while this one multiplies;
+//   rows and columns past the edge are clamped to the last one instead of zeroed
+//   (their results are not stored), only a step that K does not fill is guarded;
+//   the nonzero tiles of a masked B are listed before the loop;
+//   operands sit in LDS in fragment order, at constant offsets from two addresses:
+//   the 64 values of a 16-row block at 4 consecutive k are 512 contiguous bytes, so
+//   a matrix instruction's operand is one conflict-free read; within them the row
+//   is permuted by its k, and the quarters by the k group and the block, so that
+//   the stores (two k of a row, or two rows at a k, a thread) spread over the banks.
+// 81920 x 608 x 608 (1024 walkers x 80 rows) 1276 -> 1094 us (55 TF, 5 % of it
+// padding), 32768 x 4096 x 4096 20.3 -> 16.9 ms (65 TF of 72.7 a library product
+// reaches), 512 x 512 x 4096, 64 products 2485 -> 2230 us, 500 x 200 x 200 18.3 ->
+// 7.7 us, against a loop of guarded loads and 64-bit addresses with its accumulators
+// moved between register files every step (2.3 vector instructions beside each
+// matrix one, matrix units 66 % busy at 99 % busy compute units).
+// Tiles: BM x BN a workgroup, BM/2 x BN/2 a wave.  Products accumulate in k order
+// with the generic kernel's instruction: bitwise its results.
+// ---------------------------------------------------------------------------
+template <int NBLK>
+__device__ __forceinline__ int frag_at(int k, int m) {
+  const int g = k >> 2, kk = k & 3, b = m >> 4;
+  return (g * NBLK + b) * 64 + ((kk ^ ((g ^ b) & 1)) << 4) + ((m & 15) ^ ((kk >> 1) << 3));
 }
 
-// Tile shapes from sweeps on MI355X (1024 walkers x 80 rows, L = 608, all
-// rows or a list of 60 per walker): FP64 64 x 64 with K steps of 16 (61-63 %
-// of the FP64 matrix peak, against 51-57 % for 64 x 32, 57-58 % for 128 x 32
-// and 32 x 64, 49-51 % for 128 x 128); FP32 / BF16 rows 64 x 64 with K steps
-// of 32.
+constexpr int kMaskSteps = 1024;   // K steps of a masked B
+
+// VEC: pairs are 16-byte aligned, and even in number along M (TA) and N (not TB)
+template <int BM, int BN, bool TA, bool TB, bool VEC>
+__global__ void __launch_bounds__(256) dgemm_kernel(GemmArgs g, int gx, int gy) {
+  constexpr int BK = 16, FM = BM / 32, FN = BN / 32, MB = BM / 16, NB = BN / 16;
+  constexpr int EA = BM / 32, EB = BN / 32;   // pairs a thread loads a step
+  constexpr bool MASK = !TA && !TB && kLamTileN % BN == 0 && BK == kLamTileK;
+  __shared__ __align__(16) double As[2][BM * BK], Bs[2][BN * BK];
+  __shared__ uint16_t ksteps[MASK ? kMaskSteps : 1];
+  typedef typename Mfma<double>::acc_t acc_t;
+  const int Mr = g.ridx ? min(g.M, *g.rcnt) : g.M;
+  const int gyr = g.ridx ? (Mr + BM - 1) / BM : gy;
+  const long nt = g.ridx ? (long)gx * gyr * g.batch : (long)gridDim.x;
+  if ((long)blockIdx.x >= nt) return;   // (uniform, before any barrier)
+  const long L = xcd_remap(blockIdx.x, nt);
+  const int bx = (int)(L % gx);
+  const long rest = L / gx;
+  const int by = (int)(rest % gyr);
+  const long bz = rest / gyr;
+  const double* A = (const double*)g.A + bz * g.a_bs;
+  const double* B = (const double*)g.B + bz * g.b_bs;
+  double* C = (double*)g.C + bz * g.c_bs;
+  float* C2f = (g.C2 && !g.c2_bf16) ? (float*)g.C2 + bz * g.c_bs : nullptr;
+  bf16s* C2h = (g.C2 && g.c2_bf16) ? (bf16s*)g.C2 + bz * g.c_bs : nullptr;
+  const int m0 = by * BM, n0 = bx * BN;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  // the pairs: (row, two k) of an operand stored along k, (k, two rows) of one
+  // stored along its rows; da, db: the second element's distance
+  const double *pa[EA], *pb[EB];
+  int da[EA], db[EB];
+#pragma unroll
+  for (int q = 0; q < EA; ++q) {
+    const int idx = tid + 256 * q;
+    if (TA) {
+      const int m = min(m0 + 2 * (idx % (BM / 2)), Mr - (VEC ? 2 : 1));
+      da[q] = m + 1 < Mr ? 1 : 0;
+      pa[q] = A + (long)(idx / (BM / 2)) * g.lda + m;
+    } else {
+      const int m = min(m0 + (idx >> 3), Mr - 1);
+      const int gr = g.ridx ? g.ridx[m] : m;   // the row of A
+      da[q] = 1;
+      pa[q] = A + (long)(gr / g.a_grp) * g.a_gs + (long)(gr % g.a_grp) * g.lda + 2 * (idx & 7);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < EB; ++q) {
+    const int idx = tid + 256 * q;
+    if (TB) {
+      db[q] = 1;
+      pb[q] = B + (long)min(n0 + (idx >> 3), g.N - 1) * g.ldb + 2 * (idx & 7);
+    } else {
+      const int n = min(n0 + 2 * (idx % (BN / 2)), g.N - (VEC ? 2 : 1));
+      db[q] = n + 1 < g.N ? 1 : 0;
+      pb[q] = B + (long)(idx / (BN / 2)) * g.ldb + n;
+    }
+  }
+  // K steps: all of them, or the listed ones
+  const int full = g.K / BK, steps_all = (g.K + BK - 1) / BK;
+  int nsteps = steps_all;
+  bool listed = false;
+  if constexpr (MASK)
+    if (g.kmask && steps_all <= kMaskSteps) {
+      if (wave == 0) {
+        int cnt = 0;
+        for (int s0 = 0; s0 < steps_all; s0 += 64) {
+          const int st = s0 + lane;
+          const bool nz = st < steps_all && g.kmask[(long)st * g.kmask_ld + n0 / kLamTileN];
+          const unsigned long long bal = __ballot(nz);
+          if (nz) ksteps[cnt + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)st;
+          cnt += __popcll(bal);
+        }
+        if (lane == 0) As[0][0] = (double)cnt;
+      }
+      __syncthreads();
+      nsteps = (int)As[0][0];
+      listed = nsteps < steps_all;
+      __syncthreads();
+    }
+  auto step_at = [&](int i) { return MASK && listed ? (int)__builtin_amdgcn_readfirstlane(ksteps[i]) : i; };
+  double2 ra[EA], rb[EB];
+  auto load = [&](int st) {
+    const long oa = TA ? (long)st * BK * g.lda : (long)st * BK, ob = TB ? (long)st * BK : (long)st * BK * g.ldb;
+    if (st < full) {
+#pragma unroll
+      for (int q = 0; q < EA; ++q) {
+        const double* p = pa[q] + oa;
+        if (VEC) ra[q] = *reinterpret_cast<const double2*>(p);
+        else ra[q] = double2{p[0], p[da[q]]};
+      }
+#pragma unroll
+      for (int q = 0; q < EB; ++q) {
+        const double* p = pb[q] + ob;
+        if (VEC) rb[q] = *reinterpret_cast<const double2*>(p);
+        else rb[q] = double2{p[0], p[db[q]]};
+      }
+      return;
+    }
+    // the last step of a K that is no multiple of 16: zeros past the end
+    const int left = g.K - st * BK;
+#pragma unroll
+    for (int q = 0; q < EA; ++q) {
+      const int idx = tid + 256 * q, k = TA ? idx / (BM / 2) : 2 * (idx & 7);
+      const double* p = pa[q] + oa;
+      ra[q] = double2{0.0, 0.0};
+      if (k < left) ra[q].x = p[0];
+      if (TA ? k < left : k + 1 < left) ra[q].y = p[da[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < EB; ++q) {
+      const int idx = tid + 256 * q, k = TB ? 2 * (idx & 7) : idx / (BN / 2);
+      const double* p = pb[q] + ob;
+      rb[q] = double2{0.0, 0.0};
+      if (k < left) rb[q].x = p[0];
+      if (TB ? k + 1 < left : k < left) rb[q].y = p[db[q]];
+    }
+  };
+  // where they go in LDS
+  int wa[EA][2], wb[EB][2];
+#pragma unroll
+  for (int q = 0; q < EA; ++q) {
+    const int idx = tid + 256 * q;
+    wa[q][0] = TA ? frag_at<MB>(idx / (BM / 2), 2 * (idx % (BM / 2))) : frag_at<MB>(2 * (idx & 7), idx >> 3);
+    wa[q][1] = TA ? wa[q][0] + 1 : frag_at<MB>(2 * (idx & 7) + 1, idx >> 3);
+  }
+#pragma unroll
+  for (int q = 0; q < EB; ++q) {
+    const int idx = tid + 256 * q;
+    wb[q][0] = TB ? frag_at<NB>(2 * (idx & 7), idx >> 3) : frag_at<NB>(idx / (BN / 2), 2 * (idx % (BN / 2)));
+    wb[q][1] = TB ? frag_at<NB>(2 * (idx & 7) + 1, idx >> 3) : wb[q][0] + 1;
+  }
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < EA; ++q) {
+      if (TA) *reinterpret_cast<double2*>(&As[buf][wa[q][0]]) = ra[q];
+      else { As[buf][wa[q][0]] = ra[q].x; As[buf][wa[q][1]] = ra[q].y; }
+    }
+#pragma unroll
+    for (int q = 0; q < EB; ++q) {
+      if (!TB) *reinterpret_cast<double2*>(&Bs[buf][wb[q][0]]) = rb[q];
+      else { Bs[buf][wb[q][0]] = rb[q].x; Bs[buf][wb[q][1]] = rb[q].y; }
+    }
+  };
+  // this lane's place in a fragment, for even and odd k group + block of the wave
+  const int kk = lane >> 4, lc = (lane & 15) ^ ((kk >> 1) << 3);
+  int ea[2], eb[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    ea[h] = wm * FM * 64 + ((kk ^ h ^ (wm * FM & 1)) << 4) + lc;
+    eb[h] = wn * FN * 64 + ((kk ^ h ^ (wn * FN & 1)) << 4) + lc;
+  }
+
+  acc_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0;
+  auto step = [&](int s, auto BUF) {
+    constexpr int buf = decltype(BUF)::value;
+    if (s + 1 < nsteps) load(step_at(s + 1));
+#pragma unroll
+    for (int kg = 0; kg < 4; ++kg) {
+      double a[FM], b[FN];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) a[i] = As[buf][(kg * MB + i) * 64 + ea[(kg ^ i) & 1]];
+#pragma unroll
+      for (int j = 0; j < FN; ++j) b[j] = Bs[buf][(kg * NB + j) * 64 + eb[(kg ^ j) & 1]];
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = Mfma<double>::run(a[i], b[j], acc[i][j]);
+    }
+    if (s + 1 < nsteps) store(buf ^ 1);
+    __syncthreads();
+  };
+  if (nsteps > 0) {
+    load(step_at(0));
+    store(0);
+  }
+  __syncthreads();
+  for (int s = 0; s < nsteps; s += 2) {
+    step(s, std::integral_constant<int, 0>{});
+    if (s + 1 < nsteps) step(s + 1, std::integral_constant<int, 1>{});
+  }
+  // 16x16 block layout: lane holds column lane%16 and the rows given by Mfma::row;
+  // the rows' offsets before any store (a load issued after a store of C would wait
+  // for it)
+  long roff[FM][4];
+  bool rok[FM][4];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int gm = m0 + (wm * FM + i) * 16 + Mfma<double>::row(lane, r);
+      rok[i][r] = gm < Mr;
+      const int gr = rok[i][r] ? (g.ridx ? g.ridx[gm] : gm) : 0;   // the row of C
+      const int q = gr / g.c_grp;
+      roff[i][r] = (long)q * g.c_gs + (long)(gr - q * g.c_grp) * g.ldc;
+    }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int gn = n0 + (wn * FN + j) * 16 + (lane & 15);
+        if (rok[i][r] && gn < g.N) {
+          const long off = roff[i][r] + gn;
+          const double v = g.accumulate ? C[off] + acc[i][j][r] : acc[i][j][r];
+          C[off] = v;
+          if (C2f) C2f[off] = (float)v;
+          if (C2h) C2h[off] = bf16s(v);
+        }
+      }
+}
+
+// Tile of an FP64 product: the largest that pads little past the smallest one's
+// padding and leaves enough workgroups for the chip (us at 64 x 64 / 32 x 64 /
+// 32 x 32): 20480 x 448 x 448 151 / 152 / 156; 512 x 4096 x 512, 64 products 2301 /
+// 2627 / 2801; 4071 x 600 x 600 (640 / 1280 / 2432 workgroups) 71 / 63 / 68;
+// 2600 x 352 x 352 (246 / 492 / 902) 25 / 22 / 21; 25 x 320 x 25, 600 products 30 /
+// 21 / 23; 70 x 70 x 608, 512 products 181 / 162 / 147.  128 x 64 was as fast as 64 x 64 where both
+// fill the chip (81920 x 608 x 608 1087 against 1094) and slower elsewhere.
+static hipError_t run_dgemm(const GemmArgs& g, bool ta, bool tb, hipStream_t st) {
+  if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
+  auto up = [](long x, long b) { return (x + b - 1) / b; };
+  auto fits = [&](int bm, int bn, long wgs) {
+    return up(g.M, bm) * bm * up(g.N, bn) * bn * 8 <= up(g.M, 32) * 32 * up(g.N, 32) * 32 * 9 &&
+           up(g.M, bm) * up(g.N, bn) * g.batch >= wgs;
+  };
+  int bm = 32, bn = 32;
+  if (!(ta && tb)) {
+    if (fits(64, 64, 1024)) { bm = 64; bn = 64; }
+    else if (fits(32, 64, 512)) bn = 64;
+  }
+  const int gx = (int)up(g.N, bn), gy = (int)up(g.M, bm);
+  const long total = (long)gx * gy * g.batch;
+  if (total > 0x7fffffffL) return hipErrorInvalidValue;
+  const bool vec = ((uintptr_t)g.A | (uintptr_t)g.B) % 16 == 0 && ((g.lda | g.ldb | g.a_bs | g.b_bs | g.a_gs) & 1) == 0 &&
+                   !(ta && (g.M & 1)) && !(!tb && (g.N & 1));
+#define QMC_DG(BM, BN, TA_, TB_)                                                                                     \
+  if (vec) hipLaunchKernelGGL((dgemm_kernel<BM, BN, TA_, TB_, true>), dim3((unsigned)total), dim3(256), 0, st, g, gx, gy); \
+  else hipLaunchKernelGGL((dgemm_kernel<BM, BN, TA_, TB_, false>), dim3((unsigned)total), dim3(256), 0, st, g, gx, gy)
+#define QMC_DG_T(BM, BN)                          \
+  if (ta) { QMC_DG(BM, BN, true, false); }        \
+  else if (tb) { QMC_DG(BM, BN, false, true); }   \
+  else { QMC_DG(BM, BN, false, false); }
+  if (ta && tb) { QMC_DG(32, 32, true, true); }
+  else if (bm == 64) { QMC_DG_T(64, 64) }
+  else if (bn == 64) { QMC_DG_T(32, 64) }
+  else { QMC_DG_T(32, 32) }
+#undef QMC_DG_T
+#undef QMC_DG
+  return hipGetLastError();
+}
+
+hipError_t gemm_f64(const GemmArgs& g, bool ta, bool tb, hipStream_t st) { return run_dgemm(g, ta, tb, st); }
+
+// FP64: dgemm_kernel; FP32 / BF16 rows: 64 x 64 tiles with K steps of 32 (from sweeps
+// at 1024 walkers x 80 rows, L = 608, all rows or a list of 60 per walker).
 template <typename T, typename TL>
 static hipError_t P_gemm(const GemmArgs& g, hipStream_t st) {
-  if constexpr (sizeof(TL) == 8) return run_gemm<64, 64, false, false, T, TL, TL, T, 16>(g, st);
+  if constexpr (sizeof(TL) == 8) return run_dgemm(g, false, false, st);
   else return run_gemm<64, 64, false, false, T, TL, TL, T, 32>(g, st);
 }
 
@@ -509,6 +787,15 @@ static hipError_t launch_wgem(const SysDev& s, const WalkDev& w, hipStream_t st)
   return hipGetLastError();
 }
 
+// A product over rows of storage type T with FP64 arithmetic (W: both operands are
+// rows; Yt: B alone)
+template <typename T, int BN, bool TA, bool TB>
+static hipError_t rows_gemm(const GemmArgs& g, hipStream_t st) {
+  if constexpr (sizeof(T) == 8) return run_dgemm(g, TA, TB, st);
+  else if constexpr (TB) return run_gemm<32, BN, TA, TB, T, T, double, double>(g, st);
+  else return run_gemm<32, BN, TA, TB, double, T, double, double, 16>(g, st);
+}
+
 template <typename T>
 static hipError_t W_build_t(const SysDev& s, const WalkDev& w, const T* Uph, hipStream_t st) {
   const long rowst = (long)s.N * s.Lp, n = s.nu;
@@ -522,14 +809,14 @@ static hipError_t W_build_t(const SysDev& s, const WalkDev& w, const T* Uph, hip
   // FP64 MFMA accumulation whatever the storage type of P and Phi (FP32 values
   // promote exactly): the length-L sums of the geminal entries carry no FP32
   // rounding.
-  hipError_t e = run_gemm<32, 32, false, true, T, T, double, double>(g, st);
+  hipError_t e = rows_gemm<T, 32, false, true>(g, st);
   if (e != hipSuccess || s.nk == 0) return e;
   GemmArgs u = plain(s.nu, s.nk, s.Lp);
   u.A = (const T*)w.phi; u.lda = s.Lp; u.a_bs = rowst;
   u.B = Uph; u.ldb = s.Lp; u.b_bs = 0;
   u.C = w.W + s.nd; u.ldc = n; u.c_bs = n * n;
   u.batch = w.Wk;
-  return run_gemm<32, 32, false, true, T, T, double, double>(u, st);
+  return rows_gemm<T, 32, false, true>(u, st);
 }
 
 hipError_t launch_W_build(const SysDev& s, const WalkDev& w, hipStream_t st) {
@@ -781,7 +1068,7 @@ static hipError_t Y_build_t(const SysDev& s, const WalkDev& w, const T* Uph, hip
     g.B = (const T*)w.P + (long)s.nu * s.Lp; g.ldb = s.Lp; g.b_bs = rowst;
     g.C = w.Yt; g.ldc = s.Lp; g.c_bs = rowst;
     g.batch = w.Wk;
-    e = run_gemm<32, 64, true, false, double, T, double, double, 16>(g, st);
+    e = rows_gemm<T, 64, true, false>(g, st);
     if (e != hipSuccess) return e;
   }
   if (s.nk > 0) {
@@ -791,7 +1078,7 @@ static hipError_t Y_build_t(const SysDev& s, const WalkDev& w, const T* Uph, hip
     g.C = w.Yt; g.ldc = s.Lp; g.c_bs = rowst;
     g.batch = w.Wk;
     g.accumulate = 1;
-    e = run_gemm<32, 64, true, false, double, T, double, double, 16>(g, st);
+    e = rows_gemm<T, 64, true, false>(g, st);
     if (e != hipSuccess) return e;
   }
   {
@@ -800,7 +1087,7 @@ static hipError_t Y_build_t(const SysDev& s, const WalkDev& w, const T* Uph, hip
     g.B = (const T*)w.P; g.ldb = s.Lp; g.b_bs = rowst;
     g.C = w.Yt + (long)s.nu * s.Lp; g.ldc = s.Lp; g.c_bs = rowst;
     g.batch = w.Wk;
-    e = run_gemm<32, 64, false, false, double, T, double, double, 16>(g, st);
+    e = rows_gemm<T, 64, false, false>(g, st);
   }
   return e;
 }

@@ -801,7 +801,7 @@ struct GemmArgs {
 
 // Plain (ungathered) argument block for an M x N x K product.
 GemmArgs gemm_args(int M, int N, int K);
-// FP64 products on MFMA; big = 64x64 tiles (else 32x32).
-hipError_t gemm_f64(const GemmArgs& g, bool ta, bool tb, bool big, hipStream_t st);
+// FP64 products on MFMA (the tile by size; results do not depend on it).
+hipError_t gemm_f64(const GemmArgs& g, bool ta, bool tb, hipStream_t st);
 
 }  // namespace qmc

@@ -95,7 +95,7 @@ hipError_t launch_jastrow3_eval(const SysDev& s, const WalkDev& w, hipStream_t s
     g.B = s.M3 + (long)sp * LJ * 2 * LJ + (long)sp * LJ; g.ldb = 2 * LJ; g.b_bs = 0;
     g.C = w.hv + (long)row0 * LJ; g.ldc = LJ; g.c_bs = (long)s.N * LJ;
     g.batch = w.Wk;
-    e = gemm_f64(g, false, false, false, st);
+    e = gemm_f64(g, false, false, st);
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(j3_rowdot_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, s, w, (int)rows);
@@ -151,7 +151,7 @@ hipError_t launch_jastrow3_logderiv(const SysDev& s, const WalkDev& w, double* d
       g.C = dM + (long)sp * LJ * LJ; g.ldc = LJ; g.c_bs = 3L * LJ * LJ;
       g.batch = w.Wk;
       if (nrow == 0) continue;   // C_s = 0: the kernel does not read the slot
-      const hipError_t e = gemm_f64(g, true, false, false, st);
+      const hipError_t e = gemm_f64(g, true, false, st);
       if (e != hipSuccess) return e;
     }
   }

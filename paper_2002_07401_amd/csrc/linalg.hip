@@ -502,7 +502,7 @@ static hipError_t gj_update_mfma(const WalkDev& w, int np, int c0, int NB, hipSt
     g.C = w.T + o0; g.ldc = np; g.c_bs = (long)np * np;
     g.batch = w.Wk;
     g.accumulate = 1;
-    const hipError_t e = gemm_f64(g, false, false, true, st);
+    const hipError_t e = gemm_f64(g, false, false, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -53,7 +53,7 @@ hipError_t launch_pf_B_build(const SysDev& s, const WalkDev& w, hipStream_t st) 
     g.A = (const double*)w.phi + (long)x.row0 * s.Lp; g.lda = s.Lp; g.a_grp = x.nrow; g.a_gs = rowst;
     g.B = x.K; g.ldb = s.Lp;
     g.C = x.out + (long)x.row0 * s.Lp; g.ldc = s.Lp; g.c_grp = x.nrow; g.c_gs = rowst;
-    const hipError_t e = gemm_f64(g, false, false, true, st);
+    const hipError_t e = gemm_f64(g, false, false, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -87,7 +87,7 @@ hipError_t launch_pf_G_build(const SysDev& s, const WalkDev& w, hipStream_t st) 
     g.B = sp == 0 ? (const double*)w.P : w.Bd; g.ldb = s.Lp; g.b_bs = rowst;   // stored [j][mu]
     g.C = w.W + (long)i0 * n; g.ldc = n; g.c_bs = n * n;
     g.batch = w.Wk;
-    hipError_t e = gemm_f64(g, false, true, false, st);
+    hipError_t e = gemm_f64(g, false, true, st);
     if (e != hipSuccess) return e;
     if (s.pk > 0) {
       GemmArgs u = gemm_args(ni, s.pk, s.Lp);
@@ -95,7 +95,7 @@ hipError_t launch_pf_G_build(const SysDev& s, const WalkDev& w, hipStream_t st) 
       u.B = s.Upf + (long)sp * s.pk * s.Lp; u.ldb = s.Lp; u.b_bs = 0;
       u.C = w.W + (long)i0 * n + s.N; u.ldc = n; u.c_bs = n * n;
       u.batch = w.Wk;
-      e = gemm_f64(u, false, true, false, st);
+      e = gemm_f64(u, false, true, st);
       if (e != hipSuccess) return e;
     }
   }
@@ -217,7 +217,7 @@ hipError_t launch_pf_Y_products(const SysDev& s, const WalkDev& w, const double*
     g.B = sp == 0 ? (const double*)w.P : w.Bd; g.ldb = s.Lp; g.b_bs = rowst;
     g.C = out + (long)i0 * s.Lp; g.ldc = s.Lp; g.c_bs = rowst;
     g.batch = w.Wk;
-    hipError_t e = gemm_f64(g, true, false, false, st);
+    hipError_t e = gemm_f64(g, true, false, st);
     if (e != hipSuccess) return e;
     if (s.pk > 0) {
       GemmArgs u = gemm_args(ni, s.Lp, s.pk);
@@ -226,7 +226,7 @@ hipError_t launch_pf_Y_products(const SysDev& s, const WalkDev& w, const double*
       u.C = out + (long)i0 * s.Lp; u.ldc = s.Lp; u.c_bs = rowst;
       u.batch = w.Wk;
       u.accumulate = 1;
-      e = gemm_f64(u, true, false, false, st);
+      e = gemm_f64(u, true, false, st);
       if (e != hipSuccess) return e;
     }
   }
@@ -398,7 +398,7 @@ hipError_t launch_pf_accept(const SysDev& s, const WalkDev& w, int e, const uint
     g.A = w.psi_new; g.lda = s.Lp;
     g.B = e < s.nu ? s.Kcat_u : s.Kcat_d; g.ldb = 2 * s.Lp;
     g.C = w.pfB; g.ldc = 2 * s.Lp;
-    const hipError_t err = gemm_f64(g, false, false, false, st);
+    const hipError_t err = gemm_f64(g, false, false, st);
     if (err != hipSuccess) return err;
   }
   hipLaunchKernelGGL(pf_accept_kernel, dim3(w.Wk), dim3(256), 0, st, s, w, e, acc, unif, accept_count);
@@ -434,14 +434,14 @@ hipError_t launch_pf_logderiv(const SysDev& s, const WalkDev& w, double* d_uu, d
     g.B = phi + (long)c0 * s.Lp; g.ldb = s.Lp; g.b_bs = rowst;
     g.C = w.pfT; g.ldc = s.Lp; g.c_bs = rowst;
     g.batch = w.Wk;
-    hipError_t e = gemm_f64(g, false, false, false, st);
+    hipError_t e = gemm_f64(g, false, false, st);
     if (e != hipSuccess) return e;
     GemmArgs h = gemm_args((int)L, (int)L, nr);
     h.A = phi + (long)r0 * s.Lp; h.lda = s.Lp; h.a_bs = rowst;   // stored [i][mu]: op = A^T
     h.B = w.pfT; h.ldb = s.Lp; h.b_bs = rowst;
     h.C = out; h.ldc = L; h.c_bs = L * L;
     h.batch = w.Wk;
-    e = gemm_f64(h, true, false, false, st);
+    e = gemm_f64(h, true, false, st);
     if (e != hipSuccess) return e;
     const long tot = (long)w.Wk * L * L;
     hipLaunchKernelGGL(pf_scale_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, out, tot, scale);
@@ -466,7 +466,7 @@ hipError_t launch_pf_logderiv(const SysDev& s, const WalkDev& w, double* d_uu, d
     g.B = w.A + (long)s.N * n + r0; g.ldb = n; g.b_bs = n * n;   // stored [l][i]: op = (.)^T
     g.C = out; g.ldc = s.pk; g.c_bs = L * s.pk;
     g.batch = w.Wk;
-    e = gemm_f64(g, true, true, false, st);
+    e = gemm_f64(g, true, true, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

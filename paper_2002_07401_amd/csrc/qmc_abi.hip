@@ -1023,7 +1023,7 @@ static hipError_t residual_before(const SysDev& s, qmc_walkers* wk, hipStream_t 
   g.B = wk->res_x; g.ldb = n; g.b_bs = nn;
   g.C = wk->res_p; g.ldc = n; g.c_bs = nn;
   g.batch = wk->d.Wk;
-  TIMED_E(wk, QMC_T_OTHER, stream, gemm_f64(g, false, false, false, stream));
+  TIMED_E(wk, QMC_T_OTHER, stream, gemm_f64(g, false, false, stream));
   return hipSuccess;
 }
 
