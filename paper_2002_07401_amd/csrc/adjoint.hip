@@ -254,7 +254,7 @@ basis_backward_kernel(SysDev s, WalkDev w, const double* __restrict__ phibar, co
           const double d[3] = {r[3 * i] - Rx, r[3 * i + 1] - Ry, r[3 * i + 2] - Rz};
           const double sq = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
           double P, Pg[3];
-          angular(kind_ang(kind), d[0], d[1], d[2], P, Pg[0], Pg[1], Pg[2]);
+          angular_cases(kind_ang(kind), d[0], d[1], d[2], P, Pg[0], Pg[1], Pg[2]);
           const Radial rd = radial_all(kind, zt, sq);
           const double e = rd.e;
           const double psi = P * e;
@@ -284,11 +284,11 @@ basis_backward_kernel(SysDev s, WalkDev w, const double* __restrict__ phibar, co
           zacc += pb * zpsi + zg + hb * zlap;
           tx += t0; ty += t1; tz += t2;
         }
-        const double s0 = wave_sum(t0), s1 = wave_sum(t1), s2 = wave_sum(t2);
-        if (lane == 0) {
-          double* rp = rpart[wave][i - c0];
-          if (k == 0) { rp[0] = s0; rp[1] = s1; rp[2] = s2; }
-          else { rp[0] += s0; rp[1] += s1; rp[2] += s2; }
+        const double sum = wave_sum4(t0, t2, t1, 0.0);
+        if ((lane & 15) == 0 && lane < 48) {
+          double* rp = rpart[wave][i - c0] + (lane >> 4);
+          if (k == 0) *rp = sum;
+          else *rp += sum;
         }
       }
       if (act) {
@@ -370,11 +370,11 @@ jastrow_backward_kernel(SysDev s, WalkDev w, const double* __restrict__ ga, cons
         for (int c = 0; c < 3; ++c) t[c] += bv * Z * d[c] * ir3;
         for (int c = 0; c < 3; ++c) { rb[c] += t[c]; cR[c] = -t[c]; }
       }
-      const double s0 = wave_sum(cR[0]), s1 = wave_sum(cR[1]), s2 = wave_sum(cR[2]), s3 = wave_sum(cb);
-      if (lane == 0 && a < kMaxNucBack) {
-        double* rbw = rbin[wave][a];
-        if (c0 == 0) { rbw[0] = s0; rbw[1] = s1; rbw[2] = s2; rbw[3] = s3; }
-        else { rbw[0] += s0; rbw[1] += s1; rbw[2] += s2; rbw[3] += s3; }
+      const double sum = wave_sum4(cR[0], cR[2], cR[1], cb);
+      if ((lane & 15) == 0 && a < kMaxNucBack) {
+        double* rbw = rbin[wave][a] + (lane >> 4);
+        if (c0 == 0) *rbw = sum;
+        else *rbw += sum;
       }
     }
     // two-body terms and electron-electron repulsion: the chunk's nc electrons

@@ -160,9 +160,9 @@ __global__ void __launch_bounds__(256) rowdot_kernel(SysDev s, int rows, const d
     const double yy = s.Lq ? prim_weight(s, mu, y) : y[mu];
     sx += gx * yy; sy += gy * yy; sz += gz * yy; sl += lp * yy;
   }
-  sx = wave_sum(sx); sy = wave_sum(sy); sz = wave_sum(sz); sl = wave_sum(sl);
-  if (lane == 0) {
-    D[4 * row] = sx; D[4 * row + 1] = sy; D[4 * row + 2] = sz; D[4 * row + 3] = sl;
+  const double sum = wave_sum4(sx, sz, sy, sl);
+  if ((lane & 15) == 0) {
+    D[4 * row + (lane >> 4)] = sum;
   }
 }
 

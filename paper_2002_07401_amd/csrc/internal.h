@@ -360,20 +360,6 @@ hipError_t launch_forces(const SysDev& s, const WalkDev& w, const AdjWork& aw, c
 // ---------------------------------------------------------------------------
 
 // Angular factor P and its gradient for an unnormalised real solid harmonic.
-__device__ __forceinline__ void angular(int kind, double x, double y, double z,
-                                        double& P, double& Px, double& Py, double& Pz) {
-  switch (kind) {
-    case 0: P = 1.0;     Px = 0.0;      Py = 0.0;      Pz = 0.0;     break;
-    case 1: P = x;       Px = 1.0;      Py = 0.0;      Pz = 0.0;     break;
-    case 2: P = y;       Px = 0.0;      Py = 1.0;      Pz = 0.0;     break;
-    case 3: P = z;       Px = 0.0;      Py = 0.0;      Pz = 1.0;     break;
-    case 4: P = x * y;   Px = y;        Py = x;        Pz = 0.0;     break;
-    case 5: P = y * z;   Px = 0.0;      Py = z;        Pz = y;       break;
-    case 6: P = z * x;   Px = z;        Py = 0.0;      Pz = x;       break;
-    case 7: P = x * x - y * y;  Px = 2.0 * x;  Py = -2.0 * y;  Pz = 0.0;  break;
-    default: P = 2.0 * z * z - x * x - y * y;  Px = -2.0 * x;  Py = -2.0 * y;  Pz = 4.0 * z;  break;
-  }
-}
 
 __device__ __forceinline__ int kind_l(int kind) { return kind == 0 ? 0 : (kind < 4 ? 1 : 2); }
 
@@ -397,7 +383,12 @@ __device__ __forceinline__ int kind_ang(int kind) { return kind & (kSlaterBit - 
 
 __device__ __forceinline__ double radial_e(int kind, double zt, double q) {
   double x = q;
-  if (kind & kSlaterBit) x = sqrt(q);
+  if (__builtin_amdgcn_ballot_w64((kind & kSlaterBit) != 0)) {
+    // (a branch for the whole wave: a square root that no lane needs is 18
+    // instructions of 75; the empty statement keeps it from being speculated)
+    asm volatile("");
+    x = (kind & kSlaterBit) ? sqrt(q) : q;
+  }
   return exp(-zt * x);
 }
 
@@ -445,6 +436,47 @@ __device__ __forceinline__ double angular_value(int kind, double x, double y, do
   p = kind == 7 ? xx - yy : p;
   p = kind >= 8 ? fma(z, 2.0 * z, -xx) - yy : p;
   return p;
+}
+
+// P and its gradient, selected and rounded as angular_value (nine divergent cases
+// cost a wave twice the instructions, and a branch each)
+__device__ __forceinline__ void angular(int kind, double x, double y, double z,
+                                        double& P, double& Px, double& Py, double& Pz) {
+  P = angular_value(kind, x, y, z);
+  double gx = 0.0, gy = 0.0, gz = 0.0;
+  gx = kind == 1 ? 1.0 : gx;
+  gy = kind == 2 ? 1.0 : gy;
+  gz = kind == 3 ? 1.0 : gz;
+  gx = kind == 4 ? y : gx;
+  gy = kind == 4 ? x : gy;
+  gy = kind == 5 ? z : gy;
+  gz = kind == 5 ? y : gz;
+  gx = kind == 6 ? z : gx;
+  gz = kind == 6 ? x : gz;
+  gx = kind == 7 ? 2.0 * x : gx;
+  gx = kind >= 8 ? -2.0 * x : gx;
+  gy = kind >= 7 ? -2.0 * y : gy;
+  gz = kind >= 8 ? 4.0 * z : gz;
+  Px = gx;
+  Py = gy;
+  Pz = gz;
+}
+
+// The same by cases, where the kind stays over a loop (basis_backward_kernel: the
+// selected form took 8 % longer there).
+__device__ __forceinline__ void angular_cases(int kind, double x, double y, double z,
+                                              double& P, double& Px, double& Py, double& Pz) {
+  switch (kind) {
+    case 0: P = 1.0;     Px = 0.0;      Py = 0.0;      Pz = 0.0;     break;
+    case 1: P = x;       Px = 1.0;      Py = 0.0;      Pz = 0.0;     break;
+    case 2: P = y;       Px = 0.0;      Py = 1.0;      Pz = 0.0;     break;
+    case 3: P = z;       Px = 0.0;      Py = 0.0;      Pz = 1.0;     break;
+    case 4: P = x * y;   Px = y;        Py = x;        Pz = 0.0;     break;
+    case 5: P = y * z;   Px = 0.0;      Py = z;        Pz = y;       break;
+    case 6: P = z * x;   Px = z;        Py = 0.0;      Pz = x;       break;
+    case 7: P = x * x - y * y;  Px = 2.0 * x;  Py = -2.0 * y;  Pz = 0.0;  break;
+    default: P = 2.0 * z * z - x * x - y * y;  Px = -2.0 * x;  Py = -2.0 * y;  Pz = 4.0 * z;  break;
+  }
 }
 
 // Function mu of a basis table (packed centre + zeta, kind) at point
@@ -568,21 +600,33 @@ __device__ __forceinline__ double dpp_f64(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 // v of this lane's row (half) plus v of the row 16 (half 32) lanes away
+// (a and b: the lower half, or the even rows, sums a, the others b)
 template <bool HALF>
-__device__ __forceinline__ double row_pair_sum(double v) {
+__device__ __forceinline__ double row_pair_sum(double va, double vb) {
 #pragma clang fp contract(off)
-  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  const unsigned long long a = (unsigned long long)__double_as_longlong(va), b = (unsigned long long)__double_as_longlong(vb);
+  const unsigned al = (unsigned)a, ah = (unsigned)(a >> 32), bl = (unsigned)b, bh = (unsigned)(b >> 32);
   typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  const u2 l = HALF ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false) : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-  const u2 h = HALF ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false) : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  const u2 l = HALF ? __builtin_amdgcn_permlane32_swap(al, bl, false, false) : __builtin_amdgcn_permlane16_swap(al, bl, false, false);
+  const u2 h = HALF ? __builtin_amdgcn_permlane32_swap(ah, bh, false, false) : __builtin_amdgcn_permlane16_swap(ah, bh, false, false);
   return __longlong_as_double((long long)(((unsigned long long)h.x << 32) | l.x)) +
          __longlong_as_double((long long)(((unsigned long long)h.y << 32) | l.y));
 }
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma clang fp contract(off)
-  v = row_pair_sum<true>(v);
-  v = row_pair_sum<false>(v);
+  v = row_pair_sum<true>(v, v);
+  v = row_pair_sum<false>(v, v);
+  v += dpp_f64<0x128>(v);
+  v += dpp_f64<0x124>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0xB1>(v);
+  return v;
+}
+// Four sums at once, each bitwise wave_sum's (the same pairs are added): lanes 0..15
+// return a's, 16..31 c's, 32..47 b's, 48..63 d's.  21 instructions instead of 72.
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d) {
+#pragma clang fp contract(off)
+  double v = row_pair_sum<false>(row_pair_sum<true>(a, b), row_pair_sum<true>(c, d));
   v += dpp_f64<0x128>(v);
   v += dpp_f64<0x124>(v);
   v += dpp_f64<0x4E>(v);
@@ -595,8 +639,8 @@ __device__ __forceinline__ double lane_group_sum(double v, int m) {
 #pragma clang fp contract(off)
   if (m <= 8) v += dpp_f64<0x128>(v);
   if (m <= 4) v += dpp_f64<0x124>(v);
-  if (m <= 16) v = row_pair_sum<false>(v);
-  if (m <= 32) v = row_pair_sum<true>(v);
+  if (m <= 16) v = row_pair_sum<false>(v, v);
+  if (m <= 32) v = row_pair_sum<true>(v, v);
   return v;
 }
 __device__ __forceinline__ float wave_sum(float v) {

@@ -132,16 +132,18 @@ __global__ __launch_bounds__(256) void lrdmc_ratio_kernel(SysDev s, WalkDev w, L
       for (int k = 0; k < kHops; ++k) dj[k] += (basis_value_tab(s.jbfn, s.jkind, q, px[k], py[k], pz[k]) - c0) * g;
     }
   }
-#pragma unroll
-  for (int k = 0; k < kHops; ++k) {
-    c[k] = wave_sum(c[k]);
-    dj[k] = wave_sum(dj[k]);
-  }
-  if (lane == 0) {
+  // hop lane / 16 of the first four, then hops 4 and 5 in the even rows of 16 lanes
+  // with their Jastrow changes in the odd ones
+  const double c03 = wave_sum4(c[0], c[2], c[1], c[3]), j03 = wave_sum4(dj[0], dj[2], dj[1], dj[3]);
+  const double c45 = wave_sum4(c[4], c[5], dj[4], dj[5]);
+  const double j45 = __shfl_xor(c45, 16, 64);
+  const bool two = (lane & 16) == 0;
+  const double q03 = c03 * exp(j03), q45 = c45 * exp(two ? j45 : 0.0);
+  if ((lane & 15) == 0) {
     double* o = l.ratio + ((long)wk * s.N + i) * kHops;
-#pragma unroll
-    for (int k = 0; k < kHops; ++k) o[k] = c[k] * exp(dj[k]);
-    l.ah[(long)wk * s.N + i] = a;
+    o[lane >> 4] = q03;
+    if (two) o[4 + (lane >> 5)] = q45;
+    if (lane == 0) l.ah[(long)wk * s.N + i] = a;
   }
 }
 

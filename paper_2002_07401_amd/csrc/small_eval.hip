@@ -212,11 +212,8 @@ __global__ void __launch_bounds__(kChainT, 2) small_eval_kernel(SysDev s, WalkDe
       const double yy = s.Lq ? prim_weight(s, mu, y) : y[mu];
       sx += gx * yy; sy += gy * yy; sz += gz * yy; sl += lp * yy;
     }
-    sx = wave_sum(sx); sy = wave_sum(sy); sz = wave_sum(sz); sl = wave_sum(sl);
-    if (lane == 0) {
-      double* D = w.D + (row0 + i) * 4;
-      D[0] = sx; D[1] = sy; D[2] = sz; D[3] = sl;
-    }
+    const double sum = wave_sum4(sx, sz, sy, sl);
+    if ((lane & 15) == 0) w.D[(row0 + i) * 4 + (lane >> 4)] = sum;
   }
 }
 
