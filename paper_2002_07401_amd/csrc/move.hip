@@ -26,8 +26,16 @@
 
 namespace qmc {
 
+// Threads of the per-walker move kernels.  Past the basis sizes at which an accept is
+// fused with the next set-up, a walker's phases (its L functions and N + n_nuc Jastrow
+// terms, the buffer's dot products, the kept list, the columns of the kept functions)
+// are each long enough for 1024 threads, and a few dozen walkers leave most of the
+// chip to them: 64 walkers x 1024 e, L = 4096, us a launch with 256 -> 1024 threads:
+// set-up 51 -> 28, columns 61 -> 36, accept 25 -> 18.
+static int move_threads(const SysDev& s) { return s.screened() && s.Lp > kFuseMaxLp ? 1024 : 256; }
+
 template <bool DRIFT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 propose_prep_kernel(SysDev s, WalkDev w, int e, const double* __restrict__ r_new_in,
                     const double* __restrict__ disp) {
   const int wk = blockIdx.x;
@@ -67,7 +75,7 @@ __global__ void __launch_bounds__(256) propose_rows_generic_kernel(SysDev s, Wal
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 accept_kernel(SysDev s, WalkDev w, int e, const uint8_t* __restrict__ acc_in,
               const double* __restrict__ unif, int32_t* __restrict__ accept_count, int S) {
   const int wk = blockIdx.x;
@@ -114,9 +122,9 @@ int propose_splits(const SysDev& s) {
 hipError_t launch_propose_prep(const SysDev& s, const WalkDev& w, int e, const double* r_new,
                                const double* disp, bool drift, hipStream_t st) {
   if (drift)
-    hipLaunchKernelGGL(propose_prep_kernel<true>, dim3(w.Wk), dim3(256), 0, st, s, w, e, r_new, disp);
+    hipLaunchKernelGGL(propose_prep_kernel<true>, dim3(w.Wk), dim3(move_threads(s)), 0, st, s, w, e, r_new, disp);
   else
-    hipLaunchKernelGGL(propose_prep_kernel<false>, dim3(w.Wk), dim3(256), 0, st, s, w, e, r_new, disp);
+    hipLaunchKernelGGL(propose_prep_kernel<false>, dim3(w.Wk), dim3(move_threads(s)), 0, st, s, w, e, r_new, disp);
   return hipGetLastError();
 }
 
@@ -172,7 +180,7 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
 // each; the accept and finalize kernels sum the slots as usual.
 // ---------------------------------------------------------------------------
 constexpr int kScreenRowsNB = 2;   // rows a lane: 128 rows a workgroup
-__global__ void __launch_bounds__(256) propose_screened_kernel(SysDev s, WalkDev w, int e, int S, int chunks) {
+__global__ void __launch_bounds__(1024) propose_screened_kernel(SysDev s, WalkDev w, int e, int S, int chunks) {
   screened_rows_walker<kScreenRowsNB>(s, w, blockIdx.x / chunks, e, S, blockIdx.x % chunks);
 }
 
@@ -338,7 +346,7 @@ hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, dou
                                    hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!w.PT || !w.muk) return hipErrorInvalidValue;
   const int S = propose_splits(s);
-  const dim3 grid(w.Wk), blk(256);
+  const dim3 blk(move_threads(s));
   if (s.nu <= kBigMaxN) {
     const int chunks = (s.nu + 64 * kScreenRowsNB - 1) / (64 * kScreenRowsNB);
     QMC_LAUNCH_EV(propose_screened_kernel, dim3((unsigned)(w.Wk * chunks)), blk, 0, st, ev_start, ev_stop, s, w, e, S,
@@ -363,7 +371,7 @@ accept_prep_staged_kernel(SysDev s, WalkDev w, int e, const double* __restrict__
 static hipError_t accept_launch(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc,
                                 const double* unif, int32_t* accept_count, int S, hipStream_t st) {
   if (s.nu > kBigMaxN || !w.wv) return hipErrorNotSupported;
-  const dim3 grid(w.Wk), blk(256);
+  const dim3 grid(w.Wk), blk(move_threads(s));
   if (s.bf16()) hipLaunchKernelGGL(accept_kernel<bf16s>, grid, blk, 0, st, s, w, e, acc, unif, accept_count, S);
   else if (s.f32()) hipLaunchKernelGGL(accept_kernel<float>, grid, blk, 0, st, s, w, e, acc, unif, accept_count, S);
   else hipLaunchKernelGGL(accept_kernel<double>, grid, blk, 0, st, s, w, e, acc, unif, accept_count, S);

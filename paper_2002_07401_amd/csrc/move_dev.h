@@ -108,6 +108,7 @@ __device__ void inverse_line_body(const SysDev& s, const WalkDev& w, int wk, int
   }
   for (int j = tid; j < n; j += blockDim.x) {
     double c = sv0[j];
+#pragma unroll 8
     for (int i = 0; i < m; ++i) c -= sz[i] * V[(long)i * n + j];
     cv[j] = c;
   }
@@ -212,8 +213,8 @@ __device__ void jastrow_change(const SysDev& s, const WalkDev& w, int wk, int e,
 // are kept.  The kept ones are listed in increasing mu with their values.  Called by every thread
 // of the workgroup after psi_new and cvec of electron e are written.
 __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int e) {
-  __shared__ double red[8];
-  __shared__ int wcount[4];
+  __shared__ double red[16];
+  __shared__ int wcount[16];
   __shared__ int total;
   __syncthreads();
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -261,7 +262,7 @@ __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int 
 template <bool DRIFT>
 __device__ void prep_body(const SysDev& s, const WalkDev& w, int wk, int e, const double* __restrict__ r_new,
                           const double* __restrict__ disp) {
-  __shared__ double red[8];
+  __shared__ double red[16];
   __shared__ double rn[3];
   const int tid = threadIdx.x;
   const double* r = w.r + (long)wk * s.N * 3;

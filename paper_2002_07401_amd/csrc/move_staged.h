@@ -38,9 +38,9 @@ __host__ __device__ inline StageLayout stage_layout(int n, int kb, int mc) {
 // workgroups, so that a few walkers of a large system still fill the chip.
 template <int NB>
 __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, int e, int S, int c) {
-  __shared__ double part[4][64 * NB];
-  __shared__ double red[8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  __shared__ double part[16][64 * NB];
+  __shared__ double red[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
   const bool up = e < s.nu;
   const int j0 = 64 * NB * c;
   const int n = min(s.nu - j0, 64 * NB);   // this chunk's rows
@@ -53,11 +53,11 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 #pragma unroll
   for (int b = 0; b < NB; ++b) acc[b] = 0.0;
   int k = wave;
-  for (; k + 12 < cnt; k += 16) {   // four functions in flight per wave
+  for (; k + 3 * nw < cnt; k += 4 * nw) {   // four functions in flight per wave
     int mu[4];
     double v[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { mu[q] = mk[k + 4 * q]; v[q] = pk[k + 4 * q]; }
+    for (int q = 0; q < 4; ++q) { mu[q] = mk[k + nw * q]; v[q] = pk[k + nw * q]; }
     double x[4][NB];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
@@ -71,7 +71,7 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 #pragma unroll
       for (int b = 0; b < NB; ++b) acc[b] += v[q] * x[q][b];
   }
-  for (; k < cnt; k += 4) {
+  for (; k < cnt; k += nw) {
     const int mu = mk[k];
     const double v = pk[k];
 #pragma unroll
@@ -87,7 +87,8 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
   double* wn = w.w_new + (long)wk * s.nu + j0;
   double rp = 0.0;
   for (int j = tid; j < n; j += blockDim.x) {
-    const double x = ((part[0][j] + part[1][j]) + part[2][j]) + part[3][j];
+    double x = part[0][j];
+    for (int q = 1; q < nw; ++q) x += part[q][j];
     wn[j] = x;
     rp += x * cv[j];
   }
