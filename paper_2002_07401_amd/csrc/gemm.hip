@@ -540,11 +540,16 @@ static hipError_t P_build_t(const SysDev& s, const WalkDev& w, int halves, hipSt
   const int mask_ld = (s.Lp + kLamTileN - 1) / kLamTileN;
   int* ridx[2] = {nullptr, nullptr};
   int* rcnt[2] = {nullptr, nullptr};
-  for (int h = 0; h < 2; ++h)
-    if ((halves >> h) & 1) {
-      e = launch_moved_rows(s, w, h, (dirty >> h) & 1, &ridx[h], &rcnt[h], st);
-      if (e != hipSuccess) return e;
-    }
+  if ((halves & 3) == 3 && (dirty & 3) == 3) {
+    e = launch_moved_rows_both(s, w, true, ridx, rcnt, st);
+    if (e != hipSuccess) return e;
+  } else {
+    for (int h = 0; h < 2; ++h)
+      if ((halves >> h) & 1) {
+        e = launch_moved_rows(s, w, h, (dirty >> h) & 1, &ridx[h], &rcnt[h], st);
+        if (e != hipSuccess) return e;
+      }
+  }
   if (halves & 1) {   // P_up = Phi_up Lambda  (rows 0..nu-1 of every walker)
     GemmArgs g = plain(w.Wk * s.nu, s.Lp, s.Lp);
     g.ridx = ridx[0]; g.rcnt = rcnt[0];

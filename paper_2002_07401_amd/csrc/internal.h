@@ -697,6 +697,9 @@ hipError_t launch_P_build(const SysDev& s, const WalkDev& w, int halves, hipStre
 // list).  Nothing to do (and no list) when the walker set keeps no positions.
 hipError_t launch_moved_rows(const SysDev& s, const WalkDev& w, int h, bool moved_only, int** ridx, int** rcnt,
                              hipStream_t st);
+// both halves (ridx, rcnt: two each)
+hipError_t launch_moved_rows_both(const SysDev& s, const WalkDev& w, bool moved_only, int** ridx, int** rcnt,
+                                  hipStream_t st);
 hipError_t launch_W_build(const SysDev& s, const WalkDev& w, hipStream_t st);
 // int8 digit tiles of FP64 rows and the error-free products built from them
 long oz_plane_bytes(long rows, int Kp);

@@ -487,6 +487,73 @@ p_dirty_write_kernel(const double* __restrict__ r, double* __restrict__ rP, int 
   if (moved) { rP[o] = r[o]; rP[o + 1] = r[o + 1]; rP[o + 2] = r[o + 2]; }
 }
 
+// The list of up to kDirtySmall rows a half in one launch (one half, or both: a
+// workgroup each), eight rows a thread with all their positions in flight: three
+// launches of 4.7 us each are 10 to 20 % of an evaluation of some thousand rows.
+constexpr int kDirtySmall = 8192;
+__global__ void __launch_bounds__(1024)
+p_dirty_small_kernel(const double* __restrict__ r, double* __restrict__ rP, int Wk, int N, int nu, int h0,
+                     int* __restrict__ idx, int* __restrict__ cnt) {
+  __shared__ int wc[128];
+  const int h = h0 + blockIdx.x, i0 = h == 0 ? 0 : nu, n = h == 0 ? nu : N - nu;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, rows = Wk * n;
+  idx += h == 0 ? 0 : (long)Wk * nu;
+  long o[8];
+  double x[8][3];
+  unsigned long long b[8];
+  bool mv[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int t = tid + 1024 * q, w = t / n;
+    o[q] = t < rows ? ((long)w * N + i0 + (t - w * n)) * 3 : 0;
+    x[q][0] = r[o[q]]; x[q][1] = r[o[q] + 1]; x[q][2] = r[o[q] + 2];
+    mv[q] = t < rows && !(x[q][0] == rP[o[q]] && x[q][1] == rP[o[q] + 1] && x[q][2] == rP[o[q] + 2]);
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    b[q] = __ballot(mv[q]);
+    if (lane == 0) wc[16 * q + wave] = __popcll(b[q]);
+  }
+  __syncthreads();   // (every position is read)
+  // exclusive offsets of the 128 runs of 64 rows, in every wave
+  const int v0 = wc[lane], v1 = wc[64 + lane];
+  int s0 = v0, s1 = v1;
+  for (int k = 1; k < 64; k <<= 1) {
+    const int y0 = __shfl_up(s0, k, 64), y1 = __shfl_up(s1, k, 64);
+    if (lane >= k) { s0 += y0; s1 += y1; }
+  }
+  const int t0 = __shfl(s0, 63, 64), t1 = __shfl(s1, 63, 64);
+  s0 -= v0;
+  s1 += t0 - v1;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int off = q < 4 ? __shfl(s0, 16 * q + wave, 64) : __shfl(s1, 16 * q + wave - 64, 64);
+    if (mv[q]) {
+      idx[off + __popcll(b[q] & ((1ull << lane) - 1ull))] = tid + 1024 * q;
+      rP[o[q]] = x[q][0]; rP[o[q] + 1] = x[q][1]; rP[o[q] + 2] = x[q][2];
+    }
+  }
+  if (tid == 0) cnt[h] = t0 + t1;
+}
+
+hipError_t launch_moved_rows_both(const SysDev& s, const WalkDev& w, bool moved_only, int** ridx, int** rcnt,
+                                  hipStream_t st) {
+  if (moved_only && w.rpos_P && s.nd > 0 && (long)w.Wk * s.nu <= kDirtySmall) {
+    for (int h = 0; h < 2; ++h) {
+      ridx[h] = w.dirty_idx + (h == 0 ? 0 : (long)w.Wk * s.nu);
+      rcnt[h] = w.dirty_cnt + h;
+    }
+    hipLaunchKernelGGL(p_dirty_small_kernel, dim3(2), dim3(1024), 0, st, w.r, w.rpos_P, w.Wk, s.N, s.nu, 0,
+                       w.dirty_idx, w.dirty_cnt);
+    return hipGetLastError();
+  }
+  for (int h = 0; h < 2; ++h) {
+    const hipError_t e = launch_moved_rows(s, w, h, moved_only, &ridx[h], &rcnt[h], st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_moved_rows(const SysDev& s, const WalkDev& w, int h, bool moved_only, int** ridx, int** rcnt,
                              hipStream_t st) {
   *ridx = nullptr;
@@ -499,6 +566,11 @@ hipError_t launch_moved_rows(const SysDev& s, const WalkDev& w, int h, bool move
   if (moved_only) {
     *ridx = w.dirty_idx + (h == 0 ? 0 : (long)w.Wk * s.nu);
     *rcnt = w.dirty_cnt + h;
+    if (rows <= kDirtySmall) {
+      hipLaunchKernelGGL(p_dirty_small_kernel, dim3(1), dim3(1024), 0, st, w.r, w.rpos_P, w.Wk, s.N, s.nu, h,
+                         w.dirty_idx, w.dirty_cnt);
+      return hipGetLastError();
+    }
     int* boff = w.dirty_blk;
     hipLaunchKernelGGL(p_dirty_count_kernel, dim3(nb), dim3(256), 0, st, w.r, w.rpos_P, w.Wk, s.N, i0, n, boff);
     hipLaunchKernelGGL(p_dirty_scan_kernel, dim3(1), dim3(1024), 0, st, boff, nb, *rcnt);
@@ -522,6 +594,13 @@ hipError_t launch_P_build_oz(const SysDev& s, const WalkDev& w, int halves, cons
   const long planeB = oz_plane_bytes(s.Lp, s.Lp);
   const int mask_ld = (s.Lp + kLamTileN - 1) / kLamTileN;
   const long up_bytes = (long)s.oz_s * oz_plane_bytes((long)w.Wk * s.nu, s.Lp);
+  int* ridx2[2] = {nullptr, nullptr};
+  int* rcnt2[2] = {nullptr, nullptr};
+  const bool both = (halves & 3) == 3 && (dirty & 3) == 3;
+  if (both) {
+    const hipError_t e = launch_moved_rows_both(s, w, true, ridx2, rcnt2, st);
+    if (e != hipSuccess) return e;
+  }
   for (int h = 0; h < 2; ++h) {
     if (!(halves & (1 << h))) continue;
     const int n = h == 0 ? s.nu : s.nd;
@@ -534,10 +613,10 @@ hipError_t launch_P_build_oz(const SysDev& s, const WalkDev& w, int halves, cons
     // rows of this half that need a product (all, or those whose electron has
     // moved: the positions of the rows built are recorded either way)
     const bool dirt = (dirty >> h) & 1;
-    int* ridx = nullptr;
-    int* rcnt = nullptr;
+    int* ridx = ridx2[h];
+    int* rcnt = rcnt2[h];
     int* exc = nullptr;
-    hipError_t e = launch_moved_rows(s, w, h, dirt, &ridx, &rcnt, st);
+    hipError_t e = both ? hipSuccess : launch_moved_rows(s, w, h, dirt, &ridx, &rcnt, st);
     if (e != hipSuccess) return e;
     if (ridx) exc = w.oz_ephi_c + (h == 0 ? 0 : (long)w.Wk * s.nu);
     // rows m of this half: walker m / n, electron m % n of the spin
