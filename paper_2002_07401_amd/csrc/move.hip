@@ -93,10 +93,9 @@ accept_prep_kernel(SysDev s, WalkDev w, int e, const double* __restrict__ unif, 
 }
 
 // Sum the partial ratios (fixed order) for host-driven proposals.
-__global__ void propose_finalize_kernel(WalkDev w, int S, double* __restrict__ ratio_o,
-                                        double* __restrict__ drift_o) {
-  const int wk = blockIdx.x * blockDim.x + threadIdx.x;
-  if (wk >= w.Wk) return;
+// the proposal's ratio (and drift) from the partial sums of its rows
+__device__ void finalize_walker(const WalkDev& w, int wk, int S, double* __restrict__ ratio_o,
+                                double* __restrict__ drift_o) {
   double R = 0.0;
   for (int k = 0; k < S; ++k) R += w.rdet_part[(long)wk * S + k];
   const double ratio = R * exp(w.dJ[wk]);
@@ -111,6 +110,49 @@ __global__ void propose_finalize_kernel(WalkDev w, int S, double* __restrict__ r
       for (int c = 0; c < 3; ++c) g[c] += w.gdet_part[((long)wk * S + k) * 3 + c];
     for (int c = 0; c < 3; ++c) drift_o[3 * wk + c] = g[c] / R + w.gJ_new[3 * wk + c];
   }
+}
+
+__global__ void propose_finalize_kernel(WalkDev w, int S, double* __restrict__ ratio_o,
+                                        double* __restrict__ drift_o) {
+  const int wk = blockIdx.x * blockDim.x + threadIdx.x;
+  if (wk < w.Wk) finalize_walker(w, wk, S, ratio_o, drift_o);
+}
+
+// A proposal with a drift of a small system in one launch: set-up, every row and the
+// sums by one workgroup a walker, bitwise the three launches'.  What bounds these
+// moves is the launches: us a proposal in three launches -> one, n = 10, L = 50 at 32
+// walkers 16.1 -> 10.8 (FP32 rows), 512 walkers 15.3 -> 11.0; n = 20, L = 100 16.0 ->
+// 12.6 and 18.9 -> 14.4; n = 20, L = 200 16.4 -> 14.7 (FP32), 14.2 -> 15.5 (FP64);
+// n = 32, L = 192 15.3 -> 15.7 (FP32): up to 24 KiB of rows, past which one
+// workgroup's stream takes longer than the launches saved.
+template <typename T>
+__global__ void __launch_bounds__(256)
+propose_drift_small_kernel(SysDev s, WalkDev w, int e, const double* __restrict__ r_new, int S,
+                           double* __restrict__ ratio_o, double* __restrict__ drift_o) {
+  const int wk = blockIdx.x;
+  prep_body<true>(s, w, wk, e, r_new + 3 * (long)wk, nullptr);
+  for (int sb = 0; sb < S; ++sb) {
+    __syncthreads();
+    rows_generic_body<T, true>(s, w, wk, sb, S, e, s.prop_rows());
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) finalize_walker(w, wk, S, ratio_o, drift_o);
+}
+
+bool propose_drift_small(const SysDev& s) {
+  const long bytes = s.store() == 2 ? 2 : (s.store() == 1 ? 4 : 8);
+  return s.nu * s.Lp * bytes <= 24 * 1024;
+}
+
+hipError_t launch_propose_drift_small(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,
+                                      double* drift_new, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (s.prop_rows() < kPropRowsMin || !drift_new) return hipErrorInvalidValue;
+  const int S = propose_splits(s);
+  const dim3 grid(w.Wk), blk(256);
+  if (s.store() == 2) { QMC_LAUNCH_EV(propose_drift_small_kernel<bf16s>, grid, blk, 0, st, ev_start, ev_stop, s, w, e, r_new, S, ratio, drift_new); }
+  else if (s.store() == 1) { QMC_LAUNCH_EV(propose_drift_small_kernel<float>, grid, blk, 0, st, ev_start, ev_stop, s, w, e, r_new, S, ratio, drift_new); }
+  else { QMC_LAUNCH_EV(propose_drift_small_kernel<double>, grid, blk, 0, st, ev_start, ev_stop, s, w, e, r_new, S, ratio, drift_new); }
+  return hipGetLastError();
 }
 
 int propose_splits(const SysDev& s) {

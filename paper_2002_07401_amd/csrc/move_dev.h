@@ -437,15 +437,19 @@ __device__ void rows_generic_body(const SysDev& s, const WalkDev& w, int wk, int
       a0 += p * psi[mu];
       if (DRIFT) { ax += p * gpsi[mu]; ay += p * gpsi[s.Lp + mu]; az += p * gpsi[2 * s.Lp + mu]; }
     }
-    a0 = wave_sum(a0);
-    if (DRIFT) { ax = wave_sum(ax); ay = wave_sum(ay); az = wave_sum(az); }
-    if (lane == 0) {
-      wn_g[j] = a0;
-      const double a = cv[j];
-      part += a0 * a;
-      if (DRIFT) { gx += ax * a; gy += ay * a; gz += az * a; }
+    if (DRIFT) {   // one sum per row of 16 lanes: value, x, y, z
+      const double sum = wave_sum4(a0, ay, ax, az);
+      if (lane == 0) wn_g[j] = sum;
+      part += sum * cv[j];
+    } else {
+      a0 = wave_sum(a0);
+      if (lane == 0) {
+        wn_g[j] = a0;
+        part += a0 * cv[j];
+      }
     }
   }
+  if (DRIFT) { gx = __shfl(part, 16, 64); gy = __shfl(part, 32, 64); gz = __shfl(part, 48, 64); }
   block_partial(part, gx, gy, gz, DRIFT, w, wk, S, sb);
 }
 
