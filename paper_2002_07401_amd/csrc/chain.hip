@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       }
       dj = wave_sum(dj);
       if (lane == 0) red[4 * (t & 1) + wave] = dj;
-      if (MODE == kPropose && lane == 0) prow[wave] = cnt;
+      if (!SMALL && lane == 0) prow[wave] = cnt;   // (at the end: the last proposal's)
       __syncthreads();
       const double* ps = part + (t & 1) * a.pst;
       if (lane < n) w0 = ((ps[lane] + ps[np + lane]) + ps[2 * np + lane]) + ps[3 * np + lane];
@@ -675,7 +675,8 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
     w.sign[wk] = sg;
     w.J[wk] = Jt;
     if (SMALL) w.wm[wk] = 0;
-    if (SMALL) w.nkeep[wk] = L;   // the functions a proposal read
+    // the functions the last proposal read
+    if (MODE == kRun) w.nkeep[wk] = SMALL ? L : prow[0] + prow[1] + prow[2] + prow[3];
     if (MODE == kRun && a.cnt) a.cnt[wk] += acc_n;
   }
 }

@@ -130,3 +130,18 @@ def test_chain_with_a_wide_jastrow_basis(n):
         assert rel_err(wk.read(P.STATE_LOGABS).cpu(), out["logabs"].cpu()).max().item() <= 1e-10
         assert torch.equal(wk.read(P.STATE_SIGN).cpu(), out["sign"].cpu())
     assert t == steps and not torch.equal(wk.read(P.STATE_R).cpu(), r)
+
+
+@pytest.mark.parametrize("n", [40, 70])
+def test_kept_count_of_a_run_is_the_last_proposals(n):
+    P = need_gpu()
+    s = _system(n, n, (0, 0, 0, 1, 1), 16)
+    Wk, steps = 4, 21
+    disp, unif = (torch.tensor(x).cuda() for x in C.chain_arrays(45, steps, Wk))
+    a, _ = _setup(P, s, Wk, precision=P.QMC_REFINED)
+    b, _ = _setup(P, s, Wk, precision=P.QMC_REFINED)
+    a.vmc_steps(3, disp, unif)
+    b.vmc_steps(3, disp[:-1].contiguous(), unif[:-1].contiguous())
+    e = (3 + steps - 1) % (2 * n)
+    b.propose(e, (b.read(P.STATE_R)[:, e] + disp[-1]).contiguous())
+    assert torch.equal(a.read(P.STATE_KEPT), b.read(P.STATE_KEPT))
