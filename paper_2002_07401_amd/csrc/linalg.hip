@@ -159,7 +159,7 @@ gj_inverse_row_kernel(const double* __restrict__ Wg, double* __restrict__ Ag, do
   gj_row_body<NMAX>(Wg + b * w_bs, Ag + b * a_bs, logdet + b, detsign + b, singular + b, n, sm);
 }
 
-// Column-split variant for n <= 88 (NMAX = round_up(n, 8); NW = 2 or 4 waves): wave
+// Column-split variant for n <= 96 (NMAX = round_up(n, 8); NW = 2 or 4 waves): wave
 // w keeps columns [w H, w H + H) (H = NMAX / NW) of every row, lane l row l and, past 64 rows, row 64 + l.  Steps w H .. w H + H - 1
 // pivot on wave w's columns (its window of H columns rotates as in gj_row_body,
 // the other waves' stay in place).  Each wave takes the pivot row's values
@@ -368,8 +368,9 @@ hipError_t launch_gj_inverse_n(int Wk, int n, const double* W, double* A, double
   // n = 80 at 32 walkers 279 -> 248, 512 747 -> 696.  Past 64 rows and 512 walkers the
   // chip is full and the pivot searches of four waves cost more than they spread
   // (1024 walkers x 160 e, a sweep with six inverses 8.19 -> 8.34 ms): two waves.
-  // Up to 16 rows, and at 96 (one wave per SIMD): the row kernel.
-  if (n > 16 && n <= 88 && (n <= 64 || Wk <= 512)) {
+  // n = 96, row kernel -> four waves, 32 walkers 388 -> 315, 512 1149 -> 1059.  Up to 16
+  // rows, and at 89 to 96 past 512 walkers: the row kernel.
+  if (n > 16 && n <= 96 && (n <= 64 || Wk <= 512)) {
     switch ((n + 7) >> 3) {
 #define QMC_LU_SPLIT(C)                                                                                     \
       case C:                                                                                               \
@@ -377,7 +378,7 @@ hipError_t launch_gj_inverse_n(int Wk, int n, const double* W, double* A, double
                            singular, n, wbs, abs_);                                                         \
         break;
       QMC_LU_SPLIT(3) QMC_LU_SPLIT(4) QMC_LU_SPLIT(5) QMC_LU_SPLIT(6) QMC_LU_SPLIT(7) QMC_LU_SPLIT(8)
-      QMC_LU_SPLIT(9) QMC_LU_SPLIT(10) QMC_LU_SPLIT(11)
+      QMC_LU_SPLIT(9) QMC_LU_SPLIT(10) QMC_LU_SPLIT(11) QMC_LU_SPLIT(12)
 #undef QMC_LU_SPLIT
       default: return hipErrorNotSupported;
     }

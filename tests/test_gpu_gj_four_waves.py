@@ -1,4 +1,4 @@
-"""The inverse with its columns split between four waves (17 to 88 rows): row counts
+"""The inverse with its columns split between four waves (17 to 96 rows): row counts
 at the ends of its widths, one and two rows a lane, and the walker count at which
 two waves take over past 64 rows.  Bars as for every FP64 evaluation: |W A - I| below
 1e-9, log|Psi| 1e-10 relative; a walker's inverse does not depend on the count.
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n_up,n_dn,many", [(17, 17, 0), (24, 23, 0), (25, 25, 0), (40, 40, 0), (57, 57, 0), (64, 63, 0),
-                                            (65, 65, 513), (72, 72, 0), (88, 88, 513)])
+                                            (65, 65, 513), (72, 72, 0), (88, 88, 513), (89, 89, 0), (96, 96, 513)])
 def test_four_wave_inverse(n_up, n_dn, many):
     P = need_gpu()
     s = _system(n_up, n_dn, (0, 0, 0, 1, 1), 32)
