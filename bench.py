@@ -61,8 +61,8 @@ def parse():
 # Sources of the move kernels: a recorded counter measurement is reported only
 # while these files are unchanged.
 ROWS_SOURCES = ("paper_2002_07401_amd/csrc/move.hip", "paper_2002_07401_amd/csrc/move_dev.h",
-                "paper_2002_07401_amd/csrc/move_staged.h", "paper_2002_07401_amd/csrc/sweep.hip",
-                "paper_2002_07401_amd/csrc/internal.h")
+                "paper_2002_07401_amd/csrc/move_staged.h", "paper_2002_07401_amd/csrc/chain.hip",
+                "paper_2002_07401_amd/csrc/resident_dev.h", "paper_2002_07401_amd/csrc/internal.h")
 
 
 def rows_source_hash():
@@ -173,7 +173,7 @@ def host_cpu():
 
 def prop_roofline(models, tim):
     """Roofline fields of the proposal stream from the timed steps (None when
-    every proposal ran inside the persistent sweep)."""
+    every proposal ran inside the resident chain)."""
     ms, cnt = tim["propose"]
     if not cnt:
         return None
@@ -183,18 +183,40 @@ def prop_roofline(models, tim):
             "frac": round(ach / HBM_PEAK_GBS, 4), "avg_launch_us": round(avg * 1e3, 2)}
 
 
-def sweep_bytes(models, tim, moves):
-    """Algorithmic bytes per launch of the persistent sweep over the timed
-    steps: every proposal not launched on its own ran inside a sweep, and every
-    sweep launch ends with a proposal whose accept is a launch of its own, so a
-    sweep of k proposals holds k - 1 fused accepts (each priced as the fused
-    accept kernel: propose and accept bytes per walker from kernel_models)."""
+def sweep_bytes(s, Wk, kept, acc_rate, tim, moves):
+    """Algorithmic bytes per launch of the resident chain (a run of moves between
+    two refreshes in one launch, the walker's moving state in LDS) over the timed
+    steps: every proposal not launched on its own ran inside it.  Per walker a
+    proposal reads its kept functions' columns (8 n each), an accepted move writes
+    the W line (8 n) and the basis row (8 L), and a launch reads the inverse (8 n^2)
+    and the column maxima (8 L) and reads and writes the positions (48 N)."""
     launches = tim["sweep"][1]
-    if not launches:
+    if not launches or kept is None:
         return None
+    L, N, n = s.n_basis, s.n_up + s.n_dn, s.n_up
     props = moves - tim["propose"][1]
-    accs = props - launches
-    return (props * models["propose"][1] + accs * models["accept"][1]) / launches
+    return Wk * (props * (8 * n * kept + acc_rate * 8 * (n + L)) / launches + 8 * n * n + 8 * L + 48 * N)
+
+
+def kept_functions(P, w, wk, r, disp, tol=1e-19):
+    """Basis functions an FP64 proposal streams, averaged over the walkers r and every
+    16th electron: those whose largest contribution to a row of the new W line,
+    |psi_mu(r')| max_j |P_j[mu]|, exceeds tol / (L sum |c|), c the moved electron's
+    column of W^{-1}."""
+    from oracle import jagp as O
+    sy, n, k = O.from_workload_system(w.system), w.system.n_up, r.shape[0]
+    rc, lam = r.cpu(), torch.tensor(w.system.lam)
+    phi = O.agp_basis(sy, rc)[0]
+    cmax = ((phi[:, n:] @ lam.T).abs().amax(1), (phi[:, :n] @ lam).abs().amax(1))
+    A = wk.read(P.STATE_AINV)[:k].cpu()
+    counts = []
+    for e in range(0, rc.shape[1], 16):
+        r2 = rc.clone()
+        r2[:, e] += disp[e, :k].cpu()
+        psi = O.agp_basis(sy, r2)[0][:, e].abs()
+        c = (A[:, :, e] if e < n else A[:, e - n, :]).abs().sum(1, keepdim=True)
+        counts.append((psi * cmax[0 if e < n else 1] > tol / (psi.shape[1] * c)).sum(1).double().mean())
+    return torch.stack(counts).mean().item()
 
 
 def cpu_baseline(w, n_walk=8, n_moves=320, n_eval=32, n_moves_1t=40):
@@ -243,7 +265,7 @@ def run_precision(P, C, w, args, precision):
     prec = {"fp64": P.QMC_FP64, "mixed": P.QMC_REFINED, "mixed_fp32_rows": P.QMC_MIXED, "bf16": P.QMC_MIXED_BF16,
             "fp32": P.QMC_W_FP32}[precision]
     esz = {"fp64": 8, "mixed": 8, "bf16": 2}.get(precision, 4)
-    screened = precision == "mixed"
+    screened = precision in ("fp64", "mixed")   # rows stored in FP64
     sysh = P.JAGPSystem(s, precision=prec)
     wk = P.Walkers(sysh, Wk, adjoint=False)
     n_tot = args.warmup + args.steps
@@ -296,7 +318,9 @@ def run_precision(P, C, w, args, precision):
     # screened proposals: basis functions streamed per proposal over one sweep
     r_cur = wk.read(P.STATE_R)
     kept = None
-    if screened:
+    if precision == "fp64":
+        kept = kept_functions(P, w, wk, r_cur[:8], disp[0])
+    elif screened:
         ks = []
         for t in range(N):
             wk.vmc_steps(t, disp[0][t:t + 1].contiguous(), unif[0][t:t + 1].contiguous())
@@ -342,7 +366,7 @@ def run_precision(P, C, w, args, precision):
     p_rows = s.n_dn * f_dn if part else N
     rb_rows = s.n_up * f_up if part else s.n_up
     models = kernel_models(s, Wk, esz, acc_rate, kept, p_rows)
-    sw = sweep_bytes(models, tim, args.steps * N)
+    sw = sweep_bytes(s, Wk, kept, acc_rate, tim, args.steps * N)
     if sw is not None:
         models["sweep"] = ("hbm", sw)
     dominant = max(one, key=lambda k: one[k][0])
