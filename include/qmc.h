@@ -63,7 +63,10 @@ typedef enum {
  * basis matrices.  LU, inverse, inverse updates and ratio accumulation are
  * FP64 in every mode. */
 typedef enum {
-  QMC_FP64 = 0,    /* everything FP64                                           */
+  QMC_FP64 = 0,    /* everything FP64.  Proposals may leave out P columns of
+                      basis functions that change the determinant ratio by at
+                      most 1e-17 of itself in total (at most 1e-19 where the
+                      ratio is above 0.01)                                     */
   QMC_W_FP32 = 1,  /* Phi, P = Phi Lambda and the W products in FP32 on MFMA
                       with FP32 accumulation; FP64 LU/inverse/SM/ratios          */
   QMC_MIXED = 2,   /* moves as QMC_W_FP32 (FP32 Phi and P rows streamed by the

@@ -28,7 +28,8 @@
 //           any number of moves is one launch; every function is streamed (from
 //           LDS, where screening would cost more than it saves).
 //   large   (W of at most 128 rows): the transposed rows stay in global memory
-//           and are screened; a launch ends where the schedule refreshes or
+//           and are screened (where the kept functions give a small ratio, those
+//           that matter beside it are streamed too); a launch ends where the schedule refreshes or
 //           changes spin.  Walkers past two (n <= 90) or one per compute unit
 //           wait for the first ones to finish their run, which keeps the rows in
 //           use within the 256 MB last-level cache.  Single proposals and accepts
@@ -214,7 +215,7 @@ enum { kRun = 0, kPropose = 1, kAccept = 2 };
 
 // CON: the orbitals are contractions of Lq primitives
 template <int MODE, bool SMALL, int QL, bool CON = false>
-__global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, ChainArgs a) {
+__global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(SysDev s, WalkDev w, ChainArgs a) {
   static_assert(MODE == kRun || !SMALL, "single moves of small systems take the per-move kernels");
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wk = blockIdx.x;
@@ -501,7 +502,7 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       // (32-bit offsets: a walker's transposed rows are at most 2 MB)
       const char* src = SMALL ? (const char*)area : (const char*)(w.PT + (long)wk * Lp * s.pt_ld() + (sp == 0 ? np : 0));
       const uint32_t col = 8u * (uint32_t)(SMALL ? np : s.pt_ld());
-      constexpr int U = SMALL ? 4 : (QL > 3 ? kChainU - 2 : kChainU);
+      constexpr int U = SMALL ? 4 : (QL > 3 || MODE == kPropose ? kChainU - 2 : kChainU);
       double ax = 0.0, ay = 0.0;
       for (int k0 = fg; k0 - fg < cnt; k0 += U * fpl) {
         double2 x[U];
@@ -541,6 +542,44 @@ __global__ void __launch_bounds__(kChainT, 2) chain_kernel(SysDev s, WalkDev w, 
       if (lane + 64 < n)
         w1 = ((ps[lane + 64] + ps[np + lane + 64]) + ps[2 * np + lane + 64]) + ps[3 * np + lane + 64];
       R = wave_sum(w0 * c0 + w1 * c1);
+      if constexpr (!SMALL) {
+        if (s.screen_again(R)) {   // uniform: the wave's functions left out that matter beside R
+          const double lo = thr * s.screen_rest(R);
+          int rest = 0;
+          const int rt = chain_tid();   // (mus and cm anew: nothing more is held in registers up to here)
+#pragma unroll
+          for (int q = 0; q < QL; ++q) {
+            const int mu = kChainT * q + (((rt & 63) >> 4) * 4 + (rt >> 6)) * 16 + (rt & 15);
+            const double v = mu < L ? fabs(sv[q]) * w.cmax[((long)wk * 2 + 1 - sp) * Lp + mu] : 0.0;
+            const bool more = v > lo && v <= thr;
+            const unsigned long long b = __ballot(more);
+            if (more) {
+              const int k = rest + __popcll(b & ((1ull << lane) - 1ull));
+              lm[k] = (uint16_t)mu;
+              lv[k] = sv[q];
+            }
+            rest += __popcll(b);
+          }
+          __builtin_amdgcn_wave_barrier();
+          double bx = 0.0, by = 0.0;
+#pragma unroll 4
+          for (int k = fg; k < rest; k += fpl)
+            if (row_ok) {
+              const double2 x = *reinterpret_cast<const double2*>(src + ((uint32_t)lm[k] * col + 8u * (uint32_t)rp));
+              bx += lv[k] * x.x;
+              by += lv[k] * x.y;
+            }
+          bx = lane_group_sum(bx, lpf);
+          by = lane_group_sum(by, lpf);
+          __syncthreads();   // the kept functions' sums are read
+          if (lane < lpf && row_ok) { pt[rp] += bx; pt[rp + 1] += by; }
+          __syncthreads();
+          if (lane < n) w0 = ((ps[lane] + ps[np + lane]) + ps[2 * np + lane]) + ps[3 * np + lane];
+          if (lane + 64 < n)
+            w1 = ((ps[lane + 64] + ps[np + lane + 64]) + ps[2 * np + lane + 64]) + ps[3 * np + lane + 64];
+          R = wave_sum(w0 * c0 + w1 * c1);
+        }
+      }
       const double* rd = red + 4 * (t & 1);
       dJ = ((rd[0] + rd[1]) + rd[2]) + rd[3];
     } else {

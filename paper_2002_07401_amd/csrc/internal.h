@@ -36,13 +36,17 @@ constexpr int kOzMaxSlices = 8;   // int8 digits per FP64 row in the error-free 
 constexpr int kOzSlices = 7;      // digits used by the refined evaluation (error 7e-14 of max|x| max|y| K)
 // Screened proposals (FP64 rows): the basis functions skipped at r' change the
 // determinant ratio by at most this much in total (absolute).  QMC_REFINED
-// takes 1e-13; QMC_FP64 takes 1e-19, a thousandth of the rounding unit of a
-// ratio of order one, so that what is left out is below what FP64 sums of the
-// kept terms round away.  The line lies there because it is nearly free: the
-// kept share of the functions grows only from 28 to 33 % (160 electrons,
-// L = 600), 11 to 14 % (1024 electrons, L = 4096) and 68 to 73 % (20 electrons
-// in an 8-bohr cube, L = 44) between the two.
+// takes 1e-13.  QMC_FP64 takes 1e-19, nearly for free: the kept share of the
+// functions grows only from 28 to 33 % (160 electrons, L = 600), 11 to 14 %
+// (1024 electrons, L = 4096) and 68 to 73 % (20 electrons in an 8-bohr cube,
+// L = 44) between the two.
 constexpr double kScreenTolRefined = 1e-13, kScreenTolF64 = 1e-19;
+// QMC_FP64 skips relative to the ratio.  Where the kept functions give |R| below
+// kScreenFloor, those skipped that could change it by more than tol / floor =
+// 1e-17 of itself in total (a tenth of its rounding unit; the new line of W, whose
+// largest entry is at least |R| / |c|_1, by less of that entry) are streamed too;
+// below kScreenTiny, where R itself may be what was skipped, all of them.
+constexpr double kScreenFloor = 1e-2, kScreenTiny = 1e-16;
 
 // A launch that records ev_start / ev_stop in its own dispatch when they are
 // given (include <hip/hip_ext.h>), and is an ordinary one otherwise.
@@ -99,6 +103,10 @@ struct SysDev {
   // only the columns of P that can change the ratio, from the transposed rows
   __host__ __device__ bool screened() const { return store() == 0 && !pairing; }
   __host__ __device__ double screen_tol() const { return precision == QMC_REFINED ? kScreenTolRefined : kScreenTolF64; }
+  // the kept functions gave R: whether some of the others are to be streamed too (not
+  // for a NaN, which they would not change), those past screen_rest() of the threshold
+  __device__ bool screen_again(double R) const { return precision == QMC_FP64 && fabs(R) < kScreenFloor; }
+  static __device__ double screen_rest(double R) { return fabs(R) >= kScreenTiny ? fabs(R) / kScreenFloor : 0.0; }
   // QMC_REFINED (determinant systems): P from refined int8 products, whose
   // epilogue also writes the transposed rows
   __host__ __device__ bool oz_rows() const { return precision == QMC_REFINED && !pairing; }

@@ -93,11 +93,15 @@ accept_prep_kernel(SysDev s, WalkDev w, int e, const double* __restrict__ unif, 
 }
 
 // Sum the partial ratios (fixed order) for host-driven proposals.
-// the proposal's ratio (and drift) from the partial sums of its rows
-__device__ void finalize_walker(const WalkDev& w, int wk, int S, double* __restrict__ ratio_o,
-                                double* __restrict__ drift_o) {
+__device__ __forceinline__ double partial_ratio(const WalkDev& w, int wk, int S) {
   double R = 0.0;
   for (int k = 0; k < S; ++k) R += w.rdet_part[(long)wk * S + k];
+  return R;
+}
+
+// the proposal's ratio (and drift) from R, the sum of its rows
+__device__ void finalize_walker(const WalkDev& w, int wk, int S, double R, double* __restrict__ ratio_o,
+                                double* __restrict__ drift_o) {
   const double ratio = R * exp(w.dJ[wk]);
   w.rdet[wk] = R;
   w.ratio[wk] = ratio;
@@ -115,7 +119,15 @@ __device__ void finalize_walker(const WalkDev& w, int wk, int S, double* __restr
 __global__ void propose_finalize_kernel(WalkDev w, int S, double* __restrict__ ratio_o,
                                         double* __restrict__ drift_o) {
   const int wk = blockIdx.x * blockDim.x + threadIdx.x;
-  if (wk < w.Wk) finalize_walker(w, wk, S, ratio_o, drift_o);
+  if (wk < w.Wk) finalize_walker(w, wk, S, partial_ratio(w, wk, S), ratio_o, drift_o);
+}
+
+// ... of a screened proposal of e: a workgroup a walker, for the functions left out
+__global__ void __launch_bounds__(256)
+propose_finalize_screened_kernel(SysDev s, WalkDev w, int e, int S, double* __restrict__ ratio_o) {
+  const int wk = blockIdx.x;
+  const double R = screened_rest(s, w, wk, e, partial_ratio(w, wk, S));
+  if (threadIdx.x == 0) finalize_walker(w, wk, S, R, ratio_o, nullptr);
 }
 
 // A proposal with a drift of a small system in one launch: set-up, every row and the
@@ -136,7 +148,7 @@ propose_drift_small_kernel(SysDev s, WalkDev w, int e, const double* __restrict_
     rows_generic_body<T, true>(s, w, wk, sb, S, e, s.prop_rows());
   }
   __syncthreads();
-  if (threadIdx.x == 0) finalize_walker(w, wk, S, ratio_o, drift_o);
+  if (threadIdx.x == 0) finalize_walker(w, wk, S, partial_ratio(w, wk, S), ratio_o, drift_o);
 }
 
 bool propose_drift_small(const SysDev& s) {
@@ -218,7 +230,8 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
 // one contiguous column of the rows the move streams per kept basis function
 // (for an up move the down electrons' rows and the unpaired orbitals; the
 // skipped ones change the ratio by at most s.screen_tol(), see
-// screen_list_body).  One workgroup per 128 rows of a walker, one partial slot
+// screen_list_body; those that matter beside a small ratio are added by whoever
+// sums the partial ratios, screened_rest).  One workgroup per 128 rows of a walker, one partial slot
 // each; the accept and finalize kernels sum the slots as usual.
 // ---------------------------------------------------------------------------
 constexpr int kScreenRowsNB = 2;   // rows a lane: 128 rows a workgroup
@@ -396,8 +409,7 @@ hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, dou
   } else return hipErrorNotSupported;
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || !finalize) return err;
-  hipLaunchKernelGGL(propose_finalize_kernel, dim3((w.Wk + 255) / 256), dim3(256), 0, st, w, S, ratio,
-                     (double*)nullptr);
+  hipLaunchKernelGGL(propose_finalize_screened_kernel, dim3(w.Wk), dim3(256), 0, st, s, w, e, S, ratio);
   return hipGetLastError();
 }
 

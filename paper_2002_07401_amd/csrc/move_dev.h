@@ -210,20 +210,34 @@ __device__ void jastrow_change(const SysDev& s, const WalkDev& w, int wk, int e,
 // electron.  Functions with |psi_mu| cmax_mu |c|_1 <= tol / L (s.screen_tol())
 // are skipped, so all skipped ones together change the ratio by at most tol
 // (and each new W entry by at most tol / |c|_1).  Values that are not numbers
-// are kept.  The kept ones are listed in increasing mu with their values.  Called by every thread
+// are kept.
+
+// The threshold tol / (L |c|_1) on |psi_mu| cmax_mu, the same bits whatever the
+// number of threads (the sum is one wave's).  Called by every thread of the
+// workgroup after cvec of electron e is written.
+__device__ double screen_threshold(const SysDev& s, const WalkDev& w, int wk) {
+  __shared__ double thr_s;
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    const double* cv = w.cvec + (long)wk * s.nu;
+    double c1 = 0.0;
+#pragma unroll 8
+    for (int j = threadIdx.x; j < s.nu; j += 64) c1 += fabs(cv[j]);
+    c1 = wave_sum(c1);
+    if (threadIdx.x == 0) thr_s = (c1 > 0.0) ? s.screen_tol() / ((double)s.L * c1) : 0.0;
+  }
+  __syncthreads();
+  return thr_s;
+}
+
+// The kept functions in increasing mu with their values.  Called by every thread
 // of the workgroup after psi_new and cvec of electron e are written.
 __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int e) {
-  __shared__ double red[16];
   __shared__ int wcount[16];
   __shared__ int total;
-  __syncthreads();
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const bool up = e < s.nu;
-  const double* cv = w.cvec + (long)wk * s.nu;
-  double c1 = 0.0;
-  for (int j = tid; j < s.nu; j += blockDim.x) c1 += fabs(cv[j]);
-  c1 = block_sum_mv(c1, red);
-  const double thr = (c1 > 0.0) ? s.screen_tol() / ((double)s.L * c1) : 0.0;
+  const double thr = screen_threshold(s, w, wk);
   const double* cm = w.cmax + ((long)wk * 2 + (up ? 1 : 0)) * s.Lp;   // the rows the proposal streams
   const double* psi = w.psi_new + (long)wk * s.Lp;
   int* mk = w.muk + (long)wk * s.Lp;
@@ -257,6 +271,58 @@ __device__ void screen_list_body(const SysDev& s, const WalkDev& w, int wk, int 
     __syncthreads();
   }
   if (tid == 0) w.nkeep[wk] = total;
+}
+
+// The determinant ratio of the pending screened proposal of e, R of its kept
+// functions: where those left out matter beside it (screen_again), their columns
+// are added to the new W line and the ratio is summed anew.  Rare (a move that
+// nearly nulls the wave function), and mostly a few functions past the threshold:
+// the list in LDS is built by one wave, kRestList functions at a time, and each
+// thread adds its own rows.  Called by every thread of the workgroup.
+constexpr int kRestList = 256;
+__device__ double screened_rest(const SysDev& s, const WalkDev& w, int wk, int e, double R) {
+  if (!s.screen_again(R)) return R;   // uniform
+  __shared__ double lv[kRestList];
+  __shared__ int lm[kRestList], cnt;
+  __shared__ double red[16];
+  const int tid = threadIdx.x, n = s.nu;
+  const bool up = e < n;
+  const double hi = screen_threshold(s, w, wk), lo = hi * s.screen_rest(R);
+  const double* cm = w.cmax + ((long)wk * 2 + (up ? 1 : 0)) * s.Lp;
+  const double* psi = w.psi_new + (long)wk * s.Lp;
+  const double* PT = w.PT + (long)wk * s.Lp * s.pt_ld() + (up ? s.ptn : 0);
+  const double* cv = w.cvec + (long)wk * n;
+  double* wn = w.w_new + (long)wk * n;
+  for (int base = 0; base < s.L; base += kRestList) {
+    if (tid < 64) {
+      int c = 0;
+      for (int q = 0; q < kRestList; q += 64) {
+        const int mu = base + q + tid;
+        const double v = mu < s.L ? psi[mu] : 0.0, b = mu < s.L ? fabs(v) * cm[mu] : 0.0;
+        const bool rest = b > lo && b <= hi;
+        const unsigned long long bal = __ballot(rest);
+        if (rest) {
+          const int at = c + __popcll(bal & ((1ull << tid) - 1ull));
+          lm[at] = mu;
+          lv[at] = v;
+        }
+        c += __popcll(bal);
+      }
+      if (tid == 0) cnt = c;
+    }
+    __syncthreads();
+    const int m = cnt;
+    for (int j = tid; j < n && m > 0; j += blockDim.x) {
+      double x = 0.0;
+#pragma unroll 8
+      for (int k = 0; k < m; ++k) x += lv[k] * PT[(long)lm[k] * s.pt_ld() + j];
+      wn[j] += x;
+    }
+    __syncthreads();
+  }
+  double rp = 0.0;
+  for (int j = tid; j < n; j += blockDim.x) rp += wn[j] * cv[j];
+  return block_sum_mv(rp, red);
 }
 
 template <bool DRIFT>
@@ -506,6 +572,7 @@ __device__ void accept_body(const SysDev& s, const WalkDev& w, int wk, int e, in
   if (S > 0) {
     R = 0.0;
     for (int k = 0; k < S; ++k) R += w.rdet_part[(long)wk * S + k];
+    if constexpr (sizeof(T) == 8) R = screened_rest(s, w, wk, e, R);
     ratio = R * exp(w.dJ[wk]);
   } else {
     R = w.rdet[wk];

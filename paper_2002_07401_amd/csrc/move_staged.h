@@ -324,10 +324,7 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
 
   // screened proposals of e2 (screen_list_body)
   __syncthreads();
-  double c1 = 0.0;
-  for (int j = tid; j < n; j += blockDim.x) c1 += fabs(cvl[j]);
-  c1 = block_sum_mv(c1, red);
-  const double thr = (c1 > 0.0) ? s.screen_tol() / ((double)L * c1) : 0.0;
+  const double thr = screen_threshold(s, w, wk);
   int* mk = w.muk + (long)wk * Lp;
   double* pk = w.psk + (long)wk * Lp;
   // the kept functions in increasing mu: every slot's ballot first, one
