@@ -1824,10 +1824,13 @@ static qmc_status chains_enqueue(qmc_multi* m, int n_steps, bool expl, unsigned 
   }
   // joined whatever happened, so that the group's stream never leaves a
   // member's work behind
+  hipError_t j = hipSuccess;
   for (int q = 0; q < qmc_multi::kStreams; ++q) {
-    HIP_TRY(hipEventRecord(m->done[q], m->streams[q]), "join");
-    HIP_TRY(hipStreamWaitEvent(m->own, m->done[q], 0), "join");
+    hipError_t r = hipEventRecord(m->done[q], m->streams[q]);
+    if (r == hipSuccess) r = hipStreamWaitEvent(m->own, m->done[q], 0);
+    if (r != hipSuccess) j = r;
   }
+  if (!c) HIP_TRY(j, "join");
   return c;
 }
 
@@ -1857,11 +1860,17 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     HIP_TRY(hipMemcpyAsync(m->d_disp, m->h_disp.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
     HIP_TRY(hipMemcpyAsync(m->d_unif, m->h_unif.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
   }
+  // the caller's stream waits for what the group's has, also where enqueuing it
+  // ended in an error: the members' draws and workspaces are the caller's
+  auto join = [&]() {
+    const hipError_t r = hipEventRecord(m->ev_b, m->own);
+    return r == hipSuccess ? hipStreamWaitEvent(stream, m->ev_b, 0) : r;
+  };
   if (m->store == 0) {
     const qmc_status c = chains_enqueue(m, n_steps, expl, seed, sigma);
+    const hipError_t r = join();
     if (c) return c;
-    HIP_TRY(hipEventRecord(m->ev_b, m->own), "event");
-    HIP_TRY(hipStreamWaitEvent(stream, m->ev_b, 0), "wait");
+    HIP_TRY(r, "join");
     return QMC_OK;
   }
   std::vector<MemberState> st(m->n);
@@ -1905,7 +1914,8 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     HIP_TRY(hipGraphLaunch(m->gexec, m->own), "graph launch");
     st = st2;
   } else {
-    HIP_TRY(multi_enqueue(m, n_steps, expl, seed, sigma, st), "multi steps");
+    const hipError_t r = multi_enqueue(m, n_steps, expl, seed, sigma, st);
+    if (r != hipSuccess) { (void)join(); return hip_fail(r, "multi steps"); }
   }
   for (int k = 0; k < m->n; ++k) {
     qmc_walkers* w = m->wk[k];
@@ -1916,8 +1926,7 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     w->P_dn_valid = st[k].dn_ok;
     w->delayed = true;
   }
-  HIP_TRY(hipEventRecord(m->ev_b, m->own), "event");
-  HIP_TRY(hipStreamWaitEvent(stream, m->ev_b, 0), "wait");
+  HIP_TRY(join(), "join");
   return QMC_OK;
 }
 
