@@ -296,7 +296,8 @@ __global__ void __launch_bounds__(256) screen_colmax_kernel(SysDev s, WalkDev w,
 }
 
 // The transposed rows of half h of every walker from P (QMC_FP64), with their
-// column maxima.  One workgroup per 32 columns of a walker, 128 rows at a time
+// column maxima.  One workgroup per 32 columns of a walker (a one-dimensional
+// grid: any number of walkers), 128 rows at a time
 // through LDS: 256-byte row segments in, whole columns (8 ptn bytes,
 // contiguous) out; rows past n_up are written zero.  Bound by HBM: P half in,
 // PT half out (2 x 393 MB at 1024 walkers x 80 rows x L = 600).
@@ -306,7 +307,8 @@ __global__ void __launch_bounds__(256) pt_build_kernel(SysDev s, WalkDev w, int 
   constexpr int TC = 32, TR = 128, LD = TC + 1;
   __shared__ double tile[TR * LD];
   __shared__ double mx[16][TC];
-  const int tid = threadIdx.x, wk = blockIdx.y, c0 = blockIdx.x * TC;
+  const int cb = s.Lp / TC;
+  const int tid = threadIdx.x, wk = blockIdx.x / cb, c0 = (blockIdx.x - wk * cb) * TC;
   const int Lp = s.Lp, np = s.ptn, n = s.nu, nrow = h == 0 ? s.nu : s.nd;
   const double* P = (const double*)w.P + ((long)wk * s.N + (h == 0 ? 0 : s.nu)) * Lp + c0;
   double* out = w.PT + ((long)wk * Lp + c0) * s.pt_ld() + (h == 0 ? 0 : np);
@@ -348,7 +350,9 @@ __global__ void __launch_bounds__(256) pt_build_kernel(SysDev s, WalkDev w, int 
 
 hipError_t launch_pt_build(const SysDev& s, const WalkDev& w, int h, hipStream_t st) {
   if (!w.PT || !w.cmax || s.Lp % 32 || s.ptn % 2 || s.ptn < s.nu) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pt_build_kernel, dim3(s.Lp / 32, w.Wk), dim3(256), 0, st, s, w, h);
+  const long blocks = (long)(s.Lp / 32) * w.Wk;
+  if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(pt_build_kernel, dim3((unsigned)blocks), dim3(256), 0, st, s, w, h);
   return hipGetLastError();
 }
 
