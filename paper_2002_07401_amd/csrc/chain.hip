@@ -32,8 +32,9 @@
 //           that matter beside it are streamed too); a launch ends where the schedule refreshes or
 //           changes spin.  Walkers past two (n <= 90) or one per compute unit
 //           wait for the first ones to finish their run, which keeps the rows in
-//           use within the 256 MB last-level cache.  Single proposals and accepts
-//           of these systems are the same code with one move (bitwise).
+//           use within the 256 MB last-level cache.  Single proposals of these
+//           systems are the same code with one move, and single accepts its update a
+//           few columns a workgroup (bitwise a run's).
 // The Jastrow basis rows and their matrix are in LDS too in the small form; in the
 // large form they stay in global memory (a move reads one row of each ahead of
 // its use, an accept a block of the matrix from L2), where they kept systems out:
@@ -60,6 +61,8 @@ constexpr int kChainLogs = 32;             // accepted moves whose logarithms ar
 constexpr int kChainSmallLds = 80 * 1024;  // two workgroups per compute unit
 constexpr int kChainMaxLds = 160 * 1024;
 
+static int chain_groups(int n) { return std::min(kChainT / ((n + 1) / 2), kChainG); }
+
 struct ChainLayout {   // byte offsets in LDS
   int qv, cc, ci, cp, area, B, lv, lm, r, nuc, draw, red, part, ws, cs, lg, list, prow, chi, hv, G, jm, chin, jb, jk, M3, total;
 };
@@ -74,9 +77,8 @@ struct ChainArgs {
   const double* Ainv;       // [Wk][n][n] the inverse at the start
   const double* disp;       // [steps][Wk][3] (propose: null)
   const double* unif;       // [steps][Wk]
-  const double* r_new;      // propose: [Wk][3]
-  double* ratio_out;        // propose: [Wk]
-  const uint8_t* acc;       // accept: [Wk]
+  const double* r_new;      // propose: [Wk][3], or null and disp
+  double* ratio_out;        // propose: [Wk] or null
   int32_t* cnt;             // [Wk] or null
   int groups, pst;          // row groups of an n x n pass; doubles of one move's partial sums
   int area_bytes, cw, lsh, nuc_lds;   // P area, list entries a wave, log2 of the lanes a column takes, nuclei in LDS
@@ -84,7 +86,8 @@ struct ChainArgs {
   ChainLayout ly;
 };
 
-static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a) {
+// propose: a single proposal (which reads the one column of the inverse it needs)
+static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a, bool propose = false) {
   ChainLayout o{};
   const int n = s.nu, ld = chain_ld(n), f8 = 8;
   a.area_bytes = small ? f8 * std::max(s.ptn * s.Lp, 16 * (s.Lp + 2)) : 0;
@@ -94,13 +97,13 @@ static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a) {
   int at = 0;
   auto take = [&](int& p, int bytes) { p = at; at += (bytes + 15) / 16 * 16; };
   take(o.area, a.area_bytes);
-  take(o.B, f8 * n * ld);
+  if (!propose) take(o.B, f8 * n * ld);
   take(o.lv, f8 * 4 * a.cw);
   take(o.lm, 2 * 4 * a.cw);
   take(o.r, f8 * 3 * s.N);
   take(o.draw, f8 * 4 * kChainDraws);
   take(o.red, f8 * 16);   // partial sums of two moves, the two-body parameters
-  a.groups = std::min(kChainT / ((n + 1) / 2), kChainG);
+  a.groups = chain_groups(n);
   a.pst = std::max(4 * s.ptn, a.groups * s.ptn);
   take(o.part, f8 * std::max(2 * a.pst, 2 * kChainSmallN));   // (and two pivot columns of a refresh)
   take(o.ws, f8 * (n + 1));
@@ -211,7 +214,7 @@ __device__ void chain_rebuild(const SysDev& s, const WalkDev& w, int wk, int h, 
   }
 }
 
-enum { kRun = 0, kPropose = 1, kAccept = 2 };
+enum { kRun = 0, kPropose = 1 };
 
 // CON: the orbitals are contractions of Lq primitives
 template <int MODE, bool SMALL, int QL, bool CON = false>
@@ -221,10 +224,6 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wk = blockIdx.x;
   const int n = s.nu, ld = chain_ld(n), N = s.N, L = s.L, Lp = s.Lp, np = s.ptn, LJ = s.LJ, nn = s.n_nuc;
   const long Wk = w.Wk;
-  if (MODE == kAccept && a.acc[wk] == 0) {
-    if (tid == 0) w.acc[wk] = 0;
-    return;
-  }
   auto at = [&](int off) { return (double*)(lds + off); };
   double *area = at(a.ly.area), *B = at(a.ly.B), *r = at(a.ly.r), *nuc = at(a.ly.nuc), *draw = at(a.ly.draw),
          *red = at(a.ly.red), *part = at(a.ly.part), *ws = at(a.ly.ws), *cs = at(a.ly.cs), *lg = at(a.ly.lg);
@@ -254,13 +253,11 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   for (int q = 0; q < QL; ++q) {
     mus[q] = SMALL ? 4 * (64 * q + lane) + wave : kChainT * q + ((lane >> 4) * 4 + wave) * 16 + (lane & 15);
     const int mu = mus[q] < L ? mus[q] : 0;
-    if (MODE != kAccept) {
-      if (!CON) {
-        bf[q] = s.bfn[mu];
-        bk[q] = s.kind[mu];
-      }
-      cm[q] = SMALL ? 0.0 : w.cmax[((long)wk * 2 + 1 - spin) * Lp + mu];
+    if (!CON) {
+      bf[q] = s.bfn[mu];
+      bk[q] = s.kind[mu];
     }
+    cm[q] = SMALL ? 0.0 : w.cmax[((long)wk * 2 + 1 - spin) * Lp + mu];
   }
   double *qv = at(a.ly.qv), *cc = at(a.ly.cc);
   uint16_t* ci = (uint16_t*)(lds + a.ly.ci);
@@ -275,12 +272,12 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   double* j2p = red + 8;
   if (tid < 8) j2p[tid] = s.j2d[tid];
   // state to LDS
-  if (MODE != kPropose)
+  if (MODE == kRun)
     for (int q = tid; q < n * n; q += kChainT) {
       const int i = q / n, k = q - i * n;
       B[spin == 0 ? i * ld + k : k * ld + i] = a.Ainv[(long)wk * n * n + q];
     }
-  if (MODE != kPropose && (n & 1))   // the column that makes the pairs
+  if (MODE == kRun && (n & 1))   // the column that makes the pairs
     for (int q = tid; q < n; q += kChainT) B[q * ld + n] = 0.0;
   for (int q = tid; q < 3 * N; q += kChainT) r[q] = w.r[(long)wk * 3 * N + q];
   for (int q = tid; a.nuc_lds && q < nn; q += kChainT) {
@@ -439,12 +436,13 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
     double px, py, pz;
     if constexpr (MODE == kRun) { px = ox + dv[0]; py = oy + dv[1]; pz = oz + dv[2]; }
     else {
-      const double* p = MODE == kPropose ? a.r_new + 3 * (long)wk : w.r_new + 3 * (long)wk;
+      const double* p = (a.r_new ? a.r_new : a.disp) + 3 * (long)wk;
       px = p[0]; py = p[1]; pz = p[2];
+      if (!a.r_new) { px += ox; py += oy; pz += oz; }
     }
     // the Jastrow basis state of e, ahead of its use (LJ <= kChainT)
     double jchi = 0.0, jhv = 0.0;
-    if (MODE != kAccept && t3 < LJ) { jchi = chi[e * LJ + t3]; jhv = hv[e * LJ + t3]; }
+    if (t3 < LJ) { jchi = chi[e * LJ + t3]; jhv = hv[e * LJ + t3]; }
     // the inverse's column (lanes: rows lane and lane + 64)
     double c0 = 0.0, c1 = 0.0, w0 = 0.0, w1 = 0.0, R, dJ;
     double sv[QL];
@@ -456,7 +454,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       if (lane < n) c0 = B[lane * ld + ie];
       if (lane + 64 < n) c1 = B[(lane + 64) * ld + ie];
     }
-    if constexpr (MODE != kAccept) {
+    {
       // psi(r') of the wave's functions, the kept ones listed
       double thr = 0.0;
       if (!SMALL) {
@@ -582,20 +580,13 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       }
       const double* rd = red + 4 * (t & 1);
       dJ = ((rd[0] + rd[1]) + rd[2]) + rd[3];
-    } else {
-      if (lane < n) w0 = w.w_new[(long)wk * n + lane];
-      if (lane + 64 < n) w1 = w.w_new[(long)wk * n + lane + 64];
-      R = w.rdet[wk];
-      dJ = w.dJ[wk];
-      for (int k = tid; k < LJ; k += kChainT) chin[k] = w.chi_new[(long)wk * LJ + k];
-      __syncthreads();
     }
     const double ratio = R * exp(dJ);
     if constexpr (MODE == kPropose) {
       // the pending proposal
       if (wave == 0) {
-        if (lane < n) w.w_new[(long)wk * n + lane] = w0;
-        if (lane + 64 < n) w.w_new[(long)wk * n + lane + 64] = w1;
+        if (lane < n) { w.w_new[(long)wk * n + lane] = w0; w.cvec[(long)wk * n + lane] = c0; }
+        if (lane + 64 < n) { w.w_new[(long)wk * n + lane + 64] = w1; w.cvec[(long)wk * n + lane + 64] = c1; }
       }
 #pragma unroll
       for (int q = 0; q < QL; ++q)
@@ -611,7 +602,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       }
       return;
     }
-    const bool acc = MODE == kAccept || dv[3] < ratio * ratio;   // uniform
+    const bool acc = dv[3] < ratio * ratio;   // uniform
     if (acc) {
       // every wave writes the same w and column: its own reads need no barrier
       if (lane < n) { ws[lane] = w0; cs[lane] = c0; }
@@ -624,8 +615,8 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
 #pragma unroll 4
         for (int i = g; i < n; i += G) {
           const double2 b = *reinterpret_cast<const double2*>(B + i * ld + j);
-          u.x += ws[i] * b.x;
-          u.y += ws[i] * b.y;
+          u.x = fma(ws[i], b.x, u.x);
+          u.y = fma(ws[i], b.y, u.y);
         }
         pu[2 * (g * nh) + j] = u.x;
         pu[2 * (g * nh) + j + 1] = u.y;
@@ -636,7 +627,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       }
 #pragma unroll
       for (int q = 0; q < QL; ++q)
-        if (mus[q] < L) phi[(long)e * Lp + mus[q]] = MODE == kAccept ? w.psi_new[(long)wk * Lp + mus[q]] : sv[q];
+        if (mus[q] < L) phi[(long)e * Lp + mus[q]] = sv[q];
       // [G_u; G_d] += M3[:, s] (chi(r') - chi_e), h_e = M^{ss} chi(r'): four lanes a sum
       for (int q = tid; q < 12 * LJ; q += kChainT) {
         const int o = q >> 2, sub = q & 3;
@@ -677,17 +668,13 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
         r[3 * e] = px; r[3 * e + 1] = py; r[3 * e + 2] = pz;
         if (R < 0.0) sg = -sg;
         Jt += dJ;
-        if (MODE == kAccept) la += log(fabs(R)) + dJ;
-        else { lg[logs] = R; lg[kChainLogs + logs] = dJ; }
+        lg[logs] = R;
+        lg[kChainLogs + logs] = dJ;
       }
       acc_n += 1;
       logs += 1;
       if (MODE == kRun && logs == kChainLogs) fold_logs();
       __syncthreads();
-    }
-    if constexpr (MODE == kAccept) {
-      if (tid == 0) w.acc[wk] = 1;
-      break;
     }
     valid &= ~(1 << sp);
     since += 1;
@@ -720,6 +707,143 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   }
 }
 
+// ---------------------------------------------------------------------------
+// The accept of a single pending proposal of electron e (large form): the run's
+// update of the inverse, kAccCols of its columns (rows for a down move: B is the
+// transpose) a workgroup.  A column's sum over w and its update need that column
+// alone, beside w and column e, which the proposal left in cvec; thread (g, k) holds
+// the entries g, g + G, ... of column k in registers from the sum to the update, in
+// the run's order of sums (bitwise the run's).  The first workgroup also takes the
+// W line, the basis row, the Jastrow state and the sums.  Decided by acc (the
+// caller's) or by unif.
+// Bound by HBM: 16 n^2 bytes an accepted walker.  us for a proposal and its accept of 60 %
+// of 1024 walkers, all of the inverse staged in LDS by one workgroup (131 KB at n = 127, one
+// a compute unit) -> here: n = 127 226 -> 115 (refined 205 -> 103), n = 96 135 -> 63, n = 80
+// 67 -> 46; 16 walkers, n = 127 42 -> 34.  The delayed form of the per-move kernels, which
+// moves 3 m n numbers for m buffered moves, is still ahead of it past n = 112 at 1024
+// walkers (refined, n = 127: 97).
+// Transposed tiles (down moves) go through LDS, both ways in whole lines.
+// ---------------------------------------------------------------------------
+constexpr int kAccCols = 32, kAccLd = kAccCols + 1;
+
+template <int RP>   // entries a thread: ceil(n / G)
+__global__ void __launch_bounds__(kAccCols * kChainG) chain_accept_kernel(SysDev s, WalkDev w, int e, int G, int tiles,
+                                                                          const uint8_t* __restrict__ acc_in,
+                                                                          const double* __restrict__ unif,
+                                                                          int32_t* __restrict__ cnt) {
+  extern __shared__ __align__(16) char lds[];   // down: the tile, [n][kAccLd]
+  __shared__ double ws[kChainMaxN], cs[kChainMaxN], part[kChainG][kAccCols];
+  const int wk = blockIdx.x / tiles, tile = blockIdx.x - wk * tiles, T = blockDim.x;
+  const int tid = threadIdx.x, n = s.nu, sp = e < n ? 0 : 1, ie = sp == 0 ? e : e - n;
+  const double R = w.rdet[wk], ratio = w.ratio[wk];
+  const bool acc = unif ? unif[wk] < ratio * ratio : acc_in[wk] != 0;
+  if (tile == 0 && tid == 0) w.acc[wk] = acc ? 1 : 0;
+  if (!acc) return;   // uniform
+  double* A = w.A + (long)wk * n * n;
+  double* tl = (double*)lds;
+  const int k0 = tile * kAccCols, nc = min(kAccCols, n - k0);
+  const int g = tid / kAccCols, c = tid - g * kAccCols;
+  const bool ok = g < G && c < nc;
+  double b[RP];
+  if (sp == 0) {
+#pragma unroll
+    for (int q = 0; q < RP; ++q) {
+      const int i = g + G * q;
+      b[q] = ok && i < n ? A[(long)i * n + k0 + c] : 0.0;
+    }
+  } else {   // (nc n <= RP T entries, rows of A side by side)
+#pragma unroll
+    for (int q = 0; q < RP; ++q) b[q] = tid + T * q < nc * n ? A[(long)k0 * n + tid + T * q] : 0.0;
+  }
+  double* Wg = w.W + (long)wk * n * n;
+  for (int j = tid; j < n; j += T) {
+    const double x = w.w_new[(long)wk * n + j];
+    ws[j] = x;
+    cs[j] = w.cvec[(long)wk * n + j];
+    if (tile == 0) Wg[sp == 0 ? (long)ie * n + j : (long)j * n + ie] = x;
+  }
+  if (tile == 0) {   // (their round trips under the tile's)
+    double* phi = (double*)w.phi + ((long)wk * s.N + e) * s.Lp;
+#pragma unroll 4
+    for (int mu = tid; mu < s.L; mu += T) phi[mu] = w.psi_new[(long)wk * s.Lp + mu];
+    if (tid == 0) {
+      const double dJ = w.dJ[wk];
+      for (int k = 0; k < 3; ++k) w.r[((long)wk * s.N + e) * 3 + k] = w.r_new[3 * (long)wk + k];
+      w.logabs[wk] += log(fabs(R)) + dJ;
+      if (R < 0.0) w.sign[wk] = -w.sign[wk];
+      w.J[wk] += dJ;
+      if (cnt) cnt[wk] += 1;
+    }
+  }
+  // entry x of the tile: row i, column k (x < 2^12 and 1 / n to 24 bits: exact)
+  const float rn = 1.0f / (float)n;
+  auto at = [&](int x) {
+    const int k = (int)(((float)x + 0.5f) * rn), i = x - k * n;
+    return i * kAccLd + k;
+  };
+  if (sp == 1) {
+#pragma unroll
+    for (int q = 0; q < RP; ++q)
+      if (tid + T * q < nc * n) tl[at(tid + T * q)] = b[q];
+  }
+  __syncthreads();
+  if (sp == 1) {
+#pragma unroll
+    for (int q = 0; q < RP; ++q) {
+      const int i = g + G * q;
+      b[q] = ok && i < n ? tl[i * kAccLd + c] : 0.0;
+    }
+  }
+  double u = 0.0;
+#pragma unroll
+  for (int q = 0; q < RP; ++q)
+    if (g + G * q < n && ok) u = fma(ws[g + G * q], b[q], u);
+  if (g < G) part[g][c] = u;
+  __syncthreads();
+  if (ok) {
+    u = part[0][c];
+    for (int q = 1; q < G; ++q) u += part[q][c];
+    if (k0 + c == ie) u -= 1.0;
+    u *= 1.0 / R;
+#pragma unroll
+    for (int q = 0; q < RP; ++q) {
+      const int i = g + G * q;
+      if (i < n) {
+        const double v = fma(-cs[i], u, b[q]);
+        if (sp == 0) A[(long)i * n + k0 + c] = v;
+        else tl[i * kAccLd + c] = v;
+      }
+    }
+  }
+  if (sp == 1) {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < RP; ++q)
+      if (tid + T * q < nc * n) A[(long)k0 * n + tid + T * q] = tl[at(tid + T * q)];
+  }
+  if (tile || !s.LJ) return;
+  // the run's update of the Jastrow basis state
+  const int LJ = s.LJ;
+  const double* chin = w.chi_new + (long)wk * LJ;
+  double *ce = w.chi + ((long)wk * s.N + e) * LJ, *he = w.hv + ((long)wk * s.N + e) * LJ, *Gv = w.G3 + (long)wk * 2 * LJ;
+  for (int q = tid; q < 12 * LJ; q += T) {
+    const int o = q >> 2, sub = q & 3;
+    const bool first = o < 2 * LJ;
+    const double* row = s.M3 + (long)(first ? o : sp * LJ + o - 2 * LJ) * 2 * LJ + sp * LJ;
+    double v = 0.0;
+#pragma unroll 8
+    for (int k = sub; k < LJ; k += 4) v += row[k] * (first ? chin[k] - ce[k] : chin[k]);
+    v += dpp_f64<0xB1>(v);
+    v += dpp_f64<0x4E>(v);
+    if (sub == 0) {
+      if (first) Gv[o] += v;
+      else he[o - 2 * LJ] = v;
+    }
+  }
+  __syncthreads();   // chi_e is read
+  for (int k = tid; k < LJ; k += T) ce[k] = chin[k];
+}
+
 // The form that takes a system: FP64 rows and a walker's state within the LDS (0:
 // neither).
 int chain_class(const SysDev& s, const WalkDev& w) {
@@ -730,12 +854,26 @@ int chain_class(const SysDev& s, const WalkDev& w) {
   return chain_layout(s, false, a).total <= kChainMaxLds ? 2 : 0;
 }
 
+// A run stages the inverse in LDS and stores it again, 16 n^2 bytes a walker, for as
+// many walkers at a time as the LDS lets the chip hold: with r such rounds a run of up to
+// r moves is cheaper as single proposals and accepts, which touch the inverse of
+// accepting walkers alone and fill the chip whatever their LDS.  us a move, run / single,
+// for runs of 1, 2, 3, 4, 8: n = 80, 256 walkers (r = 1) 27/23 19/23 15/23 14/22 10/21;
+// n = 80, 1024 (2) 60/36 39/34 32/32 28/32 23/31; n = 40, 2048 (4) 57/33 38/31 31/29 29/29 24/28;
+// n = 96, 1024 (4) 120/45 86/45 72/43 61/43 50/41.  (Over a whole sweep's rows, which the
+// rounds keep in the last-level cache, long runs win: n = 96, 1024 walkers 64 / 80.)
+int chain_single(const SysDev& s, const WalkDev& w) {
+  ChainArgs a{};
+  const int at_once = 256 * (chain_layout(s, false, a).total <= kChainMaxLds / 2 ? 2 : 1);
+  return (w.Wk + at_once - 1) / at_once;
+}
+
 static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, ChainArgs& a, hipStream_t st,
                                hipEvent_t ev_start, hipEvent_t ev_stop) {
   const int cls = chain_class(s, w);
   if (cls == 0 || (mode != kRun && cls != 2) || a.steps < 1) return hipErrorInvalidValue;
   a.cap = wb_cap(s);
-  a.ly = chain_layout(s, cls == 1, a);
+  a.ly = chain_layout(s, cls == 1, a, mode == kPropose);
   const dim3 grid(w.Wk), blk(kChainT);
 #define QMC_CHAIN(M, S, Q) QMC_LAUNCH_EV((chain_kernel<M, S, Q>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
 #define QMC_CHAIN_Q(M)                                                         \
@@ -743,7 +881,7 @@ static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, Chai
   else if (s.L <= 2 * kChainT) { QMC_CHAIN(M, false, 2); }                     \
   else if (s.L <= 3 * kChainT) { QMC_CHAIN(M, false, 3); }                     \
   else { QMC_CHAIN(M, false, 4); }
-  if (s.Lq > 0 && mode != kAccept) {   // (an accept takes psi(r') from the proposal)
+  if (s.Lq > 0) {
 #define QMC_CHAIN_C(M, S, Q) QMC_LAUNCH_EV((chain_kernel<M, S, Q, true>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
     if (cls == 1) { QMC_CHAIN_C(kRun, true, 2); }
     else if (mode == kRun && s.L <= 2 * kChainT) { QMC_CHAIN_C(kRun, false, 2); }
@@ -757,8 +895,7 @@ static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, Chai
     if (s.L <= kChainT) { QMC_CHAIN(kRun, true, 1); }
     else { QMC_CHAIN(kRun, true, 2); }
   } else if (mode == kRun) { QMC_CHAIN_Q(kRun) }
-  else if (mode == kPropose) { QMC_CHAIN_Q(kPropose) }
-  else { QMC_CHAIN_Q(kAccept) }
+  else { QMC_CHAIN_Q(kPropose) }
 #undef QMC_CHAIN_Q
 #undef QMC_CHAIN
   return hipGetLastError();
@@ -774,17 +911,28 @@ hipError_t launch_chain(const SysDev& s, const WalkDev& w, int e0, int steps, co
   return chain_launch(s, w, kRun, a, st, ev_start, ev_stop);
 }
 
-hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,
-                                hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const double* r_new, const double* disp,
+                                double* ratio, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   ChainArgs a{};
-  a.e0 = e; a.steps = 1; a.Ainv = w.A; a.r_new = r_new; a.ratio_out = ratio;
+  a.e0 = e; a.steps = 1; a.Ainv = w.A; a.r_new = r_new; a.disp = disp; a.ratio_out = ratio;
   return chain_launch(s, w, kPropose, a, st, ev_start, ev_stop);
 }
 
-hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, hipStream_t st) {
-  ChainArgs a{};
-  a.e0 = e; a.steps = 1; a.store_A = 1; a.Ainv = w.A; a.acc = acc;
-  return chain_launch(s, w, kAccept, a, st, nullptr, nullptr);
+hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, const double* unif,
+                               int32_t* accept_count, hipStream_t st) {
+  if (chain_class(s, w) != 2 || s.nu > kChainMaxN || (!acc && !unif)) return hipErrorInvalidValue;
+  const int n = s.nu, G = chain_groups(n), tiles = (n + kAccCols - 1) / kAccCols;
+  const long total = (long)tiles * w.Wk;
+  if (total > 0x7fffffffL) return hipErrorInvalidValue;
+  const size_t lds = e < n ? 0 : sizeof(double) * (size_t)n * kAccLd;
+  const dim3 grid((unsigned)total), blk(kAccCols * ((G + 1) / 2 * 2));
+#define QMC_ACC(RP) hipLaunchKernelGGL(chain_accept_kernel<RP>, grid, blk, lds, st, s, w, e, G, tiles, acc, unif, accept_count)
+  const int rp = (n + G - 1) / G;
+  if (rp <= 8) QMC_ACC(8);
+  else if (rp <= 16) QMC_ACC(16);
+  else QMC_ACC(32);   // (n <= 128: G >= 4)
+#undef QMC_ACC
+  return hipGetLastError();
 }
 
 }  // namespace qmc

@@ -818,9 +818,13 @@ int chain_class(const SysDev& s, const WalkDev& w);
 hipError_t launch_chain(const SysDev& s, const WalkDev& w, int e0, int steps, const double* disp, const double* unif,
                         int32_t* accept_count, int since0, int buf_spin0, int valid0, bool all_rows, bool store_A,
                         const double* Ainv, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
-hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,
-                                hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
-hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, hipStream_t st);
+// moves up to which a run is cheaper as single proposals and accepts
+int chain_single(const SysDev& s, const WalkDev& w);
+// (r_new or, null, disp; acc or, null, unif)
+hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const double* r_new, const double* disp,
+                                double* ratio, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
+hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, const double* unif,
+                               int32_t* accept_count, hipStream_t st);
 hipError_t launch_refresh_finish(const SysDev& s, const WalkDev& w, int32_t* status, hipStream_t st);
 // max |W X - I| per walker (P = W X given) and status 3 where it exceeds tol
 hipError_t launch_refresh_residual(const double* Pm, int n, int Wk, double tol, double* res, int32_t* status,

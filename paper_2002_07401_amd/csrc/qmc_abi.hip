@@ -963,7 +963,7 @@ extern "C" qmc_status qmc_propose_move(qmc_system* sys, qmc_walkers* wk, int32_t
   if (wk->cls == 2 && !drift_new) {
     hipEvent_t ea, eb;
     HIP_TRY(wk->tm.begin_ext(QMC_T_PROPOSE, &ea, &eb), "timer begin");
-    HIP_TRY(launch_chain_propose(s, wk->d, electron, r_new, ratio, stream, ea, eb), "resident proposal");
+    HIP_TRY(launch_chain_propose(s, wk->d, electron, r_new, nullptr, ratio, stream, ea, eb), "resident proposal");
     wk->pending_e = electron;
     return QMC_OK;
   }
@@ -1107,7 +1107,7 @@ extern "C" qmc_status qmc_accept_move(qmc_system* sys, qmc_walkers* wk, int32_t 
     return pf_after_accept(wk, status, stream);
   }
   TIMED(wk, QMC_T_ACCEPT, stream,
-        wk->cls == 2 ? launch_chain_accept(sys->d, wk->d, electron, accept, stream)
+        wk->cls == 2 ? launch_chain_accept(sys->d, wk->d, electron, accept, nullptr, nullptr, stream)
                      : launch_accept(sys->d, wk->d, electron, accept, stream),
         "accept");
   return after_accept(wk, electron, status, stream);
@@ -1181,11 +1181,13 @@ static qmc_status chain_steps(qmc_walkers* wk, int32_t e_start, int32_t n_steps,
 }
 
 // The moves of a system of the large resident form: one launch per run of
-// moves between which the schedule neither refreshes nor changes spin.
+// moves between which the schedule neither refreshes nor changes spin, short runs
+// move by move.
 static qmc_status chain_runs(qmc_walkers* wk, int32_t e_start, int32_t n_steps, const double* disp, const double* unif,
                              int32_t* accept_count, hipStream_t stream) {
   const SysDev& s = wk->sys->d;
   const long Wk = wk->d.Wk;
+  const int single = chain_single(s, wk->d);
   for (int t = 0; t < n_steps;) {
     const int e = (int)((e_start + (long)t) % s.N);
     qmc_status c = before_propose(wk, e, stream);
@@ -1201,6 +1203,21 @@ static qmc_status chain_runs(qmc_walkers* wk, int32_t e_start, int32_t n_steps, 
       post = wk->since + k >= wb_cap(s);
       const int e2 = (int)((e_start + (long)t + k) % s.N);
       turn = (e2 < s.nu ? 0 : 1) != spin;
+    }
+    if (k <= single) {   // (the same moves either way, bitwise)
+      for (int j = 0; j < k; ++j) {
+        const int ej = (int)((e_start + (long)t + j) % s.N);
+        hipEvent_t ea, eb;
+        HIP_TRY(wk->tm.begin_ext(QMC_T_PROPOSE, &ea, &eb), "timer begin");
+        HIP_TRY(launch_chain_propose(s, wk->d, ej, nullptr, disp + (long)(t + j) * Wk * 3, nullptr, stream, ea, eb),
+                "resident proposal");
+        TIMED(wk, QMC_T_ACCEPT, stream,
+              launch_chain_accept(s, wk->d, ej, nullptr, unif + (long)(t + j) * Wk, accept_count, stream), "metropolis");
+        c = after_accept(wk, ej, nullptr, stream);
+        if (c) return c;
+      }
+      t += k;
+      continue;
     }
     // a refresh follows at once, now or before the other spin's first proposal
     const bool refreshed = post || (turn && t + k < n_steps);
