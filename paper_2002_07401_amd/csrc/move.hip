@@ -26,12 +26,11 @@
 
 namespace qmc {
 
-// Threads of the per-walker move kernels.  Past the basis sizes at which an accept is
-// fused with the next set-up, a walker's phases (its L functions and N + n_nuc Jastrow
-// terms, the buffer's dot products, the kept list, the columns of the kept functions)
-// are each long enough for 1024 threads, and a few dozen walkers leave most of the
-// chip to them: 64 walkers x 1024 e, L = 4096, us a launch with 256 -> 1024 threads:
-// set-up 51 -> 28, columns 61 -> 36, accept 25 -> 18.
+// Threads of the per-walker set-up and accept.  Past the basis sizes at which an accept
+// is fused with the next set-up, a walker's phases (its L functions and N + n_nuc Jastrow
+// terms, the buffer's dot products, the kept list) are each long enough for 1024 threads,
+// and a few dozen walkers leave most of the chip to them: 64 walkers x 1024 e, L = 4096, us
+// a launch with 256 -> 1024 threads: set-up 51 -> 28, accept 25 -> 18.
 static int move_threads(const SysDev& s) { return s.screened() && s.Lp > kFuseMaxLp ? 1024 : 256; }
 
 template <bool DRIFT>
@@ -231,12 +230,13 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
 // (for an up move the down electrons' rows and the unpaired orbitals; the
 // skipped ones change the ratio by at most s.screen_tol(), see
 // screen_list_body; those that matter beside a small ratio are added by whoever
-// sums the partial ratios, screened_rest).  One workgroup per 128 rows of a walker, one partial slot
-// each; the accept and finalize kernels sum the slots as usual.
+// sums the partial ratios, screened_rest).  One workgroup per 128 or 256 rows of a
+// walker, one partial slot each; the accept and finalize kernels sum the slots as usual.
 // ---------------------------------------------------------------------------
-constexpr int kScreenRowsNB = 2;   // rows a lane: 128 rows a workgroup
-__global__ void __launch_bounds__(1024) propose_screened_kernel(SysDev s, WalkDev w, int e, int S, int chunks) {
-  screened_rows_walker<kScreenRowsNB>(s, w, blockIdx.x / chunks, e, S, blockIdx.x % chunks);
+template <int NB>
+__global__ void __launch_bounds__(kScreenMaxT / NB)
+propose_screened_kernel(SysDev s, WalkDev w, int e, int S, int chunks) {
+  screened_rows_walker<NB>(s, w, blockIdx.x / chunks, e, S, blockIdx.x % chunks);
 }
 
 // Column maxima of the P halves (bit 0: up rows, bit 1: down rows):
@@ -405,11 +405,20 @@ hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, dou
                                    hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (!w.PT || !w.muk) return hipErrorInvalidValue;
   const int S = propose_splits(s);
-  const dim3 blk(move_threads(s));
   if (s.nu <= kBigMaxN) {
-    const int chunks = (s.nu + 64 * kScreenRowsNB - 1) / (64 * kScreenRowsNB);
-    QMC_LAUNCH_EV(propose_screened_kernel, dim3((unsigned)(w.Wk * chunks)), blk, 0, st, ev_start, ev_stop, s, w, e, S,
-                  chunks);
+    // 256 rows a workgroup where that still makes a workgroup for each compute unit, 512
+    // threads where 128 rows each make at most two of them.  us a proposal, 128 rows and 256
+    // threads / 512 threads / 256 rows: QMC_REFINED, 160 rows, 32 walkers 24 / 22 / -, 256
+    // 28 / 28 / 27, 1024 62 / 64 / 57; QMC_FP64, 129 rows, 1024 walkers 88 / 89 / 77, 400 rows, 32
+    // walkers 26 / 24 / -; up to 64 rows 512 threads have too little to do (20 rows, 512
+    // walkers 14.4 / 16.9).
+    const long big = (s.nu + 2 * kScreenRows - 1) / (2 * kScreenRows);
+    const int NB = s.nu > kScreenRows && w.Wk * big >= 256 ? 2 : 1;
+    const int chunks = (s.nu + NB * kScreenRows - 1) / (NB * kScreenRows);
+    const dim3 blk(NB == 1 && s.nu > 64 && (long)w.Wk * chunks <= 512 ? 512 : 256);
+    const dim3 grid((unsigned)(w.Wk * chunks));
+    if (NB == 1) QMC_LAUNCH_EV(propose_screened_kernel<1>, grid, blk, 0, st, ev_start, ev_stop, s, w, e, S, chunks);
+    else QMC_LAUNCH_EV(propose_screened_kernel<2>, grid, blk, 0, st, ev_start, ev_stop, s, w, e, S, chunks);
   } else return hipErrorNotSupported;
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || !finalize) return err;

@@ -29,71 +29,93 @@ __host__ __device__ inline StageLayout stage_layout(int n, int kb, int mc) {
   return o;
 }
 
-// The plain screened stream of one walker (any row count), one workgroup of
-// 256 threads: wave v takes kept functions v, v + 4, ..., four at a time, lane
-// l the rows l, l + 64, ...; the waves' partial rows are added in a fixed order
-// through LDS, then the ratio sum_j w'_j c_j.  The workgroup takes the rows
-// [64 NB c, 64 NB (c + 1)) and writes partial ratio c of the walker's S (chunk 0
-// also zeroes the slots past the last chunk): a walker's rows over several
-// workgroups, so that a few walkers of a large system still fill the chip.
+// The screened stream of one walker's rows [128 NB c, 128 NB (c + 1)): a wave reads
+// whole columns of kept functions, NB row pairs (16 bytes each) a lane, several functions
+// a load where the rows fill few lanes (64 / 2^lsh of them), 8 functions in flight; the
+// kept list comes to LDS first, kScreenList functions at a time, the first without
+// waiting for its length.  The lanes that hold the same rows, then the waves' partial
+// rows through LDS, are added in a fixed order, then the ratio sum_j w'_j c_j.  Partial
+// ratio c of the walker's S goes out (chunk 0 also zeroes the slots past the last
+// chunk): a walker's rows over several workgroups, so that a few walkers of a large
+// system still fill the chip.
+constexpr int kScreenRows = 128, kScreenU = 8, kScreenList = 1024, kScreenMaxT = 512;
 template <int NB>
 __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, int e, int S, int c) {
-  __shared__ double part[16][64 * NB];
+  constexpr int ROWS = kScreenRows * NB;
+  __shared__ double part[kScreenMaxT / 64 / NB][ROWS];   // (NB = 2: 256 threads)
+  __shared__ double lv[kScreenList];
+  __shared__ int lm[kScreenList];
   __shared__ double red[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
   const bool up = e < s.nu;
-  const int j0 = 64 * NB * c;
-  const int n = min(s.nu - j0, 64 * NB);   // this chunk's rows
-  const int ld = s.pt_ld();
-  const double* base = w.PT + (long)wk * s.Lp * ld + (up ? s.ptn : 0) + j0;
+  const int j0 = ROWS * c;
+  const int n = min(s.nu - j0, ROWS), np = min(s.ptn - j0, ROWS);   // this chunk's rows (np: even)
+  int lsh = 2;
+  while (lsh < 6 && (2 << lsh) < np) ++lsh;
+  const int lpf = 1 << lsh, fpl = 64 >> lsh, fg = lane >> lsh, rp = 2 * (lane & (lpf - 1));
+  const long ld = s.pt_ld();
+  const double* base = w.PT + (long)wk * s.Lp * ld + (up ? s.ptn : 0) + j0 + rp;
+  const int step = nw * fpl, Lp = s.Lp;
+  const int* mk = w.muk + (long)wk * Lp;
+  const double* pk = w.psk + (long)wk * Lp;
   const int cnt = w.nkeep[wk];
-  const int* mk = w.muk + (long)wk * s.Lp;
-  const double* pk = w.psk + (long)wk * s.Lp;
-  double acc[NB];
+  double ax[NB], ay[NB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) acc[b] = 0.0;
-  int k = wave;
-  for (; k + 3 * nw < cnt; k += 4 * nw) {   // four functions in flight per wave
-    int mu[4];
-    double v[4];
+  for (int b = 0; b < NB; ++b) ax[b] = ay[b] = 0.0;
+  for (int b0 = 0;;) {
+#pragma unroll 4
+    for (int q = tid; q < min(kScreenList, Lp - b0); q += blockDim.x) {
+      lm[q] = mk[b0 + q];
+      lv[q] = pk[b0 + q];
+    }
+    __syncthreads();
+    const int m = min(kScreenList, cnt - b0);
+    for (int kb = wave * fpl; kb < m; kb += kScreenU * step) {
+      dbl2 x[kScreenU][NB];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { mu[q] = mk[k + nw * q]; v[q] = pk[k + nw * q]; }
-    double x[4][NB];
+      for (int u = 0; u < kScreenU; ++u) {
+        const int k = kb + fg + u * step;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int j = lane + 64 * b;
-        x[q][b] = j < n ? __builtin_nontemporal_load(base + (long)mu[q] * ld + j) : 0.0;
+        for (int b = 0; b < NB; ++b) {
+          x[u][b] = dbl2{0.0, 0.0};
+          if (k < m && rp + kScreenRows * b < np)
+            x[u][b] = __builtin_nontemporal_load((const dbl2*)(base + lm[k] * ld + kScreenRows * b));
+        }
       }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+      for (int u = 0; u < kScreenU; ++u) {
+        const int k = kb + fg + u * step;
+        const double y = k < m ? lv[k] : 0.0;
 #pragma unroll
-      for (int b = 0; b < NB; ++b) acc[b] += v[q] * x[q][b];
-  }
-  for (; k < cnt; k += nw) {
-    const int mu = mk[k];
-    const double v = pk[k];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int j = lane + 64 * b;
-      if (j < n) acc[b] += v * base[(long)mu * ld + j];
+        for (int b = 0; b < NB; ++b) {
+          ax[b] += y * x[u][b].x;
+          ay[b] += y * x[u][b].y;
+        }
+      }
     }
+    b0 += kScreenList;
+    if (b0 >= cnt) break;
+    __syncthreads();   // the list is read
   }
 #pragma unroll
-  for (int b = 0; b < NB; ++b) part[wave][lane + 64 * b] = acc[b];
+  for (int b = 0; b < NB; ++b) {
+    ax[b] = lane_group_sum(ax[b], lpf);
+    ay[b] = lane_group_sum(ay[b], lpf);
+    const int j = rp + kScreenRows * b;
+    if (lane < lpf && j < np) { part[wave][j] = ax[b]; part[wave][j + 1] = ay[b]; }
+  }
   __syncthreads();
   const double* cv = w.cvec + (long)wk * s.nu + j0;
   double* wn = w.w_new + (long)wk * s.nu + j0;
-  double rp = 0.0;
+  double rsum = 0.0;
   for (int j = tid; j < n; j += blockDim.x) {
-    double x = part[0][j];
-    for (int q = 1; q < nw; ++q) x += part[q][j];
-    wn[j] = x;
-    rp += x * cv[j];
+    double y = part[0][j];
+    for (int q = 1; q < nw; ++q) y += part[q][j];
+    wn[j] = y;
+    rsum += y * cv[j];
   }
-  const double R = block_sum_mv(rp, red);
-  const int chunks = (s.nu + 64 * NB - 1) / (64 * NB);
+  const double R = block_sum_mv(rsum, red);
+  const int chunks = (s.nu + ROWS - 1) / ROWS;
   if (tid == 0) w.rdet_part[(long)wk * S + c] = R;
   if (c == 0)
     for (int q = chunks + tid; q < S; q += blockDim.x) w.rdet_part[(long)wk * S + q] = 0.0;
