@@ -268,6 +268,9 @@ struct WalkDev {
   // Lp digits each), and one exponent per row [Wk * n_up + Wk * n_dn]
   int8_t* oz_phi;
   int* oz_ephi;
+  // the per-move proposals without a drift stream the kept columns of P (else its rows):
+  // screened_columns
+  int columns;
   // screened proposals: P transposed per walker, PT[w][mu][i] = P[w][i][mu] for
   // the up electrons, PT[w][mu][ptn + j] = P[w][n_up + j][mu] for the down
   // electrons and PT[w][mu][ptn + n_dn + l] = U[mu][l] for the nk unpaired
@@ -726,6 +729,9 @@ hipError_t launch_pf_B_build_oz(const SysDev& s, const WalkDev& w, hipStream_t s
 hipError_t launch_P_build_oz(const SysDev& s, const WalkDev& w, int halves, const double* phi64, double* P64,
                              void* lo, bool lo_bf16, hipStream_t st, bool have_expo = false, double* PT = nullptr,
                              int dirty = 0);
+// Whether the per-move proposals of a system's walkers without a drift stream the kept
+// columns (cls: chain_class)
+bool screened_columns(const SysDev& s, const WalkDev& w, int cls);
 // screened proposals: column maxima of the P halves, and the streaming kernel
 hipError_t launch_screen_colmax(const SysDev& s, const WalkDev& w, int halves, hipStream_t st);
 // (QMC_FP64) the transposed rows of half h (0: up, 1: down and unpaired) from P,

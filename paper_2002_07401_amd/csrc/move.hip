@@ -203,13 +203,15 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
   } else if (chunks <= 8) {
 #define QMC_ROWS(T, NC) \
     case NC: QMC_LAUNCH_EV((propose_rows_kernel<T, NC>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); break;
-    if (store == 0) return hipErrorInvalidValue;   // FP64 proposals without a drift are screened
     if (store == 2) {
       switch (chunks) { QMC_ROWS(bf16s, 1) QMC_ROWS(bf16s, 2) QMC_ROWS(bf16s, 3) QMC_ROWS(bf16s, 4)
                         QMC_ROWS(bf16s, 5) QMC_ROWS(bf16s, 6) QMC_ROWS(bf16s, 7) QMC_ROWS(bf16s, 8) }
-    } else {
+    } else if (store == 1) {
       switch (chunks) { QMC_ROWS(float, 1) QMC_ROWS(float, 2) QMC_ROWS(float, 3) QMC_ROWS(float, 4)
                         QMC_ROWS(float, 5) QMC_ROWS(float, 6) QMC_ROWS(float, 7) QMC_ROWS(float, 8) }
+    } else {
+      switch (chunks) { QMC_ROWS(double, 1) QMC_ROWS(double, 2) QMC_ROWS(double, 3) QMC_ROWS(double, 4)
+                        QMC_ROWS(double, 5) QMC_ROWS(double, 6) QMC_ROWS(double, 7) QMC_ROWS(double, 8) }
     }
 #undef QMC_ROWS
   } else {
@@ -399,6 +401,20 @@ hipError_t launch_screen_colmax(const SysDev& s, const WalkDev& w, int halves, h
     default: hipLaunchKernelGGL(screen_colmax_kernel<8>, grid, blk, 0, st, s, w, halves); break;
   }
   return hipGetLastError();
+}
+
+// QMC_FP64 rows are streamed whole where the transposed copy and the kept list cost more
+// than they save: single moves of systems whose runs are resident in the small form (us
+// a proposal, rows / columns: 11 rows, 1024 walkers 15.3 / 18.6, 20 rows 16.9 / 17.5, 2048
+// 25.7 / 28.4), and small sets past the resident sizes up to L = 1024, where set-up and
+// accept are one launch: up to 48 MB of a spin's rows (129 rows, L = 774, 2 walkers 17.3 / 20.4,
+// 32 (25 MB) 20.4 / 27.2, 128 31.5 / 31.4; a move of a run of 160 rows, L = 800, 32 walkers (33 MB)
+// 42 / 46, of 200 rows, L = 1000, 32 (52 MB) 53.6 / 53.7).
+// QMC_REFINED rows come with their transposed copy.
+bool screened_columns(const SysDev& s, const WalkDev& w, int cls) {
+  if (!s.screened()) return false;
+  if (s.oz_rows() || cls == 2) return true;
+  return cls == 0 && (s.Lp > kFuseMaxLp || (double)w.Wk * s.nu * s.Lp * 8.0 > 48e6);
 }
 
 hipError_t launch_propose_screened(const SysDev& s, const WalkDev& w, int e, double* ratio, bool finalize,

@@ -352,13 +352,15 @@ __device__ void prep_body(const SysDev& s, const WalkDev& w, int wk, int e, cons
   inverse_line_body(s, w, wk, e);
   // (with a drift the proposal streams whole rows; QMC_REFINED still reports
   // the kept count)
-  if (s.screened() && (!DRIFT || s.oz_rows())) screen_list_body(s, w, wk, e);
+  if (w.columns && (!DRIFT || s.oz_rows())) screen_list_body(s, w, wk, e);
 }
 
 template <typename T> struct Vec16;
+template <> struct Vec16<double> { typedef double2 type; static constexpr int n = 2; };
 template <> struct Vec16<float> { typedef float4 type; static constexpr int n = 4; };
 template <> struct Vec16<bf16s> { typedef uint4 type; static constexpr int n = 8; };
 
+__device__ __forceinline__ double vget(const double2& v, int i) { return i == 0 ? v.x : v.y; }
 __device__ __forceinline__ double vget(const float4& v, int i) {
   return (double)(i == 0 ? v.x : (i == 1 ? v.y : (i == 2 ? v.z : v.w)));
 }
@@ -410,8 +412,9 @@ __device__ __forceinline__ void block_partial(double part, double gx, double gy,
 // 16-byte loads per lane (NC = ceil(Lp / (64 * 16 / sizeof(T))); chunks past Lp
 // contribute exact zeros).  The entries of the current inverse's column (up) or
 // row (down) that weight the rows are loaded once at the start, lane k holding
-// the one of the wave's k-th row.  Ordinary loads: non-temporal ones slow the
-// FP32 rows on MI355X (34 -> 50 us per launch).  (FP64 rows: the screened stream.)
+// the one of the wave's k-th row.  FP64 rows are loaded non-temporally: on
+// MI355X that streams them at 80 % of the HBM peak instead of 71 %, while it
+// slows the FP32 rows (34 -> 50 us per launch), which keep ordinary loads.
 template <typename T, int NC>
 __device__ void rows_body(const SysDev& s, const WalkDev& w, int wk, int sb, int S, int e, int R) {
   typedef typename Vec16<T>::type V;
@@ -454,8 +457,13 @@ __device__ void rows_body(const SysDev& s, const WalkDev& w, int wk, int sb, int
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
       const int i0 = c * STEP + lane * VN;
-      va[c] = (i0 < s.Lp) ? *reinterpret_cast<const V*>(pa + i0) : V{};
-      vb[c] = (two && i0 < s.Lp) ? *reinterpret_cast<const V*>(pb + i0) : V{};
+      if constexpr (sizeof(T) == 8) {
+        va[c] = (i0 < s.Lp) ? load16_nt<V>(pa + i0) : V{};
+        vb[c] = (two && i0 < s.Lp) ? load16_nt<V>(pb + i0) : V{};
+      } else {
+        va[c] = (i0 < s.Lp) ? *reinterpret_cast<const V*>(pa + i0) : V{};
+        vb[c] = (two && i0 < s.Lp) ? *reinterpret_cast<const V*>(pb + i0) : V{};
+      }
     }
     double xa = 0.0, xb = 0.0;
 #pragma unroll
@@ -572,7 +580,8 @@ __device__ void accept_body(const SysDev& s, const WalkDev& w, int wk, int e, in
   if (S > 0) {
     R = 0.0;
     for (int k = 0; k < S; ++k) R += w.rdet_part[(long)wk * S + k];
-    if constexpr (sizeof(T) == 8) R = screened_rest(s, w, wk, e, R);
+    if constexpr (sizeof(T) == 8)
+      if (w.columns) R = screened_rest(s, w, wk, e, R);
     ratio = R * exp(w.dJ[wk]);
   } else {
     R = w.rdet[wk];
@@ -698,7 +707,7 @@ __device__ void accept_prep_body(const SysDev& s, const WalkDev& w, int wk, int 
   const double dJ = block_sum_mv(jn - jo, red);
   if (tid == 0) w.dJ[wk] = dJ;
   inverse_line_body(s, w, wk, e2);
-  if (s.screened()) screen_list_body(s, w, wk, e2);
+  if (w.columns) screen_list_body(s, w, wk, e2);
 }
 
 }  // namespace qmc

@@ -744,6 +744,7 @@ extern "C" qmc_status qmc_walkers_create(qmc_system* sys, int32_t n_walkers, int
   walker_layout(sys->d, n_walkers, adjoint, cv, *wk);
   wk->aw_ready = adjoint;
   wk->cls = chain_class(sys->d, wk->d);
+  wk->d.columns = screened_columns(sys->d, wk->d, wk->cls) ? 1 : 0;
   wk->small_eval = small_eval_ok(sys->d, wk->d);
   hipError_t e = hipMemset(base, 0, need);
   if (e == hipSuccess && sys->d.oz_rows() && sys->d.nk > 0) {   // the unpaired orbitals' transposed rows
@@ -958,7 +959,7 @@ extern "C" qmc_status qmc_propose_move(qmc_system* sys, qmc_walkers* wk, int32_t
   }
   c = before_propose(wk, electron, stream);
   if (c) return c;
-  c = ensure_P(wk, electron, stream, drift_new == nullptr);
+  c = ensure_P(wk, electron, stream, drift_new == nullptr && wk->d.columns);
   if (c) return c;
   if (wk->cls == 2 && !drift_new) {
     hipEvent_t ea, eb;
@@ -979,7 +980,7 @@ extern "C" qmc_status qmc_propose_move(qmc_system* sys, qmc_walkers* wk, int32_t
   {
     hipEvent_t ea, eb;
     HIP_TRY(wk->tm.begin_ext(QMC_T_PROPOSE, &ea, &eb), "timer begin");
-    if (s.screened() && !drift_new)
+    if (wk->d.columns && !drift_new)
       HIP_TRY(launch_propose_screened(s, wk->d, electron, ratio, true, stream, ea, eb), "screened proposal");
     else
       HIP_TRY(launch_propose_rows(s, wk->d, electron, ratio, drift_new, true, stream, ea, eb), "propose rows");
@@ -1249,7 +1250,7 @@ static qmc_status run_moves(qmc_walkers* wk, int32_t e_start, int32_t n_steps, c
     if (!prepped) {
       c = before_propose(wk, e, stream);
       if (c) return c;
-      c = ensure_P(wk, e, stream);
+      c = ensure_P(wk, e, stream, wk->d.columns);
       if (c) return c;
       TIMED(wk, QMC_T_PROPOSE_PREP, stream,
             launch_propose_prep(s, wk->d, e, nullptr, disp + (long)t * Wk * 3, false, stream), "propose prep");
@@ -1257,7 +1258,7 @@ static qmc_status run_moves(qmc_walkers* wk, int32_t e_start, int32_t n_steps, c
 {
       hipEvent_t ea, eb;
       HIP_TRY(wk->tm.begin_ext(QMC_T_PROPOSE, &ea, &eb), "timer begin");
-      if (s.screened())
+      if (wk->d.columns)
         HIP_TRY(launch_propose_screened(s, wk->d, e, nullptr, false, stream, ea, eb), "screened proposal");
       else
         HIP_TRY(launch_propose_rows(s, wk->d, e, nullptr, nullptr, false, stream, ea, eb), "propose rows");
@@ -1275,7 +1276,7 @@ static qmc_status run_moves(qmc_walkers* wk, int32_t e_start, int32_t n_steps, c
       if (c) return c;
       c = before_propose(wk, e2, stream);
       if (c) return c;
-      c = ensure_P(wk, e2, stream);
+      c = ensure_P(wk, e2, stream, wk->d.columns);
       if (c) return c;
     } else {
       TIMED(wk, QMC_T_ACCEPT, stream,
