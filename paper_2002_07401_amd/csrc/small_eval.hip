@@ -226,11 +226,18 @@ __global__ void __launch_bounds__(kChainT, 2) small_eval_kernel(SysDev s, WalkDe
 //   L = 156, 12 e   64 walkers 62 -> 55, 512 87 -> 73, 1024 121 -> 131
 //   L = 256, 7 e    64 walkers 74 -> 105 (a walker's share of Lambda from L2 is all of it)
 //   L = 60 of 300 primitives, 31 e   64 walkers 86 -> 95 (basis values and row dots by one workgroup)
+//   L = 64, 32 e    512 walkers 88 -> 55, 4096 311 -> 287, 16384 1122 -> 1116
+//   L = 50, 40 e    1024 walkers 144 -> 121, 4096 395 -> 394, 16384 1381 -> 1509
+//   L = 48, 48 e    512 walkers 119 -> 89, 768 144 -> 146, 2048 281 -> 327, 16384 1825 -> 2510
+//   L = 64, 64 e    512 walkers 146 -> 121, 768 178 -> 199, 16384 2526 -> 3463
 // Past 512 walkers (two a compute unit) the batched kernels' many waves hide
-// what two workgroups cannot, unless the launches still outweigh it.
+// what two workgroups cannot, unless the launches still outweigh it: up to L = 64
+// at any number of walkers with 16 rows of W, up to 4096 walkers with 20 (one
+// workgroup's inverse and row dots grow with the rows).
 bool small_eval_ok(const SysDev& s, const WalkDev& w) {
   return s.precision == QMC_FP64 && !s.pairing && w.rpos_P && s.nu >= 1 && s.nd >= 1 && s.nu <= kChainSmallN &&
-         s.Lp % 32 == 0 && s.Lp <= 160 && s.nprim() <= 256 && (s.Lp <= 64 || w.Wk <= 512) &&
+         s.Lp % 32 == 0 && s.Lp <= 160 && s.nprim() <= 256 &&
+         (w.Wk <= 512 || (s.Lp <= 64 && (s.nu <= 16 || (s.nu <= 20 && w.Wk <= 4096)))) &&
          small_layout(s).total <= kSmallEvalLds;
 }
 

@@ -1,0 +1,27 @@
+"""Where the faster of two kernels changes with the number of walkers (recorded,
+nothing runs): each side of the lines at which both were measured."""
+import inspect
+
+import pytest
+
+from recorder import run
+from test_gpu_chain import _system
+
+HEAD = inspect.getsource(_system)
+EVAL = """
+s = _system({n}, {n}, {shells}, 64)
+s.L = len(s.zeta)
+h = P.JAGPSystem(s)
+k = P.Walkers(h, {walkers}, adjoint=False)
+out = [x[0] for x in kernels(lambda: ok(lib.qmc_eval_batch(h.h, k.h, dev(1), dev(2), dev(3), dev(4), dev(5), dev(6),
+                                                           dev(7), None)))]
+"""
+
+
+@pytest.mark.parametrize("n,shells,walkers,one", [
+    (5, (0, 0, 0, 1), 65536, True), (16, (0, 0, 0, 0), 16384, True), (20, (0, 0), 4096, True), (20, (0, 0), 4097, False),
+    (24, (0, 0), 512, True), (24, (0, 0), 513, False), (32, (0, 0), 16384, False), (16, (0, 0, 0, 1), 513, False)])
+def test_small_systems_evaluated_in_one_launch(n, shells, walkers, one):
+    out = run(HEAD + EVAL.format(n=n, shells=shells, walkers=walkers))
+    assert any(x.startswith("small_eval_kernel") for x in out) == one
+    assert one or any(x.startswith("dgemm_kernel") for x in out)
