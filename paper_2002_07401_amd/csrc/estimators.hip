@@ -332,16 +332,18 @@ __global__ void __launch_bounds__(64) sr_check_kernel(SrWork q, double tol) {
 }
 
 // The vector work of an iteration (sr_sp, sr_update, sr_dir and sr_check above) in
-// one launch of one workgroup, for up to kSrVecMaxP columns: 4 x 256 threads take
+// one launch of one workgroup, for up to kSrVecMaxP columns and 2 MB of slice sums
+// (which one compute unit reads): 4 x 256 threads take
 // the 256-column blocks four at a time and every sum is formed in those kernels'
 // order, so the results are bitwise theirs.  Four launches of some 4.5 us each
 // were two thirds of an iteration of a few hundred samples and parameters.  The
 // slice sums are read 16 loads at a time: one by one, 32 slices of 4096 columns
 // cost more than the launches saved.  200 iterations, with the unrolled loads of
 // the products: 200 x 168 5.57 -> 2.94 ms, 1000 x 1400 7.79 -> 5.08, 4096 x 4096
-// 16.7 -> 14.3, 4096 x 6000 19.65 -> 18.84.
+// 16.7 -> 14.3 (32 slices, 1 MB), 4096 x 6000 19.65 -> 18.84 (1.5 MB); with 64 slices
+// 8192 x 6144 38.6 -> 42.4 (3 MB), 8192 x 8192 47.5 -> 61.5 (4 MB).
 constexpr int kSrVecT = 1024;
-constexpr long kSrVecMaxP = 8192;
+constexpr long kSrVecMaxP = 8192, kSrVecMaxSums = 256 * 1024;
 
 // block sums (wave sums in red, blocks of four waves) added in order
 __device__ double sr_ordered_sum(const double* red, int nblk) {
@@ -736,7 +738,7 @@ hipError_t launch_sr_step(int M, long P, const double* O, const double* el, cons
   for (int it = 0; it < max_iter; ++it) {
     hipLaunchKernelGGL(sr_op_kernel, dim3(M + 1), blk, 0, st, q, O);
     hipLaunchKernelGGL(sr_colsum_kernel, g2, blk, 0, st, q, O, el, wts, 2);
-    if (P <= kSrVecMaxP) {
+    if (P <= kSrVecMaxP && q.ms * P <= kSrVecMaxSums) {
       const int per = (int)((P + kSrVecT - 1) / kSrVecT);
       if (per <= 1) hipLaunchKernelGGL(sr_vec_kernel<1>, dim3(1), dim3(kSrVecT), 0, st, q, delta, it, tol);
       else if (per <= 2) hipLaunchKernelGGL(sr_vec_kernel<2>, dim3(1), dim3(kSrVecT), 0, st, q, delta, it, tol);

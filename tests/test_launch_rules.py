@@ -25,3 +25,18 @@ def test_small_systems_evaluated_in_one_launch(n, shells, walkers, one):
     out = run(HEAD + EVAL.format(n=n, shells=shells, walkers=walkers))
     assert any(x.startswith("small_eval_kernel") for x in out) == one
     assert one or any(x.startswith("dgemm_kernel") for x in out)
+
+SR = """
+import ctypes
+n = lib.qmc_sr_workspace_size({samples}, {params})
+out = [x[0] for x in kernels(lambda: ok(lib.qmc_sr_step({samples}, {params}, dev(1), dev(2), None, ctypes.c_double(1e-3),
+    3, ctypes.c_double(0.0), dev(3), None, None, dev(4), ctypes.c_size_t(n), None)))]
+"""
+
+
+@pytest.mark.parametrize("samples,params,one", [(200, 168, True), (4096, 4096, True), (4096, 6000, True),
+                                                (8192, 6144, False), (8192, 8192, False)])
+def test_vector_work_of_a_two_pass_iteration(samples, params, one):
+    out = run(SR.format(samples=samples, params=params))
+    assert sum(x.startswith("sr_vec_kernel") for x in out) == (3 if one else 0)
+    assert sum(x.startswith("sr_sp_kernel") for x in out) == (0 if one else 3)
