@@ -371,12 +371,17 @@ hipError_t launch_pf_propose(const SysDev& s, const WalkDev& w, int e, const dou
 // What bounds an accept is latency: n dot products over rows of the inverse and its n
 // x n update, each a chain of round trips with 256 threads that wait for every load.
 // 1024 threads with a wave's rows, and a thread's elements, in flight together: 512
-// walkers x 80 e 27.3 -> 18.8 us.
-constexpr int kPfAcceptT = 1024;
-__global__ void __launch_bounds__(kPfAcceptT)
+// walkers x 80 e 27.3 -> 18.8 us.  Up to 24 rows 256 threads hold all of it, and their
+// workgroups eight times as many walkers at once: 4096 walkers, us a proposal and its
+// accept with 256 threads, loads one by one / 1024 threads: 8 rows 57 / 75, 20 rows 95 / 107; 32
+// rows 136 / 127.
+constexpr int kPfAcceptT = 1024, kPfSmallN = 24;
+template <int T, int NMAX>
+__global__ void __launch_bounds__(T)
 pf_accept_kernel(SysDev s, WalkDev w, int e, const uint8_t* __restrict__ acc_in, const double* __restrict__ unif,
                  int32_t* __restrict__ cnt) {
-  __shared__ double sp_[kPfMaxN], sq[kPfMaxN], sd[kPfMaxN];
+  constexpr int NW = T / 64;
+  __shared__ double sp_[NMAX], sq[NMAX], sd[NMAX];
   const int wk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = s.npf, N = s.N;
   const double ratio = w.ratio[wk], rd = w.rdet[wk];
@@ -391,20 +396,20 @@ pf_accept_kernel(SysDev s, WalkDev w, int e, const uint8_t* __restrict__ acc_in,
     sp_[j] = Ai[(long)j * n + e];
   }
   __syncthreads();
-  // q = G^{-1} delta: a wave's rows i = wave, wave + 16, ... all in flight
-  constexpr int RW = (kPfMaxN + 15) / 16, CW = (kPfMaxN + 63) / 64;
+  // q = G^{-1} delta: a wave's rows i = wave, wave + NW, ... all in flight
+  constexpr int RW = (NMAX + NW - 1) / NW, CW = (NMAX + 63) / 64;
   {
     double a[RW][CW];
 #pragma unroll
     for (int k = 0; k < RW; ++k)
 #pragma unroll
       for (int c = 0; c < CW; ++c) {
-        const int i = wave + 16 * k, j = lane + 64 * c;
+        const int i = wave + NW * k, j = lane + 64 * c;
         a[k][c] = i < n && j < n ? Ai[(long)i * n + j] : 0.0;
       }
 #pragma unroll
     for (int k = 0; k < RW; ++k) {
-      const int i = wave + 16 * k;
+      const int i = wave + NW * k;
       if (i >= n) break;
       double v = 0.0;
 #pragma unroll
@@ -417,13 +422,13 @@ pf_accept_kernel(SysDev s, WalkDev w, int e, const uint8_t* __restrict__ acc_in,
   __syncthreads();
   const double ir = 1.0 / rd;
   {
-    constexpr int K = (kPfMaxN * kPfMaxN + kPfAcceptT - 1) / kPfAcceptT;
+    constexpr int K = (NMAX * NMAX + T - 1) / T;
     double x[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) x[k] = tid + kPfAcceptT * k < n * n ? Ai[tid + kPfAcceptT * k] : 0.0;
+    for (int k = 0; k < K; ++k) x[k] = tid + T * k < n * n ? Ai[tid + T * k] : 0.0;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const int idx = tid + kPfAcceptT * k, i = idx / n, j = idx - i * n;
+      const int idx = tid + T * k, i = idx / n, j = idx - i * n;
       if (idx < n * n) Ai[idx] = x[k] + (sp_[i] * sq[j] - sq[i] * sp_[j]) * ir;
     }
   }
@@ -469,7 +474,11 @@ hipError_t launch_pf_accept(const SysDev& s, const WalkDev& w, int e, const uint
     const hipError_t err = gemm_f64(g, false, false, st);
     if (err != hipSuccess) return err;
   }
-  hipLaunchKernelGGL(pf_accept_kernel, dim3(w.Wk), dim3(kPfAcceptT), 0, st, s, w, e, acc, unif, accept_count);
+  if (s.npf <= kPfSmallN)
+    hipLaunchKernelGGL((pf_accept_kernel<256, kPfSmallN>), dim3(w.Wk), dim3(256), 0, st, s, w, e, acc, unif, accept_count);
+  else
+    hipLaunchKernelGGL((pf_accept_kernel<kPfAcceptT, kPfMaxN>), dim3(w.Wk), dim3(kPfAcceptT), 0, st, s, w, e, acc, unif,
+                       accept_count);
   return hipGetLastError();
 }
 

@@ -40,3 +40,21 @@ def test_vector_work_of_a_two_pass_iteration(samples, params, one):
     out = run(SR.format(samples=samples, params=params))
     assert sum(x.startswith("sr_vec_kernel") for x in out) == (3 if one else 0)
     assert sum(x.startswith("sr_sp_kernel") for x in out) == (0 if one else 3)
+
+PFAFFIAN = """
+s = _system({n}, {n}, (0, 0, 0, 1), 64)
+rng, L = np.random.default_rng(1), len(s.zeta)
+s.pairing, s.pf_uu, s.pf_dd = 1, C._skew_gaussian(rng, L, 1.0 / L), C._skew_gaussian(rng, L, 1.0 / L)
+s.unpaired_dn = np.zeros((L, 0))
+h = P.JAGPSystem(s)
+k = P.Walkers(h, 64, adjoint=False)
+ok(lib.qmc_eval_batch(h.h, k.h, dev(1), None, None, None, None, None, None, None))
+ok(lib.qmc_propose_move(h.h, k.h, 0, dev(1), dev(2), None, None))
+out = [x for x in kernels(lambda: ok(lib.qmc_accept_move(h.h, k.h, 0, dev(1), None, None)))]
+"""
+
+
+@pytest.mark.parametrize("n,threads", [(2, 256), (12, 256), (13, 1024), (40, 1024)])
+def test_threads_of_a_pfaffian_accept(n, threads):
+    out = run(HEAD + PFAFFIAN.format(n=n))
+    assert [x[2][0] for x in out if x[0].startswith("pf_accept_kernel")] == [threads]
