@@ -790,7 +790,7 @@ bool small_eval_ok(const SysDev& s, const WalkDev& w);
 hipError_t launch_small_eval(const SysDev& s, const WalkDev& w, const double* r, hipStream_t st);
 int propose_splits(const SysDev& s);
 // A drift proposal of a small system (propose_drift_small) in one launch
-bool propose_drift_small(const SysDev& s);
+bool propose_drift_small(const SysDev& s, const WalkDev& w);
 hipError_t launch_propose_drift_small(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,
                                       double* drift_new, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop);
 // Proposal in two launches: per-walker psi(r') and Jastrow change, then the

@@ -135,7 +135,9 @@ propose_finalize_screened_kernel(SysDev s, WalkDev w, int e, int S, double* __re
 // walkers 16.1 -> 10.8 (FP32 rows), 512 walkers 15.3 -> 11.0; n = 20, L = 100 16.0 ->
 // 12.6 and 18.9 -> 14.4; n = 20, L = 200 16.4 -> 14.7 (FP32), 14.2 -> 15.5 (FP64);
 // n = 32, L = 192 15.3 -> 15.7 (FP32): up to 24 KiB of rows, past which one
-// workgroup's stream takes longer than the launches saved.
+// workgroup's stream takes longer than the launches saved; past 8192 walkers, where the
+// launches are all work, up to 16 KiB (16384 walkers, FP64: 5 KiB of rows 233 -> 157, 20 KiB
+// 292 -> 301).
 template <typename T>
 __global__ void __launch_bounds__(256)
 propose_drift_small_kernel(SysDev s, WalkDev w, int e, const double* __restrict__ r_new, int S,
@@ -150,9 +152,9 @@ propose_drift_small_kernel(SysDev s, WalkDev w, int e, const double* __restrict_
   if (threadIdx.x == 0) finalize_walker(w, wk, S, partial_ratio(w, wk, S), ratio_o, drift_o);
 }
 
-bool propose_drift_small(const SysDev& s) {
+bool propose_drift_small(const SysDev& s, const WalkDev& w) {
   const long bytes = s.store() == 2 ? 2 : (s.store() == 1 ? 4 : 8);
-  return s.nu * s.Lp * bytes <= 24 * 1024;
+  return s.nu * s.Lp * bytes <= (w.Wk <= 8192 ? 24 : 16) * 1024;
 }
 
 hipError_t launch_propose_drift_small(const SysDev& s, const WalkDev& w, int e, const double* r_new, double* ratio,

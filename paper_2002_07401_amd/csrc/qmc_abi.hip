@@ -968,7 +968,7 @@ extern "C" qmc_status qmc_propose_move(qmc_system* sys, qmc_walkers* wk, int32_t
     wk->pending_e = electron;
     return QMC_OK;
   }
-  if (drift_new && propose_drift_small(s)) {
+  if (drift_new && propose_drift_small(s, wk->d)) {
     hipEvent_t ea, eb;
     HIP_TRY(wk->tm.begin_ext(QMC_T_PROPOSE, &ea, &eb), "timer begin");
     HIP_TRY(launch_propose_drift_small(s, wk->d, electron, r_new, ratio, drift_new, stream, ea, eb), "small proposal");

@@ -58,3 +58,19 @@ out = [x for x in kernels(lambda: ok(lib.qmc_accept_move(h.h, k.h, 0, dev(1), No
 def test_threads_of_a_pfaffian_accept(n, threads):
     out = run(HEAD + PFAFFIAN.format(n=n))
     assert [x[2][0] for x in out if x[0].startswith("pf_accept_kernel")] == [threads]
+
+DRIFT = """
+s = _system({n}, {n}, {shells}, 64)
+h = P.JAGPSystem(s, precision=P.{precision})
+k = P.Walkers(h, {walkers}, adjoint=False)
+ok(lib.qmc_eval_batch(h.h, k.h, dev(1), None, None, None, None, None, None, None))
+out = [x[0] for x in kernels(lambda: ok(lib.qmc_propose_move(h.h, k.h, 0, dev(1), dev(2), dev(3), None)))]
+"""
+
+
+@pytest.mark.parametrize("n,walkers,precision,launches", [
+    (10, 16384, "QMC_FP64", 1), (20, 8192, "QMC_FP64", 1), (20, 8193, "QMC_FP64", 3), (20, 16384, "QMC_MIXED", 1),
+    (25, 16, "QMC_FP64", 3)])
+def test_launches_of_a_proposal_with_a_drift(n, walkers, precision, launches):
+    out = run(HEAD + DRIFT.format(n=n, shells=(0, 0, 0, 1), walkers=walkers, precision=precision))
+    assert len(out) == launches and out[0].startswith("propose_drift_small" if launches == 1 else "propose_prep")
