@@ -757,13 +757,22 @@ def pfaffian_leg(P, C, steps=160, Wk=512):
             "kernel_launches": {k: v[1] for k, v in tim.items() if v[1]}}
 
 
-def sr_leg(P, M=4096, Pn=8192, iters=40, eps=1e-3):
+SR_SAMPLES, SR_PARAMS = 4096, 8192
+
+
+def sr_iteration_bytes(M, Pn):
+    """Bytes a conjugate-gradient iteration of the SR step streams: O once (its two
+    products share one pass at SR_SAMPLES x SR_PARAMS; the vectors of length Pn are
+    a thousandth of it)."""
+    return 8.0 * M * Pn
+
+
+def sr_leg(P, M=SR_SAMPLES, Pn=SR_PARAMS, iters=40, eps=1e-3):
     """Stochastic-reconfiguration step on the device: M samples x Pn
     parameters of synthetic logarithmic derivatives (correlated Gaussian
     columns with scales spread over two decades), `iters` conjugate-gradient
-    iterations (tol 0: all run).  Each iteration streams O twice
-    (16 M Pn bytes); the residual |S'delta - f| / |f| is checked with torch
-    products on the device."""
+    iterations (tol 0: all run).  The residual |S'delta - f| / |f| is checked
+    with torch products on the device."""
     dev = torch.device("cuda:0")
     g = torch.Generator(device=dev).manual_seed(7)
     base = torch.randn(M, Pn // 16, generator=g, device=dev, dtype=torch.float64)
@@ -787,7 +796,7 @@ def sr_leg(P, M=4096, Pn=8192, iters=40, eps=1e-3):
     Sd = (Ok @ delta) / M
     Sp = Ok.t() @ Sd - Ob * (Ob @ delta) + eps * ((Ok - Ob) ** 2).mean(0) * delta
     chk = float((Sp - f).norm() / f.norm())
-    bytes_iter = 16.0 * M * Pn
+    bytes_iter = sr_iteration_bytes(M, Pn)
     return {"samples": M, "params": Pn, "eps": eps, "iterations": iters, "precision": "fp64",
             "moments_ms": round(1e3 * t0, 3), "ms_per_iteration": round(1e3 * t_iter, 4),
             "iteration_GBps": round(bytes_iter / t_iter / 1e9, 1),
