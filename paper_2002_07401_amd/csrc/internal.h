@@ -354,9 +354,17 @@ hipError_t launch_multi_rows(const MultiArgs& a, int store, int nc, const int4* 
 hipError_t launch_multi_accept(const MultiArgs& a, int store, const int2* items, int n_items, int grid,
                                hipStream_t st);
 hipError_t launch_multi_advance(long long* steps, int n, hipStream_t st);
-// The draws of `steps` steps from step *step0 + t0 on: disp [steps][Wk][3], unif [steps][Wk]
-hipError_t launch_philox_steps(unsigned long long seed, int member, int Wk, const long long* step0, int t0, int steps,
-                               double sigma, double* disp, double* unif, hipStream_t st);
+// The draws of n members of a group for `steps` steps from step step0[k] + t0 on: disp
+// [steps][Wk][3], unif [steps][Wk]
+constexpr int kGroupMax = 32;
+struct GroupDraws {
+  int n;
+  int member[kGroupMax], Wk[kGroupMax];
+  long long step0[kGroupMax];
+  double *disp[kGroupMax], *unif[kGroupMax];
+};
+hipError_t launch_philox_group(const GroupDraws& a, unsigned long long seed, int t0, int steps, double sigma,
+                               hipStream_t st);
 hipError_t launch_philox_draws(unsigned long long seed, int member, int Wk, unsigned long long step, double sigma,
                                double* disp, double* unif, hipStream_t st);
 

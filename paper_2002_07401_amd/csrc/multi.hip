@@ -69,24 +69,32 @@ hipError_t launch_philox_draws(unsigned long long seed, int member, int Wk, unsi
   return hipGetLastError();
 }
 
-// The same draws for many steps at once (one thread per step and walker): the
-// members that run as chains of their own (FP64 rows) take them from memory.
-__global__ void __launch_bounds__(256)
-philox_steps_kernel(unsigned long long seed, int member, int Wk, const long long* __restrict__ step0, int t0, int steps,
-                    double sigma, double* __restrict__ disp, double* __restrict__ unif) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+// The same draws for many steps at once (one thread per step and walker), of some or
+// all members of a group in one launch: the members that run as chains of their own (FP64
+// rows) take them from memory.
+__global__ void __launch_bounds__(256) philox_group_kernel(GroupDraws a, unsigned long long seed, int t0, int steps, double sigma) {
+  int k = 0;
+  long b = blockIdx.x;
+  for (;; ++k) {   // (the grid is the members' blocks one after the other)
+    const long nb = ((long)steps * a.Wk[k] + 255) / 256;
+    if (b < nb) break;
+    b -= nb;
+  }
+  const long i = b * 256 + threadIdx.x;
+  const int Wk = a.Wk[k];
   if (i >= (long)steps * Wk) return;
   double d[3], u;
-  metropolis_draw(seed, member, (int)(i % Wk), (unsigned long long)(*step0 + t0 + i / Wk), sigma, d, &u);
+  metropolis_draw(seed, a.member[k], (int)(i % Wk), (unsigned long long)(a.step0[k] + t0 + i / Wk), sigma, d, &u);
+  double* disp = a.disp[k];
   disp[3 * i] = d[0]; disp[3 * i + 1] = d[1]; disp[3 * i + 2] = d[2];
-  unif[i] = u;
+  a.unif[k][i] = u;
 }
 
-hipError_t launch_philox_steps(unsigned long long seed, int member, int Wk, const long long* step0, int t0, int steps,
-                               double sigma, double* disp, double* unif, hipStream_t st) {
-  const long n = (long)steps * Wk;
-  hipLaunchKernelGGL(philox_steps_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, seed, member, Wk, step0, t0,
-                     steps, sigma, disp, unif);
+hipError_t launch_philox_group(const GroupDraws& a, unsigned long long seed, int t0, int steps, double sigma, hipStream_t st) {
+  long blocks = 0;
+  for (int k = 0; k < a.n; ++k) blocks += ((long)steps * a.Wk[k] + 255) / 256;
+  if (blocks < 1 || blocks > 0x7fffffffL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(philox_group_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a, seed, t0, steps, sigma);
   return hipGetLastError();
 }
 

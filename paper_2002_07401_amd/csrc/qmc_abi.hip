@@ -1642,7 +1642,7 @@ static hipError_t multi_build_rows(qmc_multi* m) {
 extern "C" qmc_status qmc_multi_create(int32_t n_members, qmc_system* const* systems, qmc_walkers* const* walkers,
                                        qmc_multi** out) {
   if (!systems || !walkers || !out) return fail(QMC_ERR_ARG, "null argument");
-  if (n_members < 1 || n_members > 32) return fail(QMC_ERR_ARG, "1..32 members");
+  if (n_members < 1 || n_members > kGroupMax) return fail(QMC_ERR_ARG, "1..32 members");
   *out = nullptr;
   auto* m = new qmc_multi();
   m->n = n_members;
@@ -1814,28 +1814,54 @@ static hipError_t multi_enqueue(qmc_multi* m, int n_steps, bool explicit_draws, 
 // the chip idle (256 walkers are one workgroup per compute unit, waiting on
 // their own dependent steps), and the members share no state, so their chains
 // overlap; in step with each other, phase by phase, they would wait for the
-// largest one in every launch.  Larger members are enqueued first.
+// largest one in every launch.  Larger members are enqueued first.  Short calls of a
+// few members are bound by their launches, and the thirteen event calls of a fork and
+// a join are as many again: those members follow each other on the group's stream (us
+// a step, streams / one after the other / the phases in step: 2 members of 16 and 32
+// electrons, 1 step 102 / 54 / 63, 8 steps 16 / 16 / 39; 4 members of 128, 1 step 140 /
+// 100 / 78, 4 steps 41 / 50 / 56; 16 members of 16, 1 step 197 / 262 / 108, 2 steps 120 / 178 / 97,
+// 4 steps 83 / 132 / 90, 64 steps 45 / 87 / 81).
 static qmc_status chains_enqueue(qmc_multi* m, int n_steps, bool expl, unsigned long long seed, double sigma) {
-  HIP_TRY(hipEventRecord(m->ev_b, m->own), "fork");
-  for (int q = 0; q < qmc_multi::kStreams; ++q) HIP_TRY(hipStreamWaitEvent(m->streams[q], m->ev_b, 0), "fork");
+  GroupDraws gd{};
+  auto draws = [&](int k) {   // one more member
+    const int q = gd.n++;
+    gd.member[q] = k;
+    gd.Wk[q] = m->h_wk[k].Wk;
+    gd.step0[q] = m->wk[k]->attempts;
+    gd.disp[q] = m->chains[k].disp;
+    gd.unif[q] = m->chains[k].unif;
+  };
+  // the draws of a call that fits every member's arrays come from one launch
+  bool one = !expl;
+  for (const auto& ch : m->chains) one = one && n_steps <= ch.draw_steps;
+  if (one) {
+    for (int k = 0; k < m->n; ++k) draws(k);
+    HIP_TRY(launch_philox_group(gd, seed, 0, n_steps, sigma, m->own), "draws");
+  }
+  const bool fork = n_steps > (m->n <= 2 ? 8 : (m->n <= 4 ? 1 : 0));
+  if (fork) {
+    HIP_TRY(hipEventRecord(m->ev_b, m->own), "fork");
+    for (hipStream_t st : m->streams) HIP_TRY(hipStreamWaitEvent(st, m->ev_b, 0), "fork");
+  }
   qmc_status c = QMC_OK;
   for (int k : m->order) {
     auto& ch = m->chains[k];
     qmc_walkers* w = m->wk[k];
-    const hipStream_t st = m->streams[ch.st];
-    const int N = w->sys->d.N;
+    const hipStream_t st = fork ? m->streams[ch.st] : m->own;
+    const int N = w->sys->d.N, block = one || expl ? n_steps : ch.draw_steps;
     const bool timed = w->tm.on;
     w->tm.on = false;   // (group moves are not timed)
-    if (expl) {
-      c = run_moves(w, (int)(w->attempts % N), n_steps, m->h_disp[k], m->h_unif[k], nullptr, st);
-    } else {
-      for (int t = 0; t < n_steps && !c; t += ch.draw_steps) {
-        const int steps = std::min(ch.draw_steps, n_steps - t);
-        const hipError_t e =
-            launch_philox_steps(seed, k, w->d.Wk, m->d_steps + k, t, steps, sigma, ch.disp, ch.unif, st);
-        c = e != hipSuccess ? hip_fail(e, "draws")
-                            : run_moves(w, (int)(w->attempts % N), steps, ch.disp, ch.unif, nullptr, st);
+    for (int t = 0; t < n_steps && !c; t += block) {
+      const int steps = std::min(block, n_steps - t);
+      hipError_t e = hipSuccess;
+      if (!one && !expl) {
+        gd.n = 0;
+        draws(k);
+        e = launch_philox_group(gd, seed, 0, steps, sigma, st);
       }
+      c = e != hipSuccess ? hip_fail(e, "draws")
+                          : run_moves(w, (int)(w->attempts % N), steps, expl ? m->h_disp[k] : ch.disp,
+                                      expl ? m->h_unif[k] : ch.unif, nullptr, st);
     }
     w->tm.on = timed;
     if (c) break;
@@ -1843,7 +1869,7 @@ static qmc_status chains_enqueue(qmc_multi* m, int n_steps, bool expl, unsigned 
   // joined whatever happened, so that the group's stream never leaves a
   // member's work behind
   hipError_t j = hipSuccess;
-  for (int q = 0; q < qmc_multi::kStreams; ++q) {
+  for (int q = 0; fork && q < qmc_multi::kStreams; ++q) {
     hipError_t r = hipEventRecord(m->done[q], m->streams[q]);
     if (r == hipSuccess) r = hipStreamWaitEvent(m->own, m->done[q], 0);
     if (r != hipSuccess) j = r;
@@ -1871,12 +1897,9 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
   for (int k = 0; k < m->n; ++k) m->wk[k]->yt_valid = m->wk[k]->lr_ready = false;
   HIP_TRY(hipEventRecord(m->ev_a, stream), "event");
   HIP_TRY(hipStreamWaitEvent(m->own, m->ev_a, 0), "wait");
-  HIP_TRY(multi_upload(m), "upload");
   if (expl) {
     m->h_disp.assign(disp, disp + m->n);
     m->h_unif.assign(unif, unif + m->n);
-    HIP_TRY(hipMemcpyAsync(m->d_disp, m->h_disp.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
-    HIP_TRY(hipMemcpyAsync(m->d_unif, m->h_unif.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
   }
   // the caller's stream waits for what the group's has, also where enqueuing it
   // ended in an error: the members' draws and workspaces are the caller's
@@ -1890,6 +1913,11 @@ extern "C" qmc_status qmc_multi_vmc_steps(qmc_multi* m, int32_t n_steps, const d
     if (c) return c;
     HIP_TRY(r, "join");
     return QMC_OK;
+  }
+  HIP_TRY(multi_upload(m), "upload");
+  if (expl) {
+    HIP_TRY(hipMemcpyAsync(m->d_disp, m->h_disp.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
+    HIP_TRY(hipMemcpyAsync(m->d_unif, m->h_unif.data(), sizeof(double*) * m->n, hipMemcpyHostToDevice, m->own), "ptrs");
   }
   std::vector<MemberState> st(m->n);
   for (int k = 0; k < m->n; ++k) {

@@ -8,9 +8,9 @@ from recorder import run
 
 SCRIPT = """
 CALLER = 0x77
-def group(precision, every):
+def group(precision, every, sizes=(16, 32, 64)):
     ws = []
-    for n in (16, 32, 64):
+    for n in sizes:
         w = C.multi_system(n, n_walkers=4)
         s = P.JAGPSystem(w.system, precision=precision, refresh_every=every)
         k = P.Walkers(s, 4, adjoint=False)
@@ -56,3 +56,20 @@ def test_the_callers_stream_waits_for_every_launch(precision):
     for rc, launches, _ in out[1:]:
         assert rc == -3   # QMC_ERR_HIP
     assert [n for _, n, _ in out[1:]] == [0, 1, 3, 5]
+
+
+SHORT = SCRIPT[:SCRIPT.index("out = []")] + """
+m = group(P.QMC_FP64, 8, {sizes})
+out = calls(lambda: ok(lib.qmc_multi_vmc_steps(m.h, {steps}, None, None, 7, 0.3, 0, vp(CALLER))))
+out = [out, unordered(out, hex(CALLER))]
+"""
+
+
+@pytest.mark.parametrize("sizes,steps,streams", [((16, 32), 8, 1), ((16, 32), 9, 2), ((16,) * 4, 1, 1), ((16,) * 4, 2, 4),
+                                                 ((16,) * 8, 1, 4)])
+def test_short_calls_of_a_few_members_stay_on_one_stream(sizes, steps, streams):
+    out, unordered = run(SHORT.format(sizes=sizes, steps=steps))
+    runs = [r.split() for r in out if r.startswith("launch") and "chain_kernel" in r]
+    assert unordered == [] and len({r[-1] for r in runs}) == streams
+    # one launch of draws, and nothing copied from the host
+    assert sum("philox" in r for r in out) == 1 and not any(r.startswith("copy") for r in out)
