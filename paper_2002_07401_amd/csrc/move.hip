@@ -196,12 +196,11 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
   hipError_t err;
   const int vn = store == 0 ? 2 : (store == 1 ? 4 : 8);   // elements per 16-byte load
   const int chunks = (s.Lp + 64 * vn - 1) / (64 * vn);
-#define QMC_GEN(D)                                                                                         \
-  if (store == 2) { QMC_LAUNCH_EV((propose_rows_generic_kernel<bf16s, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); } \
-  else if (store == 1) { QMC_LAUNCH_EV((propose_rows_generic_kernel<float, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); } \
-  else { QMC_LAUNCH_EV((propose_rows_generic_kernel<double, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); }
+#define QMC_GEN(T, D) QMC_LAUNCH_EV((propose_rows_generic_kernel<T, D>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S)
   if (drift) {
-    QMC_GEN(true)
+    if (store == 2) QMC_GEN(bf16s, true);
+    else if (store == 1) QMC_GEN(float, true);
+    else QMC_GEN(double, true);
   } else if (chunks <= 8) {
 #define QMC_ROWS(T, NC) \
     case NC: QMC_LAUNCH_EV((propose_rows_kernel<T, NC>), grid, dim3(256), 0, st, ev_start, ev_stop, s, w, e, S); break;
@@ -217,7 +216,9 @@ hipError_t launch_propose_rows(const SysDev& s, const WalkDev& w, int e, double*
     }
 #undef QMC_ROWS
   } else {
-    QMC_GEN(false)
+    if (store == 0) return hipErrorInvalidValue;   // FP64 rows past L = 1024: their kept columns (screened_columns)
+    if (store == 2) QMC_GEN(bf16s, false);
+    else QMC_GEN(float, false);
   }
 #undef QMC_GEN
   err = hipGetLastError();
@@ -484,7 +485,7 @@ hipError_t launch_metropolis_accept_prep(const SysDev& s, const WalkDev& w, int 
   // positions start 16-byte aligned
   const bool aligned = ((uintptr_t)w.wv | (uintptr_t)w.wd | (uintptr_t)w.wS) % 16 == 0 &&
                        ((long)w.kb * s.nu) % 2 == 0 && w.kb % 2 == 0;
-  if (s.nu <= kStageMaxN && s.N <= kStageMaxNe && s.n_nuc <= kStageMaxNuc && S > 0 && S <= kStageMaxSplits &&
+  if (s.store() != 0 && s.nu <= kStageMaxN && s.N <= kStageMaxNe && s.n_nuc <= kStageMaxNuc && S > 0 && S <= kStageMaxSplits &&
       aligned &&
       ly.total <= kStageMaxLds) {
     const int QL = (s.L + 255) / 256;
@@ -496,8 +497,7 @@ hipError_t launch_metropolis_accept_prep(const SysDev& s, const WalkDev& w, int 
   else if (QL == 3) QMC_STAGED(T, 3);                                                                      \
   else QMC_STAGED(T, 4);
     if (s.bf16()) { QMC_STAGED_QL(bf16s) }
-    else if (s.f32()) { QMC_STAGED_QL(float) }
-    else { QMC_STAGED_QL(double) }
+    else { QMC_STAGED_QL(float) }
 #undef QMC_STAGED_QL
 #undef QMC_STAGED
     return hipGetLastError();

@@ -25,7 +25,7 @@ __host__ __device__ inline StageLayout stage_layout(int n, int kb, int mc) {
   o.D = o.V + pad1k(sizeof(double) * (size_t)(mc + 1) * n);
   o.S = o.D + pad1k(sizeof(double) * (size_t)(mc + 1) * n);
   o.vec = o.S + pad1k(sizeof(double) * (size_t)(mc + 1) * kb);
-  o.total = o.vec + sizeof(double) * (3 * (size_t)n + 5 * (size_t)kb);
+  o.total = o.vec + sizeof(double) * (2 * (size_t)n + 5 * (size_t)kb);
   return o;
 }
 
@@ -122,7 +122,8 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 }
 
 // ---------------------------------------------------------------------------
-// Metropolis accept of e fused with the set-up of e2, staged through LDS.
+// Metropolis accept of e fused with the set-up of e2, staged through LDS (FP32 and BF16
+// rows; every system of FP64 rows this size has resident moves).
 // The same arithmetic in the same order as accept_prep_body (so chains are
 // bitwise those of the unstaged kernel and of the multi-system launches), but
 // every input the workgroup reads is requested at once at the start: the
@@ -139,7 +140,7 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 // most one per attempt), which the host passes.  A walker with more (not
 // reachable through the move calls) reads the buffers from global memory.
 // LDS: V, D [(mc+1) n], S^{-1} [(mc+1) kb], r [3 N] (each padded to 1 KiB,
-// the copy granule), psi(r') of e2 [Lp], three n-vectors, five kb-vectors.
+// the copy granule), psi(r') of e2 [Lp], two n-vectors, five kb-vectors.
 // ---------------------------------------------------------------------------
 // bytes (a multiple of 8) from global src to LDS dst in 1 KiB granules, 16
 // bytes per lane (global_load_lds): granule j by wave j mod the wave count.
@@ -162,7 +163,6 @@ struct StagePre {
   double4 bf[kStageQL];   // basis records of mu = tid + 256 q
   int bk[kStageQL];
   double xp[kStageQL];    // psi(r') of the pending proposal (the accepted row)
-  double xc[kStageQL];    // column maxima of the rows e2's proposal streams (screened)
   double sv[kStageQL];    // psi(r') of e2 (computed)
   double nx, ny, nz, nZ, nb;   // nucleus tid (one-body Jastrow)
   double ex, ey, ez;           // electron tid's position (two-body Jastrow)
@@ -208,7 +208,6 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
                                         double rz, double ox, double oy, double oz) {
   __shared__ double red[16];
   __shared__ double gam_s;
-  __shared__ int wcnt[QL][4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
   const int n = s.nu, kb = w.kb, N = s.N, L = s.L, Lp = s.Lp;
   const bool up = e < n;
@@ -219,8 +218,7 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
   double* Sl = (double*)(lds + ly.S);
   double* sd = (double*)(lds + ly.vec);
   double* sv0 = sd + n;
-  double* cvl = sv0 + n;
-  double* zo = cvl + n;
+  double* zo = sv0 + n;
   double* sr = zo + kb;
   double* sy = sr + kb;
   double* st = sy + kb;
@@ -324,7 +322,7 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
   if (tid < n) v0g[tid] = sv0[tid];
   const int m2 = acc ? m + 1 : m;
   if (m2 == 0) {
-    if (tid < n) { cv[tid] = sv0[tid]; cvl[tid] = sv0[tid]; }
+    if (tid < n) cv[tid] = sv0[tid];
   } else {
     double* tz = w.tz + (long)wk * 2 * kb;
     rows_dot_lds(Dr, n, m2, n, sv0, st);        // t = D^T v0
@@ -339,40 +337,8 @@ __device__ void accept_prep_staged_body(const SysDev& s, const WalkDev& w, int w
       double c = sv0[tid];
       for (int i = 0; i < m2; ++i) c -= sz[i] * Vr[(long)i * n + tid];
       cv[tid] = c;
-      cvl[tid] = c;
     }
   }
-  if (!s.screened()) return;
-
-  // screened proposals of e2 (screen_list_body)
-  __syncthreads();
-  const double thr = screen_threshold(s, w, wk);
-  int* mk = w.muk + (long)wk * Lp;
-  double* pk = w.psk + (long)wk * Lp;
-  // the kept functions in increasing mu: every slot's ballot first, one
-  // barrier, then each kept lane's place from the counts before it
-  unsigned long long bal[QL];
-#pragma unroll
-  for (int k = 0; k < QL; ++k) {
-    const int mu = 256 * k + tid;
-    const bool keep = mu < L && !(fabs(q.sv[k]) * q.xc[k] <= thr);
-    bal[k] = __ballot(keep);
-    if (lane == 0) wcnt[k][wave] = __popcll(bal[k]);
-  }
-  __syncthreads();
-  int off = 0;
-#pragma unroll
-  for (int k = 0; k < QL; ++k) {
-    int before = off;   // kept in earlier slots, then earlier waves of this slot
-    for (int k2 = 0; k2 < wave; ++k2) before += wcnt[k][k2];
-    if ((bal[k] >> lane) & 1ull) {
-      const int at = before + __popcll(bal[k] & ((1ull << lane) - 1ull));
-      mk[at] = 256 * k + tid;
-      pk[at] = q.sv[k];
-    }
-    for (int k2 = 0; k2 < nw; ++k2) off += wcnt[k][k2];
-  }
-  if (tid == 0) w.nkeep[wk] = off;
 }
 
 // One walker's fused accept and set-up (the staged kernel's work for walker
@@ -420,12 +386,10 @@ __device__ void accept_prep_staged_phase(const SysDev& s, const WalkDev& w, int 
     q.z = w.tz[(long)wk * 2 * kb + kb + (tid < kb ? tid : 0)];
   }
   const double* pn = w.psi_new + (long)wk * Lp;
-  const double* cm = s.screened() ? w.cmax + ((long)wk * 2 + (up2 ? 1 : 0)) * Lp : pn;
 #pragma unroll
   for (int k = 0; k < QL; ++k) {
     const int mu = tid + 256 * k, mc0 = mu < L ? mu : 0;
     q.xp[k] = pn[mc0];
-    q.xc[k] = cm[mc0];
   }
   // the walker's scalars, one per thread, through LDS: the S partial ratios
   // (threads 0..S-1), then dJ, log|Psi|, sign, J, u, the displacement of e2,

@@ -74,3 +74,28 @@ out = [x[0] for x in kernels(lambda: ok(lib.qmc_propose_move(h.h, k.h, 0, dev(1)
 def test_launches_of_a_proposal_with_a_drift(n, walkers, precision, launches):
     out = run(HEAD + DRIFT.format(n=n, shells=(0, 0, 0, 1), walkers=walkers, precision=precision))
     assert len(out) == launches and out[0].startswith("propose_drift_small" if launches == 1 else "propose_prep")
+
+RUNS = """
+rng = np.random.default_rng(3)
+A, n = {nuclei}, {n}
+center, l, m, zeta = C._shell_basis(rng, A, {shells}, 0.1, 10.0)
+L = len(zeta)
+s = C.System(name="wide", R=rng.uniform(0, 30.0, (A, 3)), Z=np.full(A, 2.0), center=center, l=l, m=m, zeta=zeta,
+             radial=np.zeros(L, np.int32), lam=C._sym_gaussian(rng, L, 1.0 / L), n_up=n, n_dn=n, unpaired=np.zeros((L, 0)),
+             j1_form=2, j1_b=np.ones(A), j2_form=1, j2=np.array([1.0, 1.0]), refresh_every=64)
+h = P.JAGPSystem(s, precision=P.{precision})
+k = P.Walkers(h, 2048, adjoint=False)
+ok(lib.qmc_eval_batch(h.h, k.h, dev(1), None, None, None, None, None, None, None))
+out = [x[0] for x in kernels(lambda: ok(lib.qmc_vmc_steps(h.h, k.h, 0, 40, dev(1), dev(2), None, None)))]
+"""
+
+
+@pytest.mark.parametrize("nuclei,n,shells,precision,kernel", [
+    (256, 128, (0,) * 4, "QMC_FP64", "chain_kernel"), (256, 128, (0,) * 4, "QMC_REFINED", "chain_kernel"),
+    (256, 1, (0,) * 4, "QMC_FP64", "chain_kernel"), (64, 40, (0, 0, 0, 1), "QMC_MIXED", "accept_prep_staged_kernel"),
+    (64, 129, (0, 0, 0, 1), "QMC_FP64", "accept_prep_kernel")])
+def test_fused_accepts_staged_in_lds_are_of_narrow_rows(nuclei, n, shells, precision, kernel):
+    # the largest systems that could be staged have resident moves in FP64 rows
+    out = run(RUNS.format(nuclei=nuclei, n=n, shells=shells, precision=precision))
+    names = {"chain_kernel", "accept_prep_staged_kernel", "accept_prep_kernel"}
+    assert {x for x in names if any(y.startswith(x + "I") for y in out)} == {kernel}
