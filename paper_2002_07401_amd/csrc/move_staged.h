@@ -127,11 +127,11 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 // The same arithmetic in the same order as accept_prep_body (so chains are
 // bitwise those of the unstaged kernel and of the multi-system launches), but
 // every input the workgroup reads is requested at once at the start: the
-// delayed-update buffers V and D (rows below mc), S^{-1} and the positions go
+// delayed-update buffers V and D (rows below mc) and S^{-1} go
 // global -> LDS by direct copies (no registers held), while the basis records
 // of psi(r'), the nuclei of the one-body Jastrow, the new and old W line, v0
-// and z of the pending proposal, A0's line of e2, psi(r') of the pending
-// proposal and the column maxima of the screened proposals go to registers.
+// and z of the pending proposal, A0's line of e2 and psi(r') of the pending
+// proposal go to registers.
 // psi(r') of e2 is computed while the copies are in flight.  The unstaged
 // kernel walks a chain of some fifteen dependent global round trips per
 // walker; this one, one.
@@ -139,8 +139,8 @@ __device__ void screened_rows_walker(const SysDev& s, const WalkDev& w, int wk, 
 // attempts since the last refresh (both restart together, wm grows by at
 // most one per attempt), which the host passes.  A walker with more (not
 // reachable through the move calls) reads the buffers from global memory.
-// LDS: V, D [(mc+1) n], S^{-1} [(mc+1) kb], r [3 N] (each padded to 1 KiB,
-// the copy granule), psi(r') of e2 [Lp], two n-vectors, five kb-vectors.
+// LDS: V, D [(mc+1) n], S^{-1} [(mc+1) kb] (each padded to 1 KiB, the copy
+// granule), two n-vectors, five kb-vectors.
 // ---------------------------------------------------------------------------
 // bytes (a multiple of 8) from global src to LDS dst in 1 KiB granules, 16
 // bytes per lane (global_load_lds): granule j by wave j mod the wave count.
@@ -427,7 +427,7 @@ __device__ void accept_prep_staged_phase(const SysDev& s, const WalkDev& w, int 
   const double px = sc[11] + sc[5], py = sc[12] + sc[6], pz = sc[13] + sc[7];
   const int m = ints_s[0];
   double* sv0 = (double*)(lds + ly.vec) + n;
-  double* zo = sv0 + 2 * n;
+  double* zo = sv0 + n;
   // psi(r') of e2
 #pragma unroll
   for (int k = 0; k < QL; ++k) q.sv[k] = basis_value_rec(q.bf[k], q.bk[k], px, py, pz);
