@@ -19,7 +19,7 @@
 // A wave computes psi(r') of its own basis functions, lists those it keeps and
 // streams their columns of the transposed P rows without waiting for the other
 // waves; the waves meet once for a rejected move (the sums of w and of the
-// Jastrow change) and twice more for an accepted one.  Columns are read a row
+// Jastrow change; eight waves once more) and twice more for an accepted one.  Columns are read a row
 // pair a lane, several functions a load where n is small, 12 loads in flight.
 //
 // Two forms, chosen by size (chain_class):
@@ -27,7 +27,8 @@
 //           refreshes, changes of spin and P rebuilds run in the kernel too, so
 //           any number of moves is one launch; every function is streamed (from
 //           LDS, where screening would cost more than it saves).
-//   large   (W of at most 128 rows): the transposed rows stay in global memory
+//   large   (W of at most 128 rows; 512 threads where one workgroup fills a compute
+//           unit, chain_threads): the transposed rows stay in global memory
 //           and are screened (where the kept functions give a small ratio, those
 //           that matter beside it are streamed too); a launch ends where the schedule refreshes or
 //           changes spin.  Walkers past two (n <= 90) or one per compute unit
@@ -61,7 +62,7 @@ constexpr int kChainLogs = 32;             // accepted moves whose logarithms ar
 constexpr int kChainSmallLds = 80 * 1024;  // two workgroups per compute unit
 constexpr int kChainMaxLds = 160 * 1024;
 
-static int chain_groups(int n) { return std::min(kChainT / ((n + 1) / 2), kChainG); }
+static int chain_groups(int n, int T) { return std::min(T / ((n + 1) / 2), kChainG); }
 
 struct ChainLayout {   // byte offsets in LDS
   int qv, cc, ci, cp, area, B, lv, lm, r, nuc, draw, red, part, ws, cs, lg, list, prow, chi, hv, G, jm, chin, jb, jk, M3, total;
@@ -80,36 +81,38 @@ struct ChainArgs {
   const double* r_new;      // propose: [Wk][3], or null and disp
   double* ratio_out;        // propose: [Wk] or null
   int32_t* cnt;             // [Wk] or null
-  int groups, pst;          // row groups of an n x n pass; doubles of one move's partial sums
+  int groups, pst;          // row groups of an n x n pass; from one move's partial sums to the next's
   int area_bytes, cw, lsh, nuc_lds;   // P area, list entries a wave, log2 of the lanes a column takes, nuclei in LDS
   int con_lds;              // the contraction coefficients in LDS
   ChainLayout ly;
 };
 
 // propose: a single proposal (which reads the one column of the inverse it needs)
-static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a, bool propose = false) {
+static ChainLayout chain_layout(const SysDev& s, bool small, ChainArgs& a, bool propose = false, int T = kChainT) {
   ChainLayout o{};
   const int n = s.nu, ld = chain_ld(n), f8 = 8;
   a.area_bytes = small ? f8 * std::max(s.ptn * s.Lp, 16 * (s.Lp + 2)) : 0;
-  a.cw = 64 * (small && s.Lq > 0 ? 2 : (s.L + kChainT - 1) / kChainT);   // (the kernel's QL)
+  const int W = T / 64;   // waves
+  a.cw = 64 * (small && s.Lq > 0 ? 2 : (s.L + T - 1) / T);   // (the kernel's QL)
   a.lsh = 2;
   while ((2 << a.lsh) < s.ptn) ++a.lsh;
   int at = 0;
   auto take = [&](int& p, int bytes) { p = at; at += (bytes + 15) / 16 * 16; };
   take(o.area, a.area_bytes);
   if (!propose) take(o.B, f8 * n * ld);
-  take(o.lv, f8 * 4 * a.cw);
-  take(o.lm, 2 * 4 * a.cw);
+  take(o.lv, f8 * W * a.cw);
+  take(o.lm, 2 * W * a.cw);
   take(o.r, f8 * 3 * s.N);
   take(o.draw, f8 * 4 * kChainDraws);
-  take(o.red, f8 * 16);   // partial sums of two moves, the two-body parameters
-  a.groups = chain_groups(n);
-  a.pst = std::max(4 * s.ptn, a.groups * s.ptn);
-  take(o.part, f8 * std::max(2 * a.pst, 2 * kChainSmallN));   // (and two pivot columns of a refresh)
+  take(o.red, f8 * (2 * W + 8));   // partial sums of two moves, the two-body parameters
+  a.groups = chain_groups(n, T);
+  const int sums = std::max(W, a.groups) * s.ptn;
+  a.pst = W == 4 ? sums : 0;   // (eight waves: one buffer)
+  take(o.part, f8 * std::max(sums + a.pst, 2 * kChainSmallN));   // (and two pivot columns of a refresh)
   take(o.ws, f8 * (n + 1));
   take(o.cs, f8 * (n + 1));
   take(o.lg, f8 * 2 * kChainLogs);
-  take(o.prow, 4 * (small ? kChainSmallN : 4));
+  take(o.prow, 4 * (small ? kChainSmallN : W));
   if (small) take(o.list, 4 * (kChainSmallN + 1));
   if (s.LJ > 0) {
     if (small) {   // (large form: in global memory)
@@ -216,9 +219,11 @@ __device__ void chain_rebuild(const SysDev& s, const WalkDev& w, int wk, int h, 
 
 enum { kRun = 0, kPropose = 1 };
 
-// CON: the orbitals are contractions of Lq primitives
-template <int MODE, bool SMALL, int QL, bool CON = false>
-__global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(SysDev s, WalkDev w, ChainArgs a) {
+// CON: the orbitals are contractions of Lq primitives; T: threads (512: large form only)
+template <int MODE, bool SMALL, int QL, bool CON = false, int T = kChainT>
+__global__ void __launch_bounds__(T, MODE == kRun ? 2 : 4) chain_kernel(SysDev s, WalkDev w, ChainArgs a) {
+  constexpr int NW = T / 64;
+  static_assert(!SMALL || T == kChainT, "the small form's LDS is for four waves");
   static_assert(MODE == kRun || !SMALL, "single moves of small systems take the per-move kernels");
   extern __shared__ __align__(16) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wk = blockIdx.x;
@@ -251,7 +256,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   int spin = a.e0 < n ? 0 : 1;   // (e0 < N)
 #pragma unroll
   for (int q = 0; q < QL; ++q) {
-    mus[q] = SMALL ? 4 * (64 * q + lane) + wave : kChainT * q + ((lane >> 4) * 4 + wave) * 16 + (lane & 15);
+    mus[q] = SMALL ? 4 * (64 * q + lane) + wave : T * q + ((lane >> 4) * NW + wave) * 16 + (lane & 15);
     const int mu = mus[q] < L ? mus[q] : 0;
     if (!CON) {
       bf[q] = s.bfn[mu];
@@ -263,44 +268,44 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   uint16_t* ci = (uint16_t*)(lds + a.ly.ci);
   int* cp = (int*)(lds + a.ly.cp);
   if (CON && a.con_lds) {
-    for (int q = tid; q < s.nnz_con; q += kChainT) {
+    for (int q = tid; q < s.nnz_con; q += T) {
       cc[q] = s.con_coef[q];
       ci[q] = (uint16_t)s.con_idx[q];
     }
-    for (int q = tid; q <= L; q += kChainT) cp[q] = s.con_ptr[q];
+    for (int q = tid; q <= L; q += T) cp[q] = s.con_ptr[q];
   }
-  double* j2p = red + 8;
+  double* j2p = red + 2 * NW;
   if (tid < 8) j2p[tid] = s.j2d[tid];
   // state to LDS
   if (MODE == kRun)
-    for (int q = tid; q < n * n; q += kChainT) {
+    for (int q = tid; q < n * n; q += T) {
       const int i = q / n, k = q - i * n;
       B[spin == 0 ? i * ld + k : k * ld + i] = a.Ainv[(long)wk * n * n + q];
     }
   if (MODE == kRun && (n & 1))   // the column that makes the pairs
-    for (int q = tid; q < n; q += kChainT) B[q * ld + n] = 0.0;
-  for (int q = tid; q < 3 * N; q += kChainT) r[q] = w.r[(long)wk * 3 * N + q];
-  for (int q = tid; a.nuc_lds && q < nn; q += kChainT) {
+    for (int q = tid; q < n; q += T) B[q * ld + n] = 0.0;
+  for (int q = tid; q < 3 * N; q += T) r[q] = w.r[(long)wk * 3 * N + q];
+  for (int q = tid; a.nuc_lds && q < nn; q += T) {
     nuc[5 * q] = s.R[3 * q]; nuc[5 * q + 1] = s.R[3 * q + 1]; nuc[5 * q + 2] = s.R[3 * q + 2];
     nuc[5 * q + 3] = s.Z[q];
     nuc[5 * q + 4] = s.j1_b[q];
   }
   if constexpr (SMALL)
-    for (int q = tid; q < N * LJ; q += kChainT) {
+    for (int q = tid; q < N * LJ; q += T) {
       chi[q] = w.chi[(long)wk * N * LJ + q];
       hv[q] = w.hv[(long)wk * N * LJ + q];
     }
-  for (int q = tid; q < 2 * LJ; q += kChainT) {
+  for (int q = tid; q < 2 * LJ; q += T) {
     Gv[q] = w.G3[(long)wk * 2 * LJ + q];
     jm[q] = s.jm[q];
   }
-  for (int q = tid; q < LJ; q += kChainT) {
+  for (int q = tid; q < LJ; q += T) {
     const double4 f = s.jbfn[q];
     jb[4 * q] = f.x; jb[4 * q + 1] = f.y; jb[4 * q + 2] = f.z; jb[4 * q + 3] = f.w;
     jk[q] = s.jkind[q];
   }
   if constexpr (SMALL)
-    for (int q = tid; q < 4 * LJ * LJ; q += kChainT) at(a.ly.M3)[q / (2 * LJ) * ldM + q % (2 * LJ)] = s.M3[q];
+    for (int q = tid; q < 4 * LJ * LJ; q += T) at(a.ly.M3)[q / (2 * LJ) * ldM + q % (2 * LJ)] = s.M3[q];
   double la = w.logabs[wk], sg = w.sign[wk], Jt = w.J[wk];   // kept by thread 0
   int acc_n = 0, logs = 0;   // accepted moves; those whose ratio and Jastrow change wait in lg
   // log|Psi| of the waiting moves: their logarithms side by side in wave 0, the
@@ -322,14 +327,14 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   // Jastrow basis start a wave apart, after the basis functions of the last pass
   const int nj = nn + N;
   const int off1 = (L + 63) / 64 * 64, off2 = off1 + (nj + 63) / 64 * 64, off3 = off2 + (nj + 63) / 64 * 64;
-  const int t1 = (tid - off1) & (kChainT - 1), t2 = (tid - off2) & (kChainT - 1), t3 = (tid - off3) & (kChainT - 1);
+  const int t1 = (tid - off1) & (T - 1), t2 = (tid - off2) & (T - 1), t3 = (tid - off3) & (T - 1);
   const int lpf = 1 << a.lsh, fpl = 64 >> a.lsh;   // lanes a column takes, columns a load
   const int fg = lane >> a.lsh, rp = 2 * (lane & (lpf - 1));
   const bool row_ok = rp < np;
 
   auto jsum = [&](int t, int e, double px, double py, double pz) {
     double v = 0.0;
-    for (int i = t; i < nj; i += kChainT) {
+    for (int i = t; i < nj; i += T) {
       const bool isn = i < nn;
       const int je = i - nn;
       double x, y, z, Z = 0.0, b = 0.0;
@@ -359,7 +364,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       // the per-move path's schedule
       if (due || (since > 0 && sp != buf)) {
         __syncthreads();
-        for (int q = chain_tid(); q < n * n; q += kChainT) {
+        for (int q = chain_tid(); q < n * n; q += T) {
           const int i = q / n, k = q - i * n;
           B[i * ld + k] = Wg[q];
         }
@@ -382,16 +387,16 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       if (sp != spin) {   // nothing buffered: turn the inverse over
         __syncthreads();
         const int ct = chain_tid();
-        double x[kChainSmallN * kChainSmallN / kChainT];
+        double x[kChainSmallN * kChainSmallN / T];
 #pragma unroll
-        for (int q = 0; q < kChainSmallN * kChainSmallN / kChainT; ++q) {
-          const int y = ct + kChainT * q, i = y / n, c = y - i * n;
+        for (int q = 0; q < kChainSmallN * kChainSmallN / T; ++q) {
+          const int y = ct + T * q, i = y / n, c = y - i * n;
           x[q] = y < n * n ? B[i * ld + c] : 0.0;
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < kChainSmallN * kChainSmallN / kChainT; ++q) {
-          const int y = ct + kChainT * q, i = y / n, c = y - i * n;
+        for (int q = 0; q < kChainSmallN * kChainSmallN / T; ++q) {
+          const int y = ct + T * q, i = y / n, c = y - i * n;
           if (y < n * n) B[c * ld + i] = x[q];
         }
         fence = true;
@@ -407,7 +412,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
         __syncthreads();
         const int nrow = hs == 0 ? s.nu : s.nd;
         const double* P = (const double*)w.P + ((long)wk * N + (hs == 0 ? 0 : n)) * Lp;
-        for (int q = chain_tid(); q < np * (Lp / 2); q += kChainT) {
+        for (int q = chain_tid(); q < np * (Lp / 2); q += T) {
           const int i = q / (Lp / 2), mu = 2 * (q - i * (Lp / 2));
           double2 v = double2{0.0, 0.0};   // (the row that makes ptn even)
           if (i < n) v = *reinterpret_cast<const double2*>((i < nrow ? P + (long)i * Lp : s.Uph + (long)(i - nrow) * Lp) + mu);
@@ -422,7 +427,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
     }
     if (MODE == kRun && t % kChainDraws == 0) {
       __syncthreads();
-      for (int q = chain_tid(); q < 4 * kChainDraws; q += kChainT) {
+      for (int q = chain_tid(); q < 4 * kChainDraws; q += T) {
         const int k = q >> 2, c = q & 3;
         if (t + k < a.steps)
           draw[q] = c < 3 ? a.disp[((long)(t + k) * Wk + wk) * 3 + c] : a.unif[(long)(t + k) * Wk + wk];
@@ -440,7 +445,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       px = p[0]; py = p[1]; pz = p[2];
       if (!a.r_new) { px += ox; py += oy; pz += oz; }
     }
-    // the Jastrow basis state of e, ahead of its use (LJ <= kChainT)
+    // the Jastrow basis state of e, ahead of its use (LJ <= T)
     double jchi = 0.0, jhv = 0.0;
     if (t3 < LJ) { jchi = chi[e * LJ + t3]; jhv = hv[e * LJ + t3]; }
     // the inverse's column (lanes: rows lane and lane + 64)
@@ -463,7 +468,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       }
       int cnt = SMALL ? (L - wave + 3) / 4 : 0;
       if constexpr (CON) {   // (the last move's readers are past its sums)
-        for (int mu = tid; mu < s.Lq; mu += kChainT) qv[mu] = basis_value(s, mu, px, py, pz);
+        for (int mu = tid; mu < s.Lq; mu += T) qv[mu] = basis_value(s, mu, px, py, pz);
         __syncthreads();
       }
 #pragma unroll
@@ -532,13 +537,24 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
         dj += (v - jchi) * (Gv[sp * LJ + t3] - jhv + jm[sp * LJ + t3]);
       }
       dj = wave_sum(dj);
-      if (lane == 0) red[4 * (t & 1) + wave] = dj;
+      if (lane == 0) red[NW * (t & 1) + wave] = dj;
       if (!SMALL && lane == 0) prow[wave] = cnt;   // (at the end: the last proposal's)
       __syncthreads();
       const double* ps = part + (t & 1) * a.pst;
-      if (lane < n) w0 = ((ps[lane] + ps[np + lane]) + ps[2 * np + lane]) + ps[3 * np + lane];
-      if (lane + 64 < n)
-        w1 = ((ps[lane + 64] + ps[np + lane + 64]) + ps[2 * np + lane + 64]) + ps[3 * np + lane + 64];
+      auto rows = [&]() {
+        if (lane < n) {
+          w0 = ps[lane];
+#pragma unroll
+          for (int q = 1; q < NW; ++q) w0 += ps[q * np + lane];
+        }
+        if (lane + 64 < n) {
+          w1 = ps[lane + 64];
+#pragma unroll
+          for (int q = 1; q < NW; ++q) w1 += ps[q * np + lane + 64];
+        }
+      };
+      rows();
+      if constexpr (NW == 8) __syncthreads();   // (one buffer of partial sums)
       R = wave_sum(w0 * c0 + w1 * c1);
       if constexpr (!SMALL) {
         if (s.screen_again(R)) {   // uniform: the wave's functions left out that matter beside R
@@ -547,7 +563,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
           const int rt = chain_tid();   // (mus and cm anew: nothing more is held in registers up to here)
 #pragma unroll
           for (int q = 0; q < QL; ++q) {
-            const int mu = kChainT * q + (((rt & 63) >> 4) * 4 + (rt >> 6)) * 16 + (rt & 15);
+            const int mu = T * q + (((rt & 63) >> 4) * NW + (rt >> 6)) * 16 + (rt & 15);
             const double v = mu < L ? fabs(sv[q]) * w.cmax[((long)wk * 2 + 1 - sp) * Lp + mu] : 0.0;
             const bool more = v > lo && v <= thr;
             const unsigned long long b = __ballot(more);
@@ -569,17 +585,18 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
             }
           bx = lane_group_sum(bx, lpf);
           by = lane_group_sum(by, lpf);
-          __syncthreads();   // the kept functions' sums are read
+          if constexpr (NW == 4) __syncthreads();   // the kept functions' sums are read
           if (lane < lpf && row_ok) { pt[rp] += bx; pt[rp + 1] += by; }
           __syncthreads();
-          if (lane < n) w0 = ((ps[lane] + ps[np + lane]) + ps[2 * np + lane]) + ps[3 * np + lane];
-          if (lane + 64 < n)
-            w1 = ((ps[lane + 64] + ps[np + lane + 64]) + ps[2 * np + lane + 64]) + ps[3 * np + lane + 64];
+          rows();
+          if constexpr (NW == 8) __syncthreads();
           R = wave_sum(w0 * c0 + w1 * c1);
         }
       }
-      const double* rd = red + 4 * (t & 1);
-      dJ = ((rd[0] + rd[1]) + rd[2]) + rd[3];
+      const double* rd = red + NW * (t & 1);
+      dJ = rd[0];
+#pragma unroll
+      for (int q = 1; q < NW; ++q) dJ += rd[q];
     }
     const double ratio = R * exp(dJ);
     if constexpr (MODE == kPropose) {
@@ -591,13 +608,17 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
 #pragma unroll
       for (int q = 0; q < QL; ++q)
         if (mus[q] < L) w.psi_new[(long)wk * Lp + mus[q]] = sv[q];
-      for (int k = tid; k < LJ; k += kChainT) w.chi_new[(long)wk * LJ + k] = chin[k];
+      for (int k = tid; k < LJ; k += T) w.chi_new[(long)wk * LJ + k] = chin[k];
       if (tid == 0) {
         w.r_new[3 * wk] = px; w.r_new[3 * wk + 1] = py; w.r_new[3 * wk + 2] = pz;
         w.rdet[wk] = R;
         w.ratio[wk] = ratio;
         w.dJ[wk] = dJ;
-        w.nkeep[wk] = prow[0] + prow[1] + prow[2] + prow[3];
+        {
+          int kept = 0;
+          for (int q = 0; q < NW; ++q) kept += prow[q];
+          w.nkeep[wk] = kept;
+        }
         if (a.ratio_out) a.ratio_out[wk] = ratio;
       }
       return;
@@ -629,7 +650,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
       for (int q = 0; q < QL; ++q)
         if (mus[q] < L) phi[(long)e * Lp + mus[q]] = sv[q];
       // [G_u; G_d] += M3[:, s] (chi(r') - chi_e), h_e = M^{ss} chi(r'): four lanes a sum
-      for (int q = tid; q < 12 * LJ; q += kChainT) {
+      for (int q = tid; q < 12 * LJ; q += T) {
         const int o = q >> 2, sub = q & 3;
         const bool first = o < 2 * LJ;
         const double* row = M3 + (first ? o : sp * LJ + o - 2 * LJ) * ldM + sp * LJ;
@@ -663,7 +684,7 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
           *p = double2{fma(-ci, u.x, b.x), fma(-ci, u.y, b.y)};
         }
       }
-      for (int k = tid; k < LJ; k += kChainT) chi[e * LJ + k] = chin[k];
+      for (int k = tid; k < LJ; k += T) chi[e * LJ + k] = chin[k];
       if (tid == 0) {
         r[3 * e] = px; r[3 * e + 1] = py; r[3 * e + 2] = pz;
         if (R < 0.0) sg = -sg;
@@ -685,24 +706,28 @@ __global__ void __launch_bounds__(kChainT, MODE == kRun ? 2 : 4) chain_kernel(Sy
   if (MODE == kRun) fold_logs();
   __syncthreads();
   if (SMALL || a.store_A)
-    for (int q = tid; q < n * n; q += kChainT) {
+    for (int q = tid; q < n * n; q += T) {
       const int i = q / n, k = q - i * n;
       w.A[(long)wk * n * n + q] = B[spin == 0 ? i * ld + k : k * ld + i];
     }
-  for (int q = tid; q < 3 * N; q += kChainT) w.r[(long)wk * 3 * N + q] = r[q];
+  for (int q = tid; q < 3 * N; q += T) w.r[(long)wk * 3 * N + q] = r[q];
   if constexpr (SMALL)
-    for (int q = tid; q < N * LJ; q += kChainT) {
+    for (int q = tid; q < N * LJ; q += T) {
       w.chi[(long)wk * N * LJ + q] = chi[q];
       w.hv[(long)wk * N * LJ + q] = hv[q];
     }
-  for (int q = tid; q < 2 * LJ; q += kChainT) w.G3[(long)wk * 2 * LJ + q] = Gv[q];
+  for (int q = tid; q < 2 * LJ; q += T) w.G3[(long)wk * 2 * LJ + q] = Gv[q];
   if (tid == 0) {
     w.logabs[wk] = la;
     w.sign[wk] = sg;
     w.J[wk] = Jt;
     if (SMALL) w.wm[wk] = 0;
     // the functions the last proposal read
-    if (MODE == kRun) w.nkeep[wk] = SMALL ? L : prow[0] + prow[1] + prow[2] + prow[3];
+    if (MODE == kRun) {
+      int kept = SMALL ? L : 0;
+      for (int q = 0; !SMALL && q < NW; ++q) kept += prow[q];
+      w.nkeep[wk] = kept;
+    }
     if (MODE == kRun && a.cnt) a.cnt[wk] += acc_n;
   }
 }
@@ -844,6 +869,17 @@ __global__ void __launch_bounds__(kAccCols * kChainG) chain_accept_kernel(SysDev
   for (int k = tid; k < LJ; k += T) ce[k] = chin[k];
 }
 
+// Threads of a large form: past 80 KiB one workgroup has a compute unit to itself, and
+// with four waves each SIMD waits on one wave's LDS and cache round trips.  Eight waves
+// of the same LDS (one buffer of partial sums and a barrier more a move in place of two
+// buffers); us a move of a sweep, 256 / 512 threads: n = 96 FP64 16 walkers 13.5/11.3,
+// 256 17.0/14.2, 1024 63.5/53.2, QMC_REFINED 1024 61.3/52.8; n = 128 FP64 256 walkers
+// 26.3/23.4, QMC_REFINED 1024 83.1/73.4.  (n = 80, two workgroups a compute unit: 256.)
+static int chain_threads(const SysDev& s) {
+  ChainArgs a{};
+  return chain_layout(s, false, a).total <= kChainMaxLds / 2 ? kChainT : 2 * kChainT;
+}
+
 // The form that takes a system: FP64 rows and a walker's state within the LDS (0:
 // neither).
 int chain_class(const SysDev& s, const WalkDev& w) {
@@ -851,21 +887,22 @@ int chain_class(const SysDev& s, const WalkDev& w) {
   if (s.LJ > kChainT || s.N > 4096 || s.n_nuc > 4096) return 0;
   ChainArgs a{};
   if (s.nu <= kChainSmallN && s.L <= 2 * kChainT && chain_layout(s, true, a).total <= kChainSmallLds) return 1;
-  return chain_layout(s, false, a).total <= kChainMaxLds ? 2 : 0;
+  return chain_layout(s, false, a, false, chain_threads(s)).total <= kChainMaxLds ? 2 : 0;
 }
 
 // A run stages the inverse in LDS and stores it again, 16 n^2 bytes a walker, for as
 // many walkers at a time as the LDS lets the chip hold: with r such rounds a run of up to
-// r moves is cheaper as single proposals and accepts, which touch the inverse of
-// accepting walkers alone and fill the chip whatever their LDS.  us a move, run / single,
-// for runs of 1, 2, 3, 4, 8: n = 80, 256 walkers (r = 1) 27/23 19/23 15/23 14/22 10/21;
-// n = 80, 1024 (2) 60/36 39/34 32/32 28/32 23/31; n = 40, 2048 (4) 57/33 38/31 31/29 29/29 24/28;
-// n = 96, 1024 (4) 120/45 86/45 72/43 61/43 50/41.  (Over a whole sweep's rows, which the
-// rounds keep in the last-level cache, long runs win: n = 96, 1024 walkers 64 / 80.)
+// r moves (r - 1 with 512 threads) is cheaper as single proposals and accepts, which touch
+// the inverse of accepting walkers alone and fill the chip whatever their LDS.  us a move,
+// run / single, for runs of 1, 2, 3, 4, 8: n = 80, 256 walkers (r = 1) 27/23 19/23 15/23 14/22
+// 10/21; n = 80, 1024 (2) 60/36 39/34 32/32 28/32 23/31; n = 40, 2048 (4) 57/33 38/31 31/29 29/29
+// 24/28; n = 96, 512 (2) 56/40 42/41 37/41 34/41 30/41; n = 96, 1024 (4) 110/73 85/74 77/75 72/75
+// 63/75; n = 127, 256 (1) 48/44 37/45 33/45 31/45 28/46; n = 127, 1024 (4) 178/125 138/129 120/131
+// 110/132 94/133.
 int chain_single(const SysDev& s, const WalkDev& w) {
-  ChainArgs a{};
-  const int at_once = 256 * (chain_layout(s, false, a).total <= kChainMaxLds / 2 ? 2 : 1);
-  return (w.Wk + at_once - 1) / at_once;
+  const bool two = chain_threads(s) == kChainT;   // workgroups a compute unit
+  const int at_once = two ? 512 : 256, rounds = (w.Wk + at_once - 1) / at_once;
+  return two ? rounds : std::max(1, rounds - 1);
 }
 
 static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, ChainArgs& a, hipStream_t st,
@@ -873,14 +910,27 @@ static hipError_t chain_launch(const SysDev& s, const WalkDev& w, int mode, Chai
   const int cls = chain_class(s, w);
   if (cls == 0 || (mode != kRun && cls != 2) || a.steps < 1) return hipErrorInvalidValue;
   a.cap = wb_cap(s);
-  a.ly = chain_layout(s, cls == 1, a, mode == kPropose);
-  const dim3 grid(w.Wk), blk(kChainT);
+  const int T = cls == 1 ? kChainT : chain_threads(s);
+  a.ly = chain_layout(s, cls == 1, a, mode == kPropose, T);
+  const dim3 grid(w.Wk), blk(T);
 #define QMC_CHAIN(M, S, Q) QMC_LAUNCH_EV((chain_kernel<M, S, Q>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
 #define QMC_CHAIN_Q(M)                                                         \
   if (s.L <= kChainT) { QMC_CHAIN(M, false, 1); }                              \
   else if (s.L <= 2 * kChainT) { QMC_CHAIN(M, false, 2); }                     \
   else if (s.L <= 3 * kChainT) { QMC_CHAIN(M, false, 3); }                     \
   else { QMC_CHAIN(M, false, 4); }
+  if (T == 2 * kChainT) {
+#define QMC_CHAIN_2(M, Q, C) QMC_LAUNCH_EV((chain_kernel<M, false, Q, C, 2 * kChainT>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
+#define QMC_CHAIN_2Q(M)                                                                               \
+  if (s.Lq > 0) { QMC_CHAIN_2(M, 2, true); }                                                          \
+  else if (s.L <= T) { QMC_CHAIN_2(M, 1, false); }                                                    \
+  else { QMC_CHAIN_2(M, 2, false); }
+    if (mode == kRun) { QMC_CHAIN_2Q(kRun) }
+    else { QMC_CHAIN_2Q(kPropose) }
+#undef QMC_CHAIN_2Q
+#undef QMC_CHAIN_2
+    return hipGetLastError();
+  }
   if (s.Lq > 0) {
 #define QMC_CHAIN_C(M, S, Q) QMC_LAUNCH_EV((chain_kernel<M, S, Q, true>), grid, blk, a.ly.total, st, ev_start, ev_stop, s, w, a)
     if (cls == 1) { QMC_CHAIN_C(kRun, true, 2); }
@@ -921,7 +971,7 @@ hipError_t launch_chain_propose(const SysDev& s, const WalkDev& w, int e, const 
 hipError_t launch_chain_accept(const SysDev& s, const WalkDev& w, int e, const uint8_t* acc, const double* unif,
                                int32_t* accept_count, hipStream_t st) {
   if (chain_class(s, w) != 2 || s.nu > kChainMaxN || (!acc && !unif)) return hipErrorInvalidValue;
-  const int n = s.nu, G = chain_groups(n), tiles = (n + kAccCols - 1) / kAccCols;
+  const int n = s.nu, G = chain_groups(n, chain_threads(s)), tiles = (n + kAccCols - 1) / kAccCols;
   const long total = (long)tiles * w.Wk;
   if (total > 0x7fffffffL) return hipErrorInvalidValue;
   const size_t lds = e < n ? 0 : sizeof(double) * (size_t)n * kAccLd;
