@@ -94,8 +94,8 @@ typedef enum {
                       from the largest |P| of each column and the inverse
                       column's 1-norm; an up move of a polarized system also
                       streams the unpaired orbitals' values).  One more
-                      [Wk][L][N + n_up - n_dn] FP64
-                      array (P transposed).  For a Pfaffian (pairing = 1) the
+                      [Wk][round_up(L, 32)][2 round_up(n_up, 2)]
+                      FP64 array (P transposed).  For a Pfaffian (pairing = 1) the
                       evaluation's B rows phi(r_j)^T K^{s s_j} are the same
                       error-free int8 digit products; G~, Pf, its inverse and
                       the moves are those of the FP64 path.                    */
@@ -420,7 +420,8 @@ qmc_status qmc_pfaffian_logderiv(qmc_system *sys, qmc_walkers *wk, double *d_uu,
                                  double *d_unpaired_up, double *d_unpaired_dn, hipStream_t stream);
 
 /* Bytes of device workspace qmc_sr_step makes use of (0 for non-positive
- * sizes).  For at most 8192 parameters it also runs in less, 8 (6 P + M +
+ * sizes).  For at most 8192 parameters, but for nearly square problems
+ * (2 M < 3 P < 5 M, which read O twice per iteration either way), it also runs in less, 8 (6 P + M +
  * 3 ceil(P / 256) + 16 + 2 s P) bytes with s = min(ceil(M / 128), 64) (P
  * parameters, M samples), reading O twice per iteration instead of once. */
 size_t qmc_sr_workspace_size(int32_t n_samples, int64_t n_params);
@@ -433,7 +434,7 @@ size_t qmc_sr_workspace_size(int32_t n_samples, int64_t n_params);
  *     f_k  = -2 <e_L (O_k - Obar_k)>,
  * solves (S + eps diag(S)) delta = f by conjugate gradients preconditioned by
  * the diagonal of S + eps diag(S), without forming S
- * (each iteration streams O twice), stopping when |r| <= tol |f| or after
+ * (each iteration streams O once, or twice: see qmc_sr_workspace_size), stopping when |r| <= tol |f| or after
  * max_iter iterations; the parameter change is dt * delta for a time step dt
  * the caller chooses.  Every sum is taken in a fixed order, so the result is
  * the same on every run.
@@ -477,7 +478,9 @@ qmc_status qmc_multi_destroy(qmc_multi *m);
 /* Time the streaming-rows launch for rows-per-work-item in {8, 16, 32} and
  * persistent grid sizes {512 .. 4096} on the current walker state (read-only
  * apart from proposal scratch) and keep the fastest; returns the choice in
- * *rows and *grid (host, may be NULL).  Synchronises. */
+ * *rows and *grid (host, may be NULL).  Synchronises.  Members with FP64 rows
+ * (QMC_FP64, QMC_REFINED) have no such launch: nothing is timed and the choice of
+ * qmc_multi_create is returned. */
 qmc_status qmc_multi_autotune(qmc_multi *m, int32_t *rows, int32_t *grid, hipStream_t stream);
 
 /* n_steps Metropolis steps of every walker of every member; member k moves

@@ -459,8 +459,10 @@ static long sr_fused_fixed(long P) { return 8 * P + 3 * ((P + 63) / 64) + 16; }
 // iteration does not converge in 200 steps (the smallest kept singular values of
 // O lie near zero) and carries a change of rounding into the step: 1e-9 of it at
 // 200 samples x 168 parameters, 1e-5 at 168 x 168 and 300 x 330, where the step
-// itself is 1e-8, 5e-4 and 2e-4 from the solution; 1e-12 and less from 200 x 150
-// and 207 x 359 on, which converge in 180 and 140.
+// itself is 1e-8, 5e-4 and 2e-4 from the solution; 1e-12 and less at 200 x 150
+// and 207 x 359, which converge in 180 and 140.  The band's lines (3/2 and 3/5 of
+// P samples) lie where that was measured, the lower side's with room: 200 x 150
+// is inside, 207 x 359 outside.
 static bool sr_near_square(int M, long P) { return 2L * M < 3 * P && 3 * P < 5L * M; }
 
 static int sr_fused_slices(int M, long P) {

@@ -288,10 +288,10 @@ struct WalkDev {
   int* muk;
   double* psk;
   int* nkeep;
-  // (QMC_REFINED) the positions at which each electron's P row was last built
+  // (FP64 rows) the positions at which each electron's P row was last built
   // [Wk][N][3]; the rows of a P half whose electron has moved since, as
   // indices into the half's row order (walker * n + i), and their count per
-  // half; the int8 row exponents in that compacted order
+  // half; (QMC_REFINED) the int8 row exponents in that compacted order
   double* rpos_P;
   int* dirty_idx;
   int* dirty_cnt;
