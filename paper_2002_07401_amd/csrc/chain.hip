@@ -743,10 +743,10 @@ __global__ void __launch_bounds__(T, MODE == kRun ? 2 : 4) chain_kernel(SysDev s
 // caller's) or by unif.
 // Bound by HBM: 16 n^2 bytes an accepted walker.  us for a proposal and its accept of 60 %
 // of 1024 walkers, all of the inverse staged in LDS by one workgroup (131 KB at n = 127, one
-// a compute unit) -> here: n = 127 226 -> 115 (refined 205 -> 103), n = 96 135 -> 63, n = 80
-// 67 -> 46; 16 walkers, n = 127 42 -> 34.  The delayed form of the per-move kernels, which
+// a compute unit) -> here: n = 127 226 -> 114 (refined 205 -> 105), n = 96 135 -> 63, n = 80
+// 67 -> 46; 16 walkers, n = 127 42 -> 28.  The delayed form of the per-move kernels, which
 // moves 3 m n numbers for m buffered moves, is still ahead of it past n = 112 at 1024
-// walkers (refined, n = 127: 97).
+// walkers (refined, n = 127: 96).
 // Transposed tiles (down moves) go through LDS, both ways in whole lines.
 // ---------------------------------------------------------------------------
 constexpr int kAccCols = 32, kAccLd = kAccCols + 1;
